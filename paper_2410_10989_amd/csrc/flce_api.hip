@@ -161,38 +161,6 @@ int acquire_workspace(size_t need, char** out) {
     return FLCE_OK;
 }
 
-// C[M x N] (+)= A[M x K] * B[N x K]^T on the generic guarded kernel.  With ksplit > 1
-// K is cut into ksplit ranges and range z writes its partial result to
-// C + z * split_stride (no accumulation then).
-template <typename T, typename OutT>
-int launch_gemm_generic(int kind, const T* A, int64_t lda, const T* B, int64_t ldb, OutT* C,
-                        int64_t ldc, int64_t M, int64_t N, int64_t K, bool accum, hipStream_t s,
-                        int ksplit = 1, int64_t split_stride = 0) {
-    if (M <= 0 || N <= 0) return FLCE_OK;
-    if (ksplit > 1 && accum) return FLCE_ERR_SHAPE;
-    ScopedKernelTimer timer(kind, s);
-    constexpr int VEC = GGTraits<T>::VEC;
-    constexpr int BK = GGTraits<T>::BK;
-    const bool al = (K % VEC == 0) && (lda % VEC == 0) && (ldb % VEC == 0) && aligned(A, 16) &&
-                    aligned(B, 16);
-    const int64_t k_per = round_up((K + ksplit - 1) / ksplit, BK);
-    const int64_t tiles = ((N + GG_BN - 1) / GG_BN) * ((M + GG_BM - 1) / GG_BM);
-    if (tiles > MAX_GRID_X) return FLCE_ERR_SHAPE;   // check_launch_limits refuses such shapes up front
-    dim3 grid((unsigned)tiles, 1, (unsigned)ksplit);
-    dim3 block(GG_THREADS);
-#define GG_LAUNCH(AL, AC)                                                                       \
-    hipLaunchKernelGGL((gemm_nt_generic<T, OutT, AL, AC>), grid, block, 0, s, A, lda, B, ldb, C, \
-                       ldc, (int)M, (int)N, (int)K, (int)k_per, split_stride)
-    if (al) {
-        if (accum) GG_LAUNCH(true, true); else GG_LAUNCH(true, false);
-    } else {
-        if (accum) GG_LAUNCH(false, true); else GG_LAUNCH(false, false);
-    }
-#undef GG_LAUNCH
-    HIP_TRY(hipGetLastError());
-    return FLCE_OK;
-}
-
 // What only the device knows about a product launch of a compacted chunk (see FGArgs).
 struct FastDyn {
     const int* rows = nullptr;      // live rows: replaces M (is_k = 0) or K (is_k = 1)
@@ -201,6 +169,35 @@ struct FastDyn {
     const int* first_live = nullptr;
     int launch = 0;
 };
+
+// Guarded kernel (see gemm_generic.h): any shape and alignment, both storage types.  Cin is an
+// fp32 addend or null, cin_own one of C's type.  With ksplit > 1 range z writes its partial
+// result to C + z * split_stride (no addend then).
+template <typename T, typename OutT, bool A_KM, bool B_KM>
+int launch_gemm_guarded(int kind, const T* A, int64_t lda, const T* B, int64_t ldb, OutT* C, int64_t ldc,
+                        const float* Cin, const OutT* cin_own, int64_t M, int64_t N, int64_t K,
+                        hipStream_t s, int tile, int ksplit = 1, int64_t split_stride = 0,
+                        const FastDyn& d = FastDyn{}) {
+    if (M <= 0 || N <= 0) return FLCE_OK;
+    if (ksplit > 1 && (Cin || cin_own)) return FLCE_ERR_SHAPE;
+    ScopedKernelTimer timer(kind, s);
+    constexpr int VEC = GGTraits<T>::VEC;
+    const void* in = Cin ? static_cast<const void*>(Cin) : static_cast<const void*>(cin_own);
+    GGArgs a{A, lda, B, ldb, C, ldc, in, ldc, Cin ? 1 : 0, (int)M, (int)N, (int)K, ksplit, split_stride,
+             (lda % VEC == 0 && aligned(A, 16)) ? 1 : 0, (ldb % VEC == 0 && aligned(B, 16)) ? 1 : 0,
+             (ldc % 4 == 0 && split_stride % 4 == 0 && aligned(C, 4 * sizeof(OutT))) ? 1 : 0,
+             d.rows, d.is_k, d.ksplit, d.first_live, d.launch,
+             FG_GROUP_TILES, kind == FLCE_KIND_LOGITS_GEMM ? 1 : 0, 1};
+    const int64_t total = ((M + tile - 1) / tile) * ((N + tile - 1) / tile) * ksplit;
+    if (total > MAX_GRID_X - FG_XCDS) return FLCE_ERR_SHAPE;   // check_launch_limits refuses such shapes up front
+    const dim3 grid((unsigned)((total + FG_XCDS - 1) / FG_XCDS * FG_XCDS));
+    if (tile == 64)
+        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64>), grid, dim3(GG_THREADS), 0, s, a);
+    else
+        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 128>), grid, dim3(GG_THREADS), 0, s, a);
+    HIP_TRY(hipGetLastError());
+    return FLCE_OK;
+}
 
 // Tuned bf16 kernel (see gemm_bf16_nt.h for what A_KM / B_KM / InT mean).  The
 // caller has checked the shape limits (Plan::fast_*).  tail_part: tail_bytes of
@@ -240,20 +237,6 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
                            0, s, a);
         HIP_TRY(hipGetLastError());
     }
-    return FLCE_OK;
-}
-
-template <typename T>
-int launch_transpose(const T* in, int64_t ldin, T* out, int64_t ldout, int64_t R, int64_t Cc,
-                     hipStream_t s) {
-    if (R <= 0 || Cc <= 0) return FLCE_OK;
-    ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
-    const int64_t tiles = ((Cc + 63) / 64) * ((R + 63) / 64);
-    if (tiles > MAX_GRID_X) return FLCE_ERR_SHAPE;
-    dim3 grid((unsigned)tiles);
-    hipLaunchKernelGGL((transpose_kernel<T>), grid, dim3(256), 0, s, in, ldin, out, ldout, (int)R,
-                       (int)Cc);
-    HIP_TRY(hipGetLastError());
     return FLCE_OK;
 }
 
@@ -357,9 +340,6 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
     const bool want_dx = !(flags & FLCE_SKIP_DX), want_dw = !(flags & FLCE_SKIP_DW);
     float* row_loss = reinterpret_cast<float*>(ws + p.off_row_loss);
     T* Z = reinterpret_cast<T*>(ws + p.off_z);
-    T* GT = reinterpret_cast<T*>(ws + p.off_gt);
-    T* WT = reinterpret_cast<T*>(ws + p.off_wt);
-    T* XT = reinterpret_cast<T*>(ws + p.off_xt);
     float* dWacc = reinterpret_cast<float*>(ws + p.off_dwacc);
     T* Xg = reinterpret_cast<T*>(ws + p.off_xg);     // gathered (or normalised) rows of the chunk
     T* dXg = reinterpret_cast<T*>(ws + p.off_dxg);   // their gradient
@@ -372,7 +352,6 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
     hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
                        weight, hdr);
     HIP_TRY(hipGetLastError());
-    if (want_dx && !p.fast_dx) FLCE_TRY(launch_transpose<T>(W, H, WT, p.ldz, V, H, s));   // WT[H x V]
     if (p.compact && want_dx && !dx_add) {   // rows without a target: zero gradient
         ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
         hipLaunchKernelGGL((zero_ignored_rows_kernel<T>), dim3((unsigned)(BT < 8192 ? BT : 8192)),
@@ -380,7 +359,6 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         HIP_TRY(hipGetLastError());
     }
 
-    bool dw_needs_cast = false;
     for (int64_t c = 0; c < p.nchunks; ++c) {
         const int64_t r0 = c * p.C;
         const bool last = (c == p.nchunks - 1);
@@ -439,8 +417,9 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                 FLCE_TRY((launch_gemm_fast<bf16_t, void, false, false>(
                     FLCE_KIND_LOGITS_GEMM, Xc, H, W, H, Z, p.ldz, nullptr, 0, rows, V, H, s, 1, 0, dyn_m)));
         } else {
-            FLCE_TRY((launch_gemm_generic<T, T>(FLCE_KIND_LOGITS_GEMM, Xc, H, W, H, Z, p.ldz, rows, V, H,
-                                                false, s)));
+            FLCE_TRY((launch_gemm_guarded<T, T, false, false>(FLCE_KIND_LOGITS_GEMM, Xc, H, W, H, Z, p.ldz,
+                                                              nullptr, nullptr, rows, V, H, s,
+                                                              guarded_cut(rows, V, H, 1).tile)));
         }
 
         // loss and in-place dlogits
@@ -476,14 +455,15 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             } else {
                 if (p.dx_ksplit > 1) {
                     float* part = reinterpret_cast<float*>(ws + p.off_dxpart);
-                    FLCE_TRY((launch_gemm_generic<T, float>(FLCE_KIND_DX_GEMM, Z, p.ldz, WT, p.ldz, part,
-                                                            H, rows, H, V, false, s, p.dx_ksplit,
-                                                            p.C * H)));
+                    FLCE_TRY((launch_gemm_guarded<T, float, false, true>(
+                        FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, nullptr, rows, H, V, s, p.dx_tile,
+                        p.dx_ksplit, p.C * H)));
                     FLCE_TRY(launch_splitk_reduce<T>(part, p.C * H, p.dx_ksplit, dXc, rows * H, add_in_gemm,
                                                      s));
                 } else {
-                    FLCE_TRY((launch_gemm_generic<T, T>(FLCE_KIND_DX_GEMM, Z, p.ldz, WT, p.ldz, dXc, H,
-                                                        rows, H, V, add_in_gemm, s)));
+                    FLCE_TRY((launch_gemm_guarded<T, T, false, true>(
+                        FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, nullptr, add_in_gemm ? dXc : nullptr, rows, H,
+                        V, s, p.dx_tile)));
                 }
             }
             if (norm) {
@@ -536,25 +516,19 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                     }
                 }
             } else {
-                // guarded path: GT[V x rows] times XT[H x rows]^T
-                FLCE_TRY(launch_transpose<T>(Z, p.ldz, GT, p.ldc, rows, V, s));
-                FLCE_TRY(launch_transpose<T>(Xc, H, XT, p.ldc, rows, H, s));
-                if (p.fp32_dw_acc) {
-                    FLCE_TRY((launch_gemm_generic<T, float>(FLCE_KIND_DW_GEMM, GT, p.ldc, XT, p.ldc,
-                                                            dWacc, H, V, H, rows, c > 0, s)));
-                    dw_needs_cast = last;
+                const int tile = guarded_cut(V, H, rows, 1).tile;
+                float* acc = p.fp32_dw_acc ? dWacc : nullptr;   // fp32 storage adds up in dW itself
+                if (acc && !last) {
+                    FLCE_TRY((launch_gemm_guarded<T, float, true, true>(
+                        FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, acc, H, c > 0 ? acc : nullptr, nullptr, V, H, rows, s,
+                        tile)));
                 } else {
-                    FLCE_TRY((launch_gemm_generic<T, T>(FLCE_KIND_DW_GEMM, GT, p.ldc, XT, p.ldc, dW, H,
-                                                        V, H, rows, c > 0, s)));
+                    FLCE_TRY((launch_gemm_guarded<T, T, true, true>(
+                        FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dW, H, acc, !acc && c > 0 ? dW : nullptr, V, H, rows,
+                        s, tile)));
                 }
             }
         }
-    }
-    if (want_dw && dw_needs_cast) {
-        ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
-        hipLaunchKernelGGL((cast_from_f32_kernel<T>), dim3(2048), dim3(256), 0, s, dWacc, dW,
-                           V * H);
-        HIP_TRY(hipGetLastError());
     }
     return FLCE_OK;
 }
@@ -589,8 +563,8 @@ int check_dims(int64_t BT, int64_t H, int64_t V, int dtype) {
 }
 
 // Launch-size limits of the kernels a plan uses, checked before anything is launched: the
-// guarded product and the transposes number their tiles along grid x, the row kernels and
-// the row copies take one workgroup per row of a chunk.
+// guarded product numbers its tiles along grid x, the row kernels and the row copies take one
+// workgroup per row of a chunk.
 int check_launch_limits(const Plan& p, int64_t H, int64_t V) {
     auto tiles = [](int64_t r, int64_t c, int64_t t) { return ((r + t - 1) / t) * ((c + t - 1) / t); };
     if (p.C > MAX_GRID_X) return FLCE_ERR_SHAPE;

@@ -472,7 +472,8 @@ struct FgResolved {
     int M, K, ksplit;
     bool skip, use_in;
 };
-__device__ __forceinline__ FgResolved fg_resolve(const FGArgs& a, bool has_in) {
+template <typename Args>
+__device__ __forceinline__ FgResolved fg_resolve(const Args& a, bool has_in) {
     FgResolved r{a.M, a.K, a.ksplit, false, has_in};
     if (a.first_live) {
         const int fl = *a.first_live;   // uniform: a scalar load
@@ -489,12 +490,14 @@ __device__ __forceinline__ FgResolved fg_resolve(const FGArgs& a, bool has_in) {
 
 // Position in_xcd of XCD xcd's tile list -> number in the launch's tile sequence (see
 // FGArgs::xcd_interleave and xcd_tile_number).
-__device__ __forceinline__ int fg_seq(const FGArgs& a, int xcd, int in_xcd, int per_xcd) {
+template <typename Args>
+__device__ __forceinline__ int fg_seq(const Args& a, int xcd, int in_xcd, int per_xcd) {
     return a.xcd_interleave ? xcd_tile_number(xcd, in_xcd, per_xcd) : xcd * per_xcd + in_xcd;
 }
 
 // Tile number `seq` of the grouped order (group_m tile rows at a time, column by column
-// inside a group) -> first row and column of the tile.
+// inside a group) -> first row and column of the TILE x TILE tile.
+template <int TILE>
 __device__ __forceinline__ void fg_tile_origin(int seq, int tiles_m, int tiles_n, int group_m, int group_cols,
                                                int& m0, int& n0) {
     // (rows and columns change places for the column-grouped order)
@@ -505,10 +508,9 @@ __device__ __forceinline__ void fg_tile_origin(int seq, int tiles_m, int tiles_n
     const int g = min(group_m, major - first);
     const int rem = seq - grp * group_size;
     const int in_major = first + rem % g, in_minor = rem / g;
-    m0 = (group_cols ? in_minor : in_major) * FG_BM;
-    n0 = (group_cols ? in_major : in_minor) * FG_BN;
+    m0 = (group_cols ? in_minor : in_major) * TILE;
+    n0 = (group_cols ? in_major : in_minor) * TILE;
 }
-
 
 // InT: element type of the addend Cin (float or bf16_t), void for no addend.
 template <typename OutT, typename InT, bool A_KM, bool B_KM>
@@ -550,7 +552,7 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
     if (seq_all >= total) return;
     const int split = seq_all / tiles;
     int m0, n0;
-    fg_tile_origin(seq_all - split * tiles, tiles_m, a.tiles_n, a.group_m, a.group_cols, m0, n0);
+    fg_tile_origin<FG_BM>(seq_all - split * tiles, tiles_m, a.tiles_n, a.group_m, a.group_cols, m0, n0);
 
     FgOperand<A_KM> opa;
     FgOperand<B_KM> opb;
@@ -735,7 +737,7 @@ __global__ __launch_bounds__(256) void fg_tail_reduce_kernel(FGArgs a) {
     const int seq = fg_seq(a, xcd, in_xcd, per_xcd);
     if (seq >= tiles) return;
     int m0, n0;
-    fg_tile_origin(seq, tiles_m, a.tiles_n, a.group_m, a.group_cols, m0, n0);
+    fg_tile_origin<FG_BM>(seq, tiles_m, a.tiles_n, a.group_m, a.group_cols, m0, n0);
     const float* blk = a.tail_part + (size_t)((xcd * a.tail_r + slot) * a.tail_s) * FG_TAIL_BLOCK_FLOATS;
     const int c4 = ((int)threadIdx.x % 64) * 4;       // first of the thread's 4 columns inside the tile
     const int col = n0 + c4;

@@ -80,6 +80,7 @@ struct Plan {
     // logits chunk; the others need transposed copies and the guarded kernel
     bool fast_logits = false, fast_dx = false, fast_dw_full = false, fast_dw_last = false;
     int dx_ksplit = 1;     // K ranges of the dX product (K = V), > 1 when C x H has few tiles
+    int dx_tile = 256;     // its tile size
     // every product of every chunk runs on the tuned kernel: chunks are compacted, i.e.
     // rows with an ignored target are left out of the products (see compact.h)
     bool compact = false;
@@ -125,15 +126,31 @@ inline int max_dx_ranges(size_t budget_bytes, int64_t rows, int64_t H) {
     return (int)std::max<size_t>(1, std::min<size_t>(n, 16));
 }
 
-// K ranges of the dX product (rows x H output, K = V).  The tuned kernel works on
-// 256 x 256 tiles and K steps of 64; the guarded kernel on 128 x 128 tiles, where a
-// range is at least 256 elements long.
-inline int dx_ranges(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes) {
+// Tile size and K ranges of a product on the guarded kernel.  Two 128 x 128 tiles fit a CU at a
+// time, so 512 workgroups fill the chip; 128 x 128 tiles while they (times at most max_ranges
+// K ranges of at least 512 elements) come to a workgroup per CU, else 64 x 64 tiles and ranges
+// of at least 256 elements.
+struct GuardedCut {
+    int tile, ranges;
+};
+inline GuardedCut guarded_cut(int64_t M, int64_t N, int64_t K, int64_t max_ranges) {
+    auto ranges = [&](int64_t tiles, int64_t min_k) {
+        return std::max<int64_t>(1, std::min(std::min(max_ranges, 512 / tiles), K / min_k));
+    };
+    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    if (t128 >= 256) return {128, 1};
+    const int64_t s128 = ranges(t128, 512);
+    if (t128 * s128 >= 256) return {128, (int)s128};
+    return {64, (int)ranges(((M + 63) / 64) * ((N + 63) / 64), 256)};
+}
+
+// The dX product of a chunk (rows x H output, K = V): tile size of the guarded kernel and K
+// ranges.  The tuned kernel works on 256 x 256 tiles and K steps of 64.
+inline GuardedCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes) {
     if (tuned)
-        return choose_ksplit(((rows + 255) / 256) * ((H + 255) / 256), (V + 63) / 64,
-                             max_dx_ranges(budget_bytes, round_up(rows, 256), H));
-    return choose_ksplit(((rows + 127) / 128) * ((H + 127) / 128), V / 4,
-                         max_dx_ranges(budget_bytes, round_up(rows, 128), H));
+        return {256, choose_ksplit(((rows + 255) / 256) * ((H + 255) / 256), (V + 63) / 64,
+                                   max_dx_ranges(budget_bytes, round_up(rows, 256), H))};
+    return guarded_cut(rows, H, V, max_dx_ranges(budget_bytes, round_up(rows, 128), H));
 }
 
 // Limits of the tuned kernel's 32-bit offsets inside one tile (see gemm_bf16_nt.h).
@@ -163,11 +180,11 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     }
     {
         const int64_t rows = p.nchunks > 1 ? p.C : rows_last;
-        p.dx_ksplit = dx_ranges(p.fast_dx, rows, H, V, budget_bytes);
+        const GuardedCut cut = dx_cut(p.fast_dx, rows, H, V, budget_bytes);
+        p.dx_tile = cut.tile;
+        p.dx_ksplit = cut.ranges;
     }
     p.compact = allow_compact && p.fast_logits && p.fast_dx && p.fast_dw_full && p.fast_dw_last;
-    const bool need_wt = !p.fast_dx;
-    const bool need_gt = !(p.fast_dw_full && p.fast_dw_last);
 
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -178,9 +195,7 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     p.off_hdr = take(256);
     p.off_row_loss = take((size_t)p.C * sizeof(float));
     p.off_z = take((size_t)p.C * p.ldz * es);
-    p.off_gt = take(need_gt ? (size_t)V * p.ldc * es : 0);
-    p.off_wt = take(need_wt ? (size_t)H * p.ldz * es : 0);
-    p.off_xt = take(need_gt ? (size_t)H * p.ldc * es : 0);
+    p.off_gt = p.off_wt = p.off_xt = off;   // no product needs a transposed copy
     p.off_dwacc = take(p.fp32_dw_acc ? (size_t)V * H * sizeof(float) : 0);
     const size_t dxpart = p.dx_ksplit > 1 ? (size_t)p.dx_ksplit * p.C * H * sizeof(float) : 0;
     p.off_dxpart = take(std::max(dxpart, dxpart_floor));
@@ -221,8 +236,8 @@ inline Plan make_plan(int64_t BT, int64_t H, int64_t V, int dtype, size_t budget
         // K ranges of the dX product depends on the row count through its tile count
         auto dxpart_over = [&](bool tuned, int64_t upto) {
             size_t m = 0;
-            for (int64_t c = 128; c <= upto; c += 128) {
-                const int ks = dx_ranges(tuned, c, H, V, budget_bytes);
+            for (int64_t c = 64; c <= upto; c += 64) {
+                const int ks = dx_cut(tuned, c, H, V, budget_bytes).ranges;
                 if (ks > 1) m = std::max(m, (size_t)ks * c * H * sizeof(float));
             }
             return m;

@@ -1,0 +1,93 @@
+"""The guarded product kernel (fp32 storage on split bf16 planes, any shape and alignment)
+against plain torch in 64 bits: edges of its 64 and 128 tiles, K ranges, K tails, odd leading
+dimensions, and operands the split cannot represent."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def reference(X, W, t):
+    X, W = X.double().cpu(), W.double().cpu()
+    t = t.cpu()
+    ok = (t != -100).double()[:, None]
+    n = max(1.0, float(ok.sum()))
+    z = X @ W.T
+    lse = torch.logsumexp(z, 1, keepdim=True)
+    at = t.clamp(min=0)[:, None]
+    loss = float(((lse - z.gather(1, at)) * ok).sum()) / n
+    G = (torch.exp(z - lse).scatter_add(1, at, torch.full_like(lse, -1.0))) * ok / n
+    return loss, G @ W, G.T @ X
+
+
+def inputs(BT, H, V, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    X = torch.randn(BT, H, device="cuda", generator=g)
+    W = torch.randn(V, H, device="cuda", generator=g) * 0.05
+    t = torch.randint(0, V, (BT,), device="cuda", generator=g)
+    t[3::7] = -100
+    return X, W, t
+
+
+# One fp32 rounding per accumulation step: K/16 * 6 roundings of at most 2^-24 of the running sum,
+# random signs: below 2^-24 * sqrt(6 K / 16) of the result; the operands' own rounding (logits,
+# exponentials of them) adds a few 2^-24 |z|.  4e-7 .. 1e-6 for the sizes below, stated 2e-6: a lost
+# plane product (2^-16 .. 2^-18 relative) would show as 4e-6 .. 1e-5.
+@pytest.mark.parametrize("BT,H,V", [
+    (64, 64, 64),        # one 64 x 64 tile
+    (65, 33, 67),        # one row, column and K value past a tile and a K step; odd leading dimensions
+    (127, 100, 1025),    # 64-tiles, dX cut into K ranges with a tail
+    (129, 260, 4098),    # K ranges whose last one is ragged
+    (1100, 516, 7001),   # 128-tiles in logits and dW, K ranges of 512 in dX, odd V
+    (2049, 1030, 2111),  # 128-tiles everywhere, rows that are not 16-byte aligned
+    (1, 7, 300),         # a single row
+])
+def test_fp32_products_keep_fp32_accuracy(BT, H, V):
+    import paper_2410_10989_amd as flce
+    X, W, t = inputs(BT, H, V, 7 * BT + V)
+    loss, dX, dW = flce.flce_fwd_bwd(X, W, t)
+    torch.cuda.synchronize()
+    rl, rX, rW = reference(X, W, t)
+    assert abs(float(loss) - rl) <= 2e-6 * abs(rl)
+    for name, got, ref in (("dX", dX, rX), ("dW", dW, rW)):
+        err = float((got.double().cpu() - ref).norm() / ref.norm())
+        print(f"  {BT} x {H} x {V} {name}: {err:.2e}", flush=True)
+        assert err <= 2e-6, (name, err)
+
+
+@pytest.mark.parametrize("BT,H,V", [(100, 40, 300), (1100, 128, 7000)])   # 64 and 128 tiles
+def test_operands_beyond_bf16_take_fp32_products(BT, H, V):
+    # finite fp32 values that round to infinity in bf16 times tiny ones: ordinary logits; and a class
+    # masked by a weight of -inf against positive activations: probability 0, everything else finite
+    import paper_2410_10989_amd as flce
+    X, W, t = inputs(BT, H, V, 11)
+    t = torch.where(t == 5, torch.full_like(t, 6), t)
+    X[:, 0] = 3.4e38
+    W[:, 0] = torch.randn(V, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3)) * 1e-38
+    X[:, 1] = 1.0 + X[:, 1].abs()
+    W[5, 1] = -float("inf")
+    loss, _, dW = flce.flce_fwd_bwd(X, W, t, flags=flce.SKIP_DX)
+    torch.cuda.synchronize()
+    keep = torch.arange(V, device="cuda") != 5
+    rl, _, rW = reference(X, W[keep], torch.where(t > 5, t - 1, t))
+    assert abs(float(loss) - rl) <= 1e-5 * abs(rl)
+    got = dW[keep].double().cpu()
+    assert torch.isfinite(dW).all() and (dW[5] == 0).all()
+    # column 0 of dW is sums of g * 3.4e38; compared on its own scale
+    for sl in (slice(0, 1), slice(1, None)):
+        assert float((got[:, sl] - rW[:, sl]).norm() / rW[:, sl].norm()) <= 1e-5
+
+
+def test_nan_stays_where_plain_products_put_it():
+    import paper_2410_10989_amd as flce
+    X, W, t = inputs(300, 64, 500, 13)
+    X[7, 3] = float("nan")
+    t[7] = 1
+    loss, dX, dW = flce.flce_fwd_bwd(X, W, t)
+    torch.cuda.synchronize()
+    assert torch.isnan(loss) and torch.isnan(dX[7]).all()
+    ok = torch.arange(300, device="cuda") != 7
+    n = int((t != -100).sum())
+    _, rX, _ = reference(X[ok], W, t[ok])
+    got = dX[ok].double().cpu() * n / (n - 1)     # the reference's mean is over one row less
+    assert float((got - rX).norm() / rX.norm()) <= 2e-6
