@@ -29,9 +29,10 @@
  *    kernels would exceed the launch limits (more than 2^31 - 1 tiles of 64 x 64
  *    in one matrix on the guarded path: FLCE_ERR_SHAPE, like every argument
  *    error before anything is launched).  bf16 problems with
- *    H % 64 == 0 run entirely on the tuned matrix-core kernel, whatever BT and V
- *    are; other H and fp32 storage run on slower, fully guarded kernels and need
- *    more workspace (transposed copies); the results meet the same bars.
+ *    H % 8 == 0 run entirely on the tuned matrix-core kernel, whatever BT and V
+ *    are; other H and fp32 storage run on a slower, fully guarded kernel (fp32
+ *    products on split bf16 operands, with the accuracy of fp32 products); the
+ *    results meet the same bars.
  *  - Targets must lie in [0, V) or equal ignore_index; anything else is a
  *    precondition violation (not detected: checking would need a host sync).
  *  - N == 0 gives loss = 0, dX = 0, dW = 0.
@@ -292,7 +293,9 @@ FLCE_API size_t flce_logits_budget_for_workspace(int64_t BT, int64_t H, int64_t 
                                                  size_t max_workspace_bytes);
 
 /* Number of K ranges (K = V) the dX product of one chunk is cut into so that its
- * output tiles fill whole rounds of the chip's CUs; 1 = not cut (host only). */
+ * output tiles fill whole rounds of the chip's CUs; 1 = not cut (host only).  For
+ * a bf16 product small enough to run on 128 x 128 tiles, which cut K finer, this is
+ * the number of ranges its 256 x 256 tiles would take. */
 FLCE_API int flce_dx_k_ranges(int64_t BT, int64_t H, int64_t V, int dtype);
 
 /* The paper's own chunk-size rule, 2^ceil(log2(ceil(BT / ceil(V/H)))), for

@@ -207,20 +207,20 @@ int launch_gemm_guarded(int kind, const T* A, int64_t lda, const T* B, int64_t l
 template <typename OutT, typename InT, bool A_KM, bool B_KM>
 int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, OutT* C,
                      int64_t ldc, const InT* Cin, int64_t ldcin, int64_t M, int64_t N, int64_t K,
-                     hipStream_t s, int ksplit = 1, int64_t split_stride = 0, const FastDyn& d = FastDyn{},
+                     hipStream_t s, int tile, int ksplit = 1, int64_t split_stride = 0, const FastDyn& d = FastDyn{},
                      float* tail_part = nullptr, size_t tail_bytes = 0) {
     if (M <= 0 || N <= 0 || K <= 0) return FLCE_OK;
     if (!aligned(A, 16) || !aligned(B, 16)) return FLCE_ERR_ARG;
     ScopedKernelTimer timer(kind, s);
     FGArgs a{A, lda, B, ldb, C, ldc, Cin, ldcin, (int)M, (int)N, (int)K,
-             (int)((M + FG_BM - 1) / FG_BM), (int)((N + FG_BN - 1) / FG_BN), ksplit, split_stride,
+             (int)((M + tile - 1) / tile), (int)((N + tile - 1) / tile), ksplit, split_stride,
              d.rows, d.is_k, d.ksplit, d.first_live, d.launch, 0, 0, 1, tail_part,
              FG_GROUP_TILES, kind == FLCE_KIND_LOGITS_GEMM ? 1 : 0, 1};
     const int64_t total = (int64_t)a.tiles_m * a.tiles_n * ksplit;
     if (total >= ((int64_t)1 << 30)) return FLCE_ERR_SHAPE;   // the kernel counts tiles in 32 bits
     int64_t wgs_per_xcd = (total + FG_XCDS - 1) / FG_XCDS;
     const bool m_static = !(d.rows && !d.is_k);   // a dynamic M changes the tile count on the device
-    if (tail_part && ksplit == 1 && !d.ksplit && m_static) {
+    if (tile == 256 && tail_part && ksplit == 1 && !d.ksplit && m_static) {
         const TailPlan t = tail_plan(total, (K + FG_BK - 1) / FG_BK);
         if (t.s > 1 && (size_t)FG_XCDS * t.r * t.s * TAIL_BLOCK_BYTES <= tail_bytes) {
             a.tail_begin = t.begin;
@@ -230,7 +230,10 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
         }
     }
     const dim3 grid((unsigned)(wgs_per_xcd * FG_XCDS));
-    hipLaunchKernelGGL((gemm_bf16_256<OutT, InT, A_KM, B_KM>), grid, dim3(FG_THREADS), 0, s, a);
+    if (tile == 128)
+        hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, 128>), grid, dim3(FG_THREADS), 0, s, a);
+    else
+        hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, 256>), grid, dim3(FG_THREADS), 0, s, a);
     HIP_TRY(hipGetLastError());
     if (a.tail_s > 1) {
         hipLaunchKernelGGL((fg_tail_reduce_kernel<OutT, InT>), dim3((unsigned)(FG_XCDS * a.tail_r * 8)), dim3(256),
@@ -384,7 +387,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             tc = tv;
             dyn_m.rows = dyn_dx.rows = dyn_dw.rows = n_live;
             dyn_dw.is_k = 1;
-            dyn_dx.ksplit = dyn + DYN_DX_RANGES;
+            if (p.dx_tile == 256) dyn_dx.ksplit = dyn + DYN_DX_RANGES;
             dyn_dw.first_live = dyn + DYN_FIRST_LIVE;
             dyn_dw.launch = (int)c;
         }
@@ -415,7 +418,8 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         if (BF16 && p.fast_logits) {
             if constexpr (BF16)
                 FLCE_TRY((launch_gemm_fast<bf16_t, void, false, false>(
-                    FLCE_KIND_LOGITS_GEMM, Xc, H, W, H, Z, p.ldz, nullptr, 0, rows, V, H, s, 1, 0, dyn_m)));
+                    FLCE_KIND_LOGITS_GEMM, Xc, H, W, H, Z, p.ldz, nullptr, 0, rows, V, H, s, tuned_cut(rows, V, H, 1).tile,
+                    1, 0, dyn_m)));
         } else {
             FLCE_TRY((launch_gemm_guarded<T, T, false, false>(FLCE_KIND_LOGITS_GEMM, Xc, H, W, H, Z, p.ldz,
                                                               nullptr, nullptr, rows, V, H, s,
@@ -440,15 +444,17 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                         float* part = reinterpret_cast<float*>(ws + p.off_dxpart);
                         FLCE_TRY((launch_gemm_fast<float, void, false, true>(
                             FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, 0, rows, H, V, s,
-                            p.dx_ksplit, p.C * H, dyn_dx)));
+                            p.dx_tile, p.dx_ksplit, p.C * H, dyn_dx)));
                         FLCE_TRY(launch_splitk_reduce<bf16_t>(part, p.C * H, p.dx_ksplit, dXc, rows * H,
                                                               add_in_gemm, s, dyn_dx.ksplit));
                     } else if (add_in_gemm) {
                         FLCE_TRY((launch_gemm_fast<bf16_t, bf16_t, false, true>(
-                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, dXc, H, rows, H, V, s)));
+                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, dXc, H, rows, H, V, s,
+                            p.dx_tile)));
                     } else {
                         FLCE_TRY((launch_gemm_fast<bf16_t, void, false, true>(
-                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, nullptr, 0, rows, H, V, s, 1, 0,
+                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, nullptr, 0, rows, H, V, s,
+                            p.dx_tile, 1, 0,
                             dyn_m)));
                     }
                 }
@@ -497,21 +503,22 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             const bool fast = BF16 && (last ? p.fast_dw_last : p.fast_dw_full);
             if (fast) {
                 if constexpr (BF16) {
+                    const int dw_tile = tuned_cut(V, H, rows, 1).tile;
                     if (p.nchunks == 1) {
                         FLCE_TRY((launch_gemm_fast<bf16_t, void, true, true>(
-                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dW, H, nullptr, 0, V, H, rows, s, 1, 0,
+                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dW, H, nullptr, 0, V, H, rows, s, dw_tile, 1, 0,
                             dyn_dw, tail, p.tail_bytes)));
                     } else if (c == 0) {
                         FLCE_TRY((launch_gemm_fast<float, void, true, true>(
-                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dWacc, H, nullptr, 0, V, H, rows, s, 1, 0,
+                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dWacc, H, nullptr, 0, V, H, rows, s, dw_tile, 1, 0,
                             dyn_dw, tail, p.tail_bytes)));
                     } else if (!last) {
                         FLCE_TRY((launch_gemm_fast<float, float, true, true>(
-                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dWacc, H, dWacc, H, V, H, rows, s, 1, 0,
+                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dWacc, H, dWacc, H, V, H, rows, s, dw_tile, 1, 0,
                             dyn_dw, tail, p.tail_bytes)));
                     } else {   // last chunk: add the fp32 partial sums and write dW in bf16
                         FLCE_TRY((launch_gemm_fast<bf16_t, float, true, true>(
-                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dW, H, dWacc, H, V, H, rows, s, 1, 0,
+                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dW, H, dWacc, H, V, H, rows, s, dw_tile, 1, 0,
                             dyn_dw, tail, p.tail_bytes)));
                     }
                 }
@@ -927,7 +934,12 @@ size_t flce_logits_budget_for_workspace(int64_t BT, int64_t H, int64_t V, int dt
 
 int flce_dx_k_ranges(int64_t BT, int64_t H, int64_t V, int dtype) {
     if (check_dims(BT, H, V, dtype) != FLCE_OK) return 0;
-    return plan_for(BT, H, V, dtype).dx_ksplit;
+    const Plan p = plan_for(BT, H, V, dtype);
+    if (p.dx_tile != 128 || !p.fast_dx) return p.dx_ksplit;
+    // cut finer, into small tiles: the number the large tiles would take
+    const int64_t rows = p.nchunks > 1 ? p.C : BT;
+    return choose_ksplit(((rows + 255) / 256) * ((H + 255) / 256), (V + 63) / 64,
+                         max_dx_ranges(effective_budget(global_settings(), V, dtype), round_up(rows, 256), H));
 }
 
 int64_t flce_paper_chunk_rows(int64_t BT, int64_t H, int64_t V) {

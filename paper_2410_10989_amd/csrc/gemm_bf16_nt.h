@@ -8,7 +8,8 @@
 //     dX_c       = G W          A = G   row form,  B = W   column form (K = V)
 //     dW        += G^T X_c      A = G   column form, B = X_c column form (K = chunk rows)
 //
-// Shape of the kernel
+// Shape of the kernel (256 x 256 tiles; launches too small to fill the chip with those take
+// 128 x 128 tiles, see gemm_bf16 and tuned_cut)
 //  - workgroup = 256 threads = 4 wavefronts (2 x 2); macro tile 256 x 256, K step
 //    64; each wavefront owns 128 x 128 = 4 x 4 MFMA tiles, i.e. 256 fp32
 //    accumulator registers per lane (one wavefront per SIMD, full register file).
@@ -57,9 +58,10 @@
 // 256 * ldc * sizeof(element) < 2^31 for C and Cin.  M and N are arbitrary: tile rows /
 // columns past them hold zeros or stale values and only feed outputs that are never
 // stored.  K is arbitrary for a column-form operand (its K rows past K lie outside the
-// descriptor's range and read as zero); a row-form operand needs K % 64 == 0, or rows
-// that are allocated up to the next multiple of 64 and hold zeros there (the dlogits
-// chunk is kept that way); the last K step then multiplies zeros.
+// descriptor's range and read as zero); for a row-form operand the last K step fetches zeros for
+// the 16-byte pieces past K (FgOperand::before_step), so K % 8 == 0, or rows that hold zeros up to
+// the next multiple of 8 (the dlogits chunk is padded with zeros to a multiple of 64).  Measured at
+// 2047 x 1000 x 50257: logits 489 us (guarded kernel) -> 209.
 #pragma once
 #include <type_traits>
 
@@ -69,9 +71,9 @@
 namespace flce {
 
 constexpr int FG_BM = 256, FG_BN = 256, FG_BK = 64, FG_THREADS = 256;
-constexpr int FG_TILE_BYTES = FG_BM * FG_BK * 2;    // one operand tile of one K step: 32 KB
 constexpr int FG_SLOTS = 5;                         // ring of operand-tile slots
-constexpr int FG_LDS_BYTES = FG_SLOTS * FG_TILE_BYTES;   // 160 KB: the whole LDS of a CU
+constexpr int fg_slot_bytes(int tile) { return tile * FG_BK * 2; }   // one operand tile of one K step: 32 or 16 KB
+constexpr int fg_lds_bytes(int tile) { return FG_SLOTS * fg_slot_bytes(tile); }   // 160 KB, the whole LDS of a CU, or half of it
 // Tile order (FGArgs::group_m, group_cols, xcd_interleave).  The 32 tiles an XCD runs at a time
 // are group_m tile rows x 32 / group_m tile columns (or the other way round), and with
 // xcd_interleave the 8 XCDs run 8 such rounds that follow one another in the order.  What the
@@ -149,11 +151,20 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t fg_make_rsrc(const void* base,
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
+// 16 bytes per lane from the buffer to LDS (lane l to dst + 16 l).  A free function: inside a
+// class template the host pass cannot type-check the builtin and silently drops the launch stubs
+// of the kernels that use it.
+__device__ __forceinline__ void fg_load_lds(__amdgpu_buffer_rsrc_t rsrc, unsigned char* dst, int voff, int soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (fg_lds_ptr)dst, 16, voff, soff, 0, 0);
+}
+
 // One GEMM operand: where its tiles come from in global memory, where they land
 // in LDS, and how MFMA fragments (32 rows x 16 K, lane l = row l%32, K values
 // 8*(l/32) .. +7) are read back.  KM = false: row form, KM = true: column form.
-template <bool KM>
+template <bool KM, int TILE>
 struct FgOperand {
+    static constexpr int NL = TILE / 32;   // loads a wavefront issues per tile
+    static constexpr int W = TILE / 64;    // fragments per wavefront
     // The buffer descriptor covers the operand from K step kt_base on; the loads of K
     // step kt add (kt - kt_base) * kstep as scalar offset.  All offsets are 32-bit, so
     // the descriptor is moved forward every seg_steps K steps (a rarely taken uniform
@@ -162,13 +173,15 @@ struct FgOperand {
     int64_t bytes;                // bytes from base0 to the end of the operand's valid range
     __amdgpu_buffer_rsrc_t rsrc;
     int kt_base, seg_steps;
-    int off[8];   // per-lane byte offset of each of the 8 loads a wavefront issues per tile
+    int kt_tail;  // row form: the K step that holds the last, partial group of 64 K values, if any
+    int kt_next;  // before_step has nothing to do before this K step
+    int off[NL];  // per-lane byte offset of each of the loads a wavefront issues per tile
     int kstep;    // bytes between consecutive K steps
     int rd[4];    // per-lane LDS byte offsets of the fragment reads
 
     // base/ld: the matrix; r0: first row (row form) or column (column form) of this
-    // tile; extent: number of rows / columns of the matrix; sub: which 128-wide half
-    // of the tile this wavefront multiplies.
+    // tile; extent: number of rows / columns of the matrix; sub: which half of the tile
+    // this wavefront multiplies.
     __device__ __forceinline__ void init(const bf16_t* base, int64_t ld, int r0, int extent, int K,
                                          int tid, int sub) {
         const int lane = tid & 63, wave = tid >> 6;
@@ -177,30 +190,30 @@ struct FgOperand {
             // a wavefront-wide load = 8 consecutive tile rows of 128 B; lane l owns the
             // physical position (row l/8, piece l%8) and fetches the logical piece
             // (l%8) ^ swizzle(row); wavefront w fills rows 8w..8w+7 of every 32-row group
-            const int rows = min(FG_BM, extent - r0);
+            const int rows = min(TILE, extent - r0);
             base0 = reinterpret_cast<const unsigned char*>(base + (int64_t)r0 * ld);
             bytes = (int64_t)rows * ildb;
             const int ld_row = tid >> 3;
             const int piece = (tid & 7) ^ ((ld_row >> 1) & 7);
 #pragma unroll
-            for (int r = 0; r < 8; ++r) off[r] = (ld_row + 32 * r) * ildb + piece * 16;
+            for (int r = 0; r < NL; ++r) off[r] = (ld_row + 32 * r) * ildb + piece * 16;
             kstep = FG_BK * 2;
             const int frow = lane & 31, fhalf = lane >> 5, fsw = (frow >> 1) & 7;
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk)
-                rd[kk] = (sub * 128 + frow) * 128 + ((((kk << 1) | fhalf) ^ fsw) << 4);
+                rd[kk] = (sub * (TILE / 2) + frow) * 128 + ((((kk << 1) | fhalf) ^ fsw) << 4);
         } else {
-            // a wavefront-wide load = 2 consecutive K rows of 512 B; load r of wavefront
-            // w covers K rows 8r + 2w and 8r + 2w + 1; lane l owns the physical 16-byte
-            // piece l%32 of row l/32 and fetches the logical 64-byte chunk
-            // (piece / 4) ^ f(k), f(k) = k%4 + 4 * ((k/8) % 2)
+            // a wavefront-wide load = 2 (TILE 256) or 4 (TILE 128) consecutive K rows of 512 or
+            // 256 B; load r of wavefront w covers the K rows from (4 r + w) * 2 or * 4 on; the
+            // lane owns one physical 16-byte piece of one row and fetches the logical 64-byte
+            // chunk (piece / 4) ^ f(k), f(k) = k%4 + 4 * ((k/8) % 2), for TILE 128 (4 chunks) k%4
+            constexpr int LPR = TILE / 8, RPL = 64 / LPR;   // lanes per K row, K rows per load
             base0 = reinterpret_cast<const unsigned char*>(base + r0);
             bytes = ((int64_t)K * ld - r0) * 2;
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const int k = 8 * r + 2 * wave + (lane >> 5);
-                const int f = (k & 3) | (((k >> 3) & 1) << 2);
-                const int chunk = ((lane & 31) >> 2) ^ f;
+            for (int r = 0; r < NL; ++r) {
+                const int k = (4 * r + wave) * RPL + lane / LPR;
+                const int chunk = ((lane % LPR) >> 2) ^ fold(k & 3, (k >> 3) & 1);
                 off[r] = k * ildb + chunk * 64 + (lane & 3) * 16;
             }
             kstep = FG_BK * ildb;
@@ -208,13 +221,20 @@ struct FgOperand {
             // 8*(g/2) + {0..3} (+4 for the second read), columns 16*(g%2) + 0..15 of the
             // 32-wide fragment; source lane s = l%16 supplies row s/4, columns 4*(s%4)..+3
             const int g = lane >> 4, s = lane & 15;
-            const int f = (s >> 2) | ((g >> 1) << 2);
+            const int f = fold(s >> 2, g >> 1);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                rd[i] = (8 * (g >> 1) + (s >> 2)) * 512 + (((sub * 4 + i) ^ f) * 64) + 32 * (g & 1) +
+            for (int i = 0; i < W; ++i)
+                rd[i] = (8 * (g >> 1) + (s >> 2)) * (2 * TILE) + (((sub * W + i) ^ f) * 64) + 32 * (g & 1) +
                         8 * (s & 3);
         }
+        // A row-form operand whose K is not a multiple of 64: in the last K step, the lanes whose
+        // 16-byte piece lies past K fetch from beyond the descriptor, i.e. zero (a piece that K
+        // cuts has to hold zeros past it: none when K % 8 == 0).
+        kt_tail = (!KM && (K & (FG_BK - 1))) ? K / FG_BK : 0x7fffffff;
+        piece_past = !KM && ((tid & 7) ^ (((tid >> 3) >> 1) & 7)) * 8 >= (K & (FG_BK - 1));
     }
+    bool piece_past;
+    static __device__ __forceinline__ int fold(int k4, int k8) { return TILE == 256 ? k4 | (k8 << 2) : k4; }
 
     __device__ __forceinline__ void make_rsrc() {
         const int64_t left = bytes < 0 ? 0 : (bytes > 0xFFFFFFFFll ? 0xFFFFFFFFll : bytes);
@@ -226,34 +246,44 @@ struct FgOperand {
         bytes -= (int64_t)k_begin * kstep;
         kt_base = 0;
         seg_steps = max(1, (1 << 30) / kstep);
+        if (kt_tail != 0x7fffffff) kt_tail -= k_begin;
+        kt_next = min(seg_steps, kt_tail);
         make_rsrc();
     }
     // call before the first load of K step kt (kt never decreases)
     __device__ __forceinline__ void before_step(int kt) {
-        if (kt - kt_base >= seg_steps) {
-            base0 += (int64_t)seg_steps * kstep;
-            bytes -= (int64_t)seg_steps * kstep;
-            kt_base += seg_steps;
-            make_rsrc();
+        if (kt >= kt_next) {   // uniform, rarely taken
+            if (kt - kt_base >= seg_steps) {
+                base0 += (int64_t)seg_steps * kstep;
+                bytes -= (int64_t)seg_steps * kstep;
+                kt_base += seg_steps;
+                make_rsrc();
+            }
+            if constexpr (!KM) {
+                if (kt >= kt_tail) {   // (a row-form tile's extent is below 2^30 bytes)
+#pragma unroll
+                    for (int r = 0; r < NL; ++r) off[r] = piece_past ? 0x7fffffff : off[r];
+                    kt_tail = 0x7fffffff;
+                }
+            }
+            kt_next = min(kt_base + seg_steps, kt_tail);
         }
     }
 
-    // start the 8 loads of this wavefront for K step kt into ring slot `slot`
+    // start the loads of this wavefront for K step kt into ring slot `slot`
     __device__ __forceinline__ void load(unsigned char* smem, int slot, int kt, int uwave) {
         before_step(kt);
         const int soff = (kt - kt_base) * kstep;
-        unsigned char* dst = smem + slot * FG_TILE_BYTES + uwave * 1024;
+        unsigned char* dst = smem + slot * fg_slot_bytes(TILE) + uwave * 1024;
 #pragma unroll
-        for (int r = 0; r < 8; ++r)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (fg_lds_ptr)(dst + r * 4096), 16, off[r], soff,
-                                                     0, 0);
+        for (int r = 0; r < NL; ++r)
+            fg_load_lds(rsrc, dst + r * 4096, off[r], soff);
     }
 
-    // start one of the 8 loads of this wavefront for K step kt into ring slot `slot`
+    // start one of the loads of this wavefront for K step kt into ring slot `slot`
     __device__ __forceinline__ void load_one(unsigned char* smem, int slot, int kt, int uwave, int r) const {
-        unsigned char* dst = smem + slot * FG_TILE_BYTES + uwave * 1024 + r * 4096;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (fg_lds_ptr)dst, 16, off[r], (kt - kt_base) * kstep,
-                                                 0, 0);
+        unsigned char* dst = smem + slot * fg_slot_bytes(TILE) + uwave * 1024 + r * 4096;
+        fg_load_lds(rsrc, dst, off[r], (kt - kt_base) * kstep);
     }
 };
 
@@ -265,16 +295,16 @@ template <> struct FgRaw<true> { s16x4 lo, hi; };
 
 // Issue the LDS read(s) of fragment I (32-row block) of K sub-step KK; `slot_addr`
 // is the LDS byte address of the ring slot.
-template <int KK, int I>
-__device__ __forceinline__ void fg_issue(FgRaw<false>& r, const FgOperand<false>& op, unsigned slot_addr) {
+template <int KK, int I, int TILE>
+__device__ __forceinline__ void fg_issue(FgRaw<false>& r, const FgOperand<false, TILE>& op, unsigned slot_addr) {
     const unsigned addr = slot_addr + (unsigned)op.rd[KK];
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r.v) : "v"(addr), "n"(I * 4096));
 }
-template <int KK, int I>
-__device__ __forceinline__ void fg_issue(FgRaw<true>& r, const FgOperand<true>& op, unsigned slot_addr) {
+template <int KK, int I, int TILE>
+__device__ __forceinline__ void fg_issue(FgRaw<true>& r, const FgOperand<true, TILE>& op, unsigned slot_addr) {
     const unsigned addr = slot_addr + (unsigned)op.rd[I];
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.lo) : "v"(addr), "n"(KK * 8192));
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.hi) : "v"(addr), "n"(KK * 8192 + 2048));
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.lo) : "v"(addr), "n"(KK * 32 * TILE));
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.hi) : "v"(addr), "n"(KK * 32 * TILE + 8 * TILE));
 }
 
 // Wait until every LDS read issued so far has returned.  The registers are tied
@@ -286,8 +316,12 @@ __device__ __forceinline__ void fg_tie(FgRaw<true> (&r)[4]) {
     asm volatile("" : "+v"(r[0].lo), "+v"(r[0].hi), "+v"(r[1].lo), "+v"(r[1].hi), "+v"(r[2].lo),
                  "+v"(r[2].hi), "+v"(r[3].lo), "+v"(r[3].hi));
 }
-template <bool AKM, bool BKM>
-__device__ __forceinline__ void fg_wait(FgRaw<AKM> (&ra)[4], FgRaw<BKM> (&rb)[4]) {
+__device__ __forceinline__ void fg_tie(FgRaw<false> (&r)[2]) { asm volatile("" : "+v"(r[0].v), "+v"(r[1].v)); }
+__device__ __forceinline__ void fg_tie(FgRaw<true> (&r)[2]) {
+    asm volatile("" : "+v"(r[0].lo), "+v"(r[0].hi), "+v"(r[1].lo), "+v"(r[1].hi));
+}
+template <bool AKM, bool BKM, int W>
+__device__ __forceinline__ void fg_wait(FgRaw<AKM> (&ra)[W], FgRaw<BKM> (&rb)[W]) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     fg_tie(ra);
     fg_tie(rb);
@@ -325,16 +359,18 @@ template <> struct FgInSize<void> { static constexpr int value = 4; };
 // or 8 times fewer memory instructions, each writing whole row segments.  Loads and stores go
 // through buffer descriptors that cover the tile's valid rows (rows past them are dropped by
 // the range check).  OutT: element type of C; InT: of the addend (void: none).
-template <typename OutT, typename InT>
+template <typename OutT, typename InT, int TILE>
 struct FgOut {
+    static constexpr int WN = TILE / 2;                // rows and columns of a wavefront's sub-tile
+    static constexpr int W = TILE / 64;                // passes
     static constexpr bool HAS_IN = !std::is_void<InT>::value;
     static constexpr int IS = FgInSize<InT>::value;
     static constexpr int ES = (int)sizeof(OutT);
     static constexpr int EW = 16 / ES;                 // output elements per lane and access: 4 or 8
-    static constexpr int LANES_PER_ROW = 128 / EW;     // 32 or 16
-    static constexpr int ROWS_PER_ACCESS = 64 / LANES_PER_ROW;   // rows one wavefront-wide access covers: 2 or 4
-    static constexpr int PITCH = 128 + 4;              // fp32 words per staged row: 16 lanes' 16-byte writes of one column group hit 64 different banks
-    static constexpr int NACC = 32 / ROWS_PER_ACCESS;  // accesses per 32-row pass: 16 or 8
+    static constexpr int LANES_PER_ROW = WN / EW;      // 32 or 16 (TILE 128: 16 or 8)
+    static constexpr int ROWS_PER_ACCESS = 64 / LANES_PER_ROW;   // rows one wavefront-wide access covers: 2 or 4 (4 or 8)
+    static constexpr int PITCH = WN + 4;               // fp32 words per staged row: 16 lanes' 16-byte writes of one column group hit 64 different banks
+    static constexpr int NACC = 32 / ROWS_PER_ACCESS;  // accesses per 32-row pass: 16 or 8 (8 or 4)
     static constexpr int INW = HAS_IN ? EW * IS / 4 : 1;   // dwords of addend per lane and access
 
     __amdgpu_buffer_rsrc_t rsrc_c, rsrc_in;
@@ -361,11 +397,11 @@ struct FgOut {
         rsrc_in = rsrc_c;
         if constexpr (HAS_IN)   // a range of zero bytes makes every addend load return zero without touching memory
             rsrc_in = fg_make_rsrc(cin_tile, use_in ? (uint32_t)rows * (uint32_t)ldcin * (uint32_t)IS : 0u);
-        stage = reinterpret_cast<float*>(smem + uwave * (FG_LDS_BYTES / 4));   // 40 KB per wavefront
+        stage = reinterpret_cast<float*>(smem + uwave * (fg_lds_bytes(TILE) / 4));   // 40 (20) KB per wavefront
         // output mapping of the lane: row (inside a group of ROWS_PER_ACCESS) and first column
         orow = lane / LANES_PER_ROW;
         ocol = (lane % LANES_PER_ROW) * EW;
-        colw = col0 + uwn * 128;                       // first column of the wavefront's sub-tile
+        colw = col0 + uwn * WN;                       // first column of the wavefront's sub-tile
         col_ok = colw + ocol < ((n_cols + EW - 1) / EW) * EW;
         lane_off = (orow * ldc + ocol) * ES;
         lane_off_in = (orow * ldcin + ocol) * IS;
@@ -375,7 +411,7 @@ struct FgOut {
     template <int B>
     __device__ __forceinline__ void load_addend(int pass) {
         if constexpr (HAS_IN) {
-            const int row0 = uwm * 128 + pass * 32;
+            const int row0 = uwm * WN + pass * 32;
 #pragma unroll
             for (int k = 0; k < NACC; ++k) {
                 const int soff = ((row0 + k * ROWS_PER_ACCESS) * ldcin + colw) * IS;
@@ -401,21 +437,21 @@ struct FgOut {
         }
     }
 
-    // The four passes; load_addend<0>(0) has been issued before.
-    __device__ __forceinline__ void write(f32x16 (&acc)[4][4]) {
+    // The passes; load_addend<0>(0) has been issued before.
+    __device__ __forceinline__ void write(f32x16 (&acc)[W][W]) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {                          // pass: rows 32 i .. 32 i + 31 of the sub-tile
-            const int row0 = uwm * 128 + i * 32;
+        for (int i = 0; i < W; ++i) {                          // pass: rows 32 i .. 32 i + 31 of the sub-tile
+            const int row0 = uwm * WN + i * 32;
             // the next pass's addend is requested before this pass is staged: it arrives while this
             // pass goes through LDS
             if (i == 0) load_addend<1>(1);
-            if (i == 1) load_addend<0>(2);
-            if (i == 2) load_addend<1>(3);
+            if (W > 2 && i == 1) load_addend<0>(2);
+            if (W > 2 && i == 2) load_addend<1>(3);
             uint32_t (&old)[NACC][INW] = old2[HAS_IN ? (i & 1) : 0];
             // stage the pass: the lane holds row frow and, per group of four registers, the four
             // consecutive columns 32 j + 8 (g/4) + 4 fhalf .. + 3: one 16-byte LDS write per group
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < W; ++j)
 #pragma unroll
                 for (int g4 = 0; g4 < 4; ++g4) {
                     // read the elements into scalars first: a bit_cast applied directly
@@ -513,11 +549,17 @@ __device__ __forceinline__ void fg_tile_origin(int seq, int tiles_m, int tiles_n
 }
 
 // InT: element type of the addend Cin (float or bf16_t), void for no addend.
-template <typename OutT, typename InT, bool A_KM, bool B_KM>
-__global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
+// TILE: 256, or 128 for launches whose 256 x 256 tiles would leave CUs idle (see tuned_cut):
+// 2 x 2 MFMA tiles per wavefront, half the LDS, two workgroups per CU that fill each other's
+// waits; its LDS reads (as many per K step for a quarter of the arithmetic) are as tight as the
+// matrix pipe.
+template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE>
+__global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGArgs a) {
     constexpr bool HAS_IN = !std::is_void<InT>::value;
     constexpr int IS = FgInSize<InT>::value;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[FG_LDS_BYTES];
+    constexpr int W = TILE / 64;              // 32 x 32 MFMA tiles per wavefront and direction
+    constexpr int SLOT = fg_slot_bytes(TILE);
+    __shared__ __attribute__((aligned(16))) unsigned char smem[fg_lds_bytes(TILE)];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -530,7 +572,7 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
     // The tile sequence covers the live rows only (a dynamic M can be smaller than the M the
     // grid was sized for): the live tiles are dealt evenly to the XCDs, and the workgroups
     // that are left over have the highest ids, are dispatched last and return at once.
-    const int tiles_m = (M + FG_BM - 1) / FG_BM;
+    const int tiles_m = (M + TILE - 1) / TILE;
     const int tiles = tiles_m * a.tiles_n;
     const int total = tiles * ksplit;
     const int per_xcd = (total + FG_XCDS - 1) / FG_XCDS;
@@ -538,7 +580,7 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
     int in_xcd = (int)blockIdx.x / FG_XCDS;
     // a tile of the last round that is cut along K: range tail_i of tail_n, partial block tail_blk
     int tail_i = 0, tail_n = 1, tail_blk = 0;
-    if (a.tail_s > 1 && in_xcd >= a.tail_begin) {
+    if (TILE == 256 && a.tail_s > 1 && in_xcd >= a.tail_begin) {
         const int u = in_xcd - a.tail_begin;
         if (u >= a.tail_r * a.tail_s) return;
         const int slot = u % a.tail_r;
@@ -552,38 +594,38 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
     if (seq_all >= total) return;
     const int split = seq_all / tiles;
     int m0, n0;
-    fg_tile_origin<FG_BM>(seq_all - split * tiles, tiles_m, a.tiles_n, a.group_m, a.group_cols, m0, n0);
+    fg_tile_origin<TILE>(seq_all - split * tiles, tiles_m, a.tiles_n, a.group_m, a.group_cols, m0, n0);
 
-    FgOperand<A_KM> opa;
-    FgOperand<B_KM> opb;
+    FgOperand<A_KM, TILE> opa;
+    FgOperand<B_KM, TILE> opb;
     opa.init(a.A, a.lda, m0, M, K, tid, wm);
     opb.init(a.B, a.ldb, n0, a.N, K, tid, wn);
     const int uwave = __builtin_amdgcn_readfirstlane(wave);
 
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-    f32x16 acc[4][4];
+    f32x16 acc[W][W];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < W; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < W; ++j)
 #pragma unroll
             for (int g = 0; g < 16; ++g) acc[i][j][g] = 0.f;
 
-    // two register buffers of in-flight fragments (4 of A, 4 of B each)
-    FgRaw<A_KM> raw_a[2][4];
-    FgRaw<B_KM> raw_b[2][4];
+    // two register buffers of in-flight fragments (W of A, W of B each)
+    FgRaw<A_KM> raw_a[2][W];
+    FgRaw<B_KM> raw_b[2][W];
 
     // Workgroup barrier of the pipeline.  Loads complete in order and every
-    // wavefront issues 8 per slot, so "at most 8 outstanding" means everything
+    // wavefront issues NL = TILE / 32 per slot, so "at most NL outstanding" means everything
     // but the youngest slot (the A tile two steps ahead) has landed.  All LDS
     // reads of the step are complete as well, so its two slots can be refilled.
     auto pipeline_barrier = [&]() {
-        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(TILE / 32) : "memory");
     };
 
     // One quarter of a K step: the 16 MFMAs of one K=16 sub-step on the fragments in
-    // register buffer MB, interleaved with the 8 fragment reads of sub-step KK of the
+    // register buffer MB (TILE 256; 4 for TILE 128), interleaved with the 8 (4) fragment reads of sub-step KK of the
     // tile in slots (SA, SB) into buffer 1-MB (one fragment per MFMA, in the order
     // a0 b0 b1 b2 b3 a1 a2 a3 in which the next quarter consumes them), and with 4 of
     // the 16 loads of the step, one behind every fourth MFMA (DMA = 1: loads R0..R0+3
@@ -597,20 +639,26 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
         if constexpr (DMA == 1 && R0 == 0) opb.before_step(kt);
         if constexpr (DMA == 2 && R0 == 0) opa.before_step(kt);
         fg_wait(raw_a[MB], raw_b[MB]);
-        bf16x8 fa[4], fb[4];
+        bf16x8 fa[W], fb[W];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < W; ++i) {
             fa[i] = fg_value(raw_a[MB][i]);
             fb[i] = fg_value(raw_b[MB][i]);
         }
-        const unsigned sa_addr = lds0 + SA * FG_TILE_BYTES, sb_addr = lds0 + SB * FG_TILE_BYTES;
+        const unsigned sa_addr = lds0 + SA * SLOT, sb_addr = lds0 + SB * SLOT;
         __builtin_amdgcn_sched_barrier(0);
 #define FG_MFMA(q) \
-        acc[(q) >> 2][(q) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[(q) & 3], fa[(q) >> 2], acc[(q) >> 2][(q) & 3], 0, 0, 0)
+        acc[(q) / W][(q) % W] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[(q) % W], fa[(q) / W], acc[(q) / W][(q) % W], 0, 0, 0)
 #define FG_DMA(n)                                                          \
         if constexpr (DMA == 1) opb.load_one(smem, SD, kt, uwave, R0 + (n));   \
         if constexpr (DMA == 2) opa.load_one(smem, SD, kt, uwave, R0 + (n))
 #define FG_END __builtin_amdgcn_sched_barrier(0)
+        if constexpr (W == 2) {
+            FG_MFMA(0); fg_issue<KK, 0>(raw_a[RB][0], opa, sa_addr); fg_issue<KK, 0>(raw_b[RB][0], opb, sb_addr); FG_END;
+            FG_MFMA(1); fg_issue<KK, 1>(raw_b[RB][1], opb, sb_addr); FG_DMA(0); FG_END;
+            FG_MFMA(2); fg_issue<KK, 1>(raw_a[RB][1], opa, sa_addr); FG_END;
+            FG_MFMA(3); FG_DMA(1); FG_END;
+        } else {
         FG_MFMA(0);  fg_issue<KK, 0>(raw_a[RB][0], opa, sa_addr); FG_END;
         FG_MFMA(1);  fg_issue<KK, 0>(raw_b[RB][0], opb, sb_addr); FG_END;
         FG_MFMA(2);  fg_issue<KK, 1>(raw_b[RB][1], opb, sb_addr); FG_DMA(0); FG_END;
@@ -627,6 +675,7 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
         FG_MFMA(13); FG_END;
         FG_MFMA(14); FG_DMA(3); FG_END;
         FG_MFMA(15); FG_END;
+        }
 #undef FG_MFMA
 #undef FG_DMA
 #undef FG_END
@@ -648,7 +697,7 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
         using SB = std::integral_constant<int, (2 * PH + 1) % 5>;
         using SB1 = std::integral_constant<int, (2 * PH + 3) % 5>;
         using SA2 = std::integral_constant<int, (2 * PH + 4) % 5>;
-        using I4 = std::integral_constant<int, 4>;
+        using I4 = std::integral_constant<int, TILE / 64>;   // half of a tile's loads
         quarter(I1{}, I0{}, SA{}, SB{}, I1{}, SB1{}, I0{}, t + 1);   // MFMA: sub-step 3 of tile t-1
         quarter(I0{}, I1{}, SA{}, SB{}, I1{}, SB1{}, I4{}, t + 1);   // MFMA: sub-step 0
         quarter(I1{}, I2{}, SA{}, SB{}, I2{}, SA2{}, I0{}, t + 2);   // MFMA: sub-step 1
@@ -668,7 +717,7 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
     opb.load(smem, 1, 0, uwave);
     opa.load(smem, 2, 1, uwave);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {        // the first step has no previous sub-step: add zero
+    for (int i = 0; i < W; ++i) {        // the first step has no previous sub-step: add zero
         fg_zero(raw_a[1][i]);
         fg_zero(raw_b[1][i]);
     }
@@ -689,23 +738,23 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
     // partial block (256 x 256, dense).  The first addend slice is requested before the last
     // MFMAs.
     const int uwm = __builtin_amdgcn_readfirstlane(wm), uwn = __builtin_amdgcn_readfirstlane(wn);
-    FgOut<OutT, InT> out;
-    FgOut<float, void> part;
-    if (tail_n > 1) {
+    FgOut<OutT, InT, TILE> out;
+    FgOut<float, void, TILE> part;
+    if (TILE == 256 && tail_n > 1) {
         part.init(a.tail_part + (size_t)tail_blk * FG_TAIL_BLOCK_FLOATS, FG_BN, nullptr, 0, false, FG_BM, 0, FG_BN,
                   smem, lane, uwave, uwm, uwn);
     } else {
         out.init(static_cast<OutT*>(a.C) + (int64_t)split * a.split_stride + (int64_t)m0 * a.ldc, (int)a.ldc,
                  HAS_IN ? static_cast<const unsigned char*>(a.Cin) + (int64_t)m0 * a.ldcin * IS : nullptr,
-                 (int)a.ldcin, use_in, min(FG_BM, M - m0), n0, a.N, smem, lane, uwave, uwm, uwn);
+                 (int)a.ldcin, use_in, min(TILE, M - m0), n0, a.N, smem, lane, uwave, uwm, uwn);
         out.template load_addend<0>(0);
     }
     {   // sub-step 3 of the last tile
         fg_wait(raw_a[1], raw_b[1]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < W; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < W; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     fg_value(raw_b[1][j]), fg_value(raw_a[1][i]), acc[i][j], 0, 0, 0);
     }
@@ -715,7 +764,7 @@ __global__ __launch_bounds__(FG_THREADS) void gemm_bf16_256(FGArgs a) {
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 
     // ---- epilogue (see FgOut) ----
-    if (tail_n > 1) part.write(acc); else out.write(acc);
+    if (TILE == 256 && tail_n > 1) part.write(acc); else out.write(acc);
 }
 
 // Second step of a launch whose last round was cut along K: adds the tail_s fp32 partial

@@ -130,10 +130,10 @@ inline int max_dx_ranges(size_t budget_bytes, int64_t rows, int64_t H) {
 // time, so 512 workgroups fill the chip; 128 x 128 tiles while they (times at most max_ranges
 // K ranges of at least 512 elements) come to a workgroup per CU, else 64 x 64 tiles and ranges
 // of at least 256 elements.
-struct GuardedCut {
+struct ProductCut {
     int tile, ranges;
 };
-inline GuardedCut guarded_cut(int64_t M, int64_t N, int64_t K, int64_t max_ranges) {
+inline ProductCut guarded_cut(int64_t M, int64_t N, int64_t K, int64_t max_ranges) {
     auto ranges = [&](int64_t tiles, int64_t min_k) {
         return std::max<int64_t>(1, std::min(std::min(max_ranges, 512 / tiles), K / min_k));
     };
@@ -144,12 +144,41 @@ inline GuardedCut guarded_cut(int64_t M, int64_t N, int64_t K, int64_t max_range
     return {64, (int)ranges(((M + 63) / 64) * ((N + 63) / 64), 256)};
 }
 
-// The dX product of a chunk (rows x H output, K = V): tile size of the guarded kernel and K
-// ranges.  The tuned kernel works on 256 x 256 tiles and K steps of 64.
-inline GuardedCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes) {
-    if (tuned)
-        return {256, choose_ksplit(((rows + 255) / 256) * ((H + 255) / 256), (V + 63) / 64,
-                                   max_dx_ranges(budget_bytes, round_up(rows, 256), H))};
+// Tile size and K ranges of a product on the tuned bf16 kernel, by the time (ns) a launch takes:
+// tiles run in rounds of 256 CUs; a 256 x 256 tile takes 1.55 us per K step of 64 plus 4 us, a
+// 128 x 128 tile 0.53 us per step (its operands come from L2 at 15 TB/s over the chip, twice the
+// bytes per operation) plus 0.65 us.  Measured (M x N x K, 256-tiles / 128-tiles, us):
+//   1024 x 8192 x 512 (logits)  18.8 / 12.8      4096 x 32000 x 4096 (logits)  809 / 1104
+//   2048 x 4096 x 1024 (logits) 31.9 / 21.6      2048 x 8192 x 1024 (logits)  34.9 / 37.6
+//   8192 x 512 x 1024 (dW)      24.4 / 12.1      50257 x 1000 x 2047 (dW)      202 / 217
+//   1024 x 512 x 8192 (dX)      67.1 (2 ranges) / 20.3, 14.8, 18.8 (4, 8, 16 ranges)
+// so the small tiles serve outputs that do not fill a first round or two of large ones.  Cutting
+// K costs a second launch and the fp32 partial results, written and read at about 8 TB/s.  The
+// large tiles keep at least 64 K steps per range (choose_ksplit); the small ones 8.
+inline int64_t rounds_of_256(int64_t n) { return (n + 255) / 256; }
+inline int64_t cut_ns(int64_t tiles, int64_t side, int64_t ranges) {
+    return ranges > 1 ? 4000 + tiles * side * side * ranges / 1000 : 0;
+}
+inline ProductCut tuned_cut(int64_t M, int64_t N, int64_t K, int64_t max_ranges) {
+    const int64_t steps = (K + 63) / 64;
+    const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    const int s256 = choose_ksplit(t256, steps, (int)max_ranges);
+    const int64_t ns256 = rounds_of_256(t256 * s256) * (1550 * ((steps + s256 - 1) / s256) + 4000) + cut_ns(t256, 256, s256);
+    ProductCut best{256, s256};
+    int64_t best_ns = ns256;
+    for (int64_t r = 1; r <= max_ranges && (r == 1 || steps / r >= 8); ++r) {
+        const int64_t ns = rounds_of_256(t128 * r) * (530 * ((steps + r - 1) / r) + 650) + cut_ns(t128, 128, r);
+        if (ns < best_ns) {
+            best_ns = ns;
+            best = {128, (int)r};
+        }
+    }
+    return best;
+}
+
+// The dX product of a chunk (rows x H output, K = V): tile size and K ranges.
+inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes) {
+    if (tuned) return tuned_cut(rows, H, V, max_dx_ranges(budget_bytes, round_up(rows, 256), H));
     return guarded_cut(rows, H, V, max_dx_ranges(budget_bytes, round_up(rows, 128), H));
 }
 
@@ -167,7 +196,7 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     p.fast_logits = p.fast_dx = p.fast_dw_full = p.fast_dw_last = false;
     if (dtype != 0) {
         const bool out_ok = 256 * H * 4 < ((int64_t)1 << 31);
-        p.fast_logits = (H % 64 == 0) && fits_row_form(H, H) && 256 * p.ldz * 2 < ((int64_t)1 << 31);
+        p.fast_logits = (H % 8 == 0) && fits_row_form(H, H) && 256 * p.ldz * 2 < ((int64_t)1 << 31);
         // K of the dX product is V: the dlogits rows are padded with zeros to ldz, W is read
         // K-major; K of the dW product is the chunk's row count, both operands K-major: any
         // V and any row count do
@@ -180,7 +209,7 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     }
     {
         const int64_t rows = p.nchunks > 1 ? p.C : rows_last;
-        const GuardedCut cut = dx_cut(p.fast_dx, rows, H, V, budget_bytes);
+        const ProductCut cut = dx_cut(p.fast_dx, rows, H, V, budget_bytes);
         p.dx_tile = cut.tile;
         p.dx_ksplit = cut.ranges;
     }
