@@ -31,6 +31,7 @@ namespace {
 constexpr int MAX_DEVICES = 64;
 constexpr int64_t MAX_DIM = (int64_t)1 << 30;      // per-dimension limit, keeps int tile math safe
 constexpr int64_t CE_ROWS_PER_LAUNCH = 65536;
+constexpr int64_t CE_CACHE_BYTES = (int64_t)256 << 20;   // memory-side cache
 constexpr int64_t MAX_GRID_X = 0x7fffffff;        // workgroups along grid x
 constexpr size_t AUTO_BUDGET_BYTES = (size_t)1 << 30;
 constexpr int64_t AUTO_BUDGET_MIN_ROWS = 4096;
@@ -249,25 +250,20 @@ template <typename T>
 int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int64_t V,
                    int zero_pad, int64_t ignore_index, DeviceHeader* hdr, float* row_loss,
                    hipStream_t s, const int* n_rows = nullptr, bool timed = true, float* mean_out = nullptr) {
-    const bool vec = aligned(Z, 16) && ((ldz * sizeof(T)) % 16 == 0);
     ScopedKernelTimer timer(timed ? FLCE_KIND_CE_ROWS : -1, s);
-    // Rows of whole 16-byte vectors take the kernel that keeps the row in registers between
-    // its two sweeps, in the shape that fits the row: 256 threads x 12 vectors up to 48 KB,
-    // 512 x 12 up to 96 KB, 1024 x 16 beyond (the first 256 KB cached).  Measured, 4096 rows
-    // of bf16, kernel alone, TB/s of algorithmic traffic: 5.3 at 16 KB rows, 6.3-6.7 from
-    // 32 KB to 96 KB, 5.0-5.4 from 128 KB to 256 KB; two plain sweeps: 3.4-4.7.
+    // shape by row length, nontemporal accesses by size: see ce_rows_kernel
     const int64_t row_bytes = V * (int64_t)sizeof(T);
-#define CE_CACHED(TH, NV)                                                                              \
-    hipLaunchKernelGGL((ce_rows_cached_kernel<T, TH, NV>), dim3((unsigned)rows), dim3(TH), 0, s, Z, ldz, \
+    const bool nt = rows * row_bytes > CE_CACHE_BYTES;
+#define CE_LAUNCH(TH, NV, NT)                                                                          \
+    hipLaunchKernelGGL((ce_rows_kernel<T, TH, NV, NT>), dim3((unsigned)rows), dim3(TH), 0, s, Z, ldz,  \
                        targets, (int)V, zero_pad, ignore_index, hdr, row_loss, n_rows)
-    if (vec && row_bytes > 98304) CE_CACHED(RC_THREADS, RC_NV);
-    else if (vec && row_bytes > 49152) CE_CACHED(RM_THREADS, RM_NV);
-    else if (vec) CE_CACHED(RS_THREADS, RS_NV);
-#undef CE_CACHED
-    else
-        hipLaunchKernelGGL((ce_rows_inplace_kernel<T, false>), dim3((unsigned)rows),
-                           dim3(RR_THREADS), 0, s, Z, ldz, targets, (int)V, zero_pad, ignore_index,
-                           hdr, row_loss, n_rows);
+#define CE_SHAPE(TH, NV) \
+    do { if (nt) CE_LAUNCH(TH, NV, true); else CE_LAUNCH(TH, NV, false); } while (0)
+    if (row_bytes > 112 * 1024) CE_SHAPE(RC_THREADS, RC_NV);
+    else if (row_bytes > 48 * 1024) CE_SHAPE(RM_THREADS, RM_NV);
+    else CE_SHAPE(RS_THREADS, RS_NV);
+#undef CE_SHAPE
+#undef CE_LAUNCH
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(loss_accumulate_kernel, dim3(1), dim3(256), 0, s, row_loss, (int)rows, hdr, mean_out);
     HIP_TRY(hipGetLastError());

@@ -11,8 +11,6 @@
 
 namespace flce {
 
-constexpr int RR_THREADS = 256;
-
 struct MaxSum {
     float m, s;   // running maximum and sum of exp(z - m)
 };
@@ -156,78 +154,43 @@ __device__ __forceinline__ float row_lse(MaxSum a, const T* z, int64_t t, int ro
     return *s_lse;
 }
 
-template <typename T, bool VEC16>
-__global__ __launch_bounds__(RR_THREADS) void ce_rows_inplace_kernel(
-    T* __restrict__ Z, int64_t ldz, const int64_t* __restrict__ targets, int V, int zero_pad,
-    int64_t ignore_index, const DeviceHeader* __restrict__ hdr, float* __restrict__ row_loss,
-    const int* __restrict__ live) {
-    constexpr int VEC = RowVec<T>::N;
-    const int row = blockIdx.x;
-    const int tid = threadIdx.x;
-    if (live && row >= *live) {   // past the chunk's live rows (uniform per workgroup)
-        if (tid == 0) row_loss[row] = 0.f;
-        return;
-    }
-    T* z = Z + (int64_t)row * ldz;
-    const int64_t t = targets[row];
-    const bool valid = (t != ignore_index);
-    u32x4* zv = reinterpret_cast<u32x4*>(z);
-
-    __shared__ MaxSum part[RR_THREADS / WAVE];
-    __shared__ float s_lse;
-
-    const int nvec = VEC16 ? V / VEC : 0;
-    if (tid < zero_pad) z[V + tid] = from_f32<T>(0.f);   // zero_pad < 64
-    if (!valid) {   // uniform per workgroup
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-        for (int i = tid; i < nvec; i += RR_THREADS) zv[i] = zero;
-        for (int v = nvec * VEC + tid; v < V; v += RR_THREADS) z[v] = from_f32<T>(0.f);
-        if (tid == 0) row_loss[row] = 0.f;
-        return;
-    }
-
-    MaxSum a = {-INFINITY, 0.f};
-    if constexpr (VEC16) {
-        for (int i = tid; i < nvec; i += RR_THREADS) {
-            float f[VEC];
-            RowVec<T>::unpack(zv[i], f);
-            ms_push_vec<T, VEC>(a, f);
-        }
-    }
-    for (int v = nvec * VEC + tid; v < V; v += RR_THREADS) ms_push<T>(a, to_f32(z[v]));
-    const float lse = row_lse<T, RR_THREADS / WAVE>(a, z, t, row, row_loss, part, &s_lse);
-
-    const float inv_n = hdr->inv_n;
-    const RowExp<T> ex(lse);
-    const int tcol = (int)t;
-    if constexpr (VEC16) {
-        for (int i = tid; i < nvec; i += RR_THREADS)
-            zv[i] = ce_gradient_vec<T>(zv[i], i, tcol, ex, inv_n);
-    }
-    for (int v = nvec * VEC + tid; v < V; v += RR_THREADS)
-        z[v] = ce_gradient_one<T>(z[v], v, tcol, ex, inv_n);
-}
-
-// Variant that keeps the row in registers: one workgroup of THREADS threads per row holds
-// the first THREADS * NV 16-byte vectors of the row between the two sweeps, so that part
-// of the row is read from HBM once instead of twice; what is beyond is swept twice as
-// above.  All of a thread's loads are issued before the first is consumed.  Three shapes
-// are used: 256 threads x 12 vectors for rows up to 48 KB and 512 threads x 12 vectors up
-// to 96 KB, where several workgroups fit a CU and overlap one another's memory, reduction
-// and barrier phases (6.3-6.7 TB/s of algorithmic traffic on 32 .. 96 KB rows of bf16,
-// 4096 rows, kernel alone); 1024 threads x 16 vectors (256 KB) beyond, where 16 wavefronts
-// keep the per-thread ALU phases short (5.0-5.4 TB/s; a variant with 4 wavefronts per CU
-// and the whole row cached was slower than two sweeps).  At these rates the arithmetic
-// (about 16 lane operations per logit) takes as long as the memory traffic.
+// Row kernel: one workgroup of THREADS threads per row holds the first THREADS * NV 16-byte
+// vectors of the row in registers between the two sweeps, so that part of the row is read from
+// HBM once instead of twice; what is beyond is swept twice.  All of a thread's loads are issued
+// before the first is consumed.  Rows may start anywhere (a vocabulary of odd size in a dense
+// matrix): the vectors lie between a head and a tail of a few scalars.
+// What bounds it: HBM, and next to it the arithmetic (about 16 lane operations per logit).
+// Three shapes: 256 threads x 12 vectors for rows up to 48 KB and 512 x 12 up to 112 KB, where
+// several workgroups fit a CU and overlap one another's memory, reduction and barrier phases;
+// 1024 x 16 (256 KB) beyond, where 16 wavefronts keep the per-thread ALU phases short.  TB/s of
+// algorithmic traffic, kernel alone, 256 x 12 / 512 x 12 / 1024 x 16: 7.1 / 4.5 / 2.2 at 16 KB rows
+// (16384 of them), - / 7.2 / 4.9 at 64 KB (4096), - / 5.3 / 4.8 at 100 KB, - / - / 5.2 at 240 KB.
+// NT (nontemporal accesses) where the logits exceed the 256 MB memory-side cache, ordinary / NT:
+// 8192 x 128256 bf16 803 / 717 us, 4096 x 122880 bf16 387 / 356, 4096 x 81920 fp32 525 / 419; below it
+// they would push out what the next product reads: 4096 x 32000 bf16 73 / 89.
+// Rows of 50257 bf16 at odd addresses (4096 of them): 451 us with 2-byte accesses in two sweeps
+// before, 155 / 150 (NT) now.
 constexpr int RC_THREADS = 1024;
 constexpr int RC_NV = 16;
-constexpr int RM_THREADS = 512;   // rows up to 96 KB
+constexpr int RM_THREADS = 512;   // rows up to 112 KB
 constexpr int RM_NV = 12;
 constexpr int RS_THREADS = 256;   // rows up to 48 KB
 constexpr int RS_NV = 12;
 
-template <typename T, int THREADS, int NV>
-__global__ __launch_bounds__(THREADS) void ce_rows_cached_kernel(
+// 16-byte accesses of a row; NT: nontemporal, for logits that no cache will keep anyway.
+template <bool NT>
+__device__ __forceinline__ u32x4 row_load(const u32x4* p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <bool NT>
+__device__ __forceinline__ void row_store(u32x4* p, u32x4 v) {
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
+template <typename T, int THREADS, int NV, bool NT>
+__global__ __launch_bounds__(THREADS) void ce_rows_kernel(
     T* __restrict__ Z, int64_t ldz, const int64_t* __restrict__ targets, int V, int zero_pad,
     int64_t ignore_index, const DeviceHeader* __restrict__ hdr, float* __restrict__ row_loss,
     const int* __restrict__ live) {
@@ -241,8 +204,12 @@ __global__ __launch_bounds__(THREADS) void ce_rows_cached_kernel(
     T* z = Z + (int64_t)row * ldz;
     const int64_t t = targets[row];
     const bool valid = (t != ignore_index);
-    const int nvec = V / VEC;                 // full vectors; the tail is handled by scalars
-    u32x4* zv = reinterpret_cast<u32x4*>(z);
+    // the row may start anywhere: `head` elements up to the first 16-byte boundary, full vectors,
+    // and a tail; head and tail (fewer than 2 VEC elements) are handled by scalars, one per thread
+    const int head = min(V, (int)((16 - (reinterpret_cast<uintptr_t>(z) & 15)) & 15) / (int)sizeof(T));
+    const int nvec = (V - head) / VEC;
+    u32x4* zv = reinterpret_cast<u32x4*>(z + head);
+    const int edge = tid < V - nvec * VEC ? (tid < head ? tid : nvec * VEC + tid) : -1;
 
     __shared__ MaxSum part[THREADS / WAVE];
     __shared__ float s_lse;
@@ -250,8 +217,8 @@ __global__ __launch_bounds__(THREADS) void ce_rows_cached_kernel(
     if (tid < zero_pad) z[V + tid] = from_f32<T>(0.f);   // zero_pad < 64
     if (!valid) {                              // uniform per workgroup
         const u32x4 zero = {0u, 0u, 0u, 0u};
-        for (int i = tid; i < nvec; i += THREADS) zv[i] = zero;
-        for (int v = nvec * VEC + tid; v < V; v += THREADS) z[v] = from_f32<T>(0.f);
+        for (int i = tid; i < nvec; i += THREADS) row_store<NT>(zv + i, zero);
+        if (edge >= 0) z[edge] = from_f32<T>(0.f);
         if (tid == 0) row_loss[row] = 0.f;
         return;
     }
@@ -260,7 +227,7 @@ __global__ __launch_bounds__(THREADS) void ce_rows_cached_kernel(
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         const int i = tid + k * THREADS;
-        if (i < nvec) keep[k] = zv[i];
+        if (i < nvec) keep[k] = row_load<NT>(zv + i);
     }
     MaxSum a = {-INFINITY, 0.f};
 #pragma unroll
@@ -279,25 +246,25 @@ __global__ __launch_bounds__(THREADS) void ce_rows_cached_kernel(
         RowVec<T>::unpack(zv[i], f);
         ms_push_vec<T, VEC>(a, f);
     }
-    for (int v = nvec * VEC + tid; v < V; v += THREADS) ms_push<T>(a, to_f32(z[v]));
+    if (edge >= 0) ms_push<T>(a, to_f32(z[edge]));
     const float lse = row_lse<T, THREADS / WAVE>(a, z, t, row, row_loss, part, &s_lse);
 
     const float inv_n = hdr->inv_n;
     const RowExp<T> ex(lse);
-    const int tcol = (int)t;
+    // the target's place among the vectors; a target in the head matches none of them
+    const int tcol = (int)t < head ? 0x7fffffff : (int)t - head;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         const int i = tid + k * THREADS;
         // hide the value's history: otherwise the unpacked floats of sweep 1 are kept
         // for reuse here, which does not fit the register file and spills
         asm volatile("" : "+v"(keep[k]));
-        if (i < nvec) zv[i] = ce_gradient_vec<T>(keep[k], i, tcol, ex, inv_n);
+        if (i < nvec) row_store<NT>(zv + i, ce_gradient_vec<T>(keep[k], i, tcol, ex, inv_n));
         __builtin_amdgcn_sched_barrier(0);
     }
     for (int i = tid + NV * THREADS; i < nvec; i += THREADS)
-        zv[i] = ce_gradient_vec<T>(zv[i], i, tcol, ex, inv_n);
-    for (int v = nvec * VEC + tid; v < V; v += THREADS)
-        z[v] = ce_gradient_one<T>(z[v], v, tcol, ex, inv_n);
+        row_store<NT>(zv + i, ce_gradient_vec<T>(zv[i], i, tcol, ex, inv_n));
+    if (edge >= 0) z[edge] = ce_gradient_one<T>(z[edge], edge, (int)t, ex, inv_n);
 }
 
 // Adds the per-row losses of one launch to the running sum, in a fixed order

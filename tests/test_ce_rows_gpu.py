@@ -1,0 +1,46 @@
+"""The stand-alone cross entropy over rows that start at any address: head, vectors and tail of
+the row kernel, each of its shapes, and targets in the head, at a vector's ends and in the tail."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float32, 2e-6), (torch.bfloat16, 4e-3)])   # fp32 exp and sums; one rounding to 2^-9
+@pytest.mark.parametrize("V,ldz,offset", [
+    (1, 1, 0), (5, 5, 1), (7, 9, 3),      # rows shorter than a vector: all head or tail
+    (257, 257, 1),                        # 256-thread shape, a different head every row
+    (24571, 24571, 5),                    # up to 48 / 96 KB
+    (50257, 50257, 0),                    # 512-thread shape (bf16), 1024-thread shape (fp32)
+    (57345, 57345, 3),                    # just past 112 KB of bf16
+    (131073, 131077, 7),                  # past what the registers hold (fp32)
+])
+def test_rows_at_any_address(dtype, tol, V, ldz, offset):
+    import paper_2410_10989_amd as flce
+    rows = 24
+    g = torch.Generator(device="cuda").manual_seed(V + offset)
+    flat = (torch.randn(offset + rows * ldz + 64, device="cuda", generator=g) * 2).to(dtype)
+    Z = flat[offset:offset + rows * ldz].view(rows, ldz)[:, :V]
+    t = torch.tensor([0, V - 1, V // 2, min(V - 1, 7), min(V - 1, 8), max(0, V - 9), max(0, V - 8), -100] * 3,
+                     device="cuda")
+    before = flat.clone()
+    ref = Z.double()
+    ok = t != -100
+    lse = torch.logsumexp(ref, 1, keepdim=True)
+    at = t.clamp(min=0)[:, None]
+    want_loss = float(((lse - ref.gather(1, at))[:, 0] * ok).sum() / ok.sum())
+    G = torch.exp(ref - lse).scatter_add(1, at, torch.full_like(lse, -1.0)) * ok[:, None] / ok.sum()
+    loss = flce.flce_cross_entropy_inplace(Z, t, -100)
+    torch.cuda.synchronize()
+    assert abs(float(loss) - want_loss) <= 1e-6 * max(1.0, abs(want_loss))
+    if V > 1:
+        err = float((Z.double() - G).norm() / G.norm())
+        print(f"  {V} {ldz} {offset} {dtype}: {err:.1e}", flush=True)
+        assert err <= tol
+        assert (Z[7] == 0).all()
+    else:
+        assert float(Z.double().abs().max()) <= 1e-6
+    # nothing beside the rows is touched
+    mask = torch.ones_like(flat, dtype=torch.bool)
+    mask[offset:offset + rows * ldz].view(rows, ldz)[:, :V] = False
+    assert torch.equal(flat[mask], before[mask])
