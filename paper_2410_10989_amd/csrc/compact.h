@@ -11,23 +11,109 @@
 // without compaction; only dW sums the same non-zero terms in other groups of K.
 #pragma once
 #include "flce_device.h"
+#include "rowreduce.h"
 #include "scheduler.h"
 
 namespace flce {
 
+// Batches of up to SEL_MAX_ROWS rows: one launch per chunk (select_rows_kernel) counts, collects,
+// copies and clears; larger ones count once and walk the batch with a cursor (the kernels below
+// it), because every workgroup of the one launch looks at all targets: 8 BT bytes each, from L2.
+constexpr int SEL_MAX_ROWS = 32768;
+constexpr int SEL_GRID = 1024;   // workgroups at most: 4 rows each up to 4096, 32 at SEL_MAX_ROWS
+
 constexpr int CP_THREADS = 1024;
 constexpr int CP_PER = 8;   // consecutive rows per thread and round
-
-// live rows of a part: clamp(*live - sub, 0, cap)
-__device__ __forceinline__ int dyn_live_rows(const int* live, int sub, int cap) {
-    return min(cap, max(0, *live - sub));
-}
 
 // Words of the device array that carries the chunk loop's state from kernel to kernel.
 enum { DYN_CURSOR = 0,      // first batch row the next chunk looks at
        DYN_LIVE = 1,        // rows of the current chunk
        DYN_FIRST_LIVE = 2,  // index of the first chunk launch that holds rows
        DYN_DX_RANGES = 3 }; // K ranges of the current chunk's dX product
+
+// How the N valid rows of a batch are dealt to the launches (see compact_chunk_kernel).
+struct RowDeal {
+    int first_live, quota;
+};
+__device__ __forceinline__ RowDeal deal_rows(int n_valid, int C, int nchunks) {
+    const int n_live = max(1, (n_valid + C - 1) / C);
+    return {nchunks - n_live, min(C, ((n_valid + n_live - 1) / n_live + 255) / 256 * 256)};
+}
+// K ranges of a chunk's dX product (dx_max_ranges = 1: not cut, or not chosen here)
+__device__ __forceinline__ int dx_ranges_of(int rows, int dx_tiles_n, int dx_ksteps, int dx_max_ranges) {
+    return dx_max_ranges > 1
+        ? choose_ksplit((int64_t)((rows + 255) / 256) * dx_tiles_n, dx_ksteps, dx_max_ranges) : 1;
+}
+
+// Launch `c` of `nchunks` for a batch of at most SEL_MAX_ROWS rows: what compact_chunk_kernel,
+// count_valid_kernel, gather_rows_kernel and zero_ignored_rows_kernel do, in one launch.
+// Workgroup b owns batch rows b R .. b R + R - 1 (R <= 64 rows); it counts the valid rows in front
+// of them and in the whole batch (every workgroup reads all targets), which gives each of its
+// rows its place in the chunk.  One wavefront per row copies it to Xg (X not null), or clears its
+// gradient row (zero_out not null, row ignored).  Workgroup 0 writes the header (c = 0) and dyn.
+// Measured, 1024 rows of 512 bf16: 4 launches, 19 us -> one of 5; 4096 x 4096: 32 -> 15 us.
+template <typename T>
+__global__ __launch_bounds__(256) void select_rows_kernel(
+    const int64_t* __restrict__ targets, int BT, int64_t ignore_index, float weight, int C, int c, int nchunks,
+    int dx_tiles_n, int dx_ksteps, int dx_max_ranges, DeviceHeader* __restrict__ hdr, const T* __restrict__ X,
+    int n, T* __restrict__ Xg, T* __restrict__ zero_out, int* __restrict__ idx, int64_t* __restrict__ tv,
+    int* __restrict__ dyn) {
+    __shared__ int part[4][2];
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    const int R = (BT + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int r0 = min(BT, (int)blockIdx.x * R), r1 = min(BT, r0 + R);
+    int before = 0, n_valid = 0;
+#pragma unroll 8
+    for (int i = tid; i < BT; i += 256) {
+        const int v = targets[i] != ignore_index;
+        n_valid += v;
+        before += (i < r0) ? v : 0;
+    }
+    before = wave_sum(before);
+    n_valid = wave_sum(n_valid);
+    if (lane == 0) {
+        part[wave][0] = before;
+        part[wave][1] = n_valid;
+    }
+    __syncthreads();
+    before = part[0][0] + part[1][0] + part[2][0] + part[3][0];
+    n_valid = part[0][1] + part[1][1] + part[2][1] + part[3][1];
+    const RowDeal deal = deal_rows(n_valid, C, nchunks);
+    const int begin = (c - deal.first_live) * deal.quota;   // of this chunk among the valid rows
+    const int count = c < deal.first_live ? 0 : max(0, min(deal.quota, n_valid - begin));
+    if (blockIdx.x == 0 && tid == 0) {
+        if (c == 0) write_header(hdr, n_valid, weight);
+        dyn[DYN_LIVE] = count;
+        dyn[DYN_FIRST_LIVE] = deal.first_live;
+        dyn[DYN_DX_RANGES] = dx_ranges_of(count, dx_tiles_n, dx_ksteps, dx_max_ranges);
+    }
+    const int64_t t = (r0 + lane < r1) ? targets[r0 + lane] : ignore_index;
+    const unsigned long long mask = __ballot(t != ignore_index);
+    const int at = before + __popcll(mask & ((1ull << lane) - 1)) - begin;   // place of row r0 + lane, if valid
+    constexpr int VEC = 16 / sizeof(T);
+    const int nv = n / VEC;
+    for (int j = wave; j < r1 - r0; j += 4) {
+        const int place = __shfl(at, j, WAVE);
+        const bool valid = (mask >> j) & 1;
+        const int r = r0 + j;
+        if (!valid) {
+            if (!zero_out) continue;
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            u32x4* dst = reinterpret_cast<u32x4*>(zero_out + (int64_t)r * n);
+            for (int v = lane; v < nv; v += WAVE) dst[v] = zero;
+        } else if (place >= 0 && place < count) {
+            if (lane == 0) {
+                idx[place] = r;
+                tv[place] = targets[r];
+            }
+            if (!X) continue;
+            const u32x4* src = reinterpret_cast<const u32x4*>(X + (int64_t)r * n);
+            u32x4* dst = reinterpret_cast<u32x4*>(Xg + (int64_t)place * n);
+#pragma unroll 8
+            for (int v = lane; v < nv; v += WAVE) dst[v] = src[v];
+        }
+    }
+}
 
 // One workgroup; launch `c` of `nchunks`, each sized for `C` rows.  The N valid rows of
 // the batch (N = hdr->n_valid, counted before the loop) are dealt evenly to the LAST
@@ -50,10 +136,8 @@ __global__ __launch_bounds__(CP_THREADS) void compact_chunk_kernel(
     __shared__ int s_next;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     const int n_valid = hdr->n_valid;
-    const int n_live = max(1, (n_valid + C - 1) / C);
-    const int first_live = nchunks - n_live;
-    const int quota = min(C, ((n_valid + n_live - 1) / n_live + 255) / 256 * 256);
-    const int cap = c < first_live ? 0 : quota;
+    const RowDeal deal = deal_rows(n_valid, C, nchunks);
+    const int cap = c < deal.first_live ? 0 : deal.quota;
     int cursor = c == 0 ? 0 : dyn[DYN_CURSOR];
     int found = 0;
     while (cursor < BT && found < cap) {   // uniform: every thread sees the same values
@@ -99,9 +183,8 @@ __global__ __launch_bounds__(CP_THREADS) void compact_chunk_kernel(
     if (tid == 0) {
         dyn[DYN_CURSOR] = cursor;
         dyn[DYN_LIVE] = found;
-        dyn[DYN_FIRST_LIVE] = first_live;
-        dyn[DYN_DX_RANGES] = dx_max_ranges > 1
-            ? choose_ksplit((int64_t)((found + 255) / 256) * dx_tiles_n, dx_ksteps, dx_max_ranges) : 1;
+        dyn[DYN_FIRST_LIVE] = deal.first_live;
+        dyn[DYN_DX_RANGES] = dx_ranges_of(found, dx_tiles_n, dx_ksteps, dx_max_ranges);
     }
 }
 
@@ -116,33 +199,6 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const u32x4* __restric
     const u32x4* src = in + (int64_t)idx[i] * n;
     u32x4* dst = out + (int64_t)i * n;
     for (int v = threadIdx.x; v < n; v += 256) dst[v] = src[v];
-}
-
-// The way back: out[idx[i]][:] = in[i][:] for the live rows i.  With ADD
-// the row is added to what out holds (fp32 add, one rounding).  One workgroup per
-// row; n elements per row, n % VEC == 0.
-template <typename T, bool ADD>
-__global__ __launch_bounds__(256) void scatter_rows_kernel(const T* __restrict__ in,
-                                                           const int* __restrict__ idx,
-                                                           const int* __restrict__ live, int n,
-                                                           T* __restrict__ out) {
-    constexpr int VEC = 16 / sizeof(T);
-    const int i = blockIdx.x;
-    if (i >= *live) return;
-    u32x4* dst = reinterpret_cast<u32x4*>(out + (int64_t)idx[i] * n);
-    const u32x4* from = reinterpret_cast<const u32x4*>(in + (int64_t)i * n);
-    const int nv = n / VEC;
-    for (int v = threadIdx.x; v < nv; v += 256) {
-        u32x4 a = from[v];
-        if constexpr (ADD) {
-            u32x4 b = dst[v];
-            T* ea = reinterpret_cast<T*>(&a);
-            const T* eb = reinterpret_cast<const T*>(&b);
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) ea[j] = from_f32<T>(to_f32(ea[j]) + to_f32(eb[j]));
-        }
-        dst[v] = a;
-    }
 }
 
 // Rows with an ignored target get a zero gradient.  Workgroups stride over the rows of

@@ -249,14 +249,14 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
 template <typename T>
 int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int64_t V,
                    int zero_pad, int64_t ignore_index, DeviceHeader* hdr, float* row_loss,
-                   hipStream_t s, const int* n_rows = nullptr, bool timed = true, float* mean_out = nullptr) {
+                   hipStream_t s, const int* n_rows, bool timed, int count_n, float weight) {
     ScopedKernelTimer timer(timed ? FLCE_KIND_CE_ROWS : -1, s);
     // shape by row length, nontemporal accesses by size: see ce_rows_kernel
     const int64_t row_bytes = V * (int64_t)sizeof(T);
     const bool nt = rows * row_bytes > CE_CACHE_BYTES;
 #define CE_LAUNCH(TH, NV, NT)                                                                          \
     hipLaunchKernelGGL((ce_rows_kernel<T, TH, NV, NT>), dim3((unsigned)rows), dim3(TH), 0, s, Z, ldz,  \
-                       targets, (int)V, zero_pad, ignore_index, hdr, row_loss, n_rows)
+                       targets, (int)V, zero_pad, ignore_index, hdr, row_loss, n_rows, count_n, weight)
 #define CE_SHAPE(TH, NV) \
     do { if (nt) CE_LAUNCH(TH, NV, true); else CE_LAUNCH(TH, NV, false); } while (0)
     if (row_bytes > 112 * 1024) CE_SHAPE(RC_THREADS, RC_NV);
@@ -265,7 +265,12 @@ int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int6
 #undef CE_SHAPE
 #undef CE_LAUNCH
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(loss_accumulate_kernel, dim3(1), dim3(256), 0, s, row_loss, (int)rows, hdr, mean_out);
+    return FLCE_OK;
+}
+
+int launch_loss(const float* row_loss, int64_t rows, DeviceHeader* hdr, const LossOut& out, bool timed, hipStream_t s) {
+    ScopedKernelTimer timer(timed ? FLCE_KIND_CE_ROWS : -1, s);
+    hipLaunchKernelGGL(loss_accumulate_kernel, dim3(1), dim3(256), 0, s, row_loss, (int)rows, hdr, out);
     HIP_TRY(hipGetLastError());
     return FLCE_OK;
 }
@@ -276,12 +281,7 @@ int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int6
         if (rc_ != FLCE_OK) return rc_; \
     } while (0)
 
-constexpr int MAX_HEADS = 16;   // headers of all heads share the 256-byte header slot
 static_assert(MAX_HEADS * sizeof(DeviceHeader) <= 256, "header slot too small");
-
-struct HeadWeights {
-    float w[MAX_HEADS];
-};
 
 // RMSNorm in front of the projection: the chunk loop normalises each chunk of the
 // raw hidden states just before its logits product (into the chunk buffer that
@@ -296,22 +296,24 @@ struct NormCtx {
     T* dh;           // [BT x H] out
 };
 
-// Sum of the K-range partial results of a dX product into dXc (+= with add).
-template <typename T>
-int launch_splitk_reduce(const float* part, int64_t split_stride, int nsplit, T* out, int64_t n,
-                         bool add, hipStream_t s, const int* dyn_nsplit = nullptr) {
+// See finish_dx_kernel: K-range partial results summed, rows put in place, loss summed.
+template <typename T, typename SrcT>
+int launch_finish_dx(const SrcT* src, int64_t split_stride, int nsplit, const int* dyn_nsplit, const int* idx,
+                     const int* live, int64_t rows, int64_t H, T* out, bool add, const float* row_loss,
+                     DeviceHeader* hdr, const LossOut& loss, hipStream_t s) {
     ScopedKernelTimer timer(FLCE_KIND_DX_GEMM, s);
-    const bool vec = (n % 4 == 0) && (split_stride % 4 == 0) && aligned(part, 16) &&
+    const bool vec = (H % 4 == 0) && (split_stride % 4 == 0) && aligned(src, 4 * sizeof(SrcT)) &&
                      aligned(out, 4 * sizeof(T));
-    const dim3 grid(2048), block(256);
-#define SK_LAUNCH(ADD, VEC) \
-    hipLaunchKernelGGL((splitk_reduce_kernel<T, ADD, VEC>), grid, block, 0, s, part, split_stride, nsplit, out, n, dyn_nsplit)
+    const dim3 grid((unsigned)((rows + 3) / 4 + 1)), block(256);
+#define FD_LAUNCH(ADD, VEC)                                                                                 \
+    hipLaunchKernelGGL((finish_dx_kernel<T, SrcT, ADD, VEC>), grid, block, 0, s, src, split_stride, nsplit, \
+                       dyn_nsplit, idx, live, (int)rows, (int)H, out, row_loss, hdr, loss)
     if (vec) {
-        if (add) SK_LAUNCH(true, true); else SK_LAUNCH(false, true);
+        if (add) FD_LAUNCH(true, true); else FD_LAUNCH(false, true);
     } else {
-        if (add) SK_LAUNCH(true, false); else SK_LAUNCH(false, false);
+        if (add) FD_LAUNCH(true, false); else FD_LAUNCH(false, false);
     }
-#undef SK_LAUNCH
+#undef FD_LAUNCH
     HIP_TRY(hipGetLastError());
     return FLCE_OK;
 }
@@ -329,11 +331,12 @@ int rmsnorm_vectors_per_thread(int64_t H, const void* x, const void* gamma, cons
 
 // One head: count its valid rows, then run the chunk loop.  Gradients are scaled by
 // weight / N_valid.  With dx_add the head's dX is added to what dX already holds
-// (rounded to the storage type once per head), otherwise dX is overwritten.
+// (rounded to the storage type once per head), otherwise dX is overwritten.  loss_out: where the
+// loss goes after the last head (n_heads = 0 for the others).
 template <typename T>
 int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t H, int64_t V,
-             int64_t ignore_index, float weight, DeviceHeader* hdr, bool dx_add, T* dX, T* dW,
-             unsigned flags, const Plan& p, char* ws, hipStream_t s,
+             int64_t ignore_index, float weight, DeviceHeader* hdr, const LossOut& loss_out, bool dx_add, T* dX,
+             T* dW, unsigned flags, const Plan& p, char* ws, hipStream_t s,
              const NormCtx<T>* norm = nullptr) {
     constexpr bool BF16 = (sizeof(T) == 2);
     const bool want_dx = !(flags & FLCE_SKIP_DX), want_dw = !(flags & FLCE_SKIP_DW);
@@ -348,13 +351,18 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
     float* tail = reinterpret_cast<float*>(ws + p.off_tail);   // partial blocks of the dW product's last round
     constexpr int VEC = 16 / (int)sizeof(T);
 
-    hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
-                       weight, hdr);
-    HIP_TRY(hipGetLastError());
-    if (p.compact && want_dx && !dx_add) {   // rows without a target: zero gradient
+    const bool select = p.compact && BT <= SEL_MAX_ROWS;   // one launch per chunk finds its rows
+    const bool count_in_rows = !p.compact && p.nchunks == 1 && BT <= CE_COUNT_ROWS;
+    T* zero_out = (want_dx && !dx_add) ? (norm ? norm->dh : dX) : nullptr;   // rows without a target: zero gradient
+    if (!select && !count_in_rows) {
+        hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
+                           weight, hdr);
+        HIP_TRY(hipGetLastError());
+    }
+    if (p.compact && !select && zero_out) {
         ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
         hipLaunchKernelGGL((zero_ignored_rows_kernel<T>), dim3((unsigned)(BT < 8192 ? BT : 8192)),
-                           dim3(256), 0, s, targets, BT, ignore_index, (int)H, norm ? norm->dh : dX);
+                           dim3(256), 0, s, targets, BT, ignore_index, (int)H, zero_out);
         HIP_TRY(hipGetLastError());
     }
 
@@ -375,15 +383,23 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         FastDyn dyn_m, dyn_dx, dyn_dw;   // logits (M = live rows), dX (M and K ranges), dW (K = live rows)
         if (p.compact) {
             ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
-            hipLaunchKernelGGL(compact_chunk_kernel, dim3(1), dim3(CP_THREADS), 0, s, targets, (int)BT,
-                               ignore_index, (int)p.C, (int)c, (int)p.nchunks, hdr,
-                               (int)((H + FG_BN - 1) / FG_BN), (int)((V + FG_BK - 1) / FG_BK),
-                               p.dx_ksplit, idx, tv, dyn);
+            const int dx_tiles_n = (int)((H + FG_BN - 1) / FG_BN), dx_ksteps = (int)((V + FG_BK - 1) / FG_BK);
+            if (select) {
+                const int64_t grid = std::min<int64_t>((BT + 3) / 4, SEL_GRID);
+                hipLaunchKernelGGL((select_rows_kernel<T>), dim3((unsigned)grid), dim3(256), 0, s, targets, (int)BT,
+                                   ignore_index, weight, (int)p.C, (int)c, (int)p.nchunks, dx_tiles_n, dx_ksteps,
+                                   p.dx_ksplit, hdr, norm ? static_cast<const T*>(nullptr) : X, (int)H, Xg,
+                                   c == 0 ? zero_out : static_cast<T*>(nullptr), idx, tv, dyn);
+            } else {
+                hipLaunchKernelGGL(compact_chunk_kernel, dim3(1), dim3(CP_THREADS), 0, s, targets, (int)BT,
+                                   ignore_index, (int)p.C, (int)c, (int)p.nchunks, hdr, dx_tiles_n, dx_ksteps,
+                                   p.dx_ksplit, idx, tv, dyn);
+            }
             HIP_TRY(hipGetLastError());
             tc = tv;
             dyn_m.rows = dyn_dx.rows = dyn_dw.rows = n_live;
             dyn_dw.is_k = 1;
-            if (p.dx_tile == 256) dyn_dx.ksplit = dyn + DYN_DX_RANGES;
+            if (p.fast_dx && p.dx_tile == 256) dyn_dx.ksplit = dyn + DYN_DX_RANGES;
             dyn_dw.first_live = dyn + DYN_FIRST_LIVE;
             dyn_dw.launch = (int)c;
         }
@@ -402,12 +418,14 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             HIP_TRY(hipGetLastError());
             Xc = Xg;
         } else if (p.compact) {
+            Xc = Xg;
+        }
+        if (p.compact && !norm && !select) {
             ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
             hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)rows), dim3(256), 0, s,
                                reinterpret_cast<const u32x4*>(X), idx, n_live, (int)(H / VEC),
                                reinterpret_cast<u32x4*>(Xg));
             HIP_TRY(hipGetLastError());
-            Xc = Xg;
         }
 
         // logits of the chunk: Z = X_c W^T
@@ -419,12 +437,14 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         } else {
             FLCE_TRY((launch_gemm_guarded<T, T, false, false>(FLCE_KIND_LOGITS_GEMM, Xc, H, W, H, Z, p.ldz,
                                                               nullptr, nullptr, rows, V, H, s,
-                                                              guarded_cut(rows, V, H, 1).tile)));
+                                                              guarded_cut(rows, V, H, 1).tile, 1, 0, dyn_m)));
         }
 
         // loss and in-place dlogits
         FLCE_TRY(launch_ce_rows<T>(Z, p.ldz, tc, rows, V, (int)(p.ldz - V), ignore_index, hdr,
-                                   row_loss, s, n_live));
+                                   row_loss, s, n_live, true, count_in_rows ? (int)BT : 0, weight));
+        const LossOut loss_here = last ? loss_out : LossOut{};
+        bool loss_done = false;
 
         // dX_c (+)= G W
         if (want_dx) {
@@ -433,6 +453,10 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             const bool staged = p.compact || norm;
             T* dXc = staged ? dXg : dX + r0 * H;
             const bool add_in_gemm = dx_add && !staged;
+            const bool scatter = p.compact && !norm;   // finish_dx_kernel puts the rows back in place
+            T* dXrows = scatter ? dX : dXc;
+            const bool add_rows = dx_add && (scatter || add_in_gemm);
+            const int* rows_at = scatter ? row_map : nullptr;
             if (BF16 && p.fast_dx) {
                 if constexpr (BF16) {
                     if (p.dx_ksplit > 1) {
@@ -441,8 +465,10 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                         FLCE_TRY((launch_gemm_fast<float, void, false, true>(
                             FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, 0, rows, H, V, s,
                             p.dx_tile, p.dx_ksplit, p.C * H, dyn_dx)));
-                        FLCE_TRY(launch_splitk_reduce<bf16_t>(part, p.C * H, p.dx_ksplit, dXc, rows * H,
-                                                              add_in_gemm, s, dyn_dx.ksplit));
+                        FLCE_TRY((launch_finish_dx<bf16_t, float>(part, p.C * H, p.dx_ksplit, dyn_dx.ksplit, rows_at,
+                                                                  n_live, rows, H, dXrows, add_rows, row_loss, hdr,
+                                                                  loss_here, s)));
+                        loss_done = true;
                     } else if (add_in_gemm) {
                         FLCE_TRY((launch_gemm_fast<bf16_t, bf16_t, false, true>(
                             FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, dXc, H, rows, H, V, s,
@@ -459,14 +485,20 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                     float* part = reinterpret_cast<float*>(ws + p.off_dxpart);
                     FLCE_TRY((launch_gemm_guarded<T, float, false, true>(
                         FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, nullptr, rows, H, V, s, p.dx_tile,
-                        p.dx_ksplit, p.C * H)));
-                    FLCE_TRY(launch_splitk_reduce<T>(part, p.C * H, p.dx_ksplit, dXc, rows * H, add_in_gemm,
-                                                     s));
+                        p.dx_ksplit, p.C * H, dyn_m)));
+                    FLCE_TRY((launch_finish_dx<T, float>(part, p.C * H, p.dx_ksplit, nullptr, rows_at, n_live, rows,
+                                                         H, dXrows, add_rows, row_loss, hdr, loss_here, s)));
+                    loss_done = true;
                 } else {
                     FLCE_TRY((launch_gemm_guarded<T, T, false, true>(
                         FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, nullptr, add_in_gemm ? dXc : nullptr, rows, H,
-                        V, s, p.dx_tile)));
+                        V, s, p.dx_tile, 1, 0, dyn_m)));
                 }
+            }
+            if (scatter && p.dx_ksplit == 1) {
+                FLCE_TRY((launch_finish_dx<T, T>(dXg, 0, 1, nullptr, rows_at, n_live, rows, H, dX, add_rows, row_loss,
+                                                 hdr, loss_here, s)));
+                loss_done = true;
             }
             if (norm) {
                 ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
@@ -482,17 +514,10 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                 }
 #undef RN_BWD
                 HIP_TRY(hipGetLastError());
-            } else if (p.compact) {
-                ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
-                if (dx_add)
-                    hipLaunchKernelGGL((scatter_rows_kernel<T, true>), dim3((unsigned)rows), dim3(256), 0,
-                                       s, static_cast<const T*>(dXg), idx, n_live, (int)H, dX);
-                else
-                    hipLaunchKernelGGL((scatter_rows_kernel<T, false>), dim3((unsigned)rows), dim3(256), 0,
-                                       s, static_cast<const T*>(dXg), idx, n_live, (int)H, dX);
-                HIP_TRY(hipGetLastError());
             }
         }
+
+        if (!loss_done) FLCE_TRY(launch_loss(row_loss, rows, hdr, loss_here, true, s));
 
         // dW (+)= G^T X_c   (K = the chunk's rows; in a compacted chunk K = *n_live)
         if (want_dw) {
@@ -524,11 +549,11 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                 if (acc && !last) {
                     FLCE_TRY((launch_gemm_guarded<T, float, true, true>(
                         FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, acc, H, c > 0 ? acc : nullptr, nullptr, V, H, rows, s,
-                        tile)));
+                        tile, 1, 0, dyn_dw)));
                 } else {
                     FLCE_TRY((launch_gemm_guarded<T, T, true, true>(
                         FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dW, H, acc, !acc && c > 0 ? dW : nullptr, V, H, rows,
-                        s, tile)));
+                        s, tile, 1, 0, dyn_dw)));
                 }
             }
         }
@@ -536,8 +561,8 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
     return FLCE_OK;
 }
 
-// All heads one after the other on the same stream and the same workspace; then
-// loss = sum_j weight_j * mean loss of head j.
+// All heads one after the other on the same stream and the same workspace; the last one's last
+// row losses complete loss = sum_j weight_j * mean loss of head j.
 template <typename T>
 int run_heads(const T* X, const void* const* W, const int64_t* const* targets, const float* weights,
               int n_heads, int64_t BT, int64_t H, int64_t V, int64_t ignore_index, float* loss,
@@ -545,16 +570,13 @@ int run_heads(const T* X, const void* const* W, const int64_t* const* targets, c
               hipStream_t s) {
     DeviceHeader* hdr = reinterpret_cast<DeviceHeader*>(ws + p.off_hdr);
     const bool want_dw = !(flags & FLCE_SKIP_DW);
-    HeadWeights hw{};
+    LossOut out{hdr, n_heads, loss, head_losses, {}};
     for (int j = 0; j < n_heads; ++j) {
-        hw.w[j] = weights ? weights[j] : 1.0f;
+        out.w[j] = weights ? weights[j] : 1.0f;
         FLCE_TRY(run_head<T>(X, static_cast<const T*>(W[j]), targets[j], BT, H, V, ignore_index,
-                             hw.w[j], hdr + j, j > 0, dX, want_dw ? static_cast<T*>(dW[j]) : nullptr,
+                             out.w[j], hdr + j, j == n_heads - 1 ? out : LossOut{}, j > 0, dX, want_dw ? static_cast<T*>(dW[j]) : nullptr,
                              flags, p, ws, s));
     }
-    hipLaunchKernelGGL(finalize_loss_kernel, dim3(1), dim3(64), 0, s, hdr, n_heads, hw, loss,
-                       head_losses);
-    HIP_TRY(hipGetLastError());
     return FLCE_OK;
 }
 
@@ -611,18 +633,13 @@ int run_rmsnorm_head(const T* h, const T* gamma, float eps, const T* W, const in
                            (int64_t)RN_SLOTS * H);
         HIP_TRY(hipGetLastError());
     }
-    FLCE_TRY(run_head<T>(h, W, targets, BT, H, V, ignore_index, 1.0f, hdr, false, nullptr, dW, flags, p,
-                         ws, s, &n));
+    FLCE_TRY(run_head<T>(h, W, targets, BT, H, V, ignore_index, 1.0f, hdr, LossOut{hdr, 1, loss, nullptr, {1.0f}},
+                         false, nullptr, dW, flags, p, ws, s, &n));
     if (want_dx) {
         hipLaunchKernelGGL((rmsnorm_dgamma_kernel<T>), dim3((unsigned)((H + RN_DG_COLS - 1) / RN_DG_COLS)),
                            dim3(RN_DG_COLS * RN_DG_PARTS), 0, s, n.partial, (int)H, dgamma);
         HIP_TRY(hipGetLastError());
     }
-    HeadWeights one{};
-    one.w[0] = 1.0f;
-    hipLaunchKernelGGL(finalize_loss_kernel, dim3(1), dim3(64), 0, s, hdr, 1, one, loss,
-                       static_cast<float*>(nullptr));
-    HIP_TRY(hipGetLastError());
     return FLCE_OK;
 }
 
@@ -643,18 +660,22 @@ int check_ce_args(const void* Z, const int64_t* targets, int64_t BT, int64_t V, 
 int run_ce_inplace(void* Z, const int64_t* targets, int64_t BT, int64_t V, int64_t ldz,
                    int64_t ignore_index, int dtype, float* loss, DeviceHeader* hdr, float* row_loss,
                    int64_t step, bool timed, hipStream_t s) {
-    hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
-                       1.0f, hdr);
-    HIP_TRY(hipGetLastError());
+    const int count_n = BT <= CE_COUNT_ROWS && BT <= step ? (int)BT : 0;
+    if (!count_n) {
+        hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
+                           1.0f, hdr);
+        HIP_TRY(hipGetLastError());
+    }
     for (int64_t r0 = 0; r0 < BT; r0 += step) {
         const int64_t rows = (BT - r0 < step) ? BT - r0 : step;
-        float* mean_out = (r0 + rows == BT) ? loss : nullptr;   // the last launch also writes the mean
         if (dtype == FLCE_F32)
             FLCE_TRY(launch_ce_rows<float>(static_cast<float*>(Z) + r0 * ldz, ldz, targets + r0,
-                                           rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, mean_out));
+                                           rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f));
         else
             FLCE_TRY(launch_ce_rows<bf16_t>(static_cast<bf16_t*>(Z) + r0 * ldz, ldz, targets + r0,
-                                            rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, mean_out));
+                                            rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f));
+        FLCE_TRY(launch_loss(row_loss, rows, hdr,
+                             r0 + rows == BT ? LossOut{hdr, 1, loss, nullptr, {1.0f}} : LossOut{}, timed, s));
     }
     return FLCE_OK;
 }

@@ -43,6 +43,8 @@ __device__ __forceinline__ int wave_sum(int v) {
     return v;
 }
 
+constexpr int MAX_HEADS = 16;   // headers of all heads share the 256-byte header slot
+
 // Scalars that live at the start of the workspace and are produced and
 // consumed on the device, so the host never waits for them.
 struct DeviceHeader {

@@ -1,47 +1,59 @@
-// Sum of the partial results of a product that is cut along K.
+// Last step of a dX product: partial results summed, rows put back in place, loss summed.
 #pragma once
 #include "flce_device.h"
+#include "rowreduce.h"
 
 namespace flce {
 
-// out[i] = sum_s part[s][i] in the fixed order s = 0, 1, ...: the reduction of split-K
-// partial results (n elements each, split_stride elements apart).
-// With ADD the previous content of out is added as well (dX summed over heads).
-// VEC4: four elements per thread and access (n, split_stride and the pointers' element
-// offsets are multiples of 4); the additions per element are the same either way.
-// dyn_nsplit (optional): the number of ranges when only the device knows it.
-template <typename T, bool ADD, bool VEC4>
-__global__ void splitk_reduce_kernel(const float* __restrict__ part, int64_t split_stride, int nsplit,
-                                     T* __restrict__ out, int64_t n, const int* __restrict__ dyn_nsplit) {
+// Row i of a chunk's dX, for the chunk's `rows` rows (or *live of them):
+//     out[idx ? idx[i] : i] (+)= sum_s src[s][i]        in the fixed order s = 0, 1, ...
+// src: fp32 partial results of the K ranges (split_stride elements apart, dyn_nsplit their number
+// when only the device knows it), or with nsplit = 1 the product's rows in the storage type.
+// With ADD the row is added to what out holds (dX summed over heads).  One wavefront per row, 4
+// elements per lane and access with VEC4 (n, split_stride and the pointers are multiples of 4).
+// The workgroup past the rows sums the chunk's losses (row_loss not null).
+// Latency bound at small sizes: one launch where the sum over K ranges, the scatter, the loss sum
+// and its finalisation were four of 4-5 us each.
+template <typename T, typename SrcT, bool ADD, bool VEC4>
+__global__ __launch_bounds__(256) void finish_dx_kernel(const SrcT* __restrict__ src, int64_t split_stride, int nsplit,
+                                                        const int* __restrict__ dyn_nsplit,
+                                                        const int* __restrict__ idx, const int* __restrict__ live,
+                                                        int rows, int n, T* __restrict__ out,
+                                                        const float* __restrict__ row_loss, DeviceHeader* hdr,
+                                                        LossOut loss) {
+    const int row_groups = (rows + 3) / 4;
+    if ((int)blockIdx.x == row_groups) {
+        if (row_loss) loss_accumulate(row_loss, rows, hdr, loss);
+        return;
+    }
+    const int i = (int)blockIdx.x * 4 + (int)threadIdx.x / WAVE;
+    if (i >= (live ? min(rows, *live) : rows)) return;
     if (dyn_nsplit) nsplit = *dyn_nsplit;
-    if constexpr (VEC4) {
-        typedef float f32x4v __attribute__((ext_vector_type(4)));
-        for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < n;
-             i += (int64_t)gridDim.x * blockDim.x * 4) {
-            f32x4v v = *reinterpret_cast<const f32x4v*>(part + i);
-            if constexpr (ADD) {
+    const SrcT* from = src + (int64_t)i * n;
+    T* to = out + (int64_t)(idx ? idx[i] : i) * n;
+    constexpr int E = VEC4 ? 4 : 1;
+    struct alignas(E * sizeof(SrcT)) In { SrcT e[E]; };
+    struct alignas(E * sizeof(T)) Out { T e[E]; };
+    for (int j = ((int)threadIdx.x & (WAVE - 1)) * E; j < n; j += WAVE * E) {
+        float v[E];
+        const In a = *reinterpret_cast<const In*>(from + j);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += to_f32(out[i + e]);
-            }
-            for (int s = 1; s < nsplit; ++s) v += *reinterpret_cast<const f32x4v*>(part + (int64_t)s * split_stride + i);
-            if constexpr (sizeof(T) == 4) {
-                *reinterpret_cast<f32x4v*>(out + i) = v;
-            } else {
-                typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
-                const bf16x2 p0 = {from_f32<bf16_t>(v[0]), from_f32<bf16_t>(v[1])};
-                const bf16x2 p1 = {from_f32<bf16_t>(v[2]), from_f32<bf16_t>(v[3])};
-                const u32x2v q = {__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1)};
-                *reinterpret_cast<u32x2v*>(out + i) = q;
-            }
+        for (int e = 0; e < E; ++e) v[e] = to_f32(a.e[e]);
+        Out o{};
+        if constexpr (ADD) {
+            o = *reinterpret_cast<const Out*>(to + j);
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[e] += to_f32(o.e[e]);
         }
-    } else {
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-             i += (int64_t)gridDim.x * blockDim.x) {
-            float v = part[i];
-            if constexpr (ADD) v += to_f32(out[i]);
-            for (int s = 1; s < nsplit; ++s) v += part[(int64_t)s * split_stride + i];
-            out[i] = from_f32<T>(v);
+#pragma unroll 4
+        for (int s = 1; s < nsplit; ++s) {
+            const In b = *reinterpret_cast<const In*>(from + (int64_t)s * split_stride + j);
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[e] += to_f32(b.e[e]);
         }
+#pragma unroll
+        for (int e = 0; e < E; ++e) o.e[e] = from_f32<T>(v[e]);
+        *reinterpret_cast<Out*>(to + j) = o;
     }
 }
 

@@ -189,11 +189,36 @@ __device__ __forceinline__ void row_store(u32x4* p, u32x4 v) {
     else *p = v;
 }
 
+// Valid rows among targets[0 .. n), the same value returned to every thread of the workgroup.
+template <int THREADS>
+__device__ __forceinline__ int count_rows(const int64_t* __restrict__ targets, int n, int64_t ignore_index, int* part) {
+    int c = 0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n; i += THREADS) c += (targets[i] != ignore_index);
+    c = wave_sum(c);
+    if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x / WAVE] = c;
+    __syncthreads();
+    int total = 0;
+    for (int w = 0; w < THREADS / WAVE; ++w) total += part[w];
+    return total;
+}
+__device__ __forceinline__ void write_header(DeviceHeader* hdr, int n_valid, float weight) {
+    hdr->n_valid = n_valid;
+    hdr->inv_n = n_valid > 0 ? weight / (float)n_valid : 0.f;
+    hdr->loss_sum = 0.0;
+}
+// A batch of at most this many rows is counted by every workgroup of the row kernel itself (the
+// targets are 16 KB from L2, fetched behind the row's own loads) instead of by a launch of its own
+// in front of it, which takes 4-5 us whatever it does.
+constexpr int CE_COUNT_ROWS = 2048;
+
+// count_n > 0: `targets` holds the whole batch, count_n rows; workgroup 0 writes the header for the
+// launches that follow.  count_n = 0: the header holds the count.
 template <typename T, int THREADS, int NV, bool NT>
 __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
     T* __restrict__ Z, int64_t ldz, const int64_t* __restrict__ targets, int V, int zero_pad,
-    int64_t ignore_index, const DeviceHeader* __restrict__ hdr, float* __restrict__ row_loss,
-    const int* __restrict__ live) {
+    int64_t ignore_index, DeviceHeader* __restrict__ hdr, float* __restrict__ row_loss,
+    const int* __restrict__ live, int count_n, float weight) {
     constexpr int VEC = RowVec<T>::N;
     const int row = blockIdx.x;
     const int tid = threadIdx.x;
@@ -213,6 +238,7 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
 
     __shared__ MaxSum part[THREADS / WAVE];
     __shared__ float s_lse;
+    __shared__ int counts[THREADS / WAVE];
 
     if (tid < zero_pad) z[V + tid] = from_f32<T>(0.f);   // zero_pad < 64
     if (!valid) {                              // uniform per workgroup
@@ -220,6 +246,10 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
         for (int i = tid; i < nvec; i += THREADS) row_store<NT>(zv + i, zero);
         if (edge >= 0) z[edge] = from_f32<T>(0.f);
         if (tid == 0) row_loss[row] = 0.f;
+        if (count_n > 0 && row == 0) {
+            const int n = count_rows<THREADS>(targets, count_n, ignore_index, counts);
+            if (tid == 0) write_header(hdr, n, weight);
+        }
         return;
     }
 
@@ -228,6 +258,14 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
     for (int k = 0; k < NV; ++k) {
         const int i = tid + k * THREADS;
         if (i < nvec) keep[k] = row_load<NT>(zv + i);
+    }
+    float inv_n;
+    if (count_n > 0) {
+        const int n = count_rows<THREADS>(targets, count_n, ignore_index, counts);
+        inv_n = weight / (float)n;   // this row is valid: n > 0
+        if (row == 0 && tid == 0) write_header(hdr, n, weight);
+    } else {
+        inv_n = hdr->inv_n;
     }
     MaxSum a = {-INFINITY, 0.f};
 #pragma unroll
@@ -249,7 +287,6 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
     if (edge >= 0) ms_push<T>(a, to_f32(z[edge]));
     const float lse = row_lse<T, THREADS / WAVE>(a, z, t, row, row_loss, part, &s_lse);
 
-    const float inv_n = hdr->inv_n;
     const RowExp<T> ex(lse);
     // the target's place among the vectors; a target in the head matches none of them
     const int tcol = (int)t < head ? 0x7fffffff : (int)t - head;
@@ -267,24 +304,47 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
     if (edge >= 0) z[edge] = ce_gradient_one<T>(z[edge], edge, (int)t, ex, inv_n);
 }
 
-// Adds the per-row losses of one launch to the running sum, in a fixed order
-// (one workgroup, fixed strides), so repeated runs give the same bits.  With
-// `mean_out` the mean over the valid rows is written there as well (the last
-// launch of a single-head call: saves the separate finalize launch).
-__global__ __launch_bounds__(256) void loss_accumulate_kernel(const float* __restrict__ row_loss,
-                                                              int rows, DeviceHeader* hdr,
-                                                              float* __restrict__ mean_out) {
+// Where the loss goes once the last row losses are summed (n_heads = 0: not yet).  `heads`: the
+// headers of all heads, whose weighted means make up the loss; head_losses (optional) receives the
+// unweighted ones.
+struct LossOut {
+    const DeviceHeader* heads;
+    int n_heads;
+    float* loss;
+    float* head_losses;
+    float w[MAX_HEADS];
+};
+
+// Adds the per-row losses of one launch to the head's running sum in a fixed order (256 threads of
+// one workgroup, fixed strides), so repeated runs give the same bits, and writes the loss after the
+// last.  Its own launch is mostly latency (5-8 us), so it rides along as one more workgroup of the
+// kernel that finishes dX or dgamma where there is one.
+__device__ __forceinline__ void loss_accumulate(const float* __restrict__ row_loss, int rows, DeviceHeader* hdr,
+                                                const LossOut& out) {
     __shared__ double part[4];
     double s = 0.0;
+#pragma unroll 8
     for (int i = threadIdx.x; i < rows; i += 256) s += (double)row_loss[i];
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const double total = hdr->loss_sum + ((part[0] + part[1]) + (part[2] + part[3]));
-        hdr->loss_sum = total;
-        if (mean_out) *mean_out = hdr->n_valid > 0 ? (float)(total / (double)hdr->n_valid) : 0.f;
+        hdr->loss_sum += (part[0] + part[1]) + (part[2] + part[3]);
+        if (out.n_heads > 0) {
+            double total = 0.0;
+            for (int j = 0; j < out.n_heads; ++j) {
+                const DeviceHeader& h = out.heads[j];
+                const double mean = h.n_valid > 0 ? h.loss_sum / (double)h.n_valid : 0.0;
+                if (out.head_losses) out.head_losses[j] = (float)mean;
+                total += (double)out.w[j] * mean;
+            }
+            *out.loss = (float)total;
+        }
     }
+}
+__global__ __launch_bounds__(256) void loss_accumulate_kernel(const float* row_loss, int rows, DeviceHeader* hdr,
+                                                              LossOut out) {
+    loss_accumulate(row_loss, rows, hdr, out);
 }
 
 // Counts the valid rows and resets the running loss.  Integer sum: exact in any order.
@@ -293,36 +353,8 @@ __global__ __launch_bounds__(1024) void count_valid_kernel(const int64_t* __rest
                                                            int64_t BT, int64_t ignore_index,
                                                            float weight, DeviceHeader* hdr) {
     __shared__ int part[16];
-    int c = 0;
-    for (int64_t i = threadIdx.x; i < BT; i += 1024) c += (targets[i] != ignore_index);
-    c = wave_sum(c);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int n = 0;
-        for (int w = 0; w < 16; ++w) n += part[w];
-        hdr->n_valid = n;
-        hdr->inv_n = n > 0 ? weight / (float)n : 0.f;
-        hdr->loss_sum = 0.0;
-    }
-}
-
-// loss = sum over heads of weight_j * (mean loss of head j); head_losses (optional)
-// receives the unweighted means.  One header per head; WeightsT is a struct of
-// floats w[] passed by value.
-template <typename WeightsT>
-__global__ void finalize_loss_kernel(const DeviceHeader* hdr, int n_heads, WeightsT weights,
-                                     float* loss, float* __restrict__ head_losses) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double total = 0.0;
-        for (int j = 0; j < n_heads; ++j) {
-            const double mean =
-                hdr[j].n_valid > 0 ? hdr[j].loss_sum / (double)hdr[j].n_valid : 0.0;
-            if (head_losses) head_losses[j] = (float)mean;
-            total += (double)weights.w[j] * mean;
-        }
-        *loss = (float)total;
-    }
+    const int n = count_rows<1024>(targets, (int)BT, ignore_index, part);
+    if (threadIdx.x == 0) write_header(hdr, n, weight);
 }
 
 }  // namespace flce

@@ -81,8 +81,8 @@ struct Plan {
     bool fast_logits = false, fast_dx = false, fast_dw_full = false, fast_dw_last = false;
     int dx_ksplit = 1;     // K ranges of the dX product (K = V), > 1 when C x H has few tiles
     int dx_tile = 256;     // its tile size
-    // every product of every chunk runs on the tuned kernel: chunks are compacted, i.e.
-    // rows with an ignored target are left out of the products (see compact.h)
+    // chunks are compacted, i.e. rows with an ignored target are left out of the products (see
+    // compact.h)
     bool compact = false;
     // byte offsets into the workspace
     size_t off_hdr = 0, off_row_loss = 0, off_z = 0, off_gt = 0, off_wt = 0, off_xt = 0,
@@ -213,7 +213,9 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
         p.dx_tile = cut.tile;
         p.dx_ksplit = cut.ranges;
     }
-    p.compact = allow_compact && p.fast_logits && p.fast_dx && p.fast_dw_full && p.fast_dw_last;
+    // (the copies move 16-byte vectors; bf16 rows of other lengths do not run on the tuned kernel)
+    p.compact = allow_compact &&
+                (dtype == 0 ? H % 4 == 0 : p.fast_logits && p.fast_dx && p.fast_dw_full && p.fast_dw_last);
 
     size_t off = 0;
     auto take = [&](size_t bytes) {

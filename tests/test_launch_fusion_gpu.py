@@ -1,0 +1,114 @@
+"""Launches that carry several small steps: the row selection (count, compaction, copy, clearing),
+the row kernel that counts the batch itself, and the kernel that finishes dX and sums the loss.
+Compared with plain torch in 64 bits at the sizes where a rule changes over."""
+import math
+
+import pytest
+import torch
+
+from test_guarded_product_gpu import reference
+
+pytestmark = pytest.mark.gpu
+TOL = {torch.float32: 2e-6, torch.bfloat16: 8e-3}   # as in the product tests
+
+
+def make(BT, H, V, dtype, ignore, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    X = torch.randn(BT, H, device="cuda", generator=g).to(dtype)
+    W = (torch.randn(V, H, device="cuda", generator=g) * 0.05).to(dtype)
+    t = torch.randint(0, V, (BT,), device="cuda", generator=g)
+    if ignore == "front":
+        t[:BT // 2] = -100
+    elif ignore == "row 0":
+        t[0] = -100
+    elif ignore == "all but one":
+        t[torch.arange(BT, device="cuda") != BT // 2] = -100
+    elif ignore == "all":
+        t[:] = -100
+    elif ignore == "scattered":
+        t[torch.rand(BT, device="cuda", generator=g) < 0.3] = -100
+    return X, W, t
+
+
+def check(got, X, W, t, dtype):
+    loss, dX, dW = got
+    torch.cuda.synchronize()
+    rl, rX, rW = reference(X.float(), W.float(), t)
+    tol = TOL[dtype]
+    if dtype == torch.float32:
+        # a sum over K is rounded 6 K / 16 times (six plane products per 16 K), 2^-24 of the running
+        # sum each, random signs: past K = 3000 that is more than the 2e-6 stated for short sums
+        tol = max(tol, 2.0 ** -24 * math.sqrt(6 * max(X.shape[0], *W.shape) / 16))
+    assert abs(float(loss) - rl) <= max(2e-6, tol / 4) * max(abs(rl), 1e-30)
+    for name, a, b in (("dX", dX, rX), ("dW", dW, rW)):
+        err = float((a.double().cpu() - b).norm() / b.norm().clamp(min=1e-30))
+        assert err <= tol, (name, err)
+    assert (dX[t == -100] == 0).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("ignore", ["none", "front", "row 0", "all but one", "all", "scattered"])
+@pytest.mark.parametrize("compaction", [True, False])
+@pytest.mark.parametrize("BT", [1, 5, 259])
+def test_row_selection(dtype, ignore, compaction, BT):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, 64, 300, dtype, ignore, BT)
+    check(flce.flce_fwd_bwd_opt(X, W, t, flce.flce_options(row_compaction=compaction)), X, W, t, dtype)
+
+
+@pytest.mark.parametrize("BT", [2048, 2049, 4097, 32768, 32769])   # counted by the row kernel; 5 rows per workgroup; both sides of the one-launch selection
+@pytest.mark.parametrize("compaction", [True, False])
+def test_rules_change_over_with_the_row_count(BT, compaction):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, 32, 70, torch.float32, "scattered", BT)
+    check(flce.flce_fwd_bwd_opt(X, W, t, flce.flce_options(row_compaction=compaction)), X, W, t, torch.float32)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("ignore", ["none", "front", "all but one", "all", "scattered"])
+def test_selection_over_several_chunks(dtype, ignore):
+    # 5 launches of 256 rows at most; the valid rows are dealt to the last ones
+    import paper_2410_10989_amd as flce
+    X, W, t = make(1200, 64, 320, dtype, ignore, 5)
+    o = flce.flce_options(logits_budget_bytes=256 * 320 * X.element_size(), row_compaction=True)
+    check(flce.flce_fwd_bwd_opt(X, W, t, o), X, W, t, dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("H,V", [(64, 320), (256, 9000), (66, 2600)])   # dX whole, cut along K, cut with odd rows
+@pytest.mark.parametrize("flags", [0, 1, 2])
+def test_heads_and_skipped_gradients(dtype, H, V, flags):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(150, H, V, dtype, "scattered", 9)
+    _, W2, t2 = make(150, H, V, dtype, "front", 10)
+    loss, heads, dX, dWs = flce.flce_multihead_fwd_bwd(X, [W, W2], [t, t2], [1.0, 0.5], flags=flags)
+    torch.cuda.synchronize()
+    r1, r2 = reference(X.float(), W.float(), t), reference(X.float(), W2.float(), t2)
+    tol = TOL[dtype]
+    assert abs(float(loss) - (r1[0] + 0.5 * r2[0])) <= max(2e-6, tol / 4) * abs(r1[0])
+    assert abs(float(heads[1]) - r2[0]) <= max(2e-6, tol / 4) * abs(r2[0])
+    want = r1[1] + 0.5 * r2[1]
+    if not flags & flce.SKIP_DX:
+        assert float((dX.double().cpu() - want).norm() / want.norm()) <= tol
+    if not flags & flce.SKIP_DW:
+        assert float((dWs[1].double().cpu() - 0.5 * r2[2]).norm() / (0.5 * r2[2]).norm()) <= tol
+
+
+@pytest.mark.parametrize("BT", [1, 2048, 2049])
+@pytest.mark.parametrize("noalloc", [True, False])
+@pytest.mark.parametrize("ignore", ["row 0", "all", "scattered"])
+def test_cross_entropy_counts_its_rows(BT, noalloc, ignore):
+    import paper_2410_10989_amd as flce
+    Z, _, t = make(BT, 333, 333, torch.float32, ignore, BT + 1)
+    z = Z.double()
+    ok = (t != -100).double()[:, None]
+    n = max(1.0, float(ok.sum()))
+    lse = torch.logsumexp(z, 1, keepdim=True)
+    at = t.clamp(min=0)[:, None]
+    want = torch.exp(z - lse).scatter_add(1, at, torch.full_like(lse, -1.0)) * ok / n
+    rl = float(((lse - z.gather(1, at)) * ok).sum()) / n
+    loss = torch.empty((), device="cuda")
+    flce.flce_cross_entropy_inplace(Z, t, -100, loss=loss, noalloc=noalloc)
+    torch.cuda.synchronize()
+    assert abs(float(loss) - rl) <= 2e-6 * max(1.0, abs(rl))
+    assert float((Z.double() - want).norm()) <= 2e-6 * max(float(want.norm()), 1e-30)
