@@ -192,10 +192,13 @@ int launch_gemm_guarded(int kind, const T* A, int64_t lda, const T* B, int64_t l
     const int64_t total = ((M + tile - 1) / tile) * ((N + tile - 1) / tile) * ksplit;
     if (total > MAX_GRID_X - FG_XCDS) return FLCE_ERR_SHAPE;   // check_launch_limits refuses such shapes up front
     const dim3 grid((unsigned)((total + FG_XCDS - 1) / FG_XCDS * FG_XCDS));
+    const dim3 block((unsigned)gg_threads(tile));
     if (tile == 64)
-        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64>), grid, dim3(GG_THREADS), 0, s, a);
+        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64>), grid, block, 0, s, a);
+    else if (tile == 128)
+        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 128>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 128>), grid, dim3(GG_THREADS), 0, s, a);
+        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 256>), grid, block, 0, s, a);
     HIP_TRY(hipGetLastError());
     return FLCE_OK;
 }
@@ -429,15 +432,22 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         }
 
         // logits of the chunk: Z = X_c W^T
-        if (BF16 && p.fast_logits) {
-            if constexpr (BF16)
-                FLCE_TRY((launch_gemm_fast<bf16_t, void, false, false>(
-                    FLCE_KIND_LOGITS_GEMM, Xc, H, W, H, Z, p.ldz, nullptr, 0, rows, V, H, s, tuned_cut(rows, V, H, 1).tile,
-                    1, 0, dyn_m)));
-        } else {
-            FLCE_TRY((launch_gemm_guarded<T, T, false, false>(FLCE_KIND_LOGITS_GEMM, Xc, H, W, H, Z, p.ldz,
-                                                              nullptr, nullptr, rows, V, H, s,
-                                                              guarded_cut(rows, V, H, 1).tile, 1, 0, dyn_m)));
+        {
+            const bool fast = BF16 && p.fast_logits;
+            const VocabCut cut = vocab_cut(fast, V, rows, H, false);
+            auto product = [&](int64_t v0, int64_t nv, int tile) -> int {   // columns v0 .. v0 + nv - 1
+                if constexpr (BF16) {
+                    if (fast)
+                        return launch_gemm_fast<bf16_t, void, false, false>(FLCE_KIND_LOGITS_GEMM, Xc, H, W + v0 * H, H,
+                                                                            Z + v0, p.ldz, nullptr, 0, rows, nv, H, s,
+                                                                            tile, 1, 0, dyn_m);
+                }
+                return launch_gemm_guarded<T, T, false, false>(FLCE_KIND_LOGITS_GEMM, Xc, H, W + v0 * H, H, Z + v0,
+                                                               p.ldz, nullptr, nullptr, rows, nv, H, s, tile, 1, 0,
+                                                               dyn_m);
+            };
+            FLCE_TRY(product(0, cut.main, cut.tile));
+            if (cut.main < V) FLCE_TRY(product(cut.main, V - cut.main, cut.rest_tile));
         }
 
         // loss and in-place dlogits
@@ -522,40 +532,43 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         // dW (+)= G^T X_c   (K = the chunk's rows; in a compacted chunk K = *n_live)
         if (want_dw) {
             const bool fast = BF16 && (last ? p.fast_dw_last : p.fast_dw_full);
-            if (fast) {
+            const VocabCut cut = vocab_cut(fast, V, H, rows, p.tail_bytes > 0);
+            // rows v0 .. v0 + nv - 1 of dW: the first chunk writes its sums, the others add to them, the
+            // last writes dW; bf16 sums over several chunks are kept in fp32 (dWacc)
+            auto product = [&](int64_t v0, int64_t nv, int tile) -> int {
+                const T* G = Z + v0;
+                T* out = dW + v0 * H;
+                float* acc = p.fp32_dw_acc ? dWacc + v0 * H : nullptr;
                 if constexpr (BF16) {
-                    const int dw_tile = tuned_cut(V, H, rows, 1).tile;
-                    if (p.nchunks == 1) {
-                        FLCE_TRY((launch_gemm_fast<bf16_t, void, true, true>(
-                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dW, H, nullptr, 0, V, H, rows, s, dw_tile, 1, 0,
-                            dyn_dw, tail, p.tail_bytes)));
-                    } else if (c == 0) {
-                        FLCE_TRY((launch_gemm_fast<float, void, true, true>(
-                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dWacc, H, nullptr, 0, V, H, rows, s, dw_tile, 1, 0,
-                            dyn_dw, tail, p.tail_bytes)));
-                    } else if (!last) {
-                        FLCE_TRY((launch_gemm_fast<float, float, true, true>(
-                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dWacc, H, dWacc, H, V, H, rows, s, dw_tile, 1, 0,
-                            dyn_dw, tail, p.tail_bytes)));
-                    } else {   // last chunk: add the fp32 partial sums and write dW in bf16
-                        FLCE_TRY((launch_gemm_fast<bf16_t, float, true, true>(
-                            FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dW, H, dWacc, H, V, H, rows, s, dw_tile, 1, 0,
-                            dyn_dw, tail, p.tail_bytes)));
+                    if (fast) {
+                        float* part = nv == V ? tail : nullptr;
+                        const int kind = FLCE_KIND_DW_GEMM;
+                        if (p.nchunks == 1)
+                            return launch_gemm_fast<bf16_t, void, true, true>(kind, G, p.ldz, Xc, H, out, H, nullptr, 0, nv,
+                                                                              H, rows, s, tile, 1, 0, dyn_dw, part,
+                                                                              p.tail_bytes);
+                        if (c == 0)
+                            return launch_gemm_fast<float, void, true, true>(kind, G, p.ldz, Xc, H, acc, H, nullptr, 0, nv, H,
+                                                                             rows, s, tile, 1, 0, dyn_dw, part,
+                                                                             p.tail_bytes);
+                        if (!last)
+                            return launch_gemm_fast<float, float, true, true>(kind, G, p.ldz, Xc, H, acc, H, acc, H, nv, H,
+                                                                              rows, s, tile, 1, 0, dyn_dw, part,
+                                                                              p.tail_bytes);
+                        return launch_gemm_fast<bf16_t, float, true, true>(kind, G, p.ldz, Xc, H, out, H, acc, H, nv, H, rows,
+                                                                           s, tile, 1, 0, dyn_dw, part, p.tail_bytes);
                     }
                 }
-            } else {
-                const int tile = guarded_cut(V, H, rows, 1).tile;
-                float* acc = p.fp32_dw_acc ? dWacc : nullptr;   // fp32 storage adds up in dW itself
-                if (acc && !last) {
-                    FLCE_TRY((launch_gemm_guarded<T, float, true, true>(
-                        FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, acc, H, c > 0 ? acc : nullptr, nullptr, V, H, rows, s,
-                        tile, 1, 0, dyn_dw)));
-                } else {
-                    FLCE_TRY((launch_gemm_guarded<T, T, true, true>(
-                        FLCE_KIND_DW_GEMM, Z, p.ldz, Xc, H, dW, H, acc, !acc && c > 0 ? dW : nullptr, V, H, rows,
-                        s, tile, 1, 0, dyn_dw)));
-                }
-            }
+                if (acc && !last)
+                    return launch_gemm_guarded<T, float, true, true>(FLCE_KIND_DW_GEMM, G, p.ldz, Xc, H, acc, H,
+                                                                     c > 0 ? acc : nullptr, nullptr, nv, H, rows, s, tile,
+                                                                     1, 0, dyn_dw);
+                return launch_gemm_guarded<T, T, true, true>(FLCE_KIND_DW_GEMM, G, p.ldz, Xc, H, out, H, acc,
+                                                             !acc && c > 0 ? out : nullptr, nv, H, rows, s, tile, 1, 0,
+                                                             dyn_dw);
+            };
+            FLCE_TRY(product(0, cut.main, cut.tile));
+            if (cut.main < V) FLCE_TRY(product(cut.main, V - cut.main, cut.rest_tile));
         }
     }
     return FLCE_OK;

@@ -15,26 +15,28 @@
 // NaN; a workgroup that finds a NaN among its sums computes its tile again with fp32 matrix
 // instructions, so such inputs give what plain fp32 products give.
 //
-// Shape: 256 threads = 4 wavefronts (2 x 2); macro tile TILE x TILE, TILE = 128 or 64 (each
-// wavefront owns 2 x 2 or one 32 x 32 MFMA tile), K step 32.  A thread stages 8 consecutive K
-// values of one tile row per slot: row form 32 contiguous bytes, column form 8 loads that are
-// contiguous across the wavefront's lanes.  The next K step's loads are in flight while the
-// current one is multiplied; one LDS stage, so that several workgroups fit a CU and one splits
-// while another multiplies.  LDS rows are 64 bytes whose four 16-byte pieces are XOR swizzled
-// with (row / 4) % 4: writes and fragment reads touch all banks evenly.
-// What bounds it (fp32): the six products per K, i.e. the bf16 matrix pipe, and the split's lane
-// operations (5.5 per staged element).  Measured at 2048 x 1024 x 50257: logits 2.15 -> 1.26 ms,
-// dX 4.82 -> 1.19, dW 2.31 -> 1.33 (167-178 TFLOP/s of fp32 products, 1.0-1.07 PFLOP/s on the
-// matrix pipe) against the fp32 instruction's 151 TFLOP/s peak in a large library product, and 0.29
-// ms of transposed copies are gone; at 256 x 512 x 4096, 64-tiles: 51 -> 19, 29 -> 17, 29 -> 18 us.
+// Shape: 256 threads = 4 wavefronts (2 x 2); macro tile TILE x TILE, TILE = 128 (each wavefront
+// owns 2 x 2 32 x 32 MFMA tiles; K step 16) or 64 (one MFMA tile in two accumulators, so that the
+// plane products do not wait for one another; K step 32).  A thread stages 8 consecutive K values
+// of one tile row per operand and step: row form 32 contiguous bytes, column form 8 loads that are
+// contiguous across the wavefront's lanes.  Loads run gg_depth steps ahead in registers; LDS is
+// double buffered with one barrier per step, and the split of step t + 1 (lane operations) stands
+// beside the products of step t (matrix pipe) in the same instruction stream.  LDS: per plane,
+// [K piece of 8][row] 16-byte entries, the rows of odd pieces XOR 8: writes and fragment reads
+// touch all banks evenly.
 #pragma once
 #include "flce_device.h"
 #include "gemm_bf16_nt.h"
 
 namespace flce {
 
-constexpr int GG_THREADS = 256;
-constexpr int GG_BK = 32;   // K elements per step
+constexpr int gg_threads(int tile) { return tile == 256 ? 512 : 256; }
+constexpr int gg_bk(int tile) { return tile == 64 ? 32 : 16; }      // K elements per step
+constexpr int gg_depth(int tile) { return tile == 64 ? 4 : 2; } // K steps whose loads are in flight
+
+// LDS holds the rows of K piece p permuted by XOR with this, so that the 8 or 16 neighbouring lanes
+// of a row-form write (2 or 4 pieces of 4 consecutive rows) touch all banks once.
+__device__ __forceinline__ int gg_fold(int piece) { return (0x6ac0 >> (4 * piece)) & 15; }
 
 struct GGArgs {
     const void* A;
@@ -70,95 +72,84 @@ template <> struct GGTraits<bf16_t> {
     static constexpr int VEC = 8;
 };
 
-// One operand's staging: which slots (tile row, 8 K values) this thread fetches.
+// One operand's staging: the tile row and the 8 K values of a step this thread fetches.
 template <typename T, bool KM, int TILE>
 struct GGStage {
-    static constexpr int SLOTS = TILE / 64;
     static constexpr int PLANES = GGTraits<T>::PLANES;
-    const T* ptr[SLOTS];   // row form: the slot's row; column form: the slot's column
+    static constexpr int PIECES = gg_bk(TILE) / 8;
+    static_assert(TILE * PIECES == gg_threads(TILE), "one slot per thread");
+    const T* ptr;   // row form: the slot's row; column form: the slot's column
     int64_t ld;
-    int row[SLOTS], piece[SLOTS];
-    T raw[SLOTS][8];
+    int k8;         // first of the slot's K values inside a step
+    int lds_at;
+    T raw[gg_depth(TILE)][8];
 
     __device__ __forceinline__ void init(const void* base, int64_t ld_, int r0, int extent, int tid) {
         ld = ld_;
+        // column form: a wavefront's lanes are consecutive columns of one piece
+        const int row = KM ? tid % TILE : tid / PIECES;
+        const int piece = KM ? __builtin_amdgcn_readfirstlane(tid / TILE) : tid % PIECES;
+        k8 = piece * 8;
+        lds_at = (piece * TILE + (row ^ gg_fold(piece))) * 16;
+        // rows past the matrix repeat its last row: they only feed outputs that are not stored
+        const int r = min(r0 + row, extent - 1);
+        ptr = static_cast<const T*>(base) + (KM ? (int64_t)r : (int64_t)r * ld);
+    }
+    // the whole K step starting at k0, into ring position D; V: 16-byte loads (row form)
+    template <int D, bool V>
+    __device__ __forceinline__ void load(int k0) {
+        if constexpr (KM) {
+            const T* p = ptr + (int64_t)(k0 + k8) * ld;
 #pragma unroll
-        for (int h = 0; h < SLOTS; ++h) {
-            if constexpr (KM) {
-                row[h] = tid % TILE;
-                piece[h] = __builtin_amdgcn_readfirstlane(tid / TILE + h * (GG_THREADS / TILE));
-            } else {
-                row[h] = (tid >> 2) + 64 * h;
-                piece[h] = tid & 3;
+            for (int e = 0; e < 8; ++e) raw[D][e] = p[e * ld];
+        } else if constexpr (V) {
+            constexpr int N = GGTraits<T>::VEC;
+            struct alignas(16) Vec { T e[N]; };
+#pragma unroll
+            for (int q = 0; q < 8 / N; ++q) {
+                const Vec v = *reinterpret_cast<const Vec*>(ptr + k0 + k8 + q * N);
+#pragma unroll
+                for (int e = 0; e < N; ++e) raw[D][q * N + e] = v.e[e];
             }
-            // rows past the matrix repeat its last row: they only feed outputs that are not stored
-            const int r = min(r0 + row[h], extent - 1);
-            ptr[h] = static_cast<const T*>(base) + (KM ? (int64_t)r : (int64_t)r * ld);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) raw[D][e] = ptr[k0 + k8 + e];
         }
     }
-    // K step starting at k0; K values from `K` on are zero
-    __device__ __forceinline__ void load(int k0, int K, bool vec) {
-        const bool whole = k0 + GG_BK <= K;   // uniform
+    // a K step that K cuts: zero from K on
+    template <int D>
+    __device__ __forceinline__ void load_tail(int k0, int K) {
 #pragma unroll
-        for (int h = 0; h < SLOTS; ++h) {
-            const int k = k0 + piece[h] * 8;
-            if constexpr (KM) {
-                if (whole) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) raw[h][e] = ptr[h][(int64_t)(k + e) * ld];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        raw[h][e] = (k + e < K) ? ptr[h][(int64_t)(k + e) * ld] : from_f32<T>(0.f);
-                }
-            } else {
-                if (whole && vec) {
-                    constexpr int V = GGTraits<T>::VEC;
-                    struct alignas(16) Vec { T e[V]; };
-#pragma unroll
-                    for (int q = 0; q < 8 / V; ++q) {
-                        const Vec v = *reinterpret_cast<const Vec*>(ptr[h] + k + q * V);
-#pragma unroll
-                        for (int e = 0; e < V; ++e) raw[h][q * V + e] = v.e[e];
-                    }
-                } else if (whole) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) raw[h][e] = ptr[h][k + e];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) raw[h][e] = (k + e < K) ? ptr[h][k + e] : from_f32<T>(0.f);
-                }
-            }
+        for (int e = 0; e < 8; ++e) {
+            const int k = k0 + k8 + e;
+            raw[D][e] = k < K ? ptr[KM ? (int64_t)k * ld : (int64_t)k] : from_f32<T>(0.f);
         }
     }
-    // the loaded step, split into bf16 planes, to LDS
+    // ring position D, split into bf16 planes, to LDS
+    template <int D>
     __device__ __forceinline__ void store(unsigned char* lds) const {
+        u32x4 out[PLANES];
 #pragma unroll
-        for (int h = 0; h < SLOTS; ++h) {
-            unsigned char* dst = lds + row[h] * 64 + ((piece[h] ^ ((row[h] >> 2) & 3)) << 4);
-            u32x4 out[PLANES];
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (PLANES == 1) {
+                const bf16x2 p = {raw[D][2 * q], raw[D][2 * q + 1]};
+                out[0][q] = __builtin_bit_cast(uint32_t, p);
+            } else {
+                float a = raw[D][2 * q], b = raw[D][2 * q + 1];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if constexpr (PLANES == 1) {
-                    const bf16x2 p = {raw[h][2 * q], raw[h][2 * q + 1]};
-                    out[0][q] = __builtin_bit_cast(uint32_t, p);
-                } else {
-                    float a = raw[h][2 * q], b = raw[h][2 * q + 1];
-#pragma unroll
-                    for (int p = 0; p < PLANES; ++p) {
-                        const bf16x2 c = {(bf16_t)a, (bf16_t)b};   // round to nearest even
-                        const uint32_t u = __builtin_bit_cast(uint32_t, c);
-                        out[p][q] = u;
-                        if (p + 1 < PLANES) {   // exact: the remainder of a rounding
-                            a -= __uint_as_float(u << 16);
-                            b -= __uint_as_float(u & 0xffff0000u);
-                        }
+                for (int p = 0; p < PLANES; ++p) {
+                    uint32_t u;   // both rounded to nearest even
+                    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(u) : "v"(a), "v"(b));
+                    out[p][q] = u;
+                    if (p + 1 < PLANES) {   // exact: the remainder of a rounding
+                        a -= __uint_as_float(u << 16);
+                        b -= __uint_as_float(u & 0xffff0000u);
                     }
                 }
             }
-#pragma unroll
-            for (int p = 0; p < PLANES; ++p) *reinterpret_cast<u32x4*>(dst + p * TILE * 64) = out[p];
         }
+#pragma unroll
+        for (int p = 0; p < PLANES; ++p) *reinterpret_cast<u32x4*>(lds + lds_at + p * TILE * gg_bk(TILE) * 2) = out[p];
     }
 };
 
@@ -169,15 +160,19 @@ __device__ __forceinline__ float gg_element(const float* base, int64_t ld, int r
 }
 
 template <typename T, typename OutT, bool A_KM, bool B_KM, int TILE>
-__global__ __launch_bounds__(GG_THREADS, 2) void gemm_guarded(GGArgs a) {
+__global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a) {
     constexpr int PLANES = GGTraits<T>::PLANES;
-    constexpr int W = TILE / 64;            // 32 x 32 MFMA tiles per wavefront and direction
-    constexpr int SIDE = TILE * 64;         // bytes of one plane of one operand
-    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * PLANES * SIDE];
+    constexpr int WAVES_N = TILE == 256 ? 4 : 2;              // wavefronts: 2 x WAVES_N
+    constexpr int WM = TILE / 64, WN = TILE / 32 / WAVES_N;   // 32 x 32 MFMA tiles per wavefront
+    constexpr int BK = gg_bk(TILE), DEPTH = gg_depth(TILE);
+    constexpr int PLANE = TILE * BK * 2;    // bytes of one plane of one operand
+    constexpr int SIDE = PLANES * PLANE;
+    constexpr int ACCS = TILE == 64 ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2][2 * SIDE];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
 
     const FgResolved rs = fg_resolve(a, a.Cin != nullptr);
     if (rs.skip) return;
@@ -194,146 +189,228 @@ __global__ __launch_bounds__(GG_THREADS, 2) void gemm_guarded(GGArgs a) {
     const int split = seq / tiles;
     int m0, n0;
     fg_tile_origin<TILE>(seq - split * tiles, tiles_m, tiles_n, a.group_m, a.group_cols, m0, n0);
-    const int steps = (K + GG_BK - 1) / GG_BK;
-    const int k_begin = (int)((int64_t)steps * split / rs.ksplit) * GG_BK;
-    const int k_end = min(K, (int)((int64_t)steps * (split + 1) / rs.ksplit) * GG_BK);
+    const int steps_all = (K + BK - 1) / BK;
+    const int k_begin = (int)((int64_t)steps_all * split / rs.ksplit) * BK;
+    const int k_end = min(K, (int)((int64_t)steps_all * (split + 1) / rs.ksplit) * BK);
+    const int n_whole = max(0, k_end - k_begin) / BK;   // K steps that are whole; at most one more is not
 
-    f32x16 acc[W][W];
+    f32x16 acc[WM][WN], acc2[ACCS];   // acc2[1]: the second accumulator of a 64-tile
 #pragma unroll
-    for (int i = 0; i < W; ++i)
+    for (int i = 0; i < WM; ++i)
 #pragma unroll
-        for (int j = 0; j < W; ++j)
+        for (int j = 0; j < WN; ++j)
 #pragma unroll
             for (int g = 0; g < 16; ++g) acc[i][j][g] = 0.f;
+#pragma unroll
+    for (int g = 0; g < 16; ++g) acc2[ACCS - 1][g] = 0.f;
 
     GGStage<T, A_KM, TILE> sa;
     GGStage<T, B_KM, TILE> sb;
     sa.init(a.A, a.lda, m0, M, tid);
     sb.init(a.B, a.ldb, n0, N, tid);
-    unsigned char* lds_a = lds;
-    unsigned char* lds_b = lds + PLANES * SIDE;
     const int frow = lane & 31, fhalf = lane >> 5;
+    
 
-    if (k_begin < k_end) {
-        sa.load(k_begin, k_end, a.vec_a);
-        sb.load(k_begin, k_end, a.vec_b);
-    }
-    for (int k0 = k_begin; k0 < k_end; k0 += GG_BK) {
-        __syncthreads();   // the previous step's fragments have been read
-        sa.store(lds_a);
-        sb.store(lds_b);
-        __syncthreads();
-        if (k0 + GG_BK < k_end) {
-            sa.load(k0 + GG_BK, k_end, a.vec_a);
-            sb.load(k0 + GG_BK, k_end, a.vec_b);
-        }
+    // the barrier waits for this wavefront's LDS accesses only, not for the loads in flight
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    auto multiply = [&](int buf) {
+        const unsigned char* la = lds[buf] + wm * WM * 512;
+        const unsigned char* lb = lds[buf] + SIDE + wn * WN * 512;
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            const int at = frow * 64 + (((2 * kk + fhalf) ^ ((frow >> 2) & 3)) << 4);
-            bf16x8 fa[PLANES][W], fb[PLANES][W];
+        for (int kk = 0; kk < BK / 16; ++kk) {
+            const int frag = ((2 * kk + fhalf) * TILE + (frow ^ gg_fold(2 * kk + fhalf))) * 16;   // this lane's part of fragment 0
+            bf16x8 fb[PLANES][WN];
 #pragma unroll
             for (int p = 0; p < PLANES; ++p)
 #pragma unroll
-                for (int i = 0; i < W; ++i) {
-                    fa[p][i] = *reinterpret_cast<const bf16x8*>(lds_a + p * SIDE + (wm * W + i) * 2048 + at);
-                    fb[p][i] = *reinterpret_cast<const bf16x8*>(lds_b + p * SIDE + (wn * W + i) * 2048 + at);
-                }
+                for (int j = 0; j < WN; ++j) fb[p][j] = *reinterpret_cast<const bf16x8*>(lb + p * PLANE + frag + j * 512);
             // plane pairs (of a, of b), smallest products first
             constexpr int PAIRS = PLANES == 3 ? 6 : 1;
             constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+            // IB rows of MFMA tiles at a time: few enough fragments of A to leave room for the sums
+            constexpr int IB = TILE == 256 ? 2 : WM;
 #pragma unroll
-            for (int q = 0; q < PAIRS; ++q) {
-                const int pa = PLANES == 3 ? PA[q] : 0, pb = PLANES == 3 ? PB[q] : 0;
+            for (int ib = 0; ib < WM; ib += IB) {
+                bf16x8 fa[PLANES][IB];
 #pragma unroll
-                for (int i = 0; i < W; ++i)
+                for (int p = 0; p < PLANES; ++p)
 #pragma unroll
-                    for (int j = 0; j < W; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[pb][j], fa[pa][i], acc[i][j], 0, 0, 0);
-            }
-        }
-    }
-
-    if constexpr (PLANES == 3) {
-        bool nan = false;
+                    for (int i = 0; i < IB; ++i)
+                        fa[p][i] = *reinterpret_cast<const bf16x8*>(la + p * PLANE + frag + (ib + i) * 512);
 #pragma unroll
-        for (int i = 0; i < W; ++i)
+                for (int q = 0; q < PAIRS; ++q) {
+                    const int pa = PLANES == 3 ? PA[q] : 0, pb = PLANES == 3 ? PB[q] : 0;
+                    if constexpr (ACCS == 2) {
+                        f32x16& c = (kk & 1) ? acc2[ACCS - 1] : acc[0][0];
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[pb][0], fa[pa][0], c, 0, 0, 0);
+                    } else {
 #pragma unroll
-            for (int j = 0; j < W; ++j)
+                        for (int i = 0; i < IB; ++i)
 #pragma unroll
-                for (int g = 0; g < 16; ++g) {
-                    const float v = acc[i][j][g];
-                    nan |= (v != v);
-                }
-        if (__syncthreads_or(nan)) {
-            int ra[W], rb[W];
-#pragma unroll
-            for (int i = 0; i < W; ++i) {
-                ra[i] = min(m0 + (wm * W + i) * 32 + frow, M - 1);
-                rb[i] = min(n0 + (wn * W + i) * 32 + frow, N - 1);
-#pragma unroll
-                for (int j = 0; j < W; ++j)
-#pragma unroll
-                    for (int g = 0; g < 16; ++g) acc[i][j][g] = 0.f;
-            }
-            const float* A = static_cast<const float*>(a.A);
-            const float* B = static_cast<const float*>(a.B);
-            for (int k0 = k_begin; k0 < k_end; k0 += 8) {
-                float va[4][W], vb[4][W];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int i = 0; i < W; ++i) {
-                        va[u][i] = gg_element<A_KM>(A, a.lda, ra[i], k0 + 2 * u + fhalf, k_end);
-                        vb[u][i] = gg_element<B_KM>(B, a.ldb, rb[i], k0 + 2 * u + fhalf, k_end);
+                            for (int j = 0; j < WN; ++j)
+                                acc[ib + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[pb][j], fa[pa][i], acc[ib + i][j], 0, 0, 0);
                     }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int i = 0; i < W; ++i)
-#pragma unroll
-                        for (int j = 0; j < W; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[u][j], va[u][i], acc[i][j], 0, 0, 0);
+                }
             }
         }
+    };
+    // The whole K steps.  Loads past the last one repeat it and are not used: no branch, so that
+    // the waits for a step's loads leave the later ones in flight.
+    auto run = [&](auto vec_) {
+        constexpr bool V = decltype(vec_)::value;
+        const int last = k_begin + (n_whole - 1) * BK;
+        auto fetch = [&](auto d_, int t) {
+            constexpr int D = decltype(d_)::value;
+            const int k0 = min(k_begin + t * BK, last);
+            sa.template load<D, V>(k0);
+            sb.template load<D, V>(k0);
+        };
+        auto put = [&](auto d_, int buf) {
+            constexpr int D = decltype(d_)::value;
+            sa.template store<D>(lds[buf]);
+            sb.template store<D>(lds[buf] + SIDE);
+        };
+        // step t, t % DEPTH = D: request step t + DEPTH, multiply step t, split step t + 1
+        auto step = [&](auto d_, int t) {
+            constexpr int D = decltype(d_)::value;
+            barrier();
+            fetch(d_, t + DEPTH);
+            multiply(D & 1);
+            put(std::integral_constant<int, (D + 1) % DEPTH>{}, (D + 1) & 1);
+        };
+        using I0 = std::integral_constant<int, 0>;
+        using I1 = std::integral_constant<int, 1>;
+        using I2 = std::integral_constant<int, 2 % DEPTH>;
+        using I3 = std::integral_constant<int, 3 % DEPTH>;
+        fetch(I0{}, 0);
+        fetch(I1{}, 1);
+        if constexpr (DEPTH == 4) {
+            fetch(I2{}, 2);
+            fetch(I3{}, 3);
+        }
+        put(I0{}, 0);
+        int t = 0;
+        for (; t + DEPTH <= n_whole; t += DEPTH) {
+            step(I0{}, t);
+            step(I1{}, t + 1);
+            if constexpr (DEPTH == 4) {
+                step(I2{}, t + 2);
+                step(I3{}, t + 3);
+            }
+        }
+        if (t < n_whole) step(I0{}, t++);
+        if constexpr (DEPTH == 4) {
+            if (t < n_whole) step(I1{}, t++);
+            if (t < n_whole) step(I2{}, t++);
+        }
+    };
+    if (n_whole > 0) {
+        if ((A_KM || a.vec_a) && (B_KM || a.vec_b)) run(std::true_type{}); else run(std::false_type{});
+    }
+    if (k_begin + n_whole * BK < k_end) {   // the cut step
+        sa.template load_tail<0>(k_begin + n_whole * BK, k_end);
+        sb.template load_tail<0>(k_begin + n_whole * BK, k_end);
+        barrier();
+        sa.template store<0>(lds[0]);
+        sb.template store<0>(lds[0] + SIDE);
+        barrier();
+        multiply(0);
+    }
+    if constexpr (ACCS == 2) {
+#pragma unroll
+        for (int g = 0; g < 16; ++g) acc[0][0][g] += acc2[ACCS - 1][g];
     }
 
     // the B fragment is the MFMA's first operand: accumulator register g of lane l holds row
     // l % 32, column 8*(g/4) + 4*(l/32) + g%4 of its 32 x 32 tile
     OutT* C = static_cast<OutT*>(a.C) + (int64_t)split * a.split_stride;
+    auto write = [&](const f32x16 (&sum)[WM][WN]) {
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
-        const int row = m0 + (wm * W + i) * 32 + frow;
-        if (row >= M) continue;
-        OutT* crow = C + (int64_t)row * a.ldc;
-        const unsigned char* inrow =
-            static_cast<const unsigned char*>(a.Cin) + (int64_t)row * a.ldcin * (a.cin_f32 ? 4 : (int)sizeof(OutT));
+        for (int i = 0; i < WM; ++i) {
+            const int row = m0 + (wm * WM + i) * 32 + frow;
+            if (row >= M) continue;
+            OutT* crow = C + (int64_t)row * a.ldc;
+            const unsigned char* inrow =
+                static_cast<const unsigned char*>(a.Cin) + (int64_t)row * a.ldcin * (a.cin_f32 ? 4 : (int)sizeof(OutT));
 #pragma unroll
-        for (int j = 0; j < W; ++j)
+            for (int j = 0; j < WN; ++j)
 #pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-                const int col = n0 + (wn * W + j) * 32 + 8 * g4 + 4 * fhalf;
-                float v[4];
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    __builtin_amdgcn_sched_barrier(0);   // one store's addresses at a time
+                    const int col = n0 + (wn * WN + j) * 32 + 8 * g4 + 4 * fhalf;
+                    float v[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * g4 + e];
-                if (rs.use_in) {
+                    for (int e = 0; e < 4; ++e) v[e] = sum[i][j][4 * g4 + e];
+                    if (rs.use_in) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (col + e < N)
-                            v[e] += a.cin_f32 ? reinterpret_cast<const float*>(inrow)[col + e]
-                                              : to_f32(reinterpret_cast<const OutT*>(inrow)[col + e]);
+                        for (int e = 0; e < 4; ++e)
+                            if (col + e < N)
+                                v[e] += a.cin_f32 ? reinterpret_cast<const float*>(inrow)[col + e]
+                                                  : to_f32(reinterpret_cast<const OutT*>(inrow)[col + e]);
+                    }
+                    if (a.vec_c && col + 4 <= N) {
+                        struct alignas(4 * sizeof(OutT)) Quad { OutT e[4]; } q;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) q.e[e] = from_f32<OutT>(v[e]);
+                        *reinterpret_cast<Quad*>(crow + col) = q;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (col + e < N) crow[col + e] = from_f32<OutT>(v[e]);
+                    }
                 }
-                if (a.vec_c && col + 4 <= N) {
-                    struct alignas(4 * sizeof(OutT)) Quad { OutT e[4]; } q;
+        }
+    };
+    if constexpr (PLANES == 3) {
+        bool nan = false;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) q.e[e] = from_f32<OutT>(v[e]);
-                    *reinterpret_cast<Quad*>(crow + col) = q;
-                } else {
+        for (int i = 0; i < WM; ++i)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (col + e < N) crow[col + e] = from_f32<OutT>(v[e]);
+            for (int j = 0; j < WN; ++j)
+#pragma unroll
+                for (int g = 0; g < 16; ++g) {
+                    const float v = acc[i][j][g];
+                    nan |= (v != v);
                 }
+        if (__syncthreads_or(nan)) {   // (sums of its own: no registers shared with the path below)
+            f32x16 sum[WM][WN];
+            int ra[WM], rb[WN];
+#pragma unroll
+            for (int j = 0; j < WN; ++j) rb[j] = min(n0 + (wn * WN + j) * 32 + frow, N - 1);
+#pragma unroll
+            for (int i = 0; i < WM; ++i) {
+                ra[i] = min(m0 + (wm * WM + i) * 32 + frow, M - 1);
+#pragma unroll
+                for (int j = 0; j < WN; ++j)
+#pragma unroll
+                    for (int g = 0; g < 16; ++g) sum[i][j][g] = 0.f;
             }
+            const float* A = static_cast<const float*>(a.A);
+            const float* B = static_cast<const float*>(a.B);
+            constexpr int U = TILE == 256 ? 2 : 4;   // K pairs in flight (registers)
+            for (int k0 = k_begin; k0 < k_end; k0 += 2 * U) {
+                float va[U][WM], vb[U][WN];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int i = 0; i < WM; ++i) va[u][i] = gg_element<A_KM>(A, a.lda, ra[i], k0 + 2 * u + fhalf, k_end);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int j = 0; j < WN; ++j) vb[u][j] = gg_element<B_KM>(B, a.ldb, rb[j], k0 + 2 * u + fhalf, k_end);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int i = 0; i < WM; ++i)
+#pragma unroll
+                        for (int j = 0; j < WN; ++j)
+                            sum[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[u][j], va[u][i], sum[i][j], 0, 0, 0);
+            }
+            write(sum);
+            return;
+        }
     }
+    write(acc);
 }
 
 }  // namespace flce

@@ -126,60 +126,98 @@ inline int max_dx_ranges(size_t budget_bytes, int64_t rows, int64_t H) {
     return (int)std::max<size_t>(1, std::min<size_t>(n, 16));
 }
 
-// Tile size and K ranges of a product on the guarded kernel.  Two 128 x 128 tiles fit a CU at a
-// time, so 512 workgroups fill the chip; 128 x 128 tiles while they (times at most max_ranges
-// K ranges of at least 512 elements) come to a workgroup per CU, else 64 x 64 tiles and ranges
-// of at least 256 elements.
-struct ProductCut {
-    int tile, ranges;
-};
-inline ProductCut guarded_cut(int64_t M, int64_t N, int64_t K, int64_t max_ranges) {
-    auto ranges = [&](int64_t tiles, int64_t min_k) {
-        return std::max<int64_t>(1, std::min(std::min(max_ranges, 512 / tiles), K / min_k));
-    };
-    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    if (t128 >= 256) return {128, 1};
-    const int64_t s128 = ranges(t128, 512);
-    if (t128 * s128 >= 256) return {128, (int)s128};
-    return {64, (int)ranges(((M + 63) / 64) * ((N + 63) / 64), 256)};
-}
-
-// Tile size and K ranges of a product on the tuned bf16 kernel, by the time (ns) a launch takes:
-// tiles run in rounds of 256 CUs; a 256 x 256 tile takes 1.55 us per K step of 64 plus 4 us, a
-// 128 x 128 tile 0.53 us per step (its operands come from L2 at 15 TB/s over the chip, twice the
-// bytes per operation) plus 0.65 us.  Measured (M x N x K, 256-tiles / 128-tiles, us):
+// ---- tile sizes and K ranges, by the time (ns) a launch takes ----
+// Tiles run in rounds of 256 CUs.
+//
+// Tuned bf16 kernel, K steps of 64: a 256 x 256 tile takes 1.55 us per step plus 4 us, a 128 x 128
+// tile 0.53 us per step (its operands come from L2 at 15 TB/s over the chip, twice the bytes per
+// operation) plus 0.65 us.  Measured (M x N x K, 256-tiles / 128-tiles, us):
 //   1024 x 8192 x 512 (logits)  18.8 / 12.8      4096 x 32000 x 4096 (logits)  809 / 1104
 //   2048 x 4096 x 1024 (logits) 31.9 / 21.6      2048 x 8192 x 1024 (logits)  34.9 / 37.6
 //   8192 x 512 x 1024 (dW)      24.4 / 12.1      50257 x 1000 x 2047 (dW)      202 / 217
 //   1024 x 512 x 8192 (dX)      67.1 (2 ranges) / 20.3, 14.8, 18.8 (4, 8, 16 ranges)
-// so the small tiles serve outputs that do not fill a first round or two of large ones.  Cutting
-// K costs a second launch and the fp32 partial results, written and read at about 8 TB/s.  The
-// large tiles keep at least 64 K steps per range (choose_ksplit); the small ones 8.
+// so the small tiles serve outputs that do not fill a first round or two of large ones.
+//
+// Guarded kernel, fp32 (six times the matrix instructions), K in units of 16: a 256-tile takes 2.3
+// us per unit plus 12 us (its 256 KB of output leave all CUs at once), 128-tiles 0.66 us (0.81 alone
+// on a CU) plus 3, 64-tiles 0.21 us (0.31 alone, 0.46 for two) plus 1.  Measured (256 / 128 / 64, us):
+//   4096 x 32000 x 4096  4640 / 5480 / -        2048 x 1024 x 50257  885 (8 ranges) / 1086 (4) / -
+//   2048 x 8192 x 1024    163 / 180 / -         2048 x 4096 x 1024   124 / 93 / -
+//   1024 x 4096 x 1024      - / 62 / 62         256 x 4096 x 512     - / - / 18.5
 inline int64_t rounds_of_256(int64_t n) { return (n + 255) / 256; }
-inline int64_t cut_ns(int64_t tiles, int64_t side, int64_t ranges) {
-    return ranges > 1 ? 4000 + tiles * side * side * ranges / 1000 : 0;
+inline int64_t tiles_of(int64_t m, int64_t n, int64_t tile) { return ((m + tile - 1) / tile) * ((n + tile - 1) / tile); }
+inline int64_t product_ns(bool tuned, int tile, int64_t tiles, int64_t k) {
+    const int64_t n = rounds_of_256(tiles), steps = (k + 63) / 64, units = (k + 15) / 16;
+    if (tuned) return tile == 256 ? n * (1550 * steps + 4000) : n * (530 * steps + 650);
+    if (tile == 256) return n * (2300 * units + 12000) + 3000;
+    if (tile == 128) return (n == 1 ? 810 : 660 * n) * units + 3000 * n + 6000;
+    return (n == 1 ? 310 : n == 2 ? 460 : 210 * n) * units + 1000 * n + 6000;
 }
-inline ProductCut tuned_cut(int64_t M, int64_t N, int64_t K, int64_t max_ranges) {
-    const int64_t steps = (K + 63) / 64;
-    const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    const int s256 = choose_ksplit(t256, steps, (int)max_ranges);
-    const int64_t ns256 = rounds_of_256(t256 * s256) * (1550 * ((steps + s256 - 1) / s256) + 4000) + cut_ns(t256, 256, s256);
-    ProductCut best{256, s256};
-    int64_t best_ns = ns256;
-    for (int64_t r = 1; r <= max_ranges && (r == 1 || steps / r >= 8); ++r) {
-        const int64_t ns = rounds_of_256(t128 * r) * (530 * ((steps + r - 1) / r) + 650) + cut_ns(t128, 128, r);
-        if (ns < best_ns) {
+// Cutting K costs a second launch and the fp32 partial results, written and read at about 8 TB/s.
+inline int64_t cut_ns(int64_t tiles, int64_t tile, int64_t ranges) {
+    return ranges > 1 ? 4000 + tiles * tile * tile * ranges / 1000 : 0;
+}
+
+// The dX product of a chunk (rows x H output, K = V): tile size and K ranges.  The tuned kernel's
+// large tiles keep at least 64 K steps per range (choose_ksplit), the others 512 elements (64-tiles 256).
+struct ProductCut {
+    int tile, ranges;
+};
+inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes) {
+    const int max_ranges = max_dx_ranges(budget_bytes, round_up(rows, 256), H);
+    ProductCut best{0, 1};
+    int64_t best_ns = 0;
+    auto consider = [&](int tile, int ranges) {
+        const int64_t t = tiles_of(rows, H, tile);
+        const int64_t ns = product_ns(tuned, tile, t * ranges, (V + ranges - 1) / ranges) + cut_ns(t, tile, ranges);
+        if (!best.tile || ns < best_ns) {
+            best = {tile, ranges};
             best_ns = ns;
-            best = {128, (int)r};
         }
+    };
+    if (tuned) consider(256, choose_ksplit(tiles_of(rows, H, 256), (V + 63) / 64, max_ranges));
+    for (int r = 1; r <= max_ranges && (r == 1 || V / r >= 256); ++r) {
+        if (!tuned) {
+            if (r == 1 || V / r >= 512) consider(256, r);
+            consider(64, r);
+        }
+        if (r == 1 || V / r >= 512) consider(128, r);
     }
     return best;
 }
 
-// The dX product of a chunk (rows x H output, K = V): tile size and K ranges.
-inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes) {
-    if (tuned) return tuned_cut(rows, H, V, max_dx_ranges(budget_bytes, round_up(rows, 256), H));
-    return guarded_cut(rows, H, V, max_dx_ranges(budget_bytes, round_up(rows, 128), H));
+// The logits and dW products have V along one output dimension, which can be shared out: columns (or
+// rows) 0 .. main - 1 on 256 x 256 tiles that fill whole rounds of the CUs, the rest on smaller
+// tiles in a second launch, instead of one more, mostly empty round of large ones.  tail: the last
+// round of large tiles may be cut along K instead (tail_plan).  main = V: one launch.
+struct VocabCut {
+    int64_t main;
+    int tile, rest_tile;
+};
+inline VocabCut vocab_cut(bool tuned, int64_t V, int64_t other, int64_t K, bool tail) {
+    VocabCut best{V, 256, 0};
+    const int64_t t256 = tiles_of(V, other, 256), steps = (K + 63) / 64;
+    int64_t best_ns = product_ns(tuned, 256, t256, K);
+    if (tail && tuned) {
+        const TailPlan p = tail_plan(t256, steps);
+        if (p.s > 1) best_ns += product_ns(true, 256, 1, K) / p.s + 5000 - product_ns(true, 256, 1, K);
+    }
+    const int64_t per = (other + 255) / 256, main = t256 / 256 * 256 / per * 256;   // whole rounds
+    for (int small = 128; small >= (tuned ? 128 : 64); small /= 2) {
+        const int64_t ns = product_ns(tuned, small, tiles_of(V, other, small), K);
+        if (ns < best_ns) {
+            best = {V, small, 0};
+            best_ns = ns;
+        }
+        if (main <= 0 || main >= V) continue;
+        const int64_t both = product_ns(tuned, 256, main / 256 * per, K) + 4000 +
+                             product_ns(tuned, small, tiles_of(V - main, other, small), K);
+        if (both < best_ns - best_ns / 32) {   // (3 %: the rows that turn out to have a target may be fewer)
+            best = {main, 256, small};
+            best_ns = both;
+        }
+    }
+    return best;
 }
 
 // Limits of the tuned kernel's 32-bit offsets inside one tile (see gemm_bf16_nt.h).
