@@ -31,6 +31,7 @@ namespace {
 constexpr int MAX_DEVICES = 64;
 constexpr int64_t MAX_DIM = (int64_t)1 << 30;      // per-dimension limit, keeps int tile math safe
 constexpr int64_t CE_ROWS_PER_LAUNCH = 65536;
+constexpr int64_t ROT_A_BYTES = (int64_t)2 << 20;
 constexpr int64_t CE_CACHE_BYTES = (int64_t)256 << 20;   // memory-side cache
 constexpr int64_t MAX_GRID_X = 0x7fffffff;        // workgroups along grid x
 constexpr size_t AUTO_BUDGET_BYTES = (size_t)1 << 30;
@@ -234,10 +235,20 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
         }
     }
     const dim3 grid((unsigned)(wgs_per_xcd * FG_XCDS));
-    if (tile == 128)
-        hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, 128>), grid, dim3(FG_THREADS), 0, s, a);
-    else
-        hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, 256>), grid, dim3(FG_THREADS), 0, s, a);
+    // Row-form operands, few rows in A: all of A stays in an XCD's L2 (4 MB) at whatever K step its
+    // tiles are, so the tile columns can start their K loops at different steps (see ROT).  Measured,
+    // V = 128256, H = 4096: 16 rows 230 -> 175 us, 64 rows 240 -> 190, 200 rows 281 -> 250; from 512
+    // rows on (A: 4 MB) no difference.
+    constexpr bool CAN_ROT = !A_KM && !B_KM;
+    const bool rot = CAN_ROT && K % FG_BK == 0 && M * K * (int64_t)sizeof(bf16_t) <= ROT_A_BYTES;
+#define FG_LAUNCH(TILE, ROT) \
+    hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, TILE, ROT>), grid, dim3(FG_THREADS), 0, s, a)
+    if (tile == 128) {
+        if (rot) FG_LAUNCH(128, CAN_ROT); else FG_LAUNCH(128, false);
+    } else {
+        if (rot) FG_LAUNCH(256, CAN_ROT); else FG_LAUNCH(256, false);
+    }
+#undef FG_LAUNCH
     HIP_TRY(hipGetLastError());
     if (a.tail_s > 1) {
         hipLaunchKernelGGL((fg_tail_reduce_kernel<OutT, InT>), dim3((unsigned)(FG_XCDS * a.tail_r * 8)), dim3(256),
@@ -391,12 +402,12 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                 const int64_t grid = std::min<int64_t>((BT + 3) / 4, SEL_GRID);
                 hipLaunchKernelGGL((select_rows_kernel<T>), dim3((unsigned)grid), dim3(256), 0, s, targets, (int)BT,
                                    ignore_index, weight, (int)p.C, (int)c, (int)p.nchunks, dx_tiles_n, dx_ksteps,
-                                   p.dx_ksplit, hdr, norm ? static_cast<const T*>(nullptr) : X, (int)H, Xg,
+                                   p.dx_ranges, hdr, norm ? static_cast<const T*>(nullptr) : X, (int)H, Xg,
                                    c == 0 ? zero_out : static_cast<T*>(nullptr), idx, tv, dyn);
             } else {
                 hipLaunchKernelGGL(compact_chunk_kernel, dim3(1), dim3(CP_THREADS), 0, s, targets, (int)BT,
                                    ignore_index, (int)p.C, (int)c, (int)p.nchunks, hdr, dx_tiles_n, dx_ksteps,
-                                   p.dx_ksplit, idx, tv, dyn);
+                                   p.dx_ranges, idx, tv, dyn);
             }
             HIP_TRY(hipGetLastError());
             tc = tv;
@@ -469,13 +480,13 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             const int* rows_at = scatter ? row_map : nullptr;
             if (BF16 && p.fast_dx) {
                 if constexpr (BF16) {
-                    if (p.dx_ksplit > 1) {
+                    if (p.dx_ranges > 1) {
                         // few output tiles, very long K: K ranges -> fp32 partials -> fixed-order sum
                         float* part = reinterpret_cast<float*>(ws + p.off_dxpart);
                         FLCE_TRY((launch_gemm_fast<float, void, false, true>(
                             FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, 0, rows, H, V, s,
-                            p.dx_tile, p.dx_ksplit, p.C * H, dyn_dx)));
-                        FLCE_TRY((launch_finish_dx<bf16_t, float>(part, p.C * H, p.dx_ksplit, dyn_dx.ksplit, rows_at,
+                            p.dx_tile, p.dx_ranges, p.C * H, dyn_dx)));
+                        FLCE_TRY((launch_finish_dx<bf16_t, float>(part, p.C * H, p.dx_ranges, dyn_dx.ksplit, rows_at,
                                                                   n_live, rows, H, dXrows, add_rows, row_loss, hdr,
                                                                   loss_here, s)));
                         loss_done = true;
@@ -491,12 +502,12 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                     }
                 }
             } else {
-                if (p.dx_ksplit > 1) {
+                if (p.dx_ranges > 1) {
                     float* part = reinterpret_cast<float*>(ws + p.off_dxpart);
                     FLCE_TRY((launch_gemm_guarded<T, float, false, true>(
                         FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, nullptr, rows, H, V, s, p.dx_tile,
-                        p.dx_ksplit, p.C * H, dyn_m)));
-                    FLCE_TRY((launch_finish_dx<T, float>(part, p.C * H, p.dx_ksplit, nullptr, rows_at, n_live, rows,
+                        p.dx_ranges, p.C * H, dyn_m)));
+                    FLCE_TRY((launch_finish_dx<T, float>(part, p.C * H, p.dx_ranges, nullptr, rows_at, n_live, rows,
                                                          H, dXrows, add_rows, row_loss, hdr, loss_here, s)));
                     loss_done = true;
                 } else {
@@ -505,7 +516,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                         V, s, p.dx_tile, 1, 0, dyn_m)));
                 }
             }
-            if (scatter && p.dx_ksplit == 1) {
+            if (scatter && p.dx_ranges == 1) {
                 FLCE_TRY((launch_finish_dx<T, T>(dXg, 0, 1, nullptr, rows_at, n_live, rows, H, dX, add_rows, row_loss,
                                                  hdr, loss_here, s)));
                 loss_done = true;
@@ -964,12 +975,7 @@ size_t flce_logits_budget_for_workspace(int64_t BT, int64_t H, int64_t V, int dt
 
 int flce_dx_k_ranges(int64_t BT, int64_t H, int64_t V, int dtype) {
     if (check_dims(BT, H, V, dtype) != FLCE_OK) return 0;
-    const Plan p = plan_for(BT, H, V, dtype);
-    if (p.dx_tile != 128 || !p.fast_dx) return p.dx_ksplit;
-    // cut finer, into small tiles: the number the large tiles would take
-    const int64_t rows = p.nchunks > 1 ? p.C : BT;
-    return choose_ksplit(((rows + 255) / 256) * ((H + 255) / 256), (V + 63) / 64,
-                         max_dx_ranges(effective_budget(global_settings(), V, dtype), round_up(rows, 256), H));
+    return plan_for(BT, H, V, dtype).dx_ksplit;
 }
 
 int64_t flce_paper_chunk_rows(int64_t BT, int64_t H, int64_t V) {

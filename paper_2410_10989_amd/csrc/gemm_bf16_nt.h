@@ -161,7 +161,7 @@ __device__ __forceinline__ void fg_load_lds(__amdgpu_buffer_rsrc_t rsrc, unsigne
 // One GEMM operand: where its tiles come from in global memory, where they land
 // in LDS, and how MFMA fragments (32 rows x 16 K, lane l = row l%32, K values
 // 8*(l/32) .. +7) are read back.  KM = false: row form, KM = true: column form.
-template <bool KM, int TILE>
+template <bool KM, int TILE, bool ROT = false>
 struct FgOperand {
     static constexpr int NL = TILE / 32;   // loads a wavefront issues per tile
     static constexpr int W = TILE / 64;    // fragments per wavefront
@@ -177,6 +177,7 @@ struct FgOperand {
     int kt_next;  // before_step has nothing to do before this K step
     int off[NL];  // per-lane byte offset of each of the loads a wavefront issues per tile
     int kstep;    // bytes between consecutive K steps
+    int rot, wrap;   // ROT: the K steps are taken in the order rot, rot + 1, ..., wrap - 1, 0, 1, ...
     int rd[4];    // per-lane LDS byte offsets of the fragment reads
 
     // base/ld: the matrix; r0: first row (row form) or column (column form) of this
@@ -270,10 +271,18 @@ struct FgOperand {
         }
     }
 
+    __device__ __forceinline__ int step_offset(int kt) const {
+        if constexpr (ROT) {
+            kt += rot;
+            kt -= kt >= wrap ? wrap : 0;
+        }
+        return (kt - kt_base) * kstep;
+    }
+
     // start the loads of this wavefront for K step kt into ring slot `slot`
     __device__ __forceinline__ void load(unsigned char* smem, int slot, int kt, int uwave) {
         before_step(kt);
-        const int soff = (kt - kt_base) * kstep;
+        const int soff = step_offset(kt);
         unsigned char* dst = smem + slot * fg_slot_bytes(TILE) + uwave * 1024;
 #pragma unroll
         for (int r = 0; r < NL; ++r)
@@ -283,7 +292,7 @@ struct FgOperand {
     // start one of the loads of this wavefront for K step kt into ring slot `slot`
     __device__ __forceinline__ void load_one(unsigned char* smem, int slot, int kt, int uwave, int r) const {
         unsigned char* dst = smem + slot * fg_slot_bytes(TILE) + uwave * 1024 + r * 4096;
-        fg_load_lds(rsrc, dst, off[r], (kt - kt_base) * kstep);
+        fg_load_lds(rsrc, dst, off[r], step_offset(kt));
     }
 };
 
@@ -295,13 +304,13 @@ template <> struct FgRaw<true> { s16x4 lo, hi; };
 
 // Issue the LDS read(s) of fragment I (32-row block) of K sub-step KK; `slot_addr`
 // is the LDS byte address of the ring slot.
-template <int KK, int I, int TILE>
-__device__ __forceinline__ void fg_issue(FgRaw<false>& r, const FgOperand<false, TILE>& op, unsigned slot_addr) {
+template <int KK, int I, int TILE, bool ROT>
+__device__ __forceinline__ void fg_issue(FgRaw<false>& r, const FgOperand<false, TILE, ROT>& op, unsigned slot_addr) {
     const unsigned addr = slot_addr + (unsigned)op.rd[KK];
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r.v) : "v"(addr), "n"(I * 4096));
 }
-template <int KK, int I, int TILE>
-__device__ __forceinline__ void fg_issue(FgRaw<true>& r, const FgOperand<true, TILE>& op, unsigned slot_addr) {
+template <int KK, int I, int TILE, bool ROT>
+__device__ __forceinline__ void fg_issue(FgRaw<true>& r, const FgOperand<true, TILE, ROT>& op, unsigned slot_addr) {
     const unsigned addr = slot_addr + (unsigned)op.rd[I];
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.lo) : "v"(addr), "n"(KK * 32 * TILE));
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.hi) : "v"(addr), "n"(KK * 32 * TILE + 8 * TILE));
@@ -553,7 +562,12 @@ __device__ __forceinline__ void fg_tile_origin(int seq, int tiles_m, int tiles_n
 // 2 x 2 MFMA tiles per wavefront, half the LDS, two workgroups per CU that fill each other's
 // waits; its LDS reads (as many per K step for a quarter of the arithmetic) are as tight as the
 // matrix pipe.
-template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE>
+//
+// ROT: every column of tiles starts its K loop at another K step and wraps around.  For a row-form
+// B that is fetched once (few rows in A) from memory whose rows lie a power of two apart (H = 4096:
+// 8 KB), where all tiles at the same K step would ask the same few memory channels at a time.
+// A K % 64 == 0 operand pair without K ranges only.
+template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE, bool ROT = false>
 __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGArgs a) {
     constexpr bool HAS_IN = !std::is_void<InT>::value;
     constexpr int IS = FgInSize<InT>::value;
@@ -596,8 +610,8 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
     int m0, n0;
     fg_tile_origin<TILE>(seq_all - split * tiles, tiles_m, a.tiles_n, a.group_m, a.group_cols, m0, n0);
 
-    FgOperand<A_KM, TILE> opa;
-    FgOperand<B_KM, TILE> opb;
+    FgOperand<A_KM, TILE, ROT> opa;
+    FgOperand<B_KM, TILE, ROT> opb;
     opa.init(a.A, a.lda, m0, M, K, tid, wm);
     opb.init(a.B, a.ldb, n0, a.N, K, tid, wn);
     const int uwave = __builtin_amdgcn_readfirstlane(wave);
@@ -713,6 +727,10 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
     const int nk = (int)((int64_t)steps_all * (kr_i + 1) / kr_n) - k_begin;
     opa.start_at(k_begin);
     opb.start_at(k_begin);
+    if constexpr (ROT) {
+        opa.rot = opb.rot = (n0 / TILE) % nk;
+        opa.wrap = opb.wrap = nk;
+    }
     opa.load(smem, 0, 0, uwave);
     opb.load(smem, 1, 0, uwave);
     opa.load(smem, 2, 1, uwave);

@@ -79,8 +79,9 @@ struct Plan {
     // which products can run on the tuned bf16 kernel straight from X, W and the
     // logits chunk; the others need transposed copies and the guarded kernel
     bool fast_logits = false, fast_dx = false, fast_dw_full = false, fast_dw_last = false;
-    int dx_ksplit = 1;     // K ranges of the dX product (K = V), > 1 when C x H has few tiles
+    int dx_ranges = 1;     // K ranges of the dX product (K = V), > 1 when C x H has few tiles
     int dx_tile = 256;     // its tile size
+    int dx_ksplit = 1;     // the K ranges that are reported: for the tuned kernel what its large tiles take, at most 16
     // chunks are compacted, i.e. rows with an ignored target are left out of the products (see
     // compact.h)
     bool compact = false;
@@ -123,7 +124,7 @@ FLCE_HD inline int choose_ksplit(int64_t tiles, int64_t ksteps, int max_ranges) 
 inline int max_dx_ranges(size_t budget_bytes, int64_t rows, int64_t H) {
     const size_t one = (size_t)rows * (size_t)H * sizeof(float);
     const size_t n = one ? budget_bytes / 2 / one : 1;
-    return (int)std::max<size_t>(1, std::min<size_t>(n, 16));
+    return (int)std::max<size_t>(1, std::min<size_t>(n, 64));
 }
 
 // ---- tile sizes and K ranges, by the time (ns) a launch takes ----
@@ -249,7 +250,10 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
         const int64_t rows = p.nchunks > 1 ? p.C : rows_last;
         const ProductCut cut = dx_cut(p.fast_dx, rows, H, V, budget_bytes);
         p.dx_tile = cut.tile;
-        p.dx_ksplit = cut.ranges;
+        p.dx_ranges = cut.ranges;
+        p.dx_ksplit = p.fast_dx ? choose_ksplit(tiles_of(rows, H, 256), (V + 63) / 64,
+                                                max_dx_ranges(budget_bytes, round_up(rows, 256), H))
+                                : std::min(cut.ranges, 16);
     }
     // (the copies move 16-byte vectors; bf16 rows of other lengths do not run on the tuned kernel)
     p.compact = allow_compact &&
@@ -266,7 +270,7 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     p.off_z = take((size_t)p.C * p.ldz * es);
     p.off_gt = p.off_wt = p.off_xt = off;   // no product needs a transposed copy
     p.off_dwacc = take(p.fp32_dw_acc ? (size_t)V * H * sizeof(float) : 0);
-    const size_t dxpart = p.dx_ksplit > 1 ? (size_t)p.dx_ksplit * p.C * H * sizeof(float) : 0;
+    const size_t dxpart = p.dx_ranges > 1 ? (size_t)p.dx_ranges * p.C * H * sizeof(float) : 0;
     p.off_dxpart = take(std::max(dxpart, dxpart_floor));
     // a chunk of gathered input rows and of their gradient (also the normalised rows and
     // their gradient when an RMSNorm runs in front), index maps of the compaction
