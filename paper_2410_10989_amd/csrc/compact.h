@@ -49,7 +49,8 @@ __device__ __forceinline__ int dx_ranges_of(int rows, int dx_tiles_n, int dx_kst
 // count_valid_kernel, gather_rows_kernel and zero_ignored_rows_kernel do, in one launch.
 // Workgroup b owns batch rows b R .. b R + R - 1 (R <= 64 rows); it counts the valid rows in front
 // of them and in the whole batch (every workgroup reads all targets), which gives each of its
-// rows its place in the chunk.  One wavefront per row copies it to Xg (X not null), or clears its
+// rows its place in the chunk.  One wavefront per row copies it to Xg (X not null; with gamma it
+// writes the RMS-normalised row and rstd = 1 / RMS instead, see rmsnorm_fwd_kernel), or clears its
 // gradient row (zero_out not null, row ignored).  Workgroup 0 writes the header (c = 0) and dyn.
 // Measured, 1024 rows of 512 bf16: 4 launches, 19 us -> one of 5; 4096 x 4096: 32 -> 15 us.
 template <typename T>
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(256) void select_rows_kernel(
     const int64_t* __restrict__ targets, int BT, int64_t ignore_index, float weight, int C, int c, int nchunks,
     int dx_tiles_n, int dx_ksteps, int dx_max_ranges, DeviceHeader* __restrict__ hdr, const T* __restrict__ X,
     int n, T* __restrict__ Xg, T* __restrict__ zero_out, int* __restrict__ idx, int64_t* __restrict__ tv,
-    int* __restrict__ dyn) {
+    int* __restrict__ dyn, const T* __restrict__ gamma, float eps, float* __restrict__ rstd) {
     __shared__ int part[4][2];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     const int R = (BT + (int)gridDim.x - 1) / (int)gridDim.x;
@@ -109,8 +110,32 @@ __global__ __launch_bounds__(256) void select_rows_kernel(
             if (!X) continue;
             const u32x4* src = reinterpret_cast<const u32x4*>(X + (int64_t)r * n);
             u32x4* dst = reinterpret_cast<u32x4*>(Xg + (int64_t)place * n);
+            if (!gamma) {
 #pragma unroll 8
-            for (int v = lane; v < nv; v += WAVE) dst[v] = src[v];
+                for (int v = lane; v < nv; v += WAVE) dst[v] = src[v];
+                continue;
+            }
+            const u32x4* gr = reinterpret_cast<const u32x4*>(gamma);
+            float ss = 0.f;
+#pragma unroll 8
+            for (int v = lane; v < nv; v += WAVE) {
+                float x[VEC];
+                RowVec<T>::unpack(src[v], x);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) ss += x[e] * x[e];
+            }
+            ss = wave_sum(ss);
+            const float s = 1.0f / sqrtf(ss / (float)n + eps);
+            if (lane == 0) rstd[place] = s;
+#pragma unroll 4
+            for (int v = lane; v < nv; v += WAVE) {   // (the row comes from cache this time)
+                float x[VEC], g[VEC];
+                RowVec<T>::unpack(src[v], x);
+                RowVec<T>::unpack(gr[v], g);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) x[e] = x[e] * s * g[e];
+                dst[v] = RowVec<T>::pack(x);
+            }
         }
     }
 }

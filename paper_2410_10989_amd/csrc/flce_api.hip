@@ -31,6 +31,7 @@ namespace {
 constexpr int MAX_DEVICES = 64;
 constexpr int64_t MAX_DIM = (int64_t)1 << 30;      // per-dimension limit, keeps int tile math safe
 constexpr int64_t CE_ROWS_PER_LAUNCH = 65536;
+constexpr int64_t RIDE_ROWS = 4096;   // finish_dx as workgroups of the dW launch: up to 1024 of them
 constexpr int64_t ROT_A_BYTES = (int64_t)2 << 20;
 constexpr int64_t CE_CACHE_BYTES = (int64_t)256 << 20;   // memory-side cache
 constexpr int64_t MAX_GRID_X = 0x7fffffff;        // workgroups along grid x
@@ -179,7 +180,7 @@ template <typename T, typename OutT, bool A_KM, bool B_KM>
 int launch_gemm_guarded(int kind, const T* A, int64_t lda, const T* B, int64_t ldb, OutT* C, int64_t ldc,
                         const float* Cin, const OutT* cin_own, int64_t M, int64_t N, int64_t K,
                         hipStream_t s, int tile, int ksplit = 1, int64_t split_stride = 0,
-                        const FastDyn& d = FastDyn{}) {
+                        const FastDyn& d = FastDyn{}, const FinishArgs* fin = nullptr) {
     if (M <= 0 || N <= 0) return FLCE_OK;
     if (ksplit > 1 && (Cin || cin_own)) return FLCE_ERR_SHAPE;
     ScopedKernelTimer timer(kind, s);
@@ -192,14 +193,24 @@ int launch_gemm_guarded(int kind, const T* A, int64_t lda, const T* B, int64_t l
              FG_GROUP_TILES, kind == FLCE_KIND_LOGITS_GEMM ? 1 : 0, 1};
     const int64_t total = ((M + tile - 1) / tile) * ((N + tile - 1) / tile) * ksplit;
     if (total > MAX_GRID_X - FG_XCDS) return FLCE_ERR_SHAPE;   // check_launch_limits refuses such shapes up front
-    const dim3 grid((unsigned)((total + FG_XCDS - 1) / FG_XCDS * FG_XCDS));
+    const dim3 grid((unsigned)((total + FG_XCDS - 1) / FG_XCDS * FG_XCDS + (fin ? fin->blocks : 0)));
     const dim3 block((unsigned)gg_threads(tile));
-    if (tile == 64)
-        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64>), grid, block, 0, s, a);
-    else if (tile == 128)
-        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 128>), grid, block, 0, s, a);
-    else
-        hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 256>), grid, block, 0, s, a);
+    // finish_dx rides along with the dW product of fp32 storage
+    constexpr bool CAN_FIN = A_KM && B_KM && std::is_same<T, float>::value;
+    if (fin && (!CAN_FIN || tile == 256)) return FLCE_ERR_SHAPE;   // (ride_along keeps such calls away)
+#define GG_LAUNCH(TILE) \
+    hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, TILE>), grid, block, 0, s, a, NoFinish{})
+    if (fin) {
+        if constexpr (CAN_FIN) {
+            if (tile == 64)
+                hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64, FinishArgs>), grid, block, 0, s, a, *fin);
+            else
+                hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 128, FinishArgs>), grid, block, 0, s, a, *fin);
+        }
+    } else if (tile == 64) GG_LAUNCH(64);
+    else if (tile == 128) GG_LAUNCH(128);
+    else GG_LAUNCH(256);
+#undef GG_LAUNCH
     HIP_TRY(hipGetLastError());
     return FLCE_OK;
 }
@@ -213,7 +224,7 @@ template <typename OutT, typename InT, bool A_KM, bool B_KM>
 int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, OutT* C,
                      int64_t ldc, const InT* Cin, int64_t ldcin, int64_t M, int64_t N, int64_t K,
                      hipStream_t s, int tile, int ksplit = 1, int64_t split_stride = 0, const FastDyn& d = FastDyn{},
-                     float* tail_part = nullptr, size_t tail_bytes = 0) {
+                     float* tail_part = nullptr, size_t tail_bytes = 0, const FinishArgs* fin = nullptr) {
     if (M <= 0 || N <= 0 || K <= 0) return FLCE_OK;
     if (!aligned(A, 16) || !aligned(B, 16)) return FLCE_ERR_ARG;
     ScopedKernelTimer timer(kind, s);
@@ -234,16 +245,23 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
             wgs_per_xcd = (int64_t)t.begin + (int64_t)t.r * t.s;
         }
     }
-    const dim3 grid((unsigned)(wgs_per_xcd * FG_XCDS));
-    // Row-form operands, few rows in A: all of A stays in an XCD's L2 (4 MB) at whatever K step its
-    // tiles are, so the tile columns can start their K loops at different steps (see ROT).  Measured,
-    // V = 128256, H = 4096: 16 rows 230 -> 175 us, 64 rows 240 -> 190, 200 rows 281 -> 250; from 512
-    // rows on (A: 4 MB) no difference.
+    const dim3 grid((unsigned)(wgs_per_xcd * FG_XCDS + (fin ? fin->blocks : 0)));
+    constexpr bool CAN_FIN = A_KM && B_KM && std::is_void<InT>::value && std::is_same<OutT, bf16_t>::value;
+    if (fin && (!CAN_FIN || tile != 128)) return FLCE_ERR_SHAPE;   // (ride_along keeps such calls away)
+    // Row-form operands, one 256-row tile: B is fetched once, and all of A stays in an XCD's L2 (4 MB)
+    // at whatever K step its tiles are, so the tile columns can start their K loops at different steps
+    // (see ROT).  Measured, V = 128256, H = 4096: 16 rows 230 -> 175 us, 64 rows 240 -> 190, 200 rows 281 ->
+    // 250; 512 rows: no difference, and more rows keep the plain order (1 % slower with 4096), so
+    // that the order of a row's sums does not depend on how a larger batch is cut into chunks.
     constexpr bool CAN_ROT = !A_KM && !B_KM;
-    const bool rot = CAN_ROT && K % FG_BK == 0 && M * K * (int64_t)sizeof(bf16_t) <= ROT_A_BYTES;
+    const bool rot = CAN_ROT && K % FG_BK == 0 && M <= FG_BM && M * K * (int64_t)sizeof(bf16_t) <= ROT_A_BYTES;
 #define FG_LAUNCH(TILE, ROT) \
-    hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, TILE, ROT>), grid, dim3(FG_THREADS), 0, s, a)
-    if (tile == 128) {
+    hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, TILE, ROT>), grid, dim3(FG_THREADS), 0, s, a, NoFinish{})
+    if (fin) {
+        if constexpr (CAN_FIN)
+            hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, 128, false, FinishArgs>), grid, dim3(FG_THREADS), 0, s,
+                               a, *fin);
+    } else if (tile == 128) {
         if (rot) FG_LAUNCH(128, CAN_ROT); else FG_LAUNCH(128, false);
     } else {
         if (rot) FG_LAUNCH(256, CAN_ROT); else FG_LAUNCH(256, false);
@@ -306,28 +324,24 @@ struct NormCtx {
     const T* gamma;
     float eps;
     float* rstd;     // [C]
-    float* partial;  // [RN_SLOTS x H] fp32 partial sums of dgamma, zero before the loop
+    float* partial;  // [RN_SLOTS x H] fp32 partial sums of dgamma, started by the first chunk
     T* dh;           // [BT x H] out
 };
 
 // See finish_dx_kernel: K-range partial results summed, rows put in place, loss summed.
-template <typename T, typename SrcT>
-int launch_finish_dx(const SrcT* src, int64_t split_stride, int nsplit, const int* dyn_nsplit, const int* idx,
-                     const int* live, int64_t rows, int64_t H, T* out, bool add, const float* row_loss,
-                     DeviceHeader* hdr, const LossOut& loss, hipStream_t s) {
+template <typename T>
+bool finish_is_vec(const FinishArgs& f) {
+    return f.n % 4 == 0 && f.split_stride % 4 == 0 && aligned(f.src, 4 * (f.src_f32 ? sizeof(float) : sizeof(T))) &&
+           aligned(f.out, 4 * sizeof(T));
+}
+template <typename T>
+int launch_finish_dx(const FinishArgs& f, hipStream_t s) {
     ScopedKernelTimer timer(FLCE_KIND_DX_GEMM, s);
-    const bool vec = (H % 4 == 0) && (split_stride % 4 == 0) && aligned(src, 4 * sizeof(SrcT)) &&
-                     aligned(out, 4 * sizeof(T));
-    const dim3 grid((unsigned)((rows + 3) / 4 + 1)), block(256);
-#define FD_LAUNCH(ADD, VEC)                                                                                 \
-    hipLaunchKernelGGL((finish_dx_kernel<T, SrcT, ADD, VEC>), grid, block, 0, s, src, split_stride, nsplit, \
-                       dyn_nsplit, idx, live, (int)rows, (int)H, out, row_loss, hdr, loss)
-    if (vec) {
-        if (add) FD_LAUNCH(true, true); else FD_LAUNCH(false, true);
-    } else {
-        if (add) FD_LAUNCH(true, false); else FD_LAUNCH(false, false);
-    }
-#undef FD_LAUNCH
+    const dim3 grid((unsigned)f.blocks), block(256);
+    if (finish_is_vec<T>(f))
+        hipLaunchKernelGGL((finish_dx_kernel<T, true>), grid, block, 0, s, f);
+    else
+        hipLaunchKernelGGL((finish_dx_kernel<T, false>), grid, block, 0, s, f);
     HIP_TRY(hipGetLastError());
     return FLCE_OK;
 }
@@ -366,6 +380,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
     constexpr int VEC = 16 / (int)sizeof(T);
 
     const bool select = p.compact && BT <= SEL_MAX_ROWS;   // one launch per chunk finds its rows
+    const bool norm_in_select = select && norm && aligned(norm->gamma, 16);
     const bool count_in_rows = !p.compact && p.nchunks == 1 && BT <= CE_COUNT_ROWS;
     T* zero_out = (want_dx && !dx_add) ? (norm ? norm->dh : dX) : nullptr;   // rows without a target: zero gradient
     if (!select && !count_in_rows) {
@@ -402,8 +417,10 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                 const int64_t grid = std::min<int64_t>((BT + 3) / 4, SEL_GRID);
                 hipLaunchKernelGGL((select_rows_kernel<T>), dim3((unsigned)grid), dim3(256), 0, s, targets, (int)BT,
                                    ignore_index, weight, (int)p.C, (int)c, (int)p.nchunks, dx_tiles_n, dx_ksteps,
-                                   p.dx_ranges, hdr, norm ? static_cast<const T*>(nullptr) : X, (int)H, Xg,
-                                   c == 0 ? zero_out : static_cast<T*>(nullptr), idx, tv, dyn);
+                                   p.dx_ranges, hdr, norm && !norm_in_select ? static_cast<const T*>(nullptr) : X,
+                                   (int)H, Xg, c == 0 ? zero_out : static_cast<T*>(nullptr), idx, tv, dyn,
+                                   norm_in_select ? norm->gamma : static_cast<const T*>(nullptr),
+                                   norm ? norm->eps : 0.f, norm ? norm->rstd : static_cast<float*>(nullptr));
             } else {
                 hipLaunchKernelGGL(compact_chunk_kernel, dim3(1), dim3(CP_THREADS), 0, s, targets, (int)BT,
                                    ignore_index, (int)p.C, (int)c, (int)p.nchunks, hdr, dx_tiles_n, dx_ksteps,
@@ -417,7 +434,9 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             dyn_dw.first_live = dyn + DYN_FIRST_LIVE;
             dyn_dw.launch = (int)c;
         }
-        if (norm) {   // X holds the raw hidden states: normalise the chunk's rows
+        if (norm_in_select) {
+            Xc = Xg;
+        } else if (norm) {   // X holds the raw hidden states: normalise the chunk's rows
             ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
 #define RN_FWD(KERNEL)                                                                           \
     hipLaunchKernelGGL((KERNEL), dim3((unsigned)rows), dim3(RN_THREADS), 0, s, Xin, norm->gamma, \
@@ -465,85 +484,73 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         FLCE_TRY(launch_ce_rows<T>(Z, p.ldz, tc, rows, V, (int)(p.ldz - V), ignore_index, hdr,
                                    row_loss, s, n_live, true, count_in_rows ? (int)BT : 0, weight));
         const LossOut loss_here = last ? loss_out : LossOut{};
-        bool loss_done = false;
 
-        // dX_c (+)= G W
+        // dX_c (+)= G W: straight into dX, or into the chunk buffer when the rows still have to be
+        // scattered back or to pass through the RMSNorm backward; cut along K into fp32 partial
+        // results when there are few output tiles.  `fin` is what is left to do for dX then.
+        FinishArgs fin{};
+        bool finish = false;
         if (want_dx) {
-            // where the product writes: straight into dX, or into the chunk buffer when the rows
-            // still have to be scattered back or to pass through the RMSNorm backward
             const bool staged = p.compact || norm;
+            const bool scatter = p.compact && !norm;
             T* dXc = staged ? dXg : dX + r0 * H;
             const bool add_in_gemm = dx_add && !staged;
-            const bool scatter = p.compact && !norm;   // finish_dx_kernel puts the rows back in place
-            T* dXrows = scatter ? dX : dXc;
-            const bool add_rows = dx_add && (scatter || add_in_gemm);
-            const int* rows_at = scatter ? row_map : nullptr;
-            if (BF16 && p.fast_dx) {
+            if (p.dx_ranges > 1) {
+                float* part = reinterpret_cast<float*>(ws + p.off_dxpart);
                 if constexpr (BF16) {
-                    if (p.dx_ranges > 1) {
-                        // few output tiles, very long K: K ranges -> fp32 partials -> fixed-order sum
-                        float* part = reinterpret_cast<float*>(ws + p.off_dxpart);
+                    if (p.fast_dx)
                         FLCE_TRY((launch_gemm_fast<float, void, false, true>(
-                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, 0, rows, H, V, s,
-                            p.dx_tile, p.dx_ranges, p.C * H, dyn_dx)));
-                        FLCE_TRY((launch_finish_dx<bf16_t, float>(part, p.C * H, p.dx_ranges, dyn_dx.ksplit, rows_at,
-                                                                  n_live, rows, H, dXrows, add_rows, row_loss, hdr,
-                                                                  loss_here, s)));
-                        loss_done = true;
-                    } else if (add_in_gemm) {
-                        FLCE_TRY((launch_gemm_fast<bf16_t, bf16_t, false, true>(
-                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, dXc, H, rows, H, V, s,
-                            p.dx_tile)));
-                    } else {
-                        FLCE_TRY((launch_gemm_fast<bf16_t, void, false, true>(
-                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, nullptr, 0, rows, H, V, s,
-                            p.dx_tile, 1, 0,
-                            dyn_m)));
-                    }
+                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, 0, rows, H, V, s, p.dx_tile, p.dx_ranges,
+                            p.C * H, dyn_dx)));
                 }
-            } else {
-                if (p.dx_ranges > 1) {
-                    float* part = reinterpret_cast<float*>(ws + p.off_dxpart);
+                if (!p.fast_dx)
                     FLCE_TRY((launch_gemm_guarded<T, float, false, true>(
-                        FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, nullptr, rows, H, V, s, p.dx_tile,
-                        p.dx_ranges, p.C * H, dyn_m)));
-                    FLCE_TRY((launch_finish_dx<T, float>(part, p.C * H, p.dx_ranges, nullptr, rows_at, n_live, rows,
-                                                         H, dXrows, add_rows, row_loss, hdr, loss_here, s)));
-                    loss_done = true;
-                } else {
+                        FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, nullptr, rows, H, V, s, p.dx_tile, p.dx_ranges,
+                        p.C * H, dyn_m)));
+                fin = {part, 1, p.C * H, p.dx_ranges, dyn_dx.ksplit, scatter ? row_map : nullptr, n_live, (int)rows, (int)H,
+                       scatter ? dX : dXc, dx_add && (scatter || add_in_gemm), nullptr, hdr, LossOut{}, finish_blocks(rows)};
+                finish = true;
+            } else {
+                if constexpr (BF16) {
+                    if (p.fast_dx && add_in_gemm)
+                        FLCE_TRY((launch_gemm_fast<bf16_t, bf16_t, false, true>(
+                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, dXc, H, rows, H, V, s, p.dx_tile)));
+                    else if (p.fast_dx)
+                        FLCE_TRY((launch_gemm_fast<bf16_t, void, false, true>(
+                            FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, nullptr, 0, rows, H, V, s, p.dx_tile, 1, 0, dyn_m)));
+                }
+                if (!p.fast_dx)
                     FLCE_TRY((launch_gemm_guarded<T, T, false, true>(
-                        FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, nullptr, add_in_gemm ? dXc : nullptr, rows, H,
-                        V, s, p.dx_tile, 1, 0, dyn_m)));
+                        FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, dXc, H, nullptr, add_in_gemm ? dXc : nullptr, rows, H, V, s,
+                        p.dx_tile, 1, 0, dyn_m)));
+                if (scatter) {
+                    fin = {dXg, 0, 0, 1, nullptr, row_map, n_live, (int)rows, (int)H, dX, dx_add, nullptr, hdr, LossOut{},
+                           finish_blocks(rows)};
+                    finish = true;
                 }
-            }
-            if (scatter && p.dx_ranges == 1) {
-                FLCE_TRY((launch_finish_dx<T, T>(dXg, 0, 1, nullptr, rows_at, n_live, rows, H, dX, add_rows, row_loss,
-                                                 hdr, loss_here, s)));
-                loss_done = true;
-            }
-            if (norm) {
-                ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
-#define RN_BWD(KERNEL)                                                                              \
-    hipLaunchKernelGGL((KERNEL), dim3(RN_SLOTS), dim3(RN_THREADS), 0, s, Xin, norm->gamma,           \
-                       norm->rstd, dXg, (int)rows, (int)H, p.compact ? norm->dh : norm->dh + r0 * H, \
-                       norm->partial, row_map, n_live)
-                switch (rmsnorm_vectors_per_thread<T>(H, Xin, norm->gamma, norm->dh)) {
-                    case 1: RN_BWD((rmsnorm_bwd_vec_kernel<T, 1>)); break;
-                    case 2: RN_BWD((rmsnorm_bwd_vec_kernel<T, 2>)); break;
-                    case 4: RN_BWD((rmsnorm_bwd_vec_kernel<T, 4>)); break;
-                    default: RN_BWD((rmsnorm_bwd_kernel<T>)); break;
-                }
-#undef RN_BWD
-                HIP_TRY(hipGetLastError());
             }
         }
-
-        if (!loss_done) FLCE_TRY(launch_loss(row_loss, rows, hdr, loss_here, true, s));
+        // The chunk's losses are summed by a workgroup of the RMSNorm backward launch, or of the one
+        // that finishes dX, or, with neither, by a launch of their own.
+        const bool loss_in_norm = norm && want_dx;
+        if (finish && !loss_in_norm) {
+            fin.row_loss = row_loss;
+            fin.loss = loss_here;
+        } else if (!loss_in_norm) {
+            FLCE_TRY(launch_loss(row_loss, rows, hdr, loss_here, true, s));
+        }
+        // dX is finished by workgroups of the dW launch where that is one launch on small tiles
+        const bool dw_fast = BF16 && (last ? p.fast_dw_last : p.fast_dw_full);
+        const VocabCut dw_cut = vocab_cut(dw_fast, V, H, rows, p.tail_bytes > 0);
+        const bool ride_along = finish && want_dw && p.nchunks == 1 && dw_cut.main == V && dw_cut.tile < 256 &&
+                                (dw_fast || !BF16) && rows <= RIDE_ROWS && finish_is_vec<T>(fin);
+        if (finish && !ride_along) FLCE_TRY(launch_finish_dx<T>(fin, s));
 
         // dW (+)= G^T X_c   (K = the chunk's rows; in a compacted chunk K = *n_live)
         if (want_dw) {
-            const bool fast = BF16 && (last ? p.fast_dw_last : p.fast_dw_full);
-            const VocabCut cut = vocab_cut(fast, V, H, rows, p.tail_bytes > 0);
+            const bool fast = dw_fast;
+            const VocabCut& cut = dw_cut;
+            const FinishArgs* with = ride_along ? &fin : nullptr;
             // rows v0 .. v0 + nv - 1 of dW: the first chunk writes its sums, the others add to them, the
             // last writes dW; bf16 sums over several chunks are kept in fp32 (dWacc)
             auto product = [&](int64_t v0, int64_t nv, int tile) -> int {
@@ -557,7 +564,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                         if (p.nchunks == 1)
                             return launch_gemm_fast<bf16_t, void, true, true>(kind, G, p.ldz, Xc, H, out, H, nullptr, 0, nv,
                                                                               H, rows, s, tile, 1, 0, dyn_dw, part,
-                                                                              p.tail_bytes);
+                                                                              p.tail_bytes, with);
                         if (c == 0)
                             return launch_gemm_fast<float, void, true, true>(kind, G, p.ldz, Xc, H, acc, H, nullptr, 0, nv, H,
                                                                              rows, s, tile, 1, 0, dyn_dw, part,
@@ -576,10 +583,26 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                                                                      1, 0, dyn_dw);
                 return launch_gemm_guarded<T, T, true, true>(FLCE_KIND_DW_GEMM, G, p.ldz, Xc, H, out, H, acc,
                                                              !acc && c > 0 ? out : nullptr, nv, H, rows, s, tile, 1, 0,
-                                                             dyn_dw);
+                                                             dyn_dw, with);
             };
             FLCE_TRY(product(0, cut.main, cut.tile));
             if (cut.main < V) FLCE_TRY(product(cut.main, V - cut.main, cut.rest_tile));
+        }
+        if (norm && want_dx) {   // the chunk's dX into dh and the partial sums of dgamma
+            ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
+            const RnLoss rn_loss{row_loss, (int)rows, hdr, loss_here};
+#define RN_BWD(KERNEL)                                                                              \
+    hipLaunchKernelGGL((KERNEL), dim3(RN_SLOTS + 1), dim3(RN_THREADS), 0, s, Xin, norm->gamma,       \
+                       norm->rstd, dXg, (int)rows, (int)H, p.compact ? norm->dh : norm->dh + r0 * H, \
+                       norm->partial, row_map, n_live, c == 0 ? 1 : 0, rn_loss)
+            switch (rmsnorm_vectors_per_thread<T>(H, Xin, norm->gamma, norm->dh)) {
+                case 1: RN_BWD((rmsnorm_bwd_vec_kernel<T, 1>)); break;
+                case 2: RN_BWD((rmsnorm_bwd_vec_kernel<T, 2>)); break;
+                case 4: RN_BWD((rmsnorm_bwd_vec_kernel<T, 4>)); break;
+                default: RN_BWD((rmsnorm_bwd_kernel<T>)); break;
+            }
+#undef RN_BWD
+            HIP_TRY(hipGetLastError());
         }
     }
     return FLCE_OK;
@@ -652,11 +675,6 @@ int run_rmsnorm_head(const T* h, const T* gamma, float eps, const T* W, const in
     NormCtx<T> n{gamma, eps, reinterpret_cast<float*>(ws + l.off_rstd),
                  reinterpret_cast<float*>(ws + l.off_partial), dh};
     DeviceHeader* hdr = reinterpret_cast<DeviceHeader*>(ws + p.off_hdr);
-    if (want_dx) {
-        hipLaunchKernelGGL(fill_zero_kernel, dim3(256), dim3(256), 0, s, n.partial,
-                           (int64_t)RN_SLOTS * H);
-        HIP_TRY(hipGetLastError());
-    }
     FLCE_TRY(run_head<T>(h, W, targets, BT, H, V, ignore_index, 1.0f, hdr, LossOut{hdr, 1, loss, nullptr, {1.0f}},
                          false, nullptr, dW, flags, p, ws, s, &n));
     if (want_dx) {

@@ -66,6 +66,7 @@
 #include <type_traits>
 
 #include "flce_device.h"
+#include "misc_kernels.h"
 #include "scheduler.h"
 
 namespace flce {
@@ -563,17 +564,27 @@ __device__ __forceinline__ void fg_tile_origin(int seq, int tiles_m, int tiles_n
 // waits; its LDS reads (as many per K step for a quarter of the arithmetic) are as tight as the
 // matrix pipe.
 //
-// ROT: every column of tiles starts its K loop at another K step and wraps around.  For a row-form
+// ROT: every 256 columns start their K loop at another K step and wrap around.  For a row-form
 // B that is fetched once (few rows in A) from memory whose rows lie a power of two apart (H = 4096:
 // 8 KB), where all tiles at the same K step would ask the same few memory channels at a time.
 // A K % 64 == 0 operand pair without K ranges only.
-template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE, bool ROT = false>
-__global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGArgs a) {
+// FIN: the first fin.blocks workgroups finish the chunk's dX (see finish_dx_kernel) instead.
+struct NoFinish {};
+template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE, bool ROT = false, typename Fin = NoFinish>
+__global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGArgs a, Fin fin) {
     constexpr bool HAS_IN = !std::is_void<InT>::value;
     constexpr int IS = FgInSize<InT>::value;
     constexpr int W = TILE / 64;              // 32 x 32 MFMA tiles per wavefront and direction
     constexpr int SLOT = fg_slot_bytes(TILE);
     __shared__ __attribute__((aligned(16))) unsigned char smem[fg_lds_bytes(TILE)];
+    int block = (int)blockIdx.x;
+    if constexpr (!std::is_same<Fin, NoFinish>::value) {
+        if (block < fin.blocks) {
+            finish_dx<OutT, 4>(fin, block, smem);
+            return;
+        }
+        block -= fin.blocks;   // (a multiple of 8: the XCD stays block % 8)
+    }
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -590,8 +601,8 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
     const int tiles = tiles_m * a.tiles_n;
     const int total = tiles * ksplit;
     const int per_xcd = (total + FG_XCDS - 1) / FG_XCDS;
-    const int xcd = (int)blockIdx.x % FG_XCDS;
-    int in_xcd = (int)blockIdx.x / FG_XCDS;
+    const int xcd = block % FG_XCDS;
+    int in_xcd = block / FG_XCDS;
     // a tile of the last round that is cut along K: range tail_i of tail_n, partial block tail_blk
     int tail_i = 0, tail_n = 1, tail_blk = 0;
     if (TILE == 256 && a.tail_s > 1 && in_xcd >= a.tail_begin) {
@@ -728,7 +739,7 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
     opa.start_at(k_begin);
     opb.start_at(k_begin);
     if constexpr (ROT) {
-        opa.rot = opb.rot = (n0 / TILE) % nk;
+        opa.rot = opb.rot = (n0 / FG_BN) % nk;   // (the same order of K whatever the tile size)
         opa.wrap = opb.wrap = nk;
     }
     opa.load(smem, 0, 0, uwave);

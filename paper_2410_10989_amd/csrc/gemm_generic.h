@@ -159,8 +159,9 @@ __device__ __forceinline__ float gg_element(const float* base, int64_t ld, int r
     return k < K ? (KM ? base[(int64_t)k * ld + r] : base[(int64_t)r * ld + k]) : 0.f;
 }
 
-template <typename T, typename OutT, bool A_KM, bool B_KM, int TILE>
-__global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a) {
+// Fin: as in gemm_bf16.
+template <typename T, typename OutT, bool A_KM, bool B_KM, int TILE, typename Fin = NoFinish>
+__global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fin fin) {
     constexpr int PLANES = GGTraits<T>::PLANES;
     constexpr int WAVES_N = TILE == 256 ? 4 : 2;              // wavefronts: 2 x WAVES_N
     constexpr int WM = TILE / 64, WN = TILE / 32 / WAVES_N;   // 32 x 32 MFMA tiles per wavefront
@@ -169,6 +170,14 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a) {
     constexpr int SIDE = PLANES * PLANE;
     constexpr int ACCS = TILE == 64 ? 2 : 1;
     __shared__ __attribute__((aligned(16))) unsigned char lds[2][2 * SIDE];
+    int block = (int)blockIdx.x;
+    if constexpr (!std::is_same<Fin, NoFinish>::value) {
+        if (block < fin.blocks) {
+            finish_dx<OutT, 4>(fin, block, lds);
+            return;
+        }
+        block -= fin.blocks;
+    }
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -182,9 +191,9 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a) {
     const int tiles = tiles_m * tiles_n;
     const int total = tiles * rs.ksplit;
     const int per_xcd = (total + FG_XCDS - 1) / FG_XCDS;
-    const int in_xcd = (int)blockIdx.x / FG_XCDS;
+    const int in_xcd = block / FG_XCDS;
     if (in_xcd >= per_xcd) return;
-    const int seq = fg_seq(a, (int)blockIdx.x % FG_XCDS, in_xcd, per_xcd);
+    const int seq = fg_seq(a, block % FG_XCDS, in_xcd, per_xcd);
     if (seq >= total) return;
     const int split = seq / tiles;
     int m0, n0;

@@ -13,28 +13,34 @@ namespace flce {
 // elements per lane and access with VEC4 (n, split_stride and the pointers are multiples of 4).
 // The workgroup past the rows sums the chunk's losses (row_loss not null).
 // Latency bound at small sizes: one launch where the sum over K ranges, the scatter, the loss sum
-// and its finalisation were four of 4-5 us each.
-template <typename T, typename SrcT, bool ADD, bool VEC4>
-__global__ __launch_bounds__(256) void finish_dx_kernel(const SrcT* __restrict__ src, int64_t split_stride, int nsplit,
-                                                        const int* __restrict__ dyn_nsplit,
-                                                        const int* __restrict__ idx, const int* __restrict__ live,
-                                                        int rows, int n, T* __restrict__ out,
-                                                        const float* __restrict__ row_loss, DeviceHeader* hdr,
-                                                        LossOut loss) {
-    const int row_groups = (rows + 3) / 4;
-    if ((int)blockIdx.x == row_groups) {
-        if (row_loss) loss_accumulate(row_loss, rows, hdr, loss);
-        return;
-    }
-    const int i = (int)blockIdx.x * 4 + (int)threadIdx.x / WAVE;
-    if (i >= (live ? min(rows, *live) : rows)) return;
-    if (dyn_nsplit) nsplit = *dyn_nsplit;
-    const SrcT* from = src + (int64_t)i * n;
-    T* to = out + (int64_t)(idx ? idx[i] : i) * n;
-    constexpr int E = VEC4 ? 4 : 1;
+// and its finalisation were four of 4-5 us each; in front of a dW product on small tiles its
+// workgroups ride along with that launch instead (nothing in it waits for the other).
+struct FinishArgs {
+    const void* src;
+    int src_f32;            // src: fp32 partial results, or rows in the storage type
+    int64_t split_stride;
+    int nsplit;
+    const int* dyn_nsplit;
+    const int* idx;
+    const int* live;
+    int rows, n;
+    void* out;
+    int add;
+    const float* row_loss;
+    DeviceHeader* hdr;
+    LossOut loss;
+    int blocks;             // workgroups: one per 4 rows and one for the losses, rounded up to a multiple of 8
+};
+inline int finish_blocks(int64_t rows) { return (int)(((rows + 3) / 4 + 1 + 7) / 8 * 8); }
+
+template <typename T, typename SrcT, bool ADD, int E>
+__device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int lane) {
+    const int nsplit = f.dyn_nsplit ? *f.dyn_nsplit : f.nsplit;
+    const SrcT* from = static_cast<const SrcT*>(f.src) + (int64_t)i * f.n;
+    T* to = static_cast<T*>(f.out) + (int64_t)(f.idx ? f.idx[i] : i) * f.n;
     struct alignas(E * sizeof(SrcT)) In { SrcT e[E]; };
     struct alignas(E * sizeof(T)) Out { T e[E]; };
-    for (int j = ((int)threadIdx.x & (WAVE - 1)) * E; j < n; j += WAVE * E) {
+    for (int j = lane * E; j < f.n; j += WAVE * E) {
         float v[E];
         const In a = *reinterpret_cast<const In*>(from + j);
 #pragma unroll
@@ -47,7 +53,7 @@ __global__ __launch_bounds__(256) void finish_dx_kernel(const SrcT* __restrict__
         }
 #pragma unroll 4
         for (int s = 1; s < nsplit; ++s) {
-            const In b = *reinterpret_cast<const In*>(from + (int64_t)s * split_stride + j);
+            const In b = *reinterpret_cast<const In*>(from + (int64_t)s * f.split_stride + j);
 #pragma unroll
             for (int e = 0; e < E; ++e) v[e] += to_f32(b.e[e]);
         }
@@ -55,6 +61,28 @@ __global__ __launch_bounds__(256) void finish_dx_kernel(const SrcT* __restrict__
         for (int e = 0; e < E; ++e) o.e[e] = from_f32<T>(v[e]);
         *reinterpret_cast<Out*>(to + j) = o;
     }
+}
+// One workgroup of 256 threads; part: 32 bytes of LDS.
+template <typename T, int E>
+__device__ __forceinline__ void finish_dx(const FinishArgs& f, int block, void* part) {
+    const int groups = (f.rows + 3) / 4;
+    if (block >= groups) {
+        if (block == groups && f.row_loss)
+            loss_accumulate(f.row_loss, f.rows, f.hdr, f.loss, static_cast<double*>(part));
+        return;
+    }
+    const int i = block * 4 + (int)threadIdx.x / WAVE, lane = (int)threadIdx.x & (WAVE - 1);
+    if (i >= (f.live ? min(f.rows, *f.live) : f.rows)) return;
+    if (f.src_f32) {
+        if (f.add) finish_row<T, float, true, E>(f, i, lane); else finish_row<T, float, false, E>(f, i, lane);
+    } else {
+        if (f.add) finish_row<T, T, true, E>(f, i, lane); else finish_row<T, T, false, E>(f, i, lane);
+    }
+}
+template <typename T, bool VEC4>
+__global__ __launch_bounds__(256) void finish_dx_kernel(FinishArgs f) {
+    __shared__ double part[4];
+    finish_dx<T, VEC4 ? 4 : 1>(f, (int)blockIdx.x, part);
 }
 
 }  // namespace flce

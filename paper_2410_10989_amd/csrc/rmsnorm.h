@@ -18,6 +18,7 @@
 // takes any row length.
 #pragma once
 #include "flce_device.h"
+#include "compact.h"
 #include "rowreduce.h"
 
 namespace flce {
@@ -61,18 +62,36 @@ __global__ __launch_bounds__(RN_THREADS) void rmsnorm_fwd_kernel(const T* __rest
         y[obase + j] = from_f32<T>(to_f32(x[base + j]) * r * to_f32(gamma[j]));
 }
 
+// The workgroup past the RN_SLOTS of a backward launch sums the chunk's losses (see loss_accumulate).
+struct RnLoss {
+    const float* row_loss;
+    int rows;
+    DeviceHeader* hdr;
+    LossOut out;
+};
+__device__ __forceinline__ bool rn_loss_block(const RnLoss& l) {
+    if (blockIdx.x < RN_SLOTS) return false;
+    __shared__ double part[4];
+    loss_accumulate(l.row_loss, l.rows, l.hdr, l.out, part);
+    return true;
+}
+
 // Workgroup p: rows p, p + RN_SLOTS, ... of this chunk.  dx is written; the
 // workgroup's own row of `partial` accumulates dy * xhat (column j always by the
-// same thread, so there is no race and the order of additions is fixed).
+// same thread, so there is no race and the order of additions is fixed; the first
+// chunk's launch starts the row).
 // With idx / live (a compacted chunk) dy and rstd are indexed by the chunk's row i, x and
 // dx by row idx[i], and only *live rows exist.
 template <typename T>
 __global__ __launch_bounds__(RN_THREADS) void rmsnorm_bwd_kernel(
     const T* __restrict__ x, const T* __restrict__ gamma, const float* __restrict__ rstd,
     const T* __restrict__ dy, int rows, int n, T* __restrict__ dx, float* __restrict__ partial,
-    const int* __restrict__ idx, const int* __restrict__ live) {
+    const int* __restrict__ idx, const int* __restrict__ live, int first, RnLoss loss) {
     __shared__ float red[RN_THREADS / WAVE];
+    if (rn_loss_block(loss)) return;
     float* mine = partial + (int64_t)blockIdx.x * n;
+    if (first)
+        for (int j = threadIdx.x; j < n; j += RN_THREADS) mine[j] = 0.f;
     if (live) rows = min(rows, *live);
     for (int row = blockIdx.x; row < rows; row += RN_SLOTS) {
         const int64_t base = (int64_t)(idx ? idx[row] : row) * n;
@@ -138,9 +157,10 @@ template <typename T, int NV>
 __global__ __launch_bounds__(RN_THREADS) void rmsnorm_bwd_vec_kernel(
     const T* __restrict__ x, const T* __restrict__ gamma, const float* __restrict__ rstd,
     const T* __restrict__ dy, int rows, int n, T* __restrict__ dx, float* __restrict__ partial,
-    const int* __restrict__ idx, const int* __restrict__ live) {
+    const int* __restrict__ idx, const int* __restrict__ live, int first, RnLoss loss) {
     constexpr int N = RowVec<T>::N;
     __shared__ float red[RN_THREADS / WAVE];
+    if (rn_loss_block(loss)) return;
     const int nvec = n / N;
     const u32x4* gr = reinterpret_cast<const u32x4*>(gamma);
     float gv[NV][N], acc[NV][N];
@@ -197,15 +217,9 @@ __global__ __launch_bounds__(RN_THREADS) void rmsnorm_bwd_vec_kernel(
         const int v = threadIdx.x + k * RN_THREADS;
         if (v < nvec) {
 #pragma unroll
-            for (int e = 0; e < N; ++e) mine[v * N + e] += acc[k][e];
+            for (int e = 0; e < N; ++e) mine[v * N + e] = first ? acc[k][e] : mine[v * N + e] + acc[k][e];
         }
     }
-}
-
-__global__ void fill_zero_kernel(float* __restrict__ p, int64_t count) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.f;
 }
 
 // dgamma[j] = sum_p partial[p][j].  A workgroup of 64 x 4 threads owns 64 columns: thread

@@ -320,8 +320,7 @@ struct LossOut {
 // last.  Its own launch is mostly latency (5-8 us), so it rides along as one more workgroup of the
 // kernel that finishes dX or dgamma where there is one.
 __device__ __forceinline__ void loss_accumulate(const float* __restrict__ row_loss, int rows, DeviceHeader* hdr,
-                                                const LossOut& out) {
-    __shared__ double part[4];
+                                                const LossOut& out, double* part) {   // part: 4 in LDS
     double s = 0.0;
 #pragma unroll 8
     for (int i = threadIdx.x; i < rows; i += 256) s += (double)row_loss[i];
@@ -344,7 +343,8 @@ __device__ __forceinline__ void loss_accumulate(const float* __restrict__ row_lo
 }
 __global__ __launch_bounds__(256) void loss_accumulate_kernel(const float* row_loss, int rows, DeviceHeader* hdr,
                                                               LossOut out) {
-    loss_accumulate(row_loss, rows, hdr, out);
+    __shared__ double part[4];
+    loss_accumulate(row_loss, rows, hdr, out, part);
 }
 
 // Counts the valid rows and resets the running loss.  Integer sum: exact in any order.

@@ -1,0 +1,82 @@
+// Host rules that pick tiles, K ranges and the share of the vocabulary per launch, over sweeps of
+// shapes: whatever they pick covers the product exactly, keeps to the kernels' limits and to the
+// memory a plan may take.
+#include <cstdio>
+#include <cstdlib>
+
+#include "../paper_2410_10989_amd/csrc/scheduler.h"
+
+#define CHECK(cond, ...)                                        \
+    do {                                                        \
+        if (!(cond)) {                                          \
+            std::printf("FAILED %s: ", #cond);                  \
+            std::printf(__VA_ARGS__);                           \
+            std::printf("\n");                                  \
+            std::exit(1);                                       \
+        }                                                       \
+    } while (0)
+
+int main() {
+    using namespace flce;
+    const int64_t Vs[] = {1, 63, 256, 257, 300, 1000, 4096, 7011, 8192, 12289, 32000, 50257, 128256, 152064, 262151, 1 << 20};
+    const int64_t others[] = {1, 8, 64, 127, 128, 129, 256, 300, 512, 1000, 1024, 2047, 2304, 4096, 8192, 16384, 150001};
+    const int64_t Ks[] = {1, 8, 63, 64, 65, 200, 512, 1000, 1024, 2304, 4096, 50257, 128256};
+    long n = 0, shared = 0, small = 0;
+    for (int tuned = 0; tuned < 2; ++tuned)
+        for (int64_t V : Vs)
+            for (int64_t o : others)
+                for (int64_t K : Ks)
+                    for (int tail = 0; tail < 2; ++tail) {
+                        const VocabCut c = vocab_cut(tuned != 0, V, o, K, tail != 0);
+                        ++n;
+                        CHECK(c.tile == 256 || c.tile == 128 || (!tuned && c.tile == 64), "tile %d", c.tile);
+                        CHECK(c.main >= 1 && c.main <= V, "main %lld of %lld", (long long)c.main, (long long)V);
+                        if (c.tile < 256) ++small;
+                        if (c.main == V) continue;
+                        ++shared;
+                        // whole 256-tiles that fit whole rounds of the CUs, and a rest on smaller tiles
+                        CHECK(c.tile == 256 && c.main % 256 == 0, "shared launch: main %lld tile %d", (long long)c.main, c.tile);
+                        CHECK(c.rest_tile == 128 || (!tuned && c.rest_tile == 64), "rest tile %d", c.rest_tile);
+                        const int64_t per = (o + 255) / 256, t = c.main / 256 * per, all = tiles_of(V, o, 256);
+                        CHECK(t <= all / 256 * 256 && t > all / 256 * 256 - per, "%lld tiles do not fill the rounds", (long long)t);
+                    }
+    CHECK(shared > 0 && small > 0, "a branch of the rule is never taken");
+    long cut = 0;
+    for (int tuned = 0; tuned < 2; ++tuned)
+        for (int64_t rows : others)
+            for (int64_t H : others)
+                for (int64_t V : Vs)
+                    for (size_t budget : {(size_t)1, (size_t)1 << 20, (size_t)1 << 30, (size_t)1 << 33}) {
+                        if (H > 16384) continue;
+                        const ProductCut c = dx_cut(tuned != 0, rows, H, V, budget);
+                        CHECK(c.tile == 256 || c.tile == 128 || (!tuned && c.tile == 64), "dX tile %d", c.tile);
+                        CHECK(c.ranges >= 1 && c.ranges <= 64, "dX ranges %d", c.ranges);
+                        if (c.ranges == 1) continue;
+                        ++cut;
+                        CHECK((size_t)c.ranges * (size_t)rows * (size_t)H * 4 <= budget / 2, "partial results past half the budget");
+                        CHECK(V / c.ranges >= 256 || (tuned && c.tile == 256 && (V + 63) / 64 / c.ranges >= 64), "short range");
+                        // the kernels' ranges of K steps (64, 32 or 16 elements) tile the steps and none is empty
+                        const int64_t bk = tuned ? 64 : c.tile == 64 ? 32 : 16, steps = (V + bk - 1) / bk;
+                        int64_t at = 0;
+                        for (int r = 0; r < c.ranges; ++r) {
+                            const int64_t b = steps * r / c.ranges, e = steps * (r + 1) / c.ranges;
+                            CHECK(b == at && e > b, "ranges do not tile the K steps");
+                            at = e;
+                        }
+                        CHECK(at == steps, "K steps lost");
+                    }
+    CHECK(cut > 0, "no dX product is cut");
+    // the rotated K loop visits every step once
+    for (int nk = 1; nk <= 70; ++nk)
+        for (int rot = 0; rot < nk; ++rot) {
+            unsigned char seen[70] = {0};
+            for (int kt = 0; kt < nk; ++kt) {
+                int k = kt + rot;
+                k -= k >= nk ? nk : 0;
+                CHECK(k >= 0 && k < nk && !seen[k], "step %d of %d", k, nk);
+                seen[k] = 1;
+            }
+        }
+    std::printf("product rules: %ld shares (%ld of them of two launches), %ld cut dX products\n", n, shared, cut);
+    return 0;
+}

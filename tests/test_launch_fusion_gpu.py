@@ -112,3 +112,41 @@ def test_cross_entropy_counts_its_rows(BT, noalloc, ignore):
     torch.cuda.synchronize()
     assert abs(float(loss) - rl) <= 2e-6 * max(1.0, abs(rl))
     assert float((Z.double() - want).norm()) <= 2e-6 * max(float(want.norm()), 1e-30)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("BT,H,V,budget_rows,offset", [
+    (70, 64, 300, 0, 0),       # normalised by the selection; dX finished beside dW, losses summed by the norm's backward
+    (70, 64, 300, 0, 1),       # gamma not 16-byte aligned: the scalar forms
+    (700, 264, 900, 256, 0),   # three chunks: the first starts the dgamma sums, the others add
+    (33000, 32, 70, 0, 0),     # past the one-launch selection
+    (40, 66, 200, 0, 0),       # rows that are not whole vectors (no compaction in bf16)
+])
+@pytest.mark.parametrize("flags", [0, 1, 2])
+def test_rmsnorm_in_the_fused_launches(dtype, BT, H, V, budget_rows, offset, flags):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, H, V, dtype, "scattered", BT + H)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    gamma = (1 + 0.1 * torch.randn(H + offset, device="cuda", generator=g)).to(dtype)[offset:]
+    old = flce.flce_get_logits_budget_bytes()
+    try:
+        flce.flce_set_logits_budget_bytes(budget_rows * ((V + 63) // 64 * 64) * X.element_size())
+        loss, dh, dgamma, dW = flce.flce_rmsnorm_fwd_bwd(X, gamma, 1e-6, W, t, flags=flags)
+        torch.cuda.synchronize()
+    finally:
+        flce.flce_set_logits_budget_bytes(old)
+    x, gm = X.double().cpu(), gamma.double().cpu()
+    rms = torch.sqrt((x * x).mean(1, keepdim=True) + 1e-6)
+    xhat = x / rms
+    y = (xhat * gm).to(dtype)          # what the products see
+    rl, dY, rW = reference(y.float(), W.float(), t)
+    a = dY * gm
+    want_h = (a - (xhat * a).mean(1, keepdim=True) * xhat) / rms
+    want_g = (dY * xhat).sum(0)
+    tol = TOL[dtype] if dtype == torch.bfloat16 else max(TOL[dtype], 2.0 ** -24 * math.sqrt(6 * max(BT, H, V) / 16))
+    assert abs(float(loss) - rl) <= max(2e-6, tol / 4) * abs(rl)
+    if not flags & flce.SKIP_DX:
+        assert float((dh.double().cpu() - want_h).norm() / want_h.norm()) <= tol
+        assert float((dgamma.double().cpu() - want_g).norm() / want_g.norm()) <= 4 * tol   # BT signed terms per column
+    if not flags & flce.SKIP_DW:
+        assert float((dW.double().cpu() - rW).norm() / rW.norm()) <= tol
