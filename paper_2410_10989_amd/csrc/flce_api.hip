@@ -82,9 +82,10 @@ size_t single_chunk_bytes(const Settings& st, int64_t H, int64_t V, int dtype) {
     return b + (size_t)V * (size_t)H * sizeof(float);
 }
 
-Plan plan_for(const Settings& st, int64_t BT, int64_t H, int64_t V, int dtype, bool worst_case_bt = false) {
+Plan plan_for(const Settings& st, int64_t BT, int64_t H, int64_t V, int dtype, bool worst_case_bt = false,
+              bool lean = false) {
     return make_plan(BT, H, V, dtype, effective_budget(st, V, dtype), worst_case_bt, st.compact,
-                     single_chunk_bytes(st, H, V, dtype));
+                     single_chunk_bytes(st, H, V, dtype), lean);
 }
 Plan plan_for(int64_t BT, int64_t H, int64_t V, int dtype, bool worst_case_bt = false) {
     return plan_for(global_settings(), BT, H, V, dtype, worst_case_bt);
@@ -135,14 +136,17 @@ struct ScopedKernelTimer {
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-int acquire_workspace(size_t need, char** out) {
+// The device's shared workspace.  A lent buffer that holds `least` bytes but not `need` is handed
+// out as well (*out_bytes says how much there is): the caller then runs its lean plan.
+int acquire_workspace(size_t need, char** out, size_t least = 0, size_t* out_bytes = nullptr) {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= MAX_DEVICES) return FLCE_ERR_ARG;
     std::lock_guard<std::mutex> lock(g_mutex);
     DeviceWorkspace& w = g_ws[dev];
     if (w.lent) {
-        if (w.lent_bytes < need) return FLCE_ERR_WORKSPACE;
+        if (w.lent_bytes < need && (!out_bytes || w.lent_bytes < least)) return FLCE_ERR_WORKSPACE;
+        if (out_bytes) *out_bytes = w.lent_bytes;
         *out = static_cast<char*>(w.lent);
         return FLCE_OK;
     }
@@ -160,6 +164,7 @@ int acquire_workspace(size_t need, char** out) {
         }
         w.own_bytes = need;
     }
+    if (out_bytes) *out_bytes = w.own_bytes;
     *out = static_cast<char*>(w.own);
     return FLCE_OK;
 }
@@ -746,14 +751,17 @@ int multihead_fwd_bwd(const Settings& st, const void* X, const void* const* W, c
     }
     if (ignore_index >= 0 && ignore_index < V) return FLCE_ERR_ARG;   // would shadow a class
 
-    const Plan p = plan_for(st, BT, H, V, dtype);
+    Plan p = plan_for(st, BT, H, V, dtype);
     FLCE_TRY(check_launch_limits(p, H, V));
     char* ws = static_cast<char*>(st.ws);
     if (ws) {
         if (!aligned(ws, 256)) return FLCE_ERR_ALIGN;
         if (st.ws_bytes < p.total) return FLCE_ERR_WORKSPACE;
     } else {
-        FLCE_TRY(acquire_workspace(p.total, &ws));
+        const Plan lean = plan_for(st, BT, H, V, dtype, false, true);
+        size_t have = 0;
+        FLCE_TRY(acquire_workspace(p.total, &ws, lean.total, &have));
+        if (have < p.total) p = lean;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dtype == FLCE_F32)
@@ -839,11 +847,17 @@ int flce_rmsnorm_fwd_bwd(const void* h, const void* gamma, float eps, const void
     if (ignore_index >= 0 && ignore_index < V) return FLCE_ERR_ARG;
     if (!(eps >= 0.0f) || eps - eps != 0.0f) return FLCE_ERR_ARG;   // negative, NaN or infinite
 
-    const Plan p = plan_for(BT, H, V, dtype);
+    Plan p = plan_for(BT, H, V, dtype);
     FLCE_TRY(check_launch_limits(p, H, V));
-    const NormLayout l = norm_layout(p, H);
+    NormLayout l = norm_layout(p, H);
+    const Plan lean = plan_for(global_settings(), BT, H, V, dtype, false, true);
     char* ws = nullptr;
-    FLCE_TRY(acquire_workspace(l.total, &ws));
+    size_t have = 0;
+    FLCE_TRY(acquire_workspace(l.total, &ws, norm_layout(lean, H).total, &have));
+    if (have < l.total) {
+        p = lean;
+        l = norm_layout(p, H);
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dtype == FLCE_F32)
         return run_rmsnorm_head<float>(static_cast<const float*>(h), static_cast<const float*>(gamma),

@@ -187,6 +187,14 @@ inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t 
     return best;
 }
 
+// The same with as little memory for partial results as the large tiles' rule takes: for a lent
+// workspace that holds such a plan but not the faster one.
+inline ProductCut dx_cut_lean(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes) {
+    const int tile = tuned ? 256 : 128;
+    const int max_ranges = std::min(16, max_dx_ranges(budget_bytes, round_up(rows, tile), H));
+    return {tile, choose_ksplit(tiles_of(rows, H, tile), tuned ? (V + 63) / 64 : V / 4, max_ranges)};
+}
+
 // The logits and dW products have V along one output dimension, which can be shared out: columns (or
 // rows) 0 .. main - 1 on 256 x 256 tiles that fill whole rounds of the CUs, the rest on smaller
 // tiles in a second launch, instead of one more, mostly empty round of large ones.  tail: the last
@@ -228,7 +236,7 @@ inline bool fits_col_form(int64_t ld, int64_t) { return 64 * ld * 2 + 512 < ((in
 // Byte offsets of the workspace for a plan whose chunking (C, nchunks, rows of the last
 // chunk) is decided; `dxpart_floor` is a lower bound for the K-range partials.
 inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last, size_t budget_bytes,
-                    bool allow_compact, size_t dxpart_floor) {
+                    bool allow_compact, size_t dxpart_floor, bool lean = false) {
     const size_t es = elem_size(dtype);
     p.ldc = round_up(p.C, 64);
     p.fp32_dw_acc = (dtype != 0) && p.nchunks > 1;
@@ -248,7 +256,8 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     }
     {
         const int64_t rows = p.nchunks > 1 ? p.C : rows_last;
-        const ProductCut cut = dx_cut(p.fast_dx, rows, H, V, budget_bytes);
+        const ProductCut cut = lean ? dx_cut_lean(p.fast_dx, rows, H, V, budget_bytes)
+                                    : dx_cut(p.fast_dx, rows, H, V, budget_bytes);
         p.dx_tile = cut.tile;
         p.dx_ranges = cut.ranges;
         p.dx_ksplit = p.fast_dx ? choose_ksplit(tiles_of(rows, H, 256), (V + 63) / 64,
@@ -293,9 +302,10 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
 // which only several chunks need, so that one chunk is taken whenever it needs no more
 // memory than the chunked plan would (and it is always faster: no second pass over W,
 // no fp32 round trip of dW).  worst_case_bt: the plan with the largest workspace any BT
-// can lead to (BT is ignored).
+// can lead to (BT is ignored).  lean: see dx_cut_lean.
 inline Plan make_plan(int64_t BT, int64_t H, int64_t V, int dtype, size_t budget_bytes,
-                      bool worst_case_bt = false, bool allow_compact = true, size_t single_bytes = 0) {
+                      bool worst_case_bt = false, bool allow_compact = true, size_t single_bytes = 0,
+                      bool lean = false) {
     Plan p;
     const size_t es = elem_size(dtype);
     p.ldz = round_up(V, 64);
@@ -340,7 +350,7 @@ inline Plan make_plan(int64_t BT, int64_t H, int64_t V, int dtype, size_t budget
         p.nchunks = (BT + p.C - 1) / p.C;
         rows_last = BT - (p.nchunks - 1) * p.C;
     }
-    lay_out(p, H, V, dtype, rows_last, budget_bytes, allow_compact, 0);
+    lay_out(p, H, V, dtype, rows_last, budget_bytes, allow_compact, 0, lean);
     return p;
 }
 

@@ -150,3 +150,21 @@ def test_rmsnorm_in_the_fused_launches(dtype, BT, H, V, budget_rows, offset, fla
         assert float((dgamma.double().cpu() - want_g).norm() / want_g.norm()) <= 4 * tol   # BT signed terms per column
     if not flags & flce.SKIP_DW:
         assert float((dW.double().cpu() - rW).norm() / rW.norm()) <= tol
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_lent_workspace_below_the_fast_plan(dtype):
+    # a buffer lent to the device that lacks room for the finer K ranges of dX still serves: the call
+    # takes the plan of the large tiles (the room a caller may have set aside for that)
+    import paper_2410_10989_amd as flce
+    BT, H, V = 600, 256, 16384
+    X, W, t = make(BT, H, V, dtype, "scattered", 12)
+    code = flce.FLCE_F32 if dtype == torch.float32 else flce.FLCE_BF16
+    need = flce.flce_workspace_bytes(BT, H, V, code)
+    buf = torch.full((need - 256,), 255, dtype=torch.uint8, device="cuda")
+    off = -buf.data_ptr() % 256
+    try:
+        flce.flce_set_workspace(buf[off:])
+        check(flce.flce_fwd_bwd(X, W, t), X, W, t, dtype)
+    finally:
+        flce.flce_set_workspace(None)
