@@ -31,7 +31,7 @@ namespace {
 constexpr int MAX_DEVICES = 64;
 constexpr int64_t MAX_DIM = (int64_t)1 << 30;      // per-dimension limit, keeps int tile math safe
 constexpr int64_t CE_ROWS_PER_LAUNCH = 65536;
-constexpr int64_t RIDE_ROWS = 4096;   // finish_dx as workgroups of the dW launch: up to 1024 of them
+constexpr int RIDE_BLOCKS = 1024;   // finish_dx as workgroups of the dW launch: at most this many
 constexpr int64_t ROT_A_BYTES = (int64_t)2 << 20;
 constexpr int64_t CE_CACHE_BYTES = (int64_t)256 << 20;   // memory-side cache
 constexpr int64_t MAX_GRID_X = 0x7fffffff;        // workgroups along grid x
@@ -513,7 +513,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                         FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, nullptr, rows, H, V, s, p.dx_tile, p.dx_ranges,
                         p.C * H, dyn_m)));
                 fin = {part, 1, p.C * H, p.dx_ranges, dyn_dx.ksplit, scatter ? row_map : nullptr, n_live, (int)rows, (int)H,
-                       scatter ? dX : dXc, dx_add && (scatter || add_in_gemm), nullptr, hdr, LossOut{}, finish_blocks(rows)};
+                       scatter ? dX : dXc, dx_add && (scatter || add_in_gemm), nullptr, hdr, LossOut{}, finish_segs(H), (int)finish_blocks(rows, H)};
                 finish = true;
             } else {
                 if constexpr (BF16) {
@@ -530,7 +530,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                         p.dx_tile, 1, 0, dyn_m)));
                 if (scatter) {
                     fin = {dXg, 0, 0, 1, nullptr, row_map, n_live, (int)rows, (int)H, dX, dx_add, nullptr, hdr, LossOut{},
-                           finish_blocks(rows)};
+                           finish_segs(H), (int)finish_blocks(rows, H)};
                     finish = true;
                 }
             }
@@ -548,7 +548,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         const bool dw_fast = BF16 && (last ? p.fast_dw_last : p.fast_dw_full);
         const VocabCut dw_cut = vocab_cut(dw_fast, V, H, rows, p.tail_bytes > 0);
         const bool ride_along = finish && want_dw && p.nchunks == 1 && dw_cut.main == V && dw_cut.tile < 256 &&
-                                (dw_fast || !BF16) && rows <= RIDE_ROWS && finish_is_vec<T>(fin);
+                                (dw_fast || !BF16) && fin.blocks <= RIDE_BLOCKS && finish_is_vec<T>(fin);
         if (finish && !ride_along) FLCE_TRY(launch_finish_dx<T>(fin, s));
 
         // dW (+)= G^T X_c   (K = the chunk's rows; in a compacted chunk K = *n_live)

@@ -222,20 +222,38 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
 
     // the barrier waits for this wavefront's LDS accesses only, not for the loads in flight
     auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    // plane pairs (of a, of b), smallest products first
+    constexpr int PAIRS = PLANES == 3 ? 6 : 1;
+    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
     auto multiply = [&](int buf) {
         const unsigned char* la = lds[buf] + wm * WM * 512;
         const unsigned char* lb = lds[buf] + SIDE + wn * WN * 512;
+        auto fragment = [&](const unsigned char* side, int p, int kk, int i) {   // of plane p, pieces 2 kk and 2 kk + 1
+            const int at = ((2 * kk + fhalf) * TILE + (frow ^ gg_fold(2 * kk + fhalf))) * 16;
+            return *reinterpret_cast<const bf16x8*>(side + p * PLANE + at + i * 512);
+        };
+        if constexpr (ACCS == 2) {   // the two halves of the K step alternate: neighbouring products are independent
+            bf16x8 fa[2][PLANES], fb[2][PLANES];
 #pragma unroll
-        for (int kk = 0; kk < BK / 16; ++kk) {
-            const int frag = ((2 * kk + fhalf) * TILE + (frow ^ gg_fold(2 * kk + fhalf))) * 16;   // this lane's part of fragment 0
+            for (int p = PLANES - 1; p >= 0; --p)
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) {
+                    fa[kk][p] = fragment(la, p, kk, 0);
+                    fb[kk][p] = fragment(lb, p, kk, 0);
+                }
+#pragma unroll
+            for (int q = 0; q < PAIRS; ++q) {
+                const int pa = PLANES == 3 ? PA[q] : 0, pb = PLANES == 3 ? PB[q] : 0;
+                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[0][pb], fa[0][pa], acc[0][0], 0, 0, 0);
+                acc2[ACCS - 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[1][pb], fa[1][pa], acc2[ACCS - 1], 0, 0, 0);
+            }
+        } else {
+            static_assert(BK == 16 || TILE == 64, "one K piece pair per step");
             bf16x8 fb[PLANES][WN];
 #pragma unroll
             for (int p = 0; p < PLANES; ++p)
 #pragma unroll
-                for (int j = 0; j < WN; ++j) fb[p][j] = *reinterpret_cast<const bf16x8*>(lb + p * PLANE + frag + j * 512);
-            // plane pairs (of a, of b), smallest products first
-            constexpr int PAIRS = PLANES == 3 ? 6 : 1;
-            constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+                for (int j = 0; j < WN; ++j) fb[p][j] = fragment(lb, p, 0, j);
             // IB rows of MFMA tiles at a time: few enough fragments of A to leave room for the sums
             constexpr int IB = TILE == 256 ? 2 : WM;
 #pragma unroll
@@ -244,21 +262,15 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
 #pragma unroll
                 for (int p = 0; p < PLANES; ++p)
 #pragma unroll
-                    for (int i = 0; i < IB; ++i)
-                        fa[p][i] = *reinterpret_cast<const bf16x8*>(la + p * PLANE + frag + (ib + i) * 512);
+                    for (int i = 0; i < IB; ++i) fa[p][i] = fragment(la, p, 0, ib + i);
 #pragma unroll
                 for (int q = 0; q < PAIRS; ++q) {
                     const int pa = PLANES == 3 ? PA[q] : 0, pb = PLANES == 3 ? PB[q] : 0;
-                    if constexpr (ACCS == 2) {
-                        f32x16& c = (kk & 1) ? acc2[ACCS - 1] : acc[0][0];
-                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[pb][0], fa[pa][0], c, 0, 0, 0);
-                    } else {
 #pragma unroll
-                        for (int i = 0; i < IB; ++i)
+                    for (int i = 0; i < IB; ++i)
 #pragma unroll
-                            for (int j = 0; j < WN; ++j)
-                                acc[ib + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[pb][j], fa[pa][i], acc[ib + i][j], 0, 0, 0);
-                    }
+                        for (int j = 0; j < WN; ++j)
+                            acc[ib + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[pb][j], fa[pa][i], acc[ib + i][j], 0, 0, 0);
                 }
             }
         }

@@ -9,7 +9,7 @@ namespace flce {
 //     out[idx ? idx[i] : i] (+)= sum_s src[s][i]        in the fixed order s = 0, 1, ...
 // src: fp32 partial results of the K ranges (split_stride elements apart, dyn_nsplit their number
 // when only the device knows it), or with nsplit = 1 the product's rows in the storage type.
-// With ADD the row is added to what out holds (dX summed over heads).  One wavefront per row, 4
+// With ADD the row is added to what out holds (dX summed over heads).  One wavefront per segment, 4
 // elements per lane and access with VEC4 (n, split_stride and the pointers are multiples of 4).
 // The workgroup past the rows sums the chunk's losses (row_loss not null).
 // Latency bound at small sizes: one launch where the sum over K ranges, the scatter, the loss sum
@@ -29,18 +29,25 @@ struct FinishArgs {
     const float* row_loss;
     DeviceHeader* hdr;
     LossOut loss;
-    int blocks;             // workgroups: one per 4 rows and one for the losses, rounded up to a multiple of 8
+    int segs;               // FIN_SEG elements of a row per wavefront
+    int blocks;             // workgroups: one per 4 segments and one for the losses, rounded up to a multiple of 8
 };
-inline int finish_blocks(int64_t rows) { return (int)(((rows + 3) / 4 + 1 + 7) / 8 * 8); }
+// (Rows are cut into segments so that a few long rows with many partial results fill the chip too:
+// 180 rows of 4096 with 16 ranges took 45 us with a wavefront per row.)
+constexpr int FIN_SEG = 512;
+inline int finish_segs(int64_t n) { return (int)((n + FIN_SEG - 1) / FIN_SEG); }
+inline int64_t finish_blocks(int64_t rows, int64_t n) { return ((rows * finish_segs(n) + 3) / 4 + 1 + 7) / 8 * 8; }
 
 template <typename T, typename SrcT, bool ADD, int E>
-__device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int lane) {
+__device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int j0, int lane) {
     const int nsplit = f.dyn_nsplit ? *f.dyn_nsplit : f.nsplit;
     const SrcT* from = static_cast<const SrcT*>(f.src) + (int64_t)i * f.n;
     T* to = static_cast<T*>(f.out) + (int64_t)(f.idx ? f.idx[i] : i) * f.n;
     struct alignas(E * sizeof(SrcT)) In { SrcT e[E]; };
     struct alignas(E * sizeof(T)) Out { T e[E]; };
-    for (int j = lane * E; j < f.n; j += WAVE * E) {
+    const int j1 = min(f.n, j0 + FIN_SEG);
+#pragma unroll 2
+    for (int j = j0 + lane * E; j < j1; j += WAVE * E) {
         float v[E];
         const In a = *reinterpret_cast<const In*>(from + j);
 #pragma unroll
@@ -65,18 +72,19 @@ __device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int lane)
 // One workgroup of 256 threads; part: 32 bytes of LDS.
 template <typename T, int E>
 __device__ __forceinline__ void finish_dx(const FinishArgs& f, int block, void* part) {
-    const int groups = (f.rows + 3) / 4;
+    const int groups = (int)(((int64_t)f.rows * f.segs + 3) / 4);
     if (block >= groups) {
         if (block == groups && f.row_loss)
             loss_accumulate(f.row_loss, f.rows, f.hdr, f.loss, static_cast<double*>(part));
         return;
     }
-    const int i = block * 4 + (int)threadIdx.x / WAVE, lane = (int)threadIdx.x & (WAVE - 1);
+    const int u = block * 4 + (int)threadIdx.x / WAVE, lane = (int)threadIdx.x & (WAVE - 1);
+    const int i = u / f.segs, j0 = (u - i * f.segs) * FIN_SEG;
     if (i >= (f.live ? min(f.rows, *f.live) : f.rows)) return;
     if (f.src_f32) {
-        if (f.add) finish_row<T, float, true, E>(f, i, lane); else finish_row<T, float, false, E>(f, i, lane);
+        if (f.add) finish_row<T, float, true, E>(f, i, j0, lane); else finish_row<T, float, false, E>(f, i, j0, lane);
     } else {
-        if (f.add) finish_row<T, T, true, E>(f, i, lane); else finish_row<T, T, false, E>(f, i, lane);
+        if (f.add) finish_row<T, T, true, E>(f, i, j0, lane); else finish_row<T, T, false, E>(f, i, j0, lane);
     }
 }
 template <typename T, bool VEC4>
