@@ -291,14 +291,15 @@ int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int6
     // shape by row length, nontemporal accesses by size: see ce_rows_kernel
     const int64_t row_bytes = V * (int64_t)sizeof(T);
     const bool nt = rows * row_bytes > CE_CACHE_BYTES;
-#define CE_LAUNCH(TH, NV, NT)                                                                          \
-    hipLaunchKernelGGL((ce_rows_kernel<T, TH, NV, NT>), dim3((unsigned)rows), dim3(TH), 0, s, Z, ldz,  \
+#define CE_LAUNCH(TH, NV, NT, NL)                                                                      \
+    hipLaunchKernelGGL((ce_rows_kernel<T, TH, NV, NT, NL>), dim3((unsigned)rows), dim3(TH), 0, s, Z, ldz,  \
                        targets, (int)V, zero_pad, ignore_index, hdr, row_loss, n_rows, count_n, weight)
-#define CE_SHAPE(TH, NV) \
-    do { if (nt) CE_LAUNCH(TH, NV, true); else CE_LAUNCH(TH, NV, false); } while (0)
-    if (row_bytes > 112 * 1024) CE_SHAPE(RC_THREADS, RC_NV);
-    else if (row_bytes > 48 * 1024) CE_SHAPE(RM_THREADS, RM_NV);
-    else CE_SHAPE(RS_THREADS, RS_NV);
+#define CE_SHAPE(TH, NV, NL) \
+    do { if (nt) CE_LAUNCH(TH, NV, true, NL); else CE_LAUNCH(TH, NV, false, NL); } while (0)
+    if (row_bytes > 400 * 1024) CE_SHAPE(RC_THREADS, RC_NV, RC_NL);
+    else if (row_bytes > 112 * 1024) CE_SHAPE(RC_THREADS, RC_NV, 0);
+    else if (row_bytes > 48 * 1024) CE_SHAPE(RM_THREADS, RM_NV, 0);
+    else CE_SHAPE(RS_THREADS, RS_NV, 0);
 #undef CE_SHAPE
 #undef CE_LAUNCH
     HIP_TRY(hipGetLastError());

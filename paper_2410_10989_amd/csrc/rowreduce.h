@@ -165,6 +165,10 @@ __device__ __forceinline__ float row_lse(MaxSum a, const T* z, int64_t t, int ro
 // 1024 x 16 (256 KB) beyond, where 16 wavefronts keep the per-thread ALU phases short.  TB/s of
 // algorithmic traffic, kernel alone, 256 x 12 / 512 x 12 / 1024 x 16: 7.1 / 4.5 / 2.2 at 16 KB rows
 // (16384 of them), - / 7.2 / 4.9 at 64 KB (4096), - / 5.3 / 4.8 at 100 KB, - / - / 5.2 at 240 KB.
+// NL: that many more vectors per thread stay in LDS (9 x 1024: 144 KB; one such workgroup fits a CU by
+// its registers anyway).  Used beyond 400 KB rows, without / with, us: 5734 x 256000 bf16 1164 / 1085, 3328 x
+// 152064 fp32 843 / 775, 2048 x 204807 bf16 (400 KB) 320 / 313; at 297 KB rows 348 / 368, where the little
+// that is swept twice comes from cache.
 // NT (nontemporal accesses) where the logits exceed the 256 MB memory-side cache, ordinary / NT:
 // 8192 x 128256 bf16 803 / 717 us, 4096 x 122880 bf16 387 / 356, 4096 x 81920 fp32 525 / 419; below it
 // they would push out what the next product reads: 4096 x 32000 bf16 73 / 89.
@@ -172,6 +176,7 @@ __device__ __forceinline__ float row_lse(MaxSum a, const T* z, int64_t t, int ro
 // before, 155 / 150 (NT) now.
 constexpr int RC_THREADS = 1024;
 constexpr int RC_NV = 16;
+constexpr int RC_NL = 9;
 constexpr int RM_THREADS = 512;   // rows up to 112 KB
 constexpr int RM_NV = 12;
 constexpr int RS_THREADS = 256;   // rows up to 48 KB
@@ -214,7 +219,7 @@ constexpr int CE_COUNT_ROWS = 2048;
 
 // count_n > 0: `targets` holds the whole batch, count_n rows; workgroup 0 writes the header for the
 // launches that follow.  count_n = 0: the header holds the count.
-template <typename T, int THREADS, int NV, bool NT>
+template <typename T, int THREADS, int NV, bool NT, int NL = 0>
 __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
     T* __restrict__ Z, int64_t ldz, const int64_t* __restrict__ targets, int V, int zero_pad,
     int64_t ignore_index, DeviceHeader* __restrict__ hdr, float* __restrict__ row_loss,
@@ -239,6 +244,7 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
     __shared__ MaxSum part[THREADS / WAVE];
     __shared__ float s_lse;
     __shared__ int counts[THREADS / WAVE];
+    __shared__ u32x4 more[NL ? NL * THREADS : 1];   // the row's vectors beyond the registers
 
     if (tid < zero_pad) z[V + tid] = from_f32<T>(0.f);   // zero_pad < 64
     if (!valid) {                              // uniform per workgroup
@@ -279,7 +285,20 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
         // one vector at a time: interleaving several would spill the cached row
         __builtin_amdgcn_sched_barrier(0);
     }
-    for (int i = tid + NV * THREADS; i < nvec; i += THREADS) {   // beyond the cache
+    if constexpr (NL > 0) {   // (a thread reads back what it wrote itself: no barrier)
+#pragma unroll 3
+        for (int k = 0; k < NL; ++k) {
+            const int i = tid + (NV + k) * THREADS;
+            if (i < nvec) {
+                const u32x4 raw = row_load<NT>(zv + i);
+                more[k * THREADS + tid] = raw;
+                float f[VEC];
+                RowVec<T>::unpack(raw, f);
+                ms_push_vec<T, VEC>(a, f);
+            }
+        }
+    }
+    for (int i = tid + (NV + NL) * THREADS; i < nvec; i += THREADS) {   // beyond the cache
         float f[VEC];
         RowVec<T>::unpack(zv[i], f);
         ms_push_vec<T, VEC>(a, f);
@@ -299,7 +318,14 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
         if (i < nvec) row_store<NT>(zv + i, ce_gradient_vec<T>(keep[k], i, tcol, ex, inv_n));
         __builtin_amdgcn_sched_barrier(0);
     }
-    for (int i = tid + NV * THREADS; i < nvec; i += THREADS)
+    if constexpr (NL > 0) {
+#pragma unroll 3
+        for (int k = 0; k < NL; ++k) {
+            const int i = tid + (NV + k) * THREADS;
+            if (i < nvec) row_store<NT>(zv + i, ce_gradient_vec<T>(more[k * THREADS + tid], i, tcol, ex, inv_n));
+        }
+    }
+    for (int i = tid + (NV + NL) * THREADS; i < nvec; i += THREADS)
         row_store<NT>(zv + i, ce_gradient_vec<T>(zv[i], i, tcol, ex, inv_n));
     if (edge >= 0) z[edge] = ce_gradient_one<T>(z[edge], edge, (int)t, ex, inv_n);
 }

@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
     (24571, 24571, 5),                    # up to 48 / 96 KB
     (50257, 50257, 0),                    # 512-thread shape (bf16), 1024-thread shape (fp32)
     (57345, 57345, 3),                    # just past 112 KB of bf16
-    (131073, 131077, 7),                  # past what the registers hold (fp32)
+    (131073, 131077, 7),                  # past what the registers hold (fp32: and LDS)
+    (204801, 204801, 1),                  # just past 400 KB of bf16: registers and LDS
+    (262151, 262151, 2),                  # past both
 ])
 def test_rows_at_any_address(dtype, tol, V, ldz, offset):
     import paper_2410_10989_amd as flce
