@@ -307,7 +307,7 @@ def main():
     # rows that are actually projected: with row compaction (the default) only the rows that
     # have a target, summed over the heads
     all_targets = ts if nh > 1 else [t]
-    compaction = flce.flce_get_row_compaction() and w.dtype == "bf16" and w.H % 64 == 0
+    compaction = flce.flce_get_row_compaction() and w.H % (8 if w.dtype == "bf16" else 4) == 0
     rows_projected = sum(int((x != w.ignore_index).sum().item()) for x in all_targets) if compaction \
         else w.BT * nh
 
@@ -486,7 +486,7 @@ def main():
             est, _, _ = time_steps(step_i, 1, 2)
             n = int(min(200, max(bsteps, -(-300.0 // max(est, 1e-3)))))
             msi, _, _ = time_steps(step_i, max(2, n // 4), n)
-            comp_i = flce.flce_get_row_compaction() and wi.dtype == "bf16" and wi.H % 64 == 0
+            comp_i = flce.flce_get_row_compaction() and wi.H % (8 if wi.dtype == "bf16" else 4) == 0
             line = config_line(flce, wi, ci, msi, comp_i)
             if msi < 1.0:
                 # launch-bound: the same call recorded once into a HIP graph and replayed

@@ -255,21 +255,23 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
     if (fin && (!CAN_FIN || tile != 128)) return FLCE_ERR_SHAPE;   // (ride_along keeps such calls away)
     // Row-form operands, one 256-row tile: B is fetched once, and all of A stays in an XCD's L2 (4 MB)
     // at whatever K step its tiles are, so the tile columns can start their K loops at different steps
-    // (see ROT).  Measured, V = 128256, H = 4096: 16 rows 230 -> 175 us, 64 rows 240 -> 190, 200 rows 281 ->
+    // (FG_ROTATED).  Measured, V = 128256, H = 4096: 16 rows 230 -> 175 us, 64 rows 240 -> 190, 200 rows 281 ->
     // 250; 512 rows: no difference, and more rows keep the plain order (1 % slower with 4096), so
     // that the order of a row's sums does not depend on how a larger batch is cut into chunks.
-    constexpr bool CAN_ROT = !A_KM && !B_KM;
-    const bool rot = CAN_ROT && K % FG_BK == 0 && M <= FG_BM && M * K * (int64_t)sizeof(bf16_t) <= ROT_A_BYTES;
-#define FG_LAUNCH(TILE, ROT) \
-    hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, TILE, ROT>), grid, dim3(FG_THREADS), 0, s, a, NoFinish{})
+    constexpr bool ROWS = !A_KM && !B_KM;
+    constexpr int ROT = ROWS ? FG_ROTATED : FG_PLAIN, CUT = ROWS ? FG_K_TAIL : FG_PLAIN;
+    const bool tail = ROWS && K % FG_BK != 0;
+    const bool rot = ROWS && !tail && M <= FG_BM && M * K * (int64_t)sizeof(bf16_t) <= ROT_A_BYTES;
+#define FG_LAUNCH(TILE, ORDER) \
+    hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, TILE, ORDER>), grid, dim3(FG_THREADS), 0, s, a, NoFinish{})
     if (fin) {
         if constexpr (CAN_FIN)
-            hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, 128, false, FinishArgs>), grid, dim3(FG_THREADS), 0, s,
+            hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, 128, FG_PLAIN, FinishArgs>), grid, dim3(FG_THREADS), 0, s,
                                a, *fin);
     } else if (tile == 128) {
-        if (rot) FG_LAUNCH(128, CAN_ROT); else FG_LAUNCH(128, false);
+        if (rot) FG_LAUNCH(128, ROT); else if (tail) FG_LAUNCH(128, CUT); else FG_LAUNCH(128, FG_PLAIN);
     } else {
-        if (rot) FG_LAUNCH(256, CAN_ROT); else FG_LAUNCH(256, false);
+        if (rot) FG_LAUNCH(256, ROT); else if (tail) FG_LAUNCH(256, CUT); else FG_LAUNCH(256, FG_PLAIN);
     }
 #undef FG_LAUNCH
     HIP_TRY(hipGetLastError());
@@ -286,11 +288,11 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
 template <typename T>
 int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int64_t V,
                    int zero_pad, int64_t ignore_index, DeviceHeader* hdr, float* row_loss,
-                   hipStream_t s, const int* n_rows, bool timed, int count_n, float weight) {
+                   hipStream_t s, const int* n_rows, bool timed, int count_n, float weight, bool fused) {
     ScopedKernelTimer timer(timed ? FLCE_KIND_CE_ROWS : -1, s);
     // shape by row length, nontemporal accesses by size: see ce_rows_kernel
     const int64_t row_bytes = V * (int64_t)sizeof(T);
-    const bool nt = rows * row_bytes > CE_CACHE_BYTES;
+    const bool nt = !fused && rows * row_bytes > CE_CACHE_BYTES;
 #define CE_LAUNCH(TH, NV, NT, NL)                                                                      \
     hipLaunchKernelGGL((ce_rows_kernel<T, TH, NV, NT, NL>), dim3((unsigned)rows), dim3(TH), 0, s, Z, ldz,  \
                        targets, (int)V, zero_pad, ignore_index, hdr, row_loss, n_rows, count_n, weight)
@@ -488,7 +490,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
 
         // loss and in-place dlogits
         FLCE_TRY(launch_ce_rows<T>(Z, p.ldz, tc, rows, V, (int)(p.ldz - V), ignore_index, hdr,
-                                   row_loss, s, n_live, true, count_in_rows ? (int)BT : 0, weight));
+                                   row_loss, s, n_live, true, count_in_rows ? (int)BT : 0, weight, true));
         const LossOut loss_here = last ? loss_out : LossOut{};
 
         // dX_c (+)= G W: straight into dX, or into the chunk buffer when the rows still have to be
@@ -718,10 +720,10 @@ int run_ce_inplace(void* Z, const int64_t* targets, int64_t BT, int64_t V, int64
         const int64_t rows = (BT - r0 < step) ? BT - r0 : step;
         if (dtype == FLCE_F32)
             FLCE_TRY(launch_ce_rows<float>(static_cast<float*>(Z) + r0 * ldz, ldz, targets + r0,
-                                           rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f));
+                                           rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f, false));
         else
             FLCE_TRY(launch_ce_rows<bf16_t>(static_cast<bf16_t*>(Z) + r0 * ldz, ldz, targets + r0,
-                                            rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f));
+                                            rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f, false));
         FLCE_TRY(launch_loss(row_loss, rows, hdr,
                              r0 + rows == BT ? LossOut{hdr, 1, loss, nullptr, {1.0f}} : LossOut{}, timed, s));
     }

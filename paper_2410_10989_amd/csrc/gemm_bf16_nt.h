@@ -94,6 +94,11 @@ constexpr int fg_lds_bytes(int tile) { return FG_SLOTS * fg_slot_bytes(tile); } 
 constexpr int FG_GROUP_TILES = 4;
 constexpr int FG_XCDS = 8;
 
+// How a row-form operand's K loop runs (kernel variants: one more scalar instruction per step of the
+// plain loop costs the logits product 0.6 %): plain, for K % 64 == 0 or rows padded with zeros;
+// rotated (see gemm_bf16); with a last K step that K cuts.
+enum { FG_PLAIN = 0, FG_ROTATED = 1, FG_K_TAIL = 2 };
+
 struct FGArgs {
     const bf16_t* A;
     int64_t lda;
@@ -162,7 +167,7 @@ __device__ __forceinline__ void fg_load_lds(__amdgpu_buffer_rsrc_t rsrc, unsigne
 // One GEMM operand: where its tiles come from in global memory, where they land
 // in LDS, and how MFMA fragments (32 rows x 16 K, lane l = row l%32, K values
 // 8*(l/32) .. +7) are read back.  KM = false: row form, KM = true: column form.
-template <bool KM, int TILE, bool ROT = false>
+template <bool KM, int TILE, int ORDER = FG_PLAIN>
 struct FgOperand {
     static constexpr int NL = TILE / 32;   // loads a wavefront issues per tile
     static constexpr int W = TILE / 64;    // fragments per wavefront
@@ -174,11 +179,10 @@ struct FgOperand {
     int64_t bytes;                // bytes from base0 to the end of the operand's valid range
     __amdgpu_buffer_rsrc_t rsrc;
     int kt_base, seg_steps;
-    int kt_tail;  // row form: the K step that holds the last, partial group of 64 K values, if any
-    int kt_next;  // before_step has nothing to do before this K step
+    int kt_tail;  // FG_K_TAIL: the K step that holds the last, partial group of 64 K values, if any
     int off[NL];  // per-lane byte offset of each of the loads a wavefront issues per tile
     int kstep;    // bytes between consecutive K steps
-    int rot, wrap;   // ROT: the K steps are taken in the order rot, rot + 1, ..., wrap - 1, 0, 1, ...
+    int rot, wrap;   // FG_ROTATED: the K steps are taken in the order rot, rot + 1, ..., wrap - 1, 0, 1, ...
     int rd[4];    // per-lane LDS byte offsets of the fragment reads
 
     // base/ld: the matrix; r0: first row (row form) or column (column form) of this
@@ -229,7 +233,7 @@ struct FgOperand {
                 rd[i] = (8 * (g >> 1) + (s >> 2)) * (2 * TILE) + (((sub * W + i) ^ f) * 64) + 32 * (g & 1) +
                         8 * (s & 3);
         }
-        // A row-form operand whose K is not a multiple of 64: in the last K step, the lanes whose
+        // FG_K_TAIL, a row-form operand whose K is not a multiple of 64: in the last K step, the lanes whose
         // 16-byte piece lies past K fetch from beyond the descriptor, i.e. zero (a piece that K
         // cuts has to hold zeros past it: none when K % 8 == 0).
         kt_tail = (!KM && (K & (FG_BK - 1))) ? K / FG_BK : 0x7fffffff;
@@ -249,31 +253,27 @@ struct FgOperand {
         kt_base = 0;
         seg_steps = max(1, (1 << 30) / kstep);
         if (kt_tail != 0x7fffffff) kt_tail -= k_begin;
-        kt_next = min(seg_steps, kt_tail);
         make_rsrc();
     }
     // call before the first load of K step kt (kt never decreases)
     __device__ __forceinline__ void before_step(int kt) {
-        if (kt >= kt_next) {   // uniform, rarely taken
-            if (kt - kt_base >= seg_steps) {
-                base0 += (int64_t)seg_steps * kstep;
-                bytes -= (int64_t)seg_steps * kstep;
-                kt_base += seg_steps;
-                make_rsrc();
-            }
-            if constexpr (!KM) {
-                if (kt >= kt_tail) {   // (a row-form tile's extent is below 2^30 bytes)
+        if (kt - kt_base >= seg_steps) {
+            base0 += (int64_t)seg_steps * kstep;
+            bytes -= (int64_t)seg_steps * kstep;
+            kt_base += seg_steps;
+            make_rsrc();
+        }
+        if constexpr (!KM && ORDER == FG_K_TAIL) {
+            if (kt >= kt_tail) {   // uniform, once (a row-form tile's extent is below 2^30 bytes)
 #pragma unroll
-                    for (int r = 0; r < NL; ++r) off[r] = piece_past ? 0x7fffffff : off[r];
-                    kt_tail = 0x7fffffff;
-                }
+                for (int r = 0; r < NL; ++r) off[r] = piece_past ? 0x7fffffff : off[r];
+                kt_tail = 0x7fffffff;
             }
-            kt_next = min(kt_base + seg_steps, kt_tail);
         }
     }
 
     __device__ __forceinline__ int step_offset(int kt) const {
-        if constexpr (ROT) {
+        if constexpr (ORDER == FG_ROTATED) {
             kt += rot;
             kt -= kt >= wrap ? wrap : 0;
         }
@@ -305,13 +305,13 @@ template <> struct FgRaw<true> { s16x4 lo, hi; };
 
 // Issue the LDS read(s) of fragment I (32-row block) of K sub-step KK; `slot_addr`
 // is the LDS byte address of the ring slot.
-template <int KK, int I, int TILE, bool ROT>
-__device__ __forceinline__ void fg_issue(FgRaw<false>& r, const FgOperand<false, TILE, ROT>& op, unsigned slot_addr) {
+template <int KK, int I, int TILE, int ORDER>
+__device__ __forceinline__ void fg_issue(FgRaw<false>& r, const FgOperand<false, TILE, ORDER>& op, unsigned slot_addr) {
     const unsigned addr = slot_addr + (unsigned)op.rd[KK];
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r.v) : "v"(addr), "n"(I * 4096));
 }
-template <int KK, int I, int TILE, bool ROT>
-__device__ __forceinline__ void fg_issue(FgRaw<true>& r, const FgOperand<true, TILE, ROT>& op, unsigned slot_addr) {
+template <int KK, int I, int TILE, int ORDER>
+__device__ __forceinline__ void fg_issue(FgRaw<true>& r, const FgOperand<true, TILE, ORDER>& op, unsigned slot_addr) {
     const unsigned addr = slot_addr + (unsigned)op.rd[I];
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.lo) : "v"(addr), "n"(KK * 32 * TILE));
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.hi) : "v"(addr), "n"(KK * 32 * TILE + 8 * TILE));
@@ -564,13 +564,13 @@ __device__ __forceinline__ void fg_tile_origin(int seq, int tiles_m, int tiles_n
 // waits; its LDS reads (as many per K step for a quarter of the arithmetic) are as tight as the
 // matrix pipe.
 //
-// ROT: every 256 columns start their K loop at another K step and wrap around.  For a row-form
+// FG_ROTATED: every 256 columns start their K loop at another K step and wrap around.  For a row-form
 // B that is fetched once (few rows in A) from memory whose rows lie a power of two apart (H = 4096:
 // 8 KB), where all tiles at the same K step would ask the same few memory channels at a time.
 // A K % 64 == 0 operand pair without K ranges only.
 // FIN: the first fin.blocks workgroups finish the chunk's dX (see finish_dx_kernel) instead.
 struct NoFinish {};
-template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE, bool ROT = false, typename Fin = NoFinish>
+template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE, int ORDER = FG_PLAIN, typename Fin = NoFinish>
 __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGArgs a, Fin fin) {
     constexpr bool HAS_IN = !std::is_void<InT>::value;
     constexpr int IS = FgInSize<InT>::value;
@@ -621,8 +621,8 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
     int m0, n0;
     fg_tile_origin<TILE>(seq_all - split * tiles, tiles_m, a.tiles_n, a.group_m, a.group_cols, m0, n0);
 
-    FgOperand<A_KM, TILE, ROT> opa;
-    FgOperand<B_KM, TILE, ROT> opb;
+    FgOperand<A_KM, TILE, ORDER> opa;
+    FgOperand<B_KM, TILE, ORDER> opb;
     opa.init(a.A, a.lda, m0, M, K, tid, wm);
     opb.init(a.B, a.ldb, n0, a.N, K, tid, wn);
     const int uwave = __builtin_amdgcn_readfirstlane(wave);
@@ -738,7 +738,7 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
     const int nk = (int)((int64_t)steps_all * (kr_i + 1) / kr_n) - k_begin;
     opa.start_at(k_begin);
     opb.start_at(k_begin);
-    if constexpr (ROT) {
+    if constexpr (ORDER == FG_ROTATED) {
         opa.rot = opb.rot = (n0 / FG_BN) % nk;   // (the same order of K whatever the tile size)
         opa.wrap = opb.wrap = nk;
     }

@@ -171,7 +171,9 @@ __device__ __forceinline__ float row_lse(MaxSum a, const T* z, int64_t t, int ro
 // that is swept twice comes from cache.
 // NT (nontemporal accesses) where the logits exceed the 256 MB memory-side cache, ordinary / NT:
 // 8192 x 128256 bf16 803 / 717 us, 4096 x 122880 bf16 387 / 356, 4096 x 81920 fp32 525 / 419; below it
-// they would push out what the next product reads: 4096 x 32000 bf16 73 / 89.
+// they would push out what the next product reads: 4096 x 32000 bf16 73 / 89.  Only for logits that
+// another program made: right behind the logits product, which leaves its last output in the
+// caches, they cost more than they save (8192 x 128256: 790 / 850 us).
 // Rows of 50257 bf16 at odd addresses (4096 of them): 451 us with 2-byte accesses in two sweeps
 // before, 155 / 150 (NT) now.
 constexpr int RC_THREADS = 1024;
