@@ -42,7 +42,9 @@
  *    synchronising.  Argument errors are found on the host before anything is
  *    launched.  Functions return an flce_status and never throw or abort.
  *  - Scratch memory ("workspace") lives on the device.  Either the caller
- *    lends a buffer with flce_set_workspace, or the library allocates one per
+ *    lends a buffer with flce_set_workspace (flce_workspace_bytes long; a smaller
+ *    one still serves if it holds the plan without the finer cut of a small dX
+ *    product along K), or the library allocates one per
  *    device on first use and keeps it (growing it if a later call needs more;
  *    growing synchronises the device).  Calls that overlap in time on the same
  *    device share the workspace and therefore race: serialise them on one
@@ -162,7 +164,8 @@ FLCE_API size_t flce_workspace_bytes_opt(int64_t BT, int64_t H, int64_t V, int d
  * that of a single head.  dX is summed in its storage type: head 0 writes it,
  * every later head's rows are added to the stored rows in fp32 and rounded (with
  * row compaction, see flce_set_row_compaction, the head's rows are themselves
- * rounded once before that addition).
+ * rounded once before that addition, unless the head's dX product is cut along K:
+ * then its fp32 sums are added).
  *
  *   W, targets, dW   HOST arrays of n_heads DEVICE pointers ([V x H] dtype,
  *                    [BT] int64, [V x H] dtype); read before the call returns.
@@ -271,10 +274,11 @@ FLCE_API size_t flce_get_logits_budget_bytes(void);
  * terms in other groups); the time of a chunk shrinks with its share of ignored
  * rows, in steps of the 256-row tiles.  The valid rows are dealt evenly to as few
  * of the chunk launches as can hold them (the last ones); launches before them do
- * no work, so a batch with many ignored rows runs fewer chunks.  Only problems that run entirely on the
- * tuned kernel are compacted.  Off: every row is projected; for batches known to
- * have no ignored row that saves the gather and scatter copies (about 0.5 % of
- * the time at V = 128K, 1 % at V = 32K). */
+ * no work, so a batch with many ignored rows runs fewer chunks.  Compacted are
+ * problems whose rows are whole 16-byte vectors (bf16: H % 8 == 0, fp32: H % 4 == 0).
+ * Off: every row is projected; for batches known to have no ignored row that saves
+ * the gather and scatter copies (about 0.5 % of the time at V = 128K, 1 % at
+ * V = 32K). */
 FLCE_API int flce_set_row_compaction(int on);
 FLCE_API int flce_get_row_compaction(void);
 
@@ -319,7 +323,7 @@ typedef enum {
     FLCE_KIND_CE_ROWS = 1,     /* loss + in-place dlogits             */
     FLCE_KIND_DX_GEMM = 2,     /* dX_c = G_c W                        */
     FLCE_KIND_DW_GEMM = 3,     /* dW += G_c^T X_c                     */
-    FLCE_KIND_OTHER = 4,       /* count, transposes, casts, finalize  */
+    FLCE_KIND_OTHER = 4,       /* row selection, copies, RMSNorm       */
     FLCE_NUM_KINDS = 5
 } flce_kernel_kind;
 FLCE_API int flce_timing_enable(int on);

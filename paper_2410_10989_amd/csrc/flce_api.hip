@@ -365,6 +365,9 @@ int rmsnorm_vectors_per_thread(int64_t H, const void* x, const void* gamma, cons
     return nvec <= RN_THREADS ? 1 : nvec <= 2 * RN_THREADS ? 2 : nvec <= 4 * RN_THREADS ? 4 : 0;
 }
 
+// Partial rows of dgamma that a chunk of C rows can reach.
+inline unsigned rn_slots(int64_t C) { return (unsigned)std::min<int64_t>(C, RN_SLOTS); }
+
 // One head: count its valid rows, then run the chunk loop.  Gradients are scaled by
 // weight / N_valid.  With dx_add the head's dX is added to what dX already holds
 // (rounded to the storage type once per head), otherwise dX is overwritten.  loss_out: where the
@@ -600,7 +603,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
             const RnLoss rn_loss{row_loss, (int)rows, hdr, loss_here};
 #define RN_BWD(KERNEL)                                                                              \
-    hipLaunchKernelGGL((KERNEL), dim3(RN_SLOTS + 1), dim3(RN_THREADS), 0, s, Xin, norm->gamma,       \
+    hipLaunchKernelGGL((KERNEL), dim3(rn_slots(p.C) + 1), dim3(RN_THREADS), 0, s, Xin, norm->gamma,  \
                        norm->rstd, dXg, (int)rows, (int)H, p.compact ? norm->dh : norm->dh + r0 * H, \
                        norm->partial, row_map, n_live, c == 0 ? 1 : 0, rn_loss)
             switch (rmsnorm_vectors_per_thread<T>(H, Xin, norm->gamma, norm->dh)) {
@@ -687,7 +690,7 @@ int run_rmsnorm_head(const T* h, const T* gamma, float eps, const T* W, const in
                          false, nullptr, dW, flags, p, ws, s, &n));
     if (want_dx) {
         hipLaunchKernelGGL((rmsnorm_dgamma_kernel<T>), dim3((unsigned)((H + RN_DG_COLS - 1) / RN_DG_COLS)),
-                           dim3(RN_DG_COLS * RN_DG_PARTS), 0, s, n.partial, (int)H, dgamma);
+                           dim3(RN_DG_COLS * RN_DG_PARTS), 0, s, n.partial, (int)rn_slots(p.C), (int)H, dgamma);
         HIP_TRY(hipGetLastError());
     }
     return FLCE_OK;

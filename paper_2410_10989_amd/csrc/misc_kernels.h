@@ -11,7 +11,7 @@ namespace flce {
 // when only the device knows it), or with nsplit = 1 the product's rows in the storage type.
 // With ADD the row is added to what out holds (dX summed over heads).  One wavefront per segment, 4
 // elements per lane and access with VEC4 (n, split_stride and the pointers are multiples of 4).
-// The workgroup past the rows sums the chunk's losses (row_loss not null).
+// The first workgroup sums the chunk's losses (row_loss not null).
 // Latency bound at small sizes: one launch where the sum over K ranges, the scatter, the loss sum
 // and its finalisation were four of 4-5 us each; in front of a dW product on small tiles its
 // workgroups ride along with that launch instead (nothing in it waits for the other).
@@ -72,17 +72,18 @@ __device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int j0, i
 // One workgroup of 256 threads; part: 32 bytes of LDS.
 template <typename T, int E>
 __device__ __forceinline__ void finish_dx(const FinishArgs& f, int block, void* part) {
-    const int groups = (int)(((int64_t)f.rows * f.segs + 3) / 4);
-    if (block >= groups) {
-        if (block == groups && f.row_loss)
-            loss_accumulate(f.row_loss, f.rows, f.hdr, f.loss, static_cast<double*>(part));
+    if (block == 0) {   // (first: it takes longer than a few rows do)
+        if (f.row_loss) loss_accumulate(f.row_loss, f.rows, f.hdr, f.loss, static_cast<double*>(part));
         return;
     }
-    const int u = block * 4 + (int)threadIdx.x / WAVE, lane = (int)threadIdx.x & (WAVE - 1);
+    const int u = (block - 1) * 4 + (int)threadIdx.x / WAVE, lane = (int)threadIdx.x & (WAVE - 1);
     const int i = u / f.segs, j0 = (u - i * f.segs) * FIN_SEG;
     if (i >= (f.live ? min(f.rows, *f.live) : f.rows)) return;
     if (f.src_f32) {
         if (f.add) finish_row<T, float, true, E>(f, i, j0, lane); else finish_row<T, float, false, E>(f, i, j0, lane);
+    } else if (E == 4 && sizeof(T) == 2 && f.n % 8 == 0) {   // whole rows in the storage type: 16 bytes per lane
+        constexpr int E8 = E == 4 ? 8 : E;                   // (dX and the workspace are 16-byte aligned)
+        if (f.add) finish_row<T, T, true, E8>(f, i, j0, lane); else finish_row<T, T, false, E8>(f, i, j0, lane);
     } else {
         if (f.add) finish_row<T, T, true, E>(f, i, j0, lane); else finish_row<T, T, false, E>(f, i, j0, lane);
     }

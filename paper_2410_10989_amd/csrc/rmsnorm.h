@@ -62,7 +62,7 @@ __global__ __launch_bounds__(RN_THREADS) void rmsnorm_fwd_kernel(const T* __rest
         y[obase + j] = from_f32<T>(to_f32(x[base + j]) * r * to_f32(gamma[j]));
 }
 
-// The workgroup past the RN_SLOTS of a backward launch sums the chunk's losses (see loss_accumulate).
+// The last workgroup of a backward launch sums the chunk's losses (see loss_accumulate).
 struct RnLoss {
     const float* row_loss;
     int rows;
@@ -70,7 +70,7 @@ struct RnLoss {
     LossOut out;
 };
 __device__ __forceinline__ bool rn_loss_block(const RnLoss& l) {
-    if (blockIdx.x < RN_SLOTS) return false;
+    if (blockIdx.x + 1 < gridDim.x) return false;
     __shared__ double part[4];
     loss_accumulate(l.row_loss, l.rows, l.hdr, l.out, part);
     return true;
@@ -222,22 +222,27 @@ __global__ __launch_bounds__(RN_THREADS) void rmsnorm_bwd_vec_kernel(
     }
 }
 
-// dgamma[j] = sum_p partial[p][j].  A workgroup of 64 x 4 threads owns 64 columns: thread
-// (c, q) adds rows q, q + 4, ... of column c in order, then the four sums are added in
-// the order q = 0, 1, 2, 3: a fixed order, and 4 n / 256 workgroups instead of n / 256.
-constexpr int RN_DG_COLS = 64, RN_DG_PARTS = 4;
+// dgamma[j] = sum_p partial[p][j] over the slots that exist.  A workgroup of 64 x 16 threads owns 64
+// columns: thread (c, q) adds rows q, q + 16, ... of column c in order, then the 16 sums are added in
+// the order q = 0, 1, ...: a fixed order.  Bound by the latency of a thread's loads (n / 64
+// workgroups): n = 2304, 512 slots: 4 parts 35 us, 16 parts 5.
+constexpr int RN_DG_COLS = 64, RN_DG_PARTS = 16;
 template <typename T>
 __global__ __launch_bounds__(RN_DG_COLS * RN_DG_PARTS) void rmsnorm_dgamma_kernel(
-    const float* __restrict__ partial, int n, T* __restrict__ dgamma) {
+    const float* __restrict__ partial, int slots, int n, T* __restrict__ dgamma) {
     __shared__ float sums[RN_DG_PARTS][RN_DG_COLS];
     const int c = threadIdx.x % RN_DG_COLS, q = threadIdx.x / RN_DG_COLS;
     const int j = blockIdx.x * RN_DG_COLS + c;
     float s = 0.f;
     if (j < n)
-        for (int p = q; p < RN_SLOTS; p += RN_DG_PARTS) s += partial[(int64_t)p * n + j];
+#pragma unroll 8
+        for (int p = q; p < slots; p += RN_DG_PARTS) s += partial[(int64_t)p * n + j];
     sums[q][c] = s;
     __syncthreads();
-    if (q == 0 && j < n) dgamma[j] = from_f32<T>(((sums[0][c] + sums[1][c]) + sums[2][c]) + sums[3][c]);
+    if (q == 0 && j < n) {
+        for (int k = 1; k < RN_DG_PARTS; ++k) s += sums[k][c];
+        dgamma[j] = from_f32<T>(s);
+    }
 }
 
 }  // namespace flce
