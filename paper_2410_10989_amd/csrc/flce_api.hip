@@ -392,7 +392,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
 
     const bool select = p.compact && BT <= SEL_MAX_ROWS;   // one launch per chunk finds its rows
     const bool norm_in_select = select && norm && aligned(norm->gamma, 16);
-    const bool count_in_rows = !p.compact && p.nchunks == 1 && BT <= CE_COUNT_ROWS;
+    const bool count_in_rows = !p.compact && p.nchunks == 1 && BT <= ce_count_rows(V * (int64_t)sizeof(T));
     T* zero_out = (want_dx && !dx_add) ? (norm ? norm->dh : dX) : nullptr;   // rows without a target: zero gradient
     if (!select && !count_in_rows) {
         hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
@@ -713,7 +713,7 @@ int check_ce_args(const void* Z, const int64_t* targets, int64_t BT, int64_t V, 
 int run_ce_inplace(void* Z, const int64_t* targets, int64_t BT, int64_t V, int64_t ldz,
                    int64_t ignore_index, int dtype, float* loss, DeviceHeader* hdr, float* row_loss,
                    int64_t step, bool timed, hipStream_t s) {
-    const int count_n = BT <= CE_COUNT_ROWS && BT <= step ? (int)BT : 0;
+    const int count_n = BT <= ce_count_rows(V * (int64_t)elem_size(dtype)) && BT <= step ? (int)BT : 0;
     if (!count_n) {
         hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
                            1.0f, hdr);

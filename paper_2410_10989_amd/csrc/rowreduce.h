@@ -214,10 +214,13 @@ __device__ __forceinline__ void write_header(DeviceHeader* hdr, int n_valid, flo
     hdr->inv_n = n_valid > 0 ? weight / (float)n_valid : 0.f;
     hdr->loss_sum = 0.0;
 }
-// A batch of at most this many rows is counted by every workgroup of the row kernel itself (the
-// targets are 16 KB from L2, fetched behind the row's own loads) instead of by a launch of its own
-// in front of it, which takes 4-5 us whatever it does.
-constexpr int CE_COUNT_ROWS = 2048;
+// A batch of at most this many rows is counted by every workgroup of the row kernel itself (about 1
+// us per row and workgroup slot, from L2) instead of by a launch of its own in front of it, which
+// takes 4-5 us whatever it does: as many rows as run in two rounds of the CUs in the row length's
+// shape (1, 2 or 3 and more workgroups per CU).
+inline int64_t ce_count_rows(int64_t row_bytes) {
+    return row_bytes > 112 * 1024 ? 512 : row_bytes > 48 * 1024 ? 1024 : 1536;
+}
 
 // count_n > 0: `targets` holds the whole batch, count_n rows; workgroup 0 writes the header for the
 // launches that follow.  count_n = 0: the header holds the count.
@@ -267,14 +270,6 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
         const int i = tid + k * THREADS;
         if (i < nvec) keep[k] = row_load<NT>(zv + i);
     }
-    float inv_n;
-    if (count_n > 0) {
-        const int n = count_rows<THREADS>(targets, count_n, ignore_index, counts);
-        inv_n = weight / (float)n;   // this row is valid: n > 0
-        if (row == 0 && tid == 0) write_header(hdr, n, weight);
-    } else {
-        inv_n = hdr->inv_n;
-    }
     MaxSum a = {-INFINITY, 0.f};
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -306,6 +301,14 @@ __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
         ms_push_vec<T, VEC>(a, f);
     }
     if (edge >= 0) ms_push<T>(a, to_f32(z[edge]));
+    float inv_n;   // (not in front of the sweep: that would wait for the whole row first)
+    if (count_n > 0) {
+        const int n = count_rows<THREADS>(targets, count_n, ignore_index, counts);
+        inv_n = weight / (float)n;   // this row is valid: n > 0
+        if (row == 0 && tid == 0) write_header(hdr, n, weight);
+    } else {
+        inv_n = hdr->inv_n;
+    }
     const float lse = row_lse<T, THREADS / WAVE>(a, z, t, row, row_loss, part, &s_lse);
 
     const RowExp<T> ex(lse);
