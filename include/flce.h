@@ -162,10 +162,11 @@ FLCE_API size_t flce_workspace_bytes_opt(int64_t BT, int64_t H, int64_t V, int d
  * None of the heads' logits is stored whole: the heads run one after the other
  * through the same chunk loop and the same workspace, so peak extra memory is
  * that of a single head.  dX is summed in its storage type: head 0 writes it,
- * every later head's rows are added to the stored rows in fp32 and rounded (with
- * row compaction, see flce_set_row_compaction, the head's rows are themselves
- * rounded once before that addition, unless the head's dX product is cut along K:
- * then its fp32 sums are added).
+ * every later head's rows are added to the stored rows in fp32 and rounded once.
+ * The exception: with row compaction (see flce_set_row_compaction), bf16 storage
+ * and H % 64 == 0, a later head's rows are themselves rounded once before that
+ * addition, unless the head's dX product is cut along K.  (For other H such heads
+ * run without compaction.)
  *
  *   W, targets, dW   HOST arrays of n_heads DEVICE pointers ([V x H] dtype,
  *                    [BT] int64, [V x H] dtype); read before the call returns.

@@ -390,16 +390,23 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
     float* tail = reinterpret_cast<float*>(ws + p.off_tail);   // partial blocks of the dW product's last round
     constexpr int VEC = 16 / (int)sizeof(T);
 
-    const bool select = p.compact && BT <= SEL_MAX_ROWS;   // one launch per chunk finds its rows
+    // A head whose dX is added to the heads before it: the product's epilogue adds its fp32 sums, rounded
+    // once, but only when the rows of the chunk are rows of dX; rows that are staged and scattered are
+    // rounded to the storage type first, unless K ranges hold them as fp32 sums.  bf16 with H % 64 != 0
+    // keeps the single rounding and projects the ignored rows instead (3 heads of 16384 x 200 x 4000, 10 %
+    // ignored: 816 us either way, error of dX against 64 bits 2.6e-3 with it, 2.95e-3 staged).
+    const bool adds_in_epilogue = BF16 && want_dx && dx_add && !norm && p.dx_ranges == 1 && H % 64 != 0;
+    const bool compact = p.compact && !adds_in_epilogue;
+    const bool select = compact && BT <= SEL_MAX_ROWS;   // one launch per chunk finds its rows
     const bool norm_in_select = select && norm && aligned(norm->gamma, 16);
-    const bool count_in_rows = !p.compact && p.nchunks == 1 && BT <= ce_count_rows(V * (int64_t)sizeof(T));
+    const bool count_in_rows = !compact && p.nchunks == 1 && BT <= ce_count_rows(V * (int64_t)sizeof(T));
     T* zero_out = (want_dx && !dx_add) ? (norm ? norm->dh : dX) : nullptr;   // rows without a target: zero gradient
     if (!select && !count_in_rows) {
         hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
                            weight, hdr);
         HIP_TRY(hipGetLastError());
     }
-    if (p.compact && !select && zero_out) {
+    if (compact && !select && zero_out) {
         ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
         hipLaunchKernelGGL((zero_ignored_rows_kernel<T>), dim3((unsigned)(BT < 8192 ? BT : 8192)),
                            dim3(256), 0, s, targets, BT, ignore_index, (int)H, zero_out);
@@ -414,14 +421,14 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         // compact_chunk_kernel); Xc, Z and dXc hold *n_live rows (a device value), the launches
         // below are sized for C rows, and idx maps the chunk's rows to batch rows.  Otherwise
         // the chunk is rows r0 .. r0 + rows - 1 of the batch.
-        const int64_t rows = p.compact ? p.C : ((BT - r0 < p.C) ? BT - r0 : p.C);
-        const int* n_live = p.compact ? dyn + DYN_LIVE : nullptr;
-        const int* row_map = p.compact ? idx : nullptr;
-        const T* Xin = p.compact ? X : X + r0 * H;   // what the chunk's row indices refer to
+        const int64_t rows = compact ? p.C : ((BT - r0 < p.C) ? BT - r0 : p.C);
+        const int* n_live = compact ? dyn + DYN_LIVE : nullptr;
+        const int* row_map = compact ? idx : nullptr;
+        const T* Xin = compact ? X : X + r0 * H;   // what the chunk's row indices refer to
         const T* Xc = Xin;
         const int64_t* tc = targets + r0;
         FastDyn dyn_m, dyn_dx, dyn_dw;   // logits (M = live rows), dX (M and K ranges), dW (K = live rows)
-        if (p.compact) {
+        if (compact) {
             ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
             const int dx_tiles_n = (int)((H + FG_BN - 1) / FG_BN), dx_ksteps = (int)((V + FG_BK - 1) / FG_BK);
             if (select) {
@@ -461,10 +468,10 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
 #undef RN_FWD
             HIP_TRY(hipGetLastError());
             Xc = Xg;
-        } else if (p.compact) {
+        } else if (compact) {
             Xc = Xg;
         }
-        if (p.compact && !norm && !select) {
+        if (compact && !norm && !select) {
             ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
             hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)rows), dim3(256), 0, s,
                                reinterpret_cast<const u32x4*>(X), idx, n_live, (int)(H / VEC),
@@ -502,8 +509,8 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         FinishArgs fin{};
         bool finish = false;
         if (want_dx) {
-            const bool staged = p.compact || norm;
-            const bool scatter = p.compact && !norm;
+            const bool staged = compact || norm;
+            const bool scatter = compact && !norm;
             T* dXc = staged ? dXg : dX + r0 * H;
             const bool add_in_gemm = dx_add && !staged;
             if (p.dx_ranges > 1) {
@@ -604,7 +611,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             const RnLoss rn_loss{row_loss, (int)rows, hdr, loss_here};
 #define RN_BWD(KERNEL)                                                                              \
     hipLaunchKernelGGL((KERNEL), dim3(rn_slots(p.C) + 1), dim3(RN_THREADS), 0, s, Xin, norm->gamma,  \
-                       norm->rstd, dXg, (int)rows, (int)H, p.compact ? norm->dh : norm->dh + r0 * H, \
+                       norm->rstd, dXg, (int)rows, (int)H, compact ? norm->dh : norm->dh + r0 * H, \
                        norm->partial, row_map, n_live, c == 0 ? 1 : 0, rn_loss)
             switch (rmsnorm_vectors_per_thread<T>(H, Xin, norm->gamma, norm->dh)) {
                 case 1: RN_BWD((rmsnorm_bwd_vec_kernel<T, 1>)); break;

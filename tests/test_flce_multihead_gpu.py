@@ -123,3 +123,20 @@ def test_weights_scale_each_head():
     assert (to_host(dWs[1]) == 0).all()
     assert_close("dX", to_host(dX), ref0.dX, TOL["f32"][1])
     assert_close("dW[0]", to_host(dWs[0]), ref0.dW, TOL["f32"][1])
+
+
+@pytest.mark.parametrize("BT,H,V", [(300, 136, 1000), (1500, 72, 700), (16384, 200, 4000)])   # dX not cut along K
+def test_later_heads_add_their_fp32_sums(BT, H, V):
+    # bf16, H % 64 != 0: every head's dX is added to the heads before it in fp32 and rounded once.  The
+    # same bits as without row compaction, where the product's epilogue adds; rows that were rounded on
+    # the way to the addition differ from these in about every other element.
+    import paper_2410_10989_amd as flce
+    assert flce.flce_dx_k_ranges(BT, H, V, flce.FLCE_BF16) == 1
+    m = workloads.make_multihead(3, BT, H, V, 100, "bf16", ignore=("iid", 0.15), seed=BT)
+    on = run_heads(m)
+    try:
+        flce.flce_set_row_compaction(False)
+        off = run_heads(m)
+    finally:
+        flce.flce_set_row_compaction(True)
+    assert torch.equal(on[2].view(torch.int16), off[2].view(torch.int16))
