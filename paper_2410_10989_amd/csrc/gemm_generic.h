@@ -5,15 +5,22 @@
 // memory.  It serves the fp32 storage type and the bf16 shapes the tuned kernel does not take.
 //
 // fp32 on the bf16 matrix cores.  v_mfma_f32_32x32x2_f32 runs at 1/16 of the bf16 rate, so an
-// fp32 operand is split, while it is staged, into three bf16 planes x = hi + mid + lo (each the
-// rounded remainder of the planes before: 8 + 8 + 8 bits and the signs hold all 24 bits), and
+// fp32 operand is split, while it is staged, into three bf16 planes 2^24 x = hi + mid + lo (each
+// the rounded remainder of the planes before: 8 + 8 + 8 bits and the signs hold all 24 bits), and
 // the six plane products that matter (lo*hi, mid*mid, hi*lo, mid*hi, hi*mid, hi*hi; the other
 // three are below 2^-26 of the product) are accumulated in fp32.  A product of two bf16 is exact
 // in fp32, and six 16-wide matrix instructions round the accumulator 6 times per 16 K where the
 // fp32 instruction rounds it 8 times.
-// An infinite or NaN operand (or one that rounds to infinity in bf16) makes the split remainders
-// NaN; a workgroup that finds a NaN among its sums computes its tile again with fp32 matrix
-// instructions, so such inputs give what plain fp32 products give.
+// The factor 2^24 (taken back as 2^-48 when the sums are written; both exact) is there because
+// bf16 has the exponents of fp32: without it lo is subnormal and loses bits below |x| = 2^-103,
+// mid below 2^-111, with it every plane of every fp32 value, subnormal ones too, is zero or a
+// normal bf16.  It costs 2 lane operations of 13 per pair of elements: 2048 x 1024 x 50257 2836 ->
+// 2930 us, 4096 x 4096 x 32000 13.25 -> 13.74 ms, 256 x 512 x 4096 53.8 -> 55.3 (with the factor as a
+// literal 56.5: such short launches wait for their instructions).
+// Where that leaves the range of the type (|x| >= 2^104, infinite or NaN operands, sums of 2^80
+// and more) the split remainders or the sums are infinite or NaN; a workgroup that finds one among
+// its sums computes its tile again with fp32 matrix instructions, so such inputs give what plain
+// fp32 products give.
 //
 // Shape: 256 threads = 4 wavefronts (2 x 2); macro tile TILE x TILE, TILE = 128 (each wavefront
 // owns 2 x 2 32 x 32 MFMA tiles; K step 16) or 64 (one MFMA tile in two accumulators, so that the
@@ -33,6 +40,9 @@ namespace flce {
 constexpr int gg_threads(int tile) { return tile == 256 ? 512 : 256; }
 constexpr int gg_bk(int tile) { return tile == 64 ? 32 : 16; }      // K elements per step
 constexpr int gg_depth(int tile) { return tile == 64 ? 4 : 2; } // K steps whose loads are in flight
+
+constexpr float GG_SCALE = 16777216.f;                            // 2^24, on both operands of an fp32 product
+constexpr float GG_UNSCALE = 1.f / (GG_SCALE * GG_SCALE);         // 2^-48
 
 // LDS holds the rows of K piece p permuted by XOR with this, so that the 8 or 16 neighbouring lanes
 // of a row-form write (2 or 4 pieces of 4 consecutive rows) touch all banks once.
@@ -129,13 +139,15 @@ struct GGStage {
     template <int D>
     __device__ __forceinline__ void store(unsigned char* lds) const {
         u32x4 out[PLANES];
+        float scale = GG_SCALE;
+        asm("" : "+s"(scale));   // in a register: as a literal it doubles the code of 16 operations per step
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if constexpr (PLANES == 1) {
                 const bf16x2 p = {raw[D][2 * q], raw[D][2 * q + 1]};
                 out[0][q] = __builtin_bit_cast(uint32_t, p);
             } else {
-                float a = raw[D][2 * q], b = raw[D][2 * q + 1];
+                float a = raw[D][2 * q] * scale, b = raw[D][2 * q + 1] * scale;
 #pragma unroll
                 for (int p = 0; p < PLANES; ++p) {
                     uint32_t u;   // both rounded to nearest even
@@ -345,7 +357,7 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
     // the B fragment is the MFMA's first operand: accumulator register g of lane l holds row
     // l % 32, column 8*(g/4) + 4*(l/32) + g%4 of its 32 x 32 tile
     OutT* C = static_cast<OutT*>(a.C) + (int64_t)split * a.split_stride;
-    auto write = [&](const f32x16 (&sum)[WM][WN]) {
+    auto write = [&](const f32x16 (&sum)[WM][WN], float scale) {
 #pragma unroll
         for (int i = 0; i < WM; ++i) {
             const int row = m0 + (wm * WM + i) * 32 + frow;
@@ -361,7 +373,7 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
                     const int col = n0 + (wn * WN + j) * 32 + 8 * g4 + 4 * fhalf;
                     float v[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = sum[i][j][4 * g4 + e];
+                    for (int e = 0; e < 4; ++e) v[e] = sum[i][j][4 * g4 + e] * scale;
                     if (rs.use_in) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
@@ -383,7 +395,7 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
         }
     };
     if constexpr (PLANES == 3) {
-        bool nan = false;
+        bool out = false;   // of the range: infinite or NaN
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -391,9 +403,9 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
 #pragma unroll
                 for (int g = 0; g < 16; ++g) {
                     const float v = acc[i][j][g];
-                    nan |= (v != v);
+                    out |= !(v - v == 0.f);
                 }
-        if (__syncthreads_or(nan)) {   // (sums of its own: no registers shared with the path below)
+        if (__syncthreads_or(out)) {   // (sums of its own: no registers shared with the path below)
             f32x16 sum[WM][WN];
             int ra[WM], rb[WN];
 #pragma unroll
@@ -427,11 +439,11 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
                         for (int j = 0; j < WN; ++j)
                             sum[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[u][j], va[u][i], sum[i][j], 0, 0, 0);
             }
-            write(sum);
+            write(sum, 1.f);
             return;
         }
     }
-    write(acc);
+    write(acc, PLANES == 3 ? GG_UNSCALE : 1.f);
 }
 
 }  // namespace flce

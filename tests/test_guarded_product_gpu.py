@@ -1,6 +1,8 @@
 """The guarded product kernel (fp32 storage on split bf16 planes, any shape and alignment)
 against plain torch in 64 bits: edges of its 64 and 128 tiles, K ranges, K tails, odd leading
 dimensions, and operands the split cannot represent."""
+import math
+
 import pytest
 import torch
 
@@ -91,3 +93,41 @@ def test_nan_stays_where_plain_products_put_it():
     _, rX, _ = reference(X[ok], W, t[ok])
     got = dX[ok].double().cpu() * n / (n - 1)     # the reference's mean is over one row less
     assert float((got - rX).norm() / rX.norm()) <= 2e-6
+
+
+@pytest.mark.parametrize("BT,H,V", [(100, 40, 300), (1100, 128, 7000), (4096, 64, 16384)])   # 64, 128 and 256 tiles
+@pytest.mark.parametrize("ex,ew", [(-124, 0), (0, -124), (-124, 124), (-100, 100)])
+def test_small_operands_keep_fp32_accuracy(BT, H, V, ex, ew):
+    # values near the smallest normal fp32, alone (dW = G^T X and dX = G W carry their relative error on)
+    # and against partners that bring the logits back to order 1.  The scaling by powers of two is exact:
+    # the same bound as for ordinary operands, plus the spacing of subnormal results (2^-149 per element;
+    # up to 64 partial results of dX are rounded to it each, with random signs); 8 bits of a value
+    # would show as 1e-3.
+    import paper_2410_10989_amd as flce
+    X, W, t = inputs(BT, H, V, 17)
+    X, W = X * 2.0 ** ex, W * 2.0 ** ew
+    loss, dX, dW = flce.flce_fwd_bwd(X, W, t)
+    torch.cuda.synchronize()
+    rl, rX, rW = reference(X, W, t)
+    assert abs(float(loss) - rl) <= 2e-6 * abs(rl)
+    for name, got, ref, parts in (("dX", dX, rX, 64), ("dW", dW, rW, 1)):
+        err = float((got.double().cpu() - ref).norm())
+        bound = 2e-6 * float(ref.norm()) + 2.0 ** -149 * math.sqrt(parts * ref.numel())
+        print(f"  {BT} x {H} x {V} 2^{ex} 2^{ew} {name}: {err / float(ref.norm()):.2e} of {bound / float(ref.norm()):.2e}", flush=True)
+        assert err <= bound, (name, err, bound)
+
+
+def test_gradient_rows_of_improbable_classes():
+    # classes of probability e^-83: their gradients, about 2^-127, enter dW on their own.  The logits'
+    # own rounding moves the probabilities by |z| 2^-24 = 5e-6 and a few times that; 8 bits would be 1e-3.
+    import paper_2410_10989_amd as flce
+    X, W, t = inputs(100, 40, 300, 19)
+    t = torch.where((t >= 100) & (t < 200), t - 100, t)
+    X[:, 0] = 1.0
+    W[100:200, 0] = -78.0
+    loss, _, dW = flce.flce_fwd_bwd(X, W, t, flags=flce.SKIP_DX)
+    torch.cuda.synchronize()
+    _, _, rW = reference(X, W, t)
+    err = float((dW[100:200].double().cpu() - rW[100:200]).norm() / rW[100:200].norm())
+    print(f"  {err:.2e}", flush=True)
+    assert err <= 5e-5
