@@ -20,7 +20,9 @@
 // Where that leaves the range of the type (|x| >= 2^104, infinite or NaN operands, sums of 2^80
 // and more) the split remainders or the sums are infinite or NaN; a workgroup that finds one among
 // its sums computes its tile again with fp32 matrix instructions, so such inputs give what plain
-// fp32 products give.
+// fp32 products give.  A NaN operand alone makes the same sums NaN either way: a workgroup first looks
+// through its operands (gg_needs_fp32) and keeps its sums if nothing but NaN is out of range.  Measured, one
+// NaN in X, 2048 x 1024 x 50257: 3.9 ms (21.7 with every such tile computed again; 3.0 without the NaN).
 //
 // Shape: 256 threads = 4 wavefronts (2 x 2); macro tile TILE x TILE, TILE = 128 (each wavefront
 // owns 2 x 2 32 x 32 MFMA tiles; K step 16) or 64 (one MFMA tile in two accumulators, so that the
@@ -169,6 +171,52 @@ struct GGStage {
 template <bool KM>
 __device__ __forceinline__ float gg_element(const float* base, int64_t ld, int r, int k, int K) {
     return k < K ? (KM ? base[(int64_t)k * ld + r] : base[(int64_t)r * ld + k]) : 0.f;
+}
+
+// Per row of an operand's tile, the largest |x| over K values k0 .. k1 - 1 as the bits of a float (more
+// than those of infinity: the row holds a NaN), by all threads of the workgroup; top: LDS, zero before.
+template <bool KM, int TILE>
+__device__ __forceinline__ void gg_row_tops(const float* base, int64_t ld, int r0, int rows, int k0, int k1, int tid,
+                                            unsigned* top) {
+    constexpr int THREADS = gg_threads(TILE);
+    if constexpr (KM) {   // lanes along the rows: contiguous
+        const int r = tid % TILE;
+        unsigned m = 0;
+        if (r < rows) {
+#pragma unroll 8
+            for (int k = k0 + tid / TILE; k < k1; k += THREADS / TILE)
+                m = max(m, __float_as_uint(base[(int64_t)k * ld + r0 + r]) & 0x7fffffffu);
+            atomicMax(&top[r], m);
+        }
+    } else {              // lanes along K
+        for (int r = tid / WAVE; r < rows; r += THREADS / WAVE) {
+            const float* row = base + (int64_t)(r0 + r) * ld;
+            unsigned m = 0;
+#pragma unroll 8
+            for (int k = k0 + tid % WAVE; k < k1; k += WAVE) m = max(m, __float_as_uint(row[k]) & 0x7fffffffu);
+            atomicMax(&top[r], m);
+        }
+    }
+}
+// Whether a tile whose split sums hold infinities or NaN needs the fp32 instructions: not if every
+// one of them stems from a NaN operand, which makes its whole row or column NaN in any arithmetic
+// while all other sums stayed in range, i.e. if among the rows without a NaN all |a| and |b| are
+// below 2^103 and K |a| |b| below 2^79.  The same answer for every thread.
+template <bool A_KM, bool B_KM, int TILE>
+__device__ __forceinline__ bool gg_needs_fp32(const GGArgs& a, int m0, int M, int n0, int N, int k0, int k1, int tid,
+                                              unsigned* lds) {   // 2 TILE + 2 words
+    constexpr int THREADS = gg_threads(TILE);
+    for (int i = tid; i < 2 * TILE + 2; i += THREADS) lds[i] = 0;
+    __syncthreads();
+    gg_row_tops<A_KM, TILE>(static_cast<const float*>(a.A), a.lda, m0, min(TILE, M - m0), k0, k1, tid, lds);
+    gg_row_tops<B_KM, TILE>(static_cast<const float*>(a.B), a.ldb, n0, min(TILE, N - n0), k0, k1, tid, lds + TILE);
+    __syncthreads();
+    unsigned* both = lds + 2 * TILE;
+    for (int i = tid; i < 2 * TILE; i += THREADS)
+        if (lds[i] <= 0x7f800000u) atomicMax(&both[i / TILE], lds[i]);
+    __syncthreads();
+    const float ta = __uint_as_float(both[0]), tb = __uint_as_float(both[1]);
+    return ta >= 0x1p103f || tb >= 0x1p103f || (double)ta * tb * (k1 - k0) >= 0x1p79;
 }
 
 // Fin: as in gemm_bf16.
@@ -405,7 +453,9 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
                     const float v = acc[i][j][g];
                     out |= !(v - v == 0.f);
                 }
-        if (__syncthreads_or(out)) {   // (sums of its own: no registers shared with the path below)
+        if (__syncthreads_or(out) && gg_needs_fp32<A_KM, B_KM, TILE>(a, m0, M, n0, N, k_begin, k_end, tid,
+                                                                     reinterpret_cast<unsigned*>(lds))) {
+            // (sums of its own: no registers shared with the path below)
             f32x16 sum[WM][WN];
             int ra[WM], rb[WN];
 #pragma unroll

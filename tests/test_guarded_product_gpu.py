@@ -131,3 +131,41 @@ def test_gradient_rows_of_improbable_classes():
     err = float((dW[100:200].double().cpu() - rW[100:200]).norm() / rW[100:200].norm())
     print(f"  {err:.2e}", flush=True)
     assert err <= 5e-5
+
+
+@pytest.mark.parametrize("BT,H,V", [(100, 40, 300), (1100, 128, 7000), (4096, 64, 16384), (513, 70, 300)])   # 64, 128, 256 tiles; odd rows
+def test_a_nan_leaves_the_other_rows_their_bits(BT, H, V):
+    # a NaN in one row of X makes that row's logits and dX, and all of dW, NaN; every other row of dX is
+    # computed as it is without the NaN
+    import paper_2410_10989_amd as flce
+    X, W, t = inputs(BT, H, V, 23)
+    t[7] = 1
+    _, want, _ = flce.flce_fwd_bwd(X, W, t)
+    X[7, 3] = float("nan")
+    loss, dX, dW = flce.flce_fwd_bwd(X, W, t)
+    torch.cuda.synchronize()
+    assert torch.isnan(loss) and torch.isnan(dX[7]).all() and torch.isnan(dW).all()
+    other = torch.arange(BT, device="cuda") != 7
+    assert torch.equal(dX[other].view(torch.int32), want[other].view(torch.int32))
+
+
+def test_sums_beyond_the_split_range():
+    # operands within the range of the split whose sums are not (logits of 2^90): the largest logit wins,
+    # probability 1, and an infinite one beside a NaN row
+    import paper_2410_10989_amd as flce
+    X, W, t = inputs(130, 33, 300, 29)
+    X = X * 2.0 ** 60
+    W = W * 2.0 ** 30
+    z = X.double() @ W.double().T
+    best = z.argmax(1)
+    t = torch.where(t == -100, t, best)
+    loss, dX, dW = flce.flce_fwd_bwd(X, W, t)
+    torch.cuda.synchronize()
+    assert float(loss) == 0.0 and (dX == 0).all() and (dW == 0).all()
+    X[4, 5] = float("nan")
+    X[9, 2] = float("inf")
+    t[9] = -100
+    loss, dX, dW = flce.flce_fwd_bwd_opt(X, W, t, flce.flce_options(row_compaction=False))
+    torch.cuda.synchronize()
+    other = torch.arange(130, device="cuda") != 4
+    assert torch.isnan(loss) and torch.isnan(dX[4]).all() and (dX[other] == 0).all()
