@@ -42,11 +42,13 @@
  *    synchronising.  Argument errors are found on the host before anything is
  *    launched.  Functions return an flce_status and never throw or abort.
  *  - Scratch memory ("workspace") lives on the device.  Either the caller
- *    lends a buffer with flce_set_workspace (flce_workspace_bytes long; a smaller
- *    one still serves if it holds the plan without the finer cut of a small dX
- *    product along K), or the library allocates one per
- *    device on first use and keeps it (growing it if a later call needs more;
- *    growing synchronises the device).  Calls that overlap in time on the same
+ *    lends a buffer with flce_set_workspace (flce_workspace_bytes long), or the
+ *    library allocates one per device on first use and keeps it (growing it if a
+ *    later call needs more; growing synchronises the device).  Where less memory is
+ *    at hand (a smaller buffer, an allocation that fails) the call runs a slower plan
+ *    that fits: without the finer cut of a small dX product along K, then also
+ *    without row compaction for bf16 with H % 64 != 0 (12 bytes per row of a chunk);
+ *    FLCE_ERR_WORKSPACE if even that does not fit.  Calls that overlap in time on the same
  *    device share the workspace and therefore race: serialise them on one
  *    stream, or give each call a workspace of its own (flce_options).
  *  - Once the workspace is large enough (after a first call of the same size, or
@@ -123,9 +125,10 @@ FLCE_API int flce_fwd_bwd_ex(const void* X, const void* W, const int64_t* target
  *                        scratch memory instead of the device's shared workspace, or
  *                        NULL for the shared one; owned by the caller, who keeps it
  *                        alive until the call's work on the stream has finished
- *   workspace_bytes      its size: at least flce_workspace_bytes_opt of the same
- *                        arguments (FLCE_ERR_WORKSPACE otherwise; FLCE_ERR_ALIGN for
- *                        a misaligned buffer)
+ *   workspace_bytes      its size: flce_workspace_bytes_opt of the same arguments, or
+ *                        less at the price of a slower plan (see Scratch memory
+ *                        above; FLCE_ERR_WORKSPACE if none fits; FLCE_ERR_ALIGN for a
+ *                        misaligned buffer)
  * Calls that bring their own workspace share nothing on the device, so they may
  * overlap on one GPU (different streams, different threads) as long as their
  * workspaces and outputs are distinct.
@@ -262,7 +265,8 @@ FLCE_API int flce_release_workspace(void);
  * take no more than that budget plus the V x H fp32 partial sums a chunked run
  * needs is not chunked at all (no more memory than chunking, and faster).  A
  * non-zero value is taken literally: chunks of at most that many bytes, one chunk
- * only when the whole logits fit in it.  The getter returns the setting
+ * only when the whole logits fit in it, and no finer cut of a small dX product along
+ * K (more workspace for more speed, which only the automatic rule takes).  The getter returns the setting
  * (0 = automatic). */
 FLCE_API int flce_set_logits_budget_bytes(size_t bytes);
 FLCE_API size_t flce_get_logits_budget_bytes(void);

@@ -30,6 +30,7 @@ enum { DYN_CURSOR = 0,      // first batch row the next chunk looks at
        DYN_LIVE = 1,        // rows of the current chunk
        DYN_FIRST_LIVE = 2,  // index of the first chunk launch that holds rows
        DYN_DX_RANGES = 3 }; // K ranges of the current chunk's dX product
+static_assert(DYN_DX_RANGES < (int)DYN_WORDS, "room for the words");
 
 // How the N valid rows of a batch are dealt to the launches (see compact_chunk_kernel).
 struct RowDeal {

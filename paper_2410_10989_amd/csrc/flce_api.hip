@@ -43,6 +43,7 @@ struct DeviceWorkspace {
     size_t lent_bytes = 0;
     void* own = nullptr;
     size_t own_bytes = 0;
+    size_t own_failed = 0;   // an allocation of this size failed
 };
 
 std::mutex g_mutex;
@@ -82,14 +83,14 @@ size_t single_chunk_bytes(const Settings& st, int64_t H, int64_t V, int dtype) {
     return b + (size_t)V * (size_t)H * sizeof(float);
 }
 
-Plan plan_for(const Settings& st, int64_t BT, int64_t H, int64_t V, int dtype, bool worst_case_bt = false,
-              bool lean = false) {
+// An explicit budget never takes the full plan: its caller limits memory (see Room).
+Plan plan_for(const Settings& st, int64_t BT, int64_t H, int64_t V, int dtype, Room room = Room::full,
+              bool worst_case_bt = false) {
+    if (st.budget && room == Room::full) room = Room::bounded;
     return make_plan(BT, H, V, dtype, effective_budget(st, V, dtype), worst_case_bt, st.compact,
-                     single_chunk_bytes(st, H, V, dtype), lean);
+                     single_chunk_bytes(st, H, V, dtype), room);
 }
-Plan plan_for(int64_t BT, int64_t H, int64_t V, int dtype, bool worst_case_bt = false) {
-    return plan_for(global_settings(), BT, H, V, dtype, worst_case_bt);
-}
+Plan plan_for(int64_t BT, int64_t H, int64_t V, int dtype) { return plan_for(global_settings(), BT, H, V, dtype); }
 
 // ---- optional per-kernel timing (benchmarks only) ----
 struct TimingRecord {
@@ -136,21 +137,22 @@ struct ScopedKernelTimer {
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-// The device's shared workspace.  A lent buffer that holds `least` bytes but not `need` is handed
-// out as well (*out_bytes says how much there is): the caller then runs its lean plan.
-int acquire_workspace(size_t need, char** out, size_t least = 0, size_t* out_bytes = nullptr) {
+// The device's shared workspace: the lent buffer, or memory of the library's own that grows as needed.
+// last = false: the caller has a plan that needs less, so an allocation that failed once is not tried
+// again (until flce_release_workspace).
+int acquire_workspace(size_t need, char** out, bool last = true) {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= MAX_DEVICES) return FLCE_ERR_ARG;
     std::lock_guard<std::mutex> lock(g_mutex);
     DeviceWorkspace& w = g_ws[dev];
     if (w.lent) {
-        if (w.lent_bytes < need && (!out_bytes || w.lent_bytes < least)) return FLCE_ERR_WORKSPACE;
-        if (out_bytes) *out_bytes = w.lent_bytes;
+        if (w.lent_bytes < need) return FLCE_ERR_WORKSPACE;
         *out = static_cast<char*>(w.lent);
         return FLCE_OK;
     }
     if (w.own_bytes < need) {
+        if (!last && w.own_failed && need >= w.own_failed) return FLCE_ERR_WORKSPACE;
         if (w.own) {
             HIP_TRY(hipDeviceSynchronize());
             HIP_TRY(hipFree(w.own));
@@ -160,11 +162,11 @@ int acquire_workspace(size_t need, char** out, size_t least = 0, size_t* out_byt
         if (hipMalloc(&w.own, need) != hipSuccess) {
             (void)hipGetLastError();
             w.own = nullptr;
+            w.own_failed = need;
             return FLCE_ERR_WORKSPACE;
         }
         w.own_bytes = need;
     }
-    if (out_bytes) *out_bytes = w.own_bytes;
     *out = static_cast<char*>(w.own);
     return FLCE_OK;
 }
@@ -667,6 +669,31 @@ int check_launch_limits(const Plan& p, int64_t H, int64_t V) {
     return FLCE_OK;
 }
 
+// The fastest plan whose workspace (need_of(plan) bytes) there is room for, and that workspace: the
+// call's own, the buffer lent to the device or the library's.
+template <typename NeedOf>
+int plan_and_workspace(const Settings& st, int64_t BT, int64_t H, int64_t V, int dtype, NeedOf need_of, Plan* p,
+                       char** ws) {
+    for (const Room room : {Room::full, Room::bounded, Room::least}) {
+        *p = plan_for(st, BT, H, V, dtype, room);
+        if (room == Room::full) {   // (the launches' sizes do not depend on the room)
+            FLCE_TRY(check_launch_limits(*p, H, V));
+            if (st.ws && !aligned(st.ws, 256)) return FLCE_ERR_ALIGN;
+        }
+        const size_t need = need_of(*p);
+        if (st.ws) {
+            if (st.ws_bytes >= need) {
+                *ws = static_cast<char*>(st.ws);
+                return FLCE_OK;
+            }
+        } else {
+            const int rc = acquire_workspace(need, ws, room == Room::least);
+            if (rc != FLCE_ERR_WORKSPACE) return rc;
+        }
+    }
+    return FLCE_ERR_WORKSPACE;
+}
+
 struct NormLayout {
     size_t off_rstd, off_partial, total;
 };
@@ -764,18 +791,9 @@ int multihead_fwd_bwd(const Settings& st, const void* X, const void* const* W, c
     }
     if (ignore_index >= 0 && ignore_index < V) return FLCE_ERR_ARG;   // would shadow a class
 
-    Plan p = plan_for(st, BT, H, V, dtype);
-    FLCE_TRY(check_launch_limits(p, H, V));
-    char* ws = static_cast<char*>(st.ws);
-    if (ws) {
-        if (!aligned(ws, 256)) return FLCE_ERR_ALIGN;
-        if (st.ws_bytes < p.total) return FLCE_ERR_WORKSPACE;
-    } else {
-        const Plan lean = plan_for(st, BT, H, V, dtype, false, true);
-        size_t have = 0;
-        FLCE_TRY(acquire_workspace(p.total, &ws, lean.total, &have));
-        if (have < p.total) p = lean;
-    }
+    Plan p;
+    char* ws = nullptr;
+    FLCE_TRY(plan_and_workspace(st, BT, H, V, dtype, [](const Plan& q) { return q.total; }, &p, &ws));
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dtype == FLCE_F32)
         return run_heads<float>(static_cast<const float*>(X), W, targets, weights, n_heads, BT, H, V,
@@ -860,17 +878,11 @@ int flce_rmsnorm_fwd_bwd(const void* h, const void* gamma, float eps, const void
     if (ignore_index >= 0 && ignore_index < V) return FLCE_ERR_ARG;
     if (!(eps >= 0.0f) || eps - eps != 0.0f) return FLCE_ERR_ARG;   // negative, NaN or infinite
 
-    Plan p = plan_for(BT, H, V, dtype);
-    FLCE_TRY(check_launch_limits(p, H, V));
-    NormLayout l = norm_layout(p, H);
-    const Plan lean = plan_for(global_settings(), BT, H, V, dtype, false, true);
+    Plan p;
     char* ws = nullptr;
-    size_t have = 0;
-    FLCE_TRY(acquire_workspace(l.total, &ws, norm_layout(lean, H).total, &have));
-    if (have < l.total) {
-        p = lean;
-        l = norm_layout(p, H);
-    }
+    FLCE_TRY(plan_and_workspace(global_settings(), BT, H, V, dtype,
+                                [&](const Plan& q) { return norm_layout(q, H).total; }, &p, &ws));
+    const NormLayout l = norm_layout(p, H);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dtype == FLCE_F32)
         return run_rmsnorm_head<float>(static_cast<const float*>(h), static_cast<const float*>(gamma),
@@ -951,7 +963,7 @@ size_t flce_workspace_bytes(int64_t BT, int64_t H, int64_t V, int dtype) {
 
 size_t flce_workspace_bytes_max(int64_t H, int64_t V, int dtype) {
     if (check_dims(1, H, V, dtype) != FLCE_OK) return 0;
-    return plan_for(0, H, V, dtype, true).total;
+    return plan_for(global_settings(), 0, H, V, dtype, Room::full, true).total;
 }
 
 int flce_set_workspace(void* ws, size_t bytes) {
@@ -977,6 +989,7 @@ int flce_release_workspace(void) {
         w.own = nullptr;
         w.own_bytes = 0;
     }
+    w.own_failed = 0;
     return FLCE_OK;
 }
 

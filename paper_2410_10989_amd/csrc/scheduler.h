@@ -20,6 +20,7 @@
 
 namespace flce {
 
+constexpr size_t DYN_WORDS = 4;        // device words of the compaction (see compact.h)
 constexpr int64_t CHUNK_ALIGN = 256;   // chunk rows are a multiple of the GEMM macro tile
 
 // A launch of one workgroup per 256 x 256 tile runs in rounds of as many tiles as the chip
@@ -164,8 +165,16 @@ inline int64_t cut_ns(int64_t tiles, int64_t tile, int64_t ranges) {
 struct ProductCut {
     int tile, ranges;
 };
-inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes) {
-    const int max_ranges = max_dx_ranges(budget_bytes, round_up(rows, 256), H);
+//
+// bounded: the partial results may take no more memory than those of the large tiles cut to fill
+// whole rounds (choose_ksplit, at most 16 ranges), which for many small products is none at all.
+inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes, bool bounded) {
+    int max_ranges = max_dx_ranges(budget_bytes, round_up(rows, 256), H);
+    if (bounded) {
+        const int tile = tuned ? 256 : 128;
+        max_ranges = std::min(max_ranges, choose_ksplit(tiles_of(rows, H, tile), tuned ? (V + 63) / 64 : V / 4,
+                                                        std::min(16, max_dx_ranges(budget_bytes, round_up(rows, tile), H))));
+    }
     ProductCut best{0, 1};
     int64_t best_ns = 0;
     auto consider = [&](int tile, int ranges) {
@@ -185,14 +194,6 @@ inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t 
         if (r == 1 || V / r >= 512) consider(128, r);
     }
     return best;
-}
-
-// The same with as little memory for partial results as the large tiles' rule takes: for a lent
-// workspace that holds such a plan but not the faster one.
-inline ProductCut dx_cut_lean(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes) {
-    const int tile = tuned ? 256 : 128;
-    const int max_ranges = std::min(16, max_dx_ranges(budget_bytes, round_up(rows, tile), H));
-    return {tile, choose_ksplit(tiles_of(rows, H, tile), tuned ? (V + 63) / 64 : V / 4, max_ranges)};
 }
 
 // The logits and dW products have V along one output dimension, which can be shared out: columns (or
@@ -233,10 +234,18 @@ inline VocabCut vocab_cut(bool tuned, int64_t V, int64_t other, int64_t K, bool 
 inline bool fits_row_form(int64_t ld, int64_t) { return 256 * ld * 2 + 128 < ((int64_t)1 << 30); }
 inline bool fits_col_form(int64_t ld, int64_t) { return 64 * ld * 2 + 512 < ((int64_t)1 << 30); }
 
+// How much workspace a plan may take, the fastest plan first:
+//   full     up to 64 K ranges of dX on small tiles (dx_cut); what the automatic chunk rule takes
+//   bounded  partial results as under dx_cut's bound: what an explicit logits budget takes, whose
+//            caller limits memory, and calls whose buffer is too small for `full`
+//   least    bounded, and without the index maps of the row compaction (12 bytes per row) where the
+//            problem is a bf16 one with H % 64 != 0, for buffers that were sized without them
+enum class Room { full, bounded, least };
+
 // Byte offsets of the workspace for a plan whose chunking (C, nchunks, rows of the last
 // chunk) is decided; `dxpart_floor` is a lower bound for the K-range partials.
 inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last, size_t budget_bytes,
-                    bool allow_compact, size_t dxpart_floor, bool lean = false) {
+                    bool allow_compact, size_t dxpart_floor, Room room) {
     const size_t es = elem_size(dtype);
     p.ldc = round_up(p.C, 64);
     p.fp32_dw_acc = (dtype != 0) && p.nchunks > 1;
@@ -256,8 +265,7 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     }
     {
         const int64_t rows = p.nchunks > 1 ? p.C : rows_last;
-        const ProductCut cut = lean ? dx_cut_lean(p.fast_dx, rows, H, V, budget_bytes)
-                                    : dx_cut(p.fast_dx, rows, H, V, budget_bytes);
+        const ProductCut cut = dx_cut(p.fast_dx, rows, H, V, budget_bytes, room != Room::full);
         p.dx_tile = cut.tile;
         p.dx_ranges = cut.ranges;
         p.dx_ksplit = p.fast_dx ? choose_ksplit(tiles_of(rows, H, 256), (V + 63) / 64,
@@ -265,7 +273,7 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
                                 : std::min(cut.ranges, 16);
     }
     // (the copies move 16-byte vectors; bf16 rows of other lengths do not run on the tuned kernel)
-    p.compact = allow_compact &&
+    p.compact = allow_compact && !(room == Room::least && dtype != 0 && H % 64 != 0) &&
                 (dtype == 0 ? H % 4 == 0 : p.fast_logits && p.fast_dx && p.fast_dw_full && p.fast_dw_last);
 
     size_t off = 0;
@@ -275,19 +283,22 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
         return at;
     };
     p.off_hdr = take(256);
-    p.off_row_loss = take((size_t)p.C * sizeof(float));
+    // per-row values in one piece: losses, the compaction's targets and batch rows, its device words
+    const size_t maps = p.compact ? (size_t)p.C : 0;
+    p.off_row_loss = take((size_t)round_up(p.C, 2) * sizeof(float) + maps * (sizeof(int64_t) + sizeof(int32_t)) +
+                          DYN_WORDS * sizeof(int32_t));
+    p.off_tv = p.off_row_loss + (size_t)round_up(p.C, 2) * sizeof(float);
+    p.off_idx = p.off_tv + maps * sizeof(int64_t);
+    p.off_dyn = p.off_idx + maps * sizeof(int32_t);
     p.off_z = take((size_t)p.C * p.ldz * es);
     p.off_gt = p.off_wt = p.off_xt = off;   // no product needs a transposed copy
     p.off_dwacc = take(p.fp32_dw_acc ? (size_t)V * H * sizeof(float) : 0);
     const size_t dxpart = p.dx_ranges > 1 ? (size_t)p.dx_ranges * p.C * H * sizeof(float) : 0;
     p.off_dxpart = take(std::max(dxpart, dxpart_floor));
     // a chunk of gathered input rows and of their gradient (also the normalised rows and
-    // their gradient when an RMSNorm runs in front), index maps of the compaction
+    // their gradient when an RMSNorm runs in front)
     p.off_xg = take((size_t)p.C * H * es);
     p.off_dxg = take((size_t)p.C * H * es);
-    p.off_idx = take(p.compact ? (size_t)p.C * sizeof(int32_t) : 0);
-    p.off_tv = take(p.compact ? (size_t)p.C * sizeof(int64_t) : 0);
-    p.off_dyn = take(256);
     // fp32 partial blocks of the dW product's last, partly filled round of tiles when it is cut
     // along K (tail_plan; a shorter last chunk has fewer K steps and never needs more)
     const int64_t dw_tiles = ((V + 255) / 256) * ((H + 255) / 256);
@@ -302,10 +313,10 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
 // which only several chunks need, so that one chunk is taken whenever it needs no more
 // memory than the chunked plan would (and it is always faster: no second pass over W,
 // no fp32 round trip of dW).  worst_case_bt: the plan with the largest workspace any BT
-// can lead to (BT is ignored).  lean: see dx_cut_lean.
+// can lead to (BT is ignored).
 inline Plan make_plan(int64_t BT, int64_t H, int64_t V, int dtype, size_t budget_bytes,
                       bool worst_case_bt = false, bool allow_compact = true, size_t single_bytes = 0,
-                      bool lean = false) {
+                      Room room = Room::full) {
     Plan p;
     const size_t es = elem_size(dtype);
     p.ldz = round_up(V, 64);
@@ -319,8 +330,9 @@ inline Plan make_plan(int64_t BT, int64_t H, int64_t V, int dtype, size_t budget
         // K ranges of the dX product depends on the row count through its tile count
         auto dxpart_over = [&](bool tuned, int64_t upto) {
             size_t m = 0;
-            for (int64_t c = 64; c <= upto; c += 64) {
-                const int ks = dx_cut(tuned, c, H, V, budget_bytes).ranges;
+            if (V < 512) return m;   // never cut
+            for (int64_t c = 64; c <= upto && max_dx_ranges(budget_bytes, round_up(c, 256), H) > 1; c += 64) {
+                const int ks = dx_cut(tuned, c, H, V, budget_bytes, room != Room::full).ranges;
                 if (ks > 1) m = std::max(m, (size_t)ks * c * H * sizeof(float));
             }
             return m;
@@ -328,15 +340,15 @@ inline Plan make_plan(int64_t BT, int64_t H, int64_t V, int dtype, size_t budget
         // several chunks, the last one ragged (the most expensive case) ...
         p.C = cmax;
         p.nchunks = 2;
-        lay_out(p, H, V, dtype, 1, budget_bytes, allow_compact, 0);
-        lay_out(p, H, V, dtype, 1, budget_bytes, allow_compact, dxpart_over(p.fast_dx, cmax));
+        lay_out(p, H, V, dtype, 1, budget_bytes, allow_compact, 0, room);
+        lay_out(p, H, V, dtype, 1, budget_bytes, allow_compact, dxpart_over(p.fast_dx, cmax), room);
         // ... or the largest batch that still runs as one chunk
         Plan q;
         q.ldz = p.ldz;
         q.C = single_max;
         q.nchunks = 1;
-        lay_out(q, H, V, dtype, single_max, budget_bytes, allow_compact, 0);
-        lay_out(q, H, V, dtype, single_max, budget_bytes, allow_compact, dxpart_over(q.fast_dx, single_max));
+        lay_out(q, H, V, dtype, single_max, budget_bytes, allow_compact, 0, room);
+        lay_out(q, H, V, dtype, single_max, budget_bytes, allow_compact, dxpart_over(q.fast_dx, single_max), room);
         return q.total > p.total ? q : p;
     }
     int64_t rows_last;
@@ -350,7 +362,7 @@ inline Plan make_plan(int64_t BT, int64_t H, int64_t V, int dtype, size_t budget
         p.nchunks = (BT + p.C - 1) / p.C;
         rows_last = BT - (p.nchunks - 1) * p.C;
     }
-    lay_out(p, H, V, dtype, rows_last, budget_bytes, allow_compact, 0, lean);
+    lay_out(p, H, V, dtype, rows_last, budget_bytes, allow_compact, 0, room);
     return p;
 }
 

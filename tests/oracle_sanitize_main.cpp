@@ -208,11 +208,18 @@ static void scheduler_sweep() {
                             CHECK((p.nchunks - 1) * p.C < BT, "an empty chunk");
                             CHECK(p.nchunks == 1 || p.C % flce::CHUNK_ALIGN == 0, "unaligned chunk size");
                             CHECK(p.ldz >= V && p.ldz % 64 == 0 && p.ldc >= p.C, "leading dimensions");
-                            const size_t offs[] = {p.off_hdr, p.off_row_loss, p.off_z, p.off_gt, p.off_wt,
-                                                   p.off_xt, p.off_dwacc, p.off_dxpart, p.off_xg, p.off_dxg,
-                                                   p.off_idx, p.off_tv, p.off_dyn, p.off_tail, p.total};
-                            for (size_t k = 0; k + 1 < sizeof(offs) / sizeof(offs[0]); ++k)
-                                CHECK(offs[k] % 256 == 0 && offs[k] <= offs[k + 1], "workspace layout");
+                            // the regions in their order: where they start, what they hold, their alignment
+                            const size_t es = dtype ? 2 : 4, C = (size_t)p.C, maps = p.compact ? C : 0;
+                            const size_t regions[][3] = {
+                                {p.off_hdr, 256, 256}, {p.off_row_loss, 4 * C, 256}, {p.off_tv, 8 * maps, 8},
+                                {p.off_idx, 4 * maps, 4}, {p.off_dyn, 16, 4}, {p.off_z, C * p.ldz * es, 256},
+                                {p.off_dwacc, p.fp32_dw_acc ? (size_t)V * H * 4 : 0, 256},
+                                {p.off_dxpart, p.dx_ranges > 1 ? p.dx_ranges * C * H * 4 : 0, 256},
+                                {p.off_xg, C * H * es, 256}, {p.off_dxg, C * H * es, 256},
+                                {p.off_tail, p.tail_bytes, 256}, {p.total, 0, 256}};
+                            for (size_t k = 0; k + 1 < sizeof(regions) / sizeof(regions[0]); ++k)
+                                CHECK(regions[k][0] % regions[k][2] == 0 && regions[k][0] + regions[k][1] <= regions[k + 1][0],
+                                      "workspace layout, region %zu", k);
                             CHECK(p.off_z - p.off_row_loss >= (size_t)p.C * 4, "row losses overlap the logits");
                             CHECK(p.total <= cap.total, "workspace %zu above the bound %zu (BT %lld H %lld V %lld)",
                                   p.total, cap.total, (long long)BT, (long long)H, (long long)V);

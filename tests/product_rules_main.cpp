@@ -46,9 +46,14 @@ int main() {
         for (int64_t rows : others)
             for (int64_t H : others)
                 for (int64_t V : Vs)
-                    for (size_t budget : {(size_t)1, (size_t)1 << 20, (size_t)1 << 30, (size_t)1 << 33}) {
+                    for (size_t budget : {(size_t)1, (size_t)1 << 20, (size_t)1 << 30, (size_t)1 << 33})
+                    for (bool bounded : {false, true}) {
                         if (H > 16384) continue;
-                        const ProductCut c = dx_cut(tuned != 0, rows, H, V, budget);
+                        const ProductCut c = dx_cut(tuned != 0, rows, H, V, budget, bounded);
+                        const int tile = tuned ? 256 : 128;
+                        CHECK(!bounded || c.ranges <= choose_ksplit(tiles_of(rows, H, tile), tuned ? (V + 63) / 64 : V / 4,
+                                                                    std::min(16, max_dx_ranges(budget, round_up(rows, tile), H))),
+                              "a bounded cut takes %d ranges", c.ranges);
                         CHECK(c.tile == 256 || c.tile == 128 || (!tuned && c.tile == 64), "dX tile %d", c.tile);
                         CHECK(c.ranges >= 1 && c.ranges <= 64, "dX ranges %d", c.ranges);
                         if (c.ranges == 1) continue;
@@ -66,6 +71,36 @@ int main() {
                         CHECK(at == steps, "K steps lost");
                     }
     CHECK(cut > 0, "no dX product is cut");
+    // Workspace: the least plan fits the sizes that callers may have set aside for the plan of large tiles
+    // (with the index maps of the compaction only for fp32 and H % 64 == 0), the bounded one too but for the maps.
+    long plans = 0;
+    for (int dtype = 0; dtype < 2; ++dtype)
+        for (int64_t BT : {1, 4, 100, 600, 1000, 2047, 8192, 33000})
+            for (int64_t H : {1, 7, 8, 64, 100, 256, 968, 1000, 4096})
+                for (int64_t V : {1, 300, 1000, 4096, 16384, 16916, 50257})
+                    for (int chunk_rows : {0, 256}) {
+                        const size_t es = elem_size(dtype);
+                        const size_t budget = chunk_rows ? chunk_rows * (size_t)round_up(V, 64) * es : (size_t)1 << 30;
+                        auto plan = [&](Room r) { return make_plan(BT, H, V, dtype, budget, false, true, budget, r); };
+                        const Plan full = plan(Room::full), bounded = plan(Room::bounded), least = plan(Room::least);
+                        const bool tuned = dtype != 0 && H % 8 == 0;
+                        const int64_t C = full.C, rows = full.nchunks > 1 ? C : BT, tile = tuned ? 256 : 128;
+                        const int ranges = choose_ksplit(tiles_of(rows, H, tile), tuned ? (V + 63) / 64 : V / 4,
+                                                         std::min(16, max_dx_ranges(budget, round_up(rows, tile), H)));
+                        auto r256 = [](size_t b) { return (b + 255) / 256 * 256; };
+                        const size_t aside = 256 + r256(4 * C) + r256((size_t)C * full.ldz * es) +
+                                             r256(full.fp32_dw_acc ? (size_t)V * H * 4 : 0) +
+                                             r256(ranges > 1 ? (size_t)ranges * C * H * 4 : 0) + 2 * r256((size_t)C * H * es) + 256 +
+                                             r256(full.tail_bytes);
+                        const size_t maps = full.compact ? r256(4 * C) + r256(8 * C) : 0;
+                        const bool without = dtype != 0 && H % 64 != 0;
+                        ++plans;
+                        CHECK(least.total <= aside + (without ? 0 : maps), "dtype %d %lld x %lld x %lld: least %zu, set aside %zu", dtype,
+                              (long long)BT, (long long)H, (long long)V, least.total, aside);
+                        CHECK(bounded.total <= aside + maps, "bounded %zu, set aside %zu", bounded.total, aside + maps);
+                        CHECK(least.C == full.C && bounded.C == full.C && least.nchunks == full.nchunks, "the room changes the chunks");
+                    }
+    CHECK(plans > 0, "no plan");
     // the rotated K loop visits every step once
     for (int nk = 1; nk <= 70; ++nk)
         for (int rot = 0; rot < nk; ++rot) {

@@ -168,3 +168,51 @@ def test_lent_workspace_below_the_fast_plan(dtype):
         check(flce.flce_fwd_bwd(X, W, t), X, W, t, dtype)
     finally:
         flce.flce_set_workspace(None)
+
+
+@pytest.mark.parametrize("BT,H,V,compacted", [
+    (600, 256, 16384, True),     # dX cut into more K ranges than the buffer has room for
+    (1500, 72, 700, False),      # H % 64 != 0, dX not cut: no room for the index maps either
+    (1911, 968, 16916, False),   # both
+])
+@pytest.mark.parametrize("how", ["options", "lent", "rmsnorm"])
+def test_workspace_without_the_fast_plan(BT, H, V, compacted, how):
+    # a buffer with room for the large tiles' K ranges only (what an explicit budget reports) and, with
+    # H % 64 != 0, without row compaction, serves however it is passed; 256 bytes less are refused
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, H, V, torch.bfloat16, "scattered", 31)
+    auto = max(1 << 30, 4096 * ((V + 63) // 64 * 64) * 2)
+    o = flce.flce_options(logits_budget_bytes=auto, row_compaction=compacted)
+    need = flce.flce_workspace_bytes_opt(BT, H, V, flce.FLCE_BF16, o)
+    assert need < flce.flce_workspace_bytes(BT, H, V, flce.FLCE_BF16)
+    if how == "rmsnorm":   # rstd and the 512 partial sums of dgamma
+        need += (4 * BT + 255) // 256 * 256 + 512 * H * 4
+    buf = torch.full((need + 256,), 255, dtype=torch.uint8, device="cuda")
+    at = -buf.data_ptr() % 256
+
+    def call(nbytes):
+        ws = buf[at:at + nbytes]
+        if how == "options":
+            return flce.flce_fwd_bwd_opt(X, W, t, flce.flce_options(workspace=ws))
+        try:
+            flce.flce_set_workspace(ws)
+            if how == "lent":
+                return flce.flce_fwd_bwd(X, W, t)
+            ones = torch.ones(H, dtype=torch.bfloat16, device="cuda")
+            loss, dh, _, dW = flce.flce_rmsnorm_fwd_bwd(X, ones, 1e-6, W, t)
+            return loss, dh, dW
+        finally:
+            torch.cuda.synchronize()
+            flce.flce_set_workspace(None)
+
+    got = call(need)
+    if how == "rmsnorm":
+        x = X.double()
+        y = (x / torch.sqrt((x * x).mean(1, keepdim=True) + 1e-6)).to(torch.bfloat16)
+        rl, _, rW = reference(y.float(), W.float(), t)
+        assert abs(float(got[0]) - rl) <= 2e-3 * rl
+        assert float((got[2].double().cpu() - rW).norm() / rW.norm()) <= TOL[torch.bfloat16]
+    else:
+        check(got, X, W, t, torch.bfloat16)
+    with pytest.raises(flce.FlceError):
+        call(need - 256)
