@@ -301,10 +301,10 @@ FLCE_API int64_t flce_num_chunks(int64_t BT, int64_t H, int64_t V, int dtype);
 FLCE_API size_t flce_logits_budget_for_workspace(int64_t BT, int64_t H, int64_t V, int dtype,
                                                  size_t max_workspace_bytes);
 
-/* Number of K ranges (K = V) the dX product of one chunk is cut into so that its
- * output tiles fill whole rounds of the chip's CUs; 1 = not cut (host only).  For
- * a bf16 product small enough to run on 128 x 128 tiles, which cut K finer, this is
- * the number of ranges its 256 x 256 tiles would take. */
+/* Number of K ranges (K = V) the launch of one chunk's dX product is sized for, so
+ * that few output tiles still fill the chip's CUs; 1 = not cut, at most 64 (host only).
+ * In a compacted chunk on 256 x 256 tiles the device takes fewer of them where the
+ * chunk's live rows fill whole rounds better with fewer. */
 FLCE_API int flce_dx_k_ranges(int64_t BT, int64_t H, int64_t V, int dtype);
 
 /* The paper's own chunk-size rule, 2^ceil(log2(ceil(BT / ceil(V/H)))), for

@@ -1033,7 +1033,7 @@ size_t flce_logits_budget_for_workspace(int64_t BT, int64_t H, int64_t V, int dt
 
 int flce_dx_k_ranges(int64_t BT, int64_t H, int64_t V, int dtype) {
     if (check_dims(BT, H, V, dtype) != FLCE_OK) return 0;
-    return plan_for(BT, H, V, dtype).dx_ksplit;
+    return plan_for(BT, H, V, dtype).dx_ranges;
 }
 
 int64_t flce_paper_chunk_rows(int64_t BT, int64_t H, int64_t V) {

@@ -82,7 +82,6 @@ struct Plan {
     bool fast_logits = false, fast_dx = false, fast_dw_full = false, fast_dw_last = false;
     int dx_ranges = 1;     // K ranges of the dX product (K = V), > 1 when C x H has few tiles
     int dx_tile = 256;     // its tile size
-    int dx_ksplit = 1;     // the K ranges that are reported: for the tuned kernel what its large tiles take, at most 16
     // chunks are compacted, i.e. rows with an ignored target are left out of the products (see
     // compact.h)
     bool compact = false;
@@ -268,9 +267,6 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
         const ProductCut cut = dx_cut(p.fast_dx, rows, H, V, budget_bytes, room != Room::full);
         p.dx_tile = cut.tile;
         p.dx_ranges = cut.ranges;
-        p.dx_ksplit = p.fast_dx ? choose_ksplit(tiles_of(rows, H, 256), (V + 63) / 64,
-                                                max_dx_ranges(budget_bytes, round_up(rows, 256), H))
-                                : std::min(cut.ranges, 16);
     }
     // (the copies move 16-byte vectors; bf16 rows of other lengths do not run on the tuned kernel)
     p.compact = allow_compact && !(room == Room::least && dtype != 0 && H % 64 != 0) &&

@@ -223,7 +223,7 @@ static void scheduler_sweep() {
                             CHECK(p.off_z - p.off_row_loss >= (size_t)p.C * 4, "row losses overlap the logits");
                             CHECK(p.total <= cap.total, "workspace %zu above the bound %zu (BT %lld H %lld V %lld)",
                                   p.total, cap.total, (long long)BT, (long long)H, (long long)V);
-                            CHECK(p.dx_ksplit >= 1 && p.dx_ksplit <= 16, "K ranges");
+                            CHECK(p.dx_ranges >= 1 && p.dx_ranges <= 64, "K ranges");
                             CHECK(p.total - p.off_tail >= p.tail_bytes && p.tail_bytes <= ((size_t)64 << 20),
                                   "room for the partial blocks of the dW product's last round");
                         }

@@ -71,6 +71,16 @@ int main() {
                         CHECK(at == steps, "K steps lost");
                     }
     CHECK(cut > 0, "no dX product is cut");
+    // a few outputs of either size: what the dX tests rely on to reach both tile sizes, and the device's own
+    // choice of ranges for fewer live rows (256-tiles only)
+    const size_t gib = (size_t)1 << 30;
+    CHECK(dx_cut(true, 1024, 512, 8192, gib, false).tile == 128, "small outputs take small tiles");
+    CHECK(dx_cut(true, 600, 256, 16384, gib, false).tile == 128, "small outputs take small tiles");
+    CHECK(dx_cut(true, 2047, 1000, 50257, gib, false).tile == 256, "long products keep the large tiles");
+    const ProductCut dyn = dx_cut(true, 4100, 2048, 29596, gib, false);
+    auto live = [&](int64_t rows) { return choose_ksplit(tiles_of(rows, 2048, 256), (29596 + 63) / 64, dyn.ranges); };
+    CHECK(dyn.tile == 256 && dyn.ranges == 7 && live(2460) == 3 && live(1148) == 6, "tile %d, ranges %d, live %d and %d",
+          dyn.tile, dyn.ranges, live(2460), live(1148));
     // Workspace: the least plan fits the sizes that callers may have set aside for the plan of large tiles
     // (with the index maps of the compaction only for fp32 and H % 64 == 0), the bounded one too but for the maps.
     long plans = 0;

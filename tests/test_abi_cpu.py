@@ -82,13 +82,14 @@ def test_dx_product_is_cut_along_k_to_fill_whole_rounds_of_cus():
     code = flce.FLCE_BF16
     k = flce.flce_dx_k_ranges
     assert k(8192, 4096, 128256, code) == 1       # 2 chunks of 4096 rows: 16 x 16 = 256 tiles, one full round
-    assert k(4352, 4096, 8192, code) == 2         # 272 tiles, K = 128 steps: at most 2 ranges of 64 steps
+    assert k(4352, 4096, 8192, code) == 1         # 272 tiles of 256 x 256: 128 x 128 tiles instead, 1088 of them, not cut
+    assert k(600, 256, 16384, code) == 24         # 5 x 2 tiles of 128 x 128
     assert k(16384, 3584, 152064, code) >= 4      # chunks of 3328 rows: 13 x 14 = 182 tiles
     assert k(8192, 2304, 256000, code) >= 3       # chunks of 2048 rows: 8 x 9 = 72 tiles
     assert k(65536, 4096, 32000, code) == 1       # 16384-row chunks: 1024 tiles, many rounds
     assert k(256, 512, 4096, flce.FLCE_F32) == 16 # guarded kernels (fp32 storage): 2 x 4 tiles of 128 x 128
     assert k(4096, 4096, 32000, flce.FLCE_F32) == 1
-    for bt, h, v in [(4352, 4096, 8192), (16384, 3584, 152064), (8192, 2304, 256000)]:
+    for bt, h, v in [(600, 256, 16384), (16384, 3584, 152064), (8192, 2304, 256000)]:
         # the fp32 partial results are part of the reported workspace and stay within the budget
         c = flce.flce_chunk_rows(bt, h, v, code)
         part = k(bt, h, v, code) * c * h * 4

@@ -64,20 +64,19 @@ def test_ragged_shapes(dtype, BT, H, V, ignore):
     check_full(workloads.make(BT, H, V, dtype, ignore=ignore, seed=1000 + BT + V, name="ragged"))
 
 
-def test_dx_is_cut_along_k_when_the_tile_count_leaves_a_poor_last_round():
-    # 17 x 16 = 272 output tiles of dX on 256 CUs would run as two rounds; the scheduler
-    # cuts K = V in two ranges instead (fp32 partials, fixed-order sum)
+def test_dx_tile_count_that_would_leave_a_poor_last_round():
+    # 17 x 16 = 272 output tiles of 256 x 256 on 256 CUs would run as two rounds; the scheduler takes
+    # 34 x 32 tiles of 128 x 128 instead
     check_full(workloads.make(4352, 4096, 8192, "bf16", ignore=("iid", 0.1), seed=272, name="tail"))
 
 
 @pytest.mark.parametrize("ignore_frac", [0.0, 0.4, 0.75])
-def test_dx_k_ranges_follow_the_live_row_count(ignore_frac):
-    # 3 x 1 output tiles of dX, K = V = 16384 (256 K steps): a full chunk is cut into 4 K
-    # ranges; with rows ignored the device picks fewer ranges for the live tiles (2 tile rows:
-    # 3 ranges, 1 tile row: 4 again), sums their partial results in a fixed order, and the
-    # result matches the oracle element by element; without compaction the host's choice runs
+def test_dx_in_many_k_ranges(ignore_frac):
+    # 5 x 2 output tiles of dX (128 x 128), K = V = 16384: cut into 24 K ranges whatever the live row
+    # count is, their partial results summed in a fixed order; the result matches the oracle element by
+    # element, with and without compaction
     import paper_2410_10989_amd as flce
-    assert flce.flce_dx_k_ranges(600, 256, 16384, flce.FLCE_BF16) == 4
+    assert flce.flce_dx_k_ranges(600, 256, 16384, flce.FLCE_BF16) == 24
     w = workloads.make(600, 256, 16384, "bf16", ignore=("iid", ignore_frac) if ignore_frac else ("none",),
                        seed=4242 + int(100 * ignore_frac), name="k_ranges")
     on = check_full(w)
@@ -88,6 +87,32 @@ def test_dx_k_ranges_follow_the_live_row_count(ignore_frac):
         flce.flce_set_row_compaction(True)
     err = (on[1].float() - off[1].float()).abs().max().item()
     assert err <= 2.0 ** -7 * off[1].float().abs().max().item()   # other K ranges: other rounding, not more
+
+
+@pytest.mark.parametrize("ignored", [0, 1640, 2952])
+def test_dx_k_ranges_follow_the_live_row_count(ignored):
+    # 17 x 8 output tiles of dX (256 x 256), K = V = 29596: a full chunk is cut into 7 K ranges; with rows
+    # ignored the device picks fewer for the live tiles (2460 rows: 3, 1148 rows: 6; the rule is checked
+    # on the CPU), and dX agrees with plain torch in 64 bits.  bf16 storage of logits, gradients and
+    # results: at most about 4 * 2^-9 of the norm; a lost range would be 1 / 7 of it.
+    import paper_2410_10989_amd as flce
+    BT, H, V = 4100, 2048, 29596
+    assert flce.flce_dx_k_ranges(BT, H, V, flce.FLCE_BF16) == 7
+    g = torch.Generator(device="cuda").manual_seed(41 + ignored)
+    X = torch.randn(BT, H, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(V, H, device="cuda", generator=g) * 0.02).bfloat16()
+    t = torch.randint(0, V, (BT,), device="cuda", generator=g)
+    t[torch.randperm(BT, device="cuda", generator=g)[:ignored]] = -100
+    _, dX, _ = flce.flce_fwd_bwd(X, W, t, flags=flce.SKIP_DW)
+    ok = t != -100
+    x, w = X[ok].double(), W.double()
+    G = torch.softmax(x @ w.T, 1)
+    G[torch.arange(len(x), device="cuda"), t[ok]] -= 1.0
+    want = (G / len(x)) @ w
+    err = float((dX[ok].double() - want).norm() / want.norm())
+    print(f"  {ignored} ignored: {err:.1e}", flush=True)
+    assert err <= 8e-3
+    assert (dX[~ok] == 0).all()
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

@@ -47,9 +47,9 @@ def test_tile_edges_and_k_tails(BT, H, V, compaction):
     check(BT, H, V, compaction)
 
 
-def test_tile_choice_covers_both_sizes():
-    # what the rule picks at the sizes above is the host's choice by size alone: small outputs take
-    # small tiles, and a product that fills the chip the large ones (its K ranges are the reported ones)
+def test_k_ranges_of_both_tile_sizes():
+    # (which tile size the rule picks at these sizes is checked on the CPU)
     import paper_2410_10989_amd as flce
+    assert flce.flce_dx_k_ranges(1024, 512, 8192, flce.FLCE_BF16) == 8       # 8 x 4 tiles of 128 x 128
     assert flce.flce_dx_k_ranges(2047, 1000, 50257, flce.FLCE_BF16) == 8     # 8 x 4 tiles of 256 x 256
     assert flce.flce_dx_k_ranges(4096, 4096, 32000, flce.FLCE_BF16) == 1
