@@ -273,10 +273,7 @@ struct FgOperand {
     }
 
     __device__ __forceinline__ int step_offset(int kt) const {
-        if constexpr (ORDER == FG_ROTATED) {
-            kt += rot;
-            kt -= kt >= wrap ? wrap : 0;
-        }
+        if constexpr (ORDER == FG_ROTATED) kt = rotated_step(kt, rot, wrap);
         return (kt - kt_base) * kstep;
     }
 

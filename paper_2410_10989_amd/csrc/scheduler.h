@@ -62,6 +62,11 @@ FLCE_HD inline int xcd_tile_number(int xcd, int in_xcd, int per_xcd) {
         return ((in_xcd / TAIL_CUS_PER_XCD) * TAIL_XCDS + xcd) * TAIL_CUS_PER_XCD + in_xcd % TAIL_CUS_PER_XCD;
     return full * TAIL_XCDS + xcd * (per_xcd - full) + (in_xcd - full);
 }
+// K step that a K loop of `steps` steps takes as its kt-th when it starts at step rot < steps and wraps around.
+FLCE_HD inline int rotated_step(int kt, int rot, int steps) {
+    kt += rot;
+    return kt - (kt >= steps ? steps : 0);
+}
 // bytes of partial blocks such a launch needs (0 when it is not cut)
 inline size_t tail_partial_bytes(int64_t total, int64_t ksteps) {
     const TailPlan t = tail_plan(total, ksteps);

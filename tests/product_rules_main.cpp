@@ -116,8 +116,7 @@ int main() {
         for (int rot = 0; rot < nk; ++rot) {
             unsigned char seen[70] = {0};
             for (int kt = 0; kt < nk; ++kt) {
-                int k = kt + rot;
-                k -= k >= nk ? nk : 0;
+                const int k = rotated_step(kt, rot, nk);
                 CHECK(k >= 0 && k < nk && !seen[k], "step %d of %d", k, nk);
                 seen[k] = 1;
             }
