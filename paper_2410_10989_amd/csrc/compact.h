@@ -16,10 +16,21 @@
 
 namespace flce {
 
-// Batches of up to SEL_MAX_ROWS rows: one launch per chunk (select_rows_kernel) counts, collects,
-// copies and clears; larger ones count once and walk the batch with a cursor (the kernels below
-// it), because every workgroup of the one launch looks at all targets: 8 BT bytes each, from L2.
-constexpr int SEL_MAX_ROWS = 32768;
+// Which batches one launch per chunk (select_rows_kernel) counts, collects, copies and clears; the
+// others count once and walk the batch with a cursor (the kernels below it).  Every workgroup of the
+// one launch looks at all targets, 8 BT bytes from L2, once per chunk; the cursor needs three more
+// launches, two of them once per batch.  Whole calls at V = 64, H = 64, cursor / one launch per chunk, us:
+//   BT 4096   1 chunk 65 / 57, 4 chunks 142 / 130, 16 chunks 437 / 410
+//   BT 8192   1 chunk 106 / 92, 4 chunks 181 / 170, 16 chunks 482 / 472
+//   BT 12288  1 chunk 147 / 129, 4 chunks 222 / 215, 16 chunks 526 / 541
+//   BT 16384  1 chunk 188 / 166, 4 chunks 258 / 252, 16 chunks 567 / 606, 64 chunks 1797 / 2015
+//   BT 24576  2 chunks 293 / 271, 4 chunks 335 / 335, 16 chunks 661 / 744
+//   BT 32768  1 chunk 346 / 307, 2 chunks 376 / 347, 4 chunks 424 / 416, 16 chunks 713 / 865
+// (with H = 4096 the same differences in us): break-even at about 4, 5, 8 and 12 chunks.
+constexpr int64_t SEL_MAX_ROWS = 32768, SEL_ANY_CHUNKS_ROWS = 8192, SEL_MAX_SCANS = 131072;
+inline bool one_launch_selects(int64_t BT, int64_t nchunks) {
+    return BT <= SEL_ANY_CHUNKS_ROWS || (BT <= SEL_MAX_ROWS && BT * nchunks <= SEL_MAX_SCANS);
+}
 constexpr int SEL_GRID = 1024;   // workgroups at most: 4 rows each up to 4096, 32 at SEL_MAX_ROWS
 
 constexpr int CP_THREADS = 1024;

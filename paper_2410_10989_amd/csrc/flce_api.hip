@@ -400,7 +400,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
     // ignored: 816 us either way, error of dX against 64 bits 2.6e-3 with it, 2.95e-3 staged).
     const bool adds_in_epilogue = BF16 && want_dx && dx_add && !norm && p.dx_ranges == 1 && H % 64 != 0;
     const bool compact = p.compact && !adds_in_epilogue;
-    const bool select = compact && BT <= SEL_MAX_ROWS;   // one launch per chunk finds its rows
+    const bool select = compact && one_launch_selects(BT, p.nchunks);   // one launch per chunk finds its rows
     const bool norm_in_select = select && norm && aligned(norm->gamma, 16);
     const bool count_in_rows = !compact && p.nchunks == 1 && BT <= ce_count_rows(V * (int64_t)sizeof(T));
     T* zero_out = (want_dx && !dx_add) ? (norm ? norm->dh : dX) : nullptr;   // rows without a target: zero gradient

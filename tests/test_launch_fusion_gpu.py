@@ -216,3 +216,12 @@ def test_workspace_without_the_fast_plan(BT, H, V, compacted, how):
         check(got, X, W, t, torch.bfloat16)
     with pytest.raises(flce.FlceError):
         call(need - 256)
+
+
+@pytest.mark.parametrize("BT", [8192, 8193])   # 32 chunks of 256 rows selected by one launch each; 33 found with the cursor
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_selection_changes_over_with_the_chunk_count(BT, dtype):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, 32, 70, dtype, "scattered", BT)
+    o = flce.flce_options(logits_budget_bytes=256 * 128 * X.element_size(), row_compaction=True)
+    check(flce.flce_fwd_bwd_opt(X, W, t, o), X, W, t, dtype)
