@@ -31,7 +31,9 @@
  *    error before anything is launched).  bf16 problems with
  *    H % 8 == 0 run entirely on the tuned matrix-core kernel, whatever BT and V
  *    are; other H and fp32 storage run on a slower, fully guarded kernel (fp32
- *    products on split bf16 operands, with the accuracy of fp32 products); the
+ *    products on split bf16 operands, with the accuracy of fp32 products over the
+ *    whole range of the type; infinite or NaN operands and values beyond 2^103
+ *    give what plain fp32 products give and take up to about twice the time); the
  *    results meet the same bars.
  *  - Targets must lie in [0, V) or equal ignore_index; anything else is a
  *    precondition violation (not detected: checking would need a host sync).

@@ -14,25 +14,27 @@
 // The factor 2^24 (taken back as 2^-48 when the sums are written; both exact) is there because
 // bf16 has the exponents of fp32: without it lo is subnormal and loses bits below |x| = 2^-103,
 // mid below 2^-111, with it every plane of every fp32 value, subnormal ones too, is zero or a
-// normal bf16.  It costs 2 lane operations of 13 per pair of elements: 2048 x 1024 x 50257 2836 ->
-// 2930 us, 4096 x 4096 x 32000 13.25 -> 13.74 ms, 256 x 512 x 4096 53.8 -> 55.3 (with the factor as a
-// literal 56.5: such short launches wait for their instructions).
+// normal bf16.  It costs 2 lane operations of 13 per pair of elements: 2048 x 1024 x 50257 2854 ->
+// 2938 us, 4096 x 4096 x 32000 13.13 -> 13.48 ms, 256 x 512 x 4096 54.7 -> 55.9 (with the factor as a
+// literal 1.2 more: such short launches wait for their instructions).
 // Where that leaves the range of the type (|x| >= 2^104, infinite or NaN operands, sums of 2^80
 // and more) the split remainders or the sums are infinite or NaN; a workgroup that finds one among
-// its sums computes its tile again with fp32 matrix instructions, so such inputs give what plain
-// fp32 products give.  A NaN operand alone makes the same sums NaN either way: a workgroup first looks
-// through its operands (gg_needs_fp32) and keeps its sums if nothing but NaN is out of range.  Measured, one
-// NaN in X, 2048 x 1024 x 50257: 3.9 ms (21.7 with every such tile computed again; 3.0 without the NaN).
+// its sums computes them again with fp32 matrix instructions, so such inputs give what plain
+// fp32 products give.  A NaN operand alone makes the same sums NaN either way, so the workgroup first
+// looks through its operands and computes only the 32 x 32 blocks again in which something else is out of
+// range (gg_needs_fp32).  2048 x 1024 x 50257, 2.94 ms: with a NaN in X 3.8 ms (21.7 when every such tile was
+// computed again), with an infinite X 4.1, with a weight of -inf 6.2 (19.5 and 17.5; products on the fp32
+// instructions alone took 9.6).
 //
-// Shape: 256 threads = 4 wavefronts (2 x 2); macro tile TILE x TILE, TILE = 128 (each wavefront
-// owns 2 x 2 32 x 32 MFMA tiles; K step 16) or 64 (one MFMA tile in two accumulators, so that the
-// plane products do not wait for one another; K step 32).  A thread stages 8 consecutive K values
-// of one tile row per operand and step: row form 32 contiguous bytes, column form 8 loads that are
-// contiguous across the wavefront's lanes.  Loads run gg_depth steps ahead in registers; LDS is
-// double buffered with one barrier per step, and the split of step t + 1 (lane operations) stands
-// beside the products of step t (matrix pipe) in the same instruction stream.  LDS: per plane,
-// [K piece of 8][row] 16-byte entries, the rows of odd pieces XOR 8: writes and fragment reads
-// touch all banks evenly.
+// Shape: macro tile TILE x TILE.  TILE = 256: 512 threads = 8 wavefronts (2 x 4), each with 4 x 2 MFMA
+// tiles of 32 x 32, K step 16; 128: 256 threads = 4 wavefronts (2 x 2) with 2 x 2 MFMA tiles, K step
+// 16; 64: 4 wavefronts with one MFMA tile in two accumulators, so that the plane products do not wait
+// for one another, K step 32.  A thread stages 8 consecutive K values of one tile row per operand and
+// step: row form 32 contiguous bytes, column form 8 loads that are contiguous across the wavefront's
+// lanes.  Loads run gg_depth steps ahead in registers; LDS is double buffered with one barrier per step,
+// and the split of step t + 1 (lane operations) stands beside the products of step t (matrix pipe) in the
+// same instruction stream.  LDS: per plane, [K piece of 8][row] 16-byte entries, the rows of a piece
+// permuted by gg_fold: writes and fragment reads touch all banks evenly.
 #pragma once
 #include "flce_device.h"
 #include "gemm_bf16_nt.h"
@@ -198,25 +200,34 @@ __device__ __forceinline__ void gg_row_tops(const float* base, int64_t ld, int r
         }
     }
 }
-// Whether a tile whose split sums hold infinities or NaN needs the fp32 instructions: not if every
-// one of them stems from a NaN operand, which makes its whole row or column NaN in any arithmetic
-// while all other sums stayed in range, i.e. if among the rows without a NaN all |a| and |b| are
-// below 2^103 and K |a| |b| below 2^79.  The same answer for every thread.
-template <bool A_KM, bool B_KM, int TILE>
-__device__ __forceinline__ bool gg_needs_fp32(const GGArgs& a, int m0, int M, int n0, int N, int k0, int k1, int tid,
-                                              unsigned* lds) {   // 2 TILE + 2 words
-    constexpr int THREADS = gg_threads(TILE);
-    for (int i = tid; i < 2 * TILE + 2; i += THREADS) lds[i] = 0;
+// Which 32 x 32 blocks (bit i WN + j) of a wavefront's part of a tile whose split sums hold infinities or
+// NaN need the fp32 instructions: not those where every one of them stems from a NaN operand, which
+// makes its whole row or column NaN in any arithmetic while all other sums stayed in range, i.e. where
+// among the block's rows without a NaN all |a| and |b| are below 2^103 and K |a| |b| below 2^79.
+template <bool A_KM, bool B_KM, int TILE, int WM, int WN>
+__device__ __forceinline__ unsigned gg_needs_fp32(const GGArgs& a, int m0, int M, int n0, int N, int k0, int k1, int tid,
+                                                  int wm, int wn, unsigned* lds) {   // 2 TILE words
+    for (int i = tid; i < 2 * TILE; i += gg_threads(TILE))   // (rows past the matrix count as NaN)
+        lds[i] = (i < TILE ? m0 + i < M : n0 + i - TILE < N) ? 0u : 0xffffffffu;
     __syncthreads();
     gg_row_tops<A_KM, TILE>(static_cast<const float*>(a.A), a.lda, m0, min(TILE, M - m0), k0, k1, tid, lds);
     gg_row_tops<B_KM, TILE>(static_cast<const float*>(a.B), a.ldb, n0, min(TILE, N - n0), k0, k1, tid, lds + TILE);
     __syncthreads();
-    unsigned* both = lds + 2 * TILE;
-    for (int i = tid; i < 2 * TILE; i += THREADS)
-        if (lds[i] <= 0x7f800000u) atomicMax(&both[i / TILE], lds[i]);
-    __syncthreads();
-    const float ta = __uint_as_float(both[0]), tb = __uint_as_float(both[1]);
-    return ta >= 0x1p103f || tb >= 0x1p103f || (double)ta * tb * (k1 - k0) >= 0x1p79;
+    auto top_of = [&](const unsigned* row) {   // of 32 rows: 1 + the largest that is no NaN, 0 if there is none
+        const unsigned u = row[tid & 31];
+        unsigned m = u <= 0x7f800000u ? u + 1 : 0u;
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o, WAVE));
+        return m;
+    };
+    unsigned blocks = 0;
+#pragma unroll 1
+    for (int ij = 0; ij < WM * WN; ++ij) {
+        const unsigned ma = top_of(lds + (wm * WM + ij / WN) * 32), mb = top_of(lds + TILE + (wn * WN + ij % WN) * 32);
+        const float ta = __uint_as_float(ma - 1), tb = __uint_as_float(mb - 1);
+        if (ma && mb && (ta >= 0x1p103f || tb >= 0x1p103f || (double)ta * tb * (k1 - k0) >= 0x1p79)) blocks |= 1u << ij;
+    }
+    return __builtin_amdgcn_readfirstlane(blocks);
 }
 
 // Fin: as in gemm_bf16.
@@ -246,7 +257,7 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
     const FgResolved rs = fg_resolve(a, a.Cin != nullptr);
     if (rs.skip) return;
     const int M = rs.M, K = rs.K, N = a.N;
-    // workgroup id -> (K range, tile): as in gemm_bf16_256
+    // workgroup id -> (K range, tile): as in gemm_bf16
     const int tiles_m = (M + TILE - 1) / TILE, tiles_n = (N + TILE - 1) / TILE;
     const int tiles = tiles_m * tiles_n;
     const int total = tiles * rs.ksplit;
@@ -278,7 +289,6 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
     sa.init(a.A, a.lda, m0, M, tid);
     sb.init(a.B, a.ldb, n0, N, tid);
     const int frow = lane & 31, fhalf = lane >> 5;
-    
 
     // the barrier waits for this wavefront's LDS accesses only, not for the loads in flight
     auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
@@ -405,43 +415,39 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
     // the B fragment is the MFMA's first operand: accumulator register g of lane l holds row
     // l % 32, column 8*(g/4) + 4*(l/32) + g%4 of its 32 x 32 tile
     OutT* C = static_cast<OutT*>(a.C) + (int64_t)split * a.split_stride;
-    auto write = [&](const f32x16 (&sum)[WM][WN], float scale) {
+    auto write = [&](int i, int j, const f32x16& sum, float scale) {   // MFMA tile (i, j) of the wavefront
+        const int row = m0 + (wm * WM + i) * 32 + frow;
+        if (row >= M) return;
+        OutT* crow = C + (int64_t)row * a.ldc;
+        const unsigned char* inrow =
+            static_cast<const unsigned char*>(a.Cin) + (int64_t)row * a.ldcin * (a.cin_f32 ? 4 : (int)sizeof(OutT));
 #pragma unroll
-        for (int i = 0; i < WM; ++i) {
-            const int row = m0 + (wm * WM + i) * 32 + frow;
-            if (row >= M) continue;
-            OutT* crow = C + (int64_t)row * a.ldc;
-            const unsigned char* inrow =
-                static_cast<const unsigned char*>(a.Cin) + (int64_t)row * a.ldcin * (a.cin_f32 ? 4 : (int)sizeof(OutT));
+        for (int g4 = 0; g4 < 4; ++g4) {
+            __builtin_amdgcn_sched_barrier(0);   // one store's addresses at a time
+            const int col = n0 + (wn * WN + j) * 32 + 8 * g4 + 4 * fhalf;
+            float v[4];
 #pragma unroll
-            for (int j = 0; j < WN; ++j)
+            for (int e = 0; e < 4; ++e) v[e] = sum[4 * g4 + e] * scale;
+            if (rs.use_in) {
 #pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    __builtin_amdgcn_sched_barrier(0);   // one store's addresses at a time
-                    const int col = n0 + (wn * WN + j) * 32 + 8 * g4 + 4 * fhalf;
-                    float v[4];
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < N)
+                        v[e] += a.cin_f32 ? reinterpret_cast<const float*>(inrow)[col + e]
+                                          : to_f32(reinterpret_cast<const OutT*>(inrow)[col + e]);
+            }
+            if (a.vec_c && col + 4 <= N) {
+                struct alignas(4 * sizeof(OutT)) Quad { OutT e[4]; } q;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = sum[i][j][4 * g4 + e] * scale;
-                    if (rs.use_in) {
+                for (int e = 0; e < 4; ++e) q.e[e] = from_f32<OutT>(v[e]);
+                *reinterpret_cast<Quad*>(crow + col) = q;
+            } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (col + e < N)
-                                v[e] += a.cin_f32 ? reinterpret_cast<const float*>(inrow)[col + e]
-                                                  : to_f32(reinterpret_cast<const OutT*>(inrow)[col + e]);
-                    }
-                    if (a.vec_c && col + 4 <= N) {
-                        struct alignas(4 * sizeof(OutT)) Quad { OutT e[4]; } q;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) q.e[e] = from_f32<OutT>(v[e]);
-                        *reinterpret_cast<Quad*>(crow + col) = q;
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (col + e < N) crow[col + e] = from_f32<OutT>(v[e]);
-                    }
-                }
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < N) crow[col + e] = from_f32<OutT>(v[e]);
+            }
         }
     };
+    unsigned again = 0;   // MFMA tiles to compute on the fp32 instructions
     if constexpr (PLANES == 3) {
         bool out = false;   // of the range: infinite or NaN
 #pragma unroll
@@ -453,47 +459,41 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
                     const float v = acc[i][j][g];
                     out |= !(v - v == 0.f);
                 }
-        if (__syncthreads_or(out) && gg_needs_fp32<A_KM, B_KM, TILE>(a, m0, M, n0, N, k_begin, k_end, tid,
-                                                                     reinterpret_cast<unsigned*>(lds))) {
-            // (sums of its own: no registers shared with the path below)
-            f32x16 sum[WM][WN];
-            int ra[WM], rb[WN];
-#pragma unroll
-            for (int j = 0; j < WN; ++j) rb[j] = min(n0 + (wn * WN + j) * 32 + frow, N - 1);
-#pragma unroll
-            for (int i = 0; i < WM; ++i) {
-                ra[i] = min(m0 + (wm * WM + i) * 32 + frow, M - 1);
-#pragma unroll
-                for (int j = 0; j < WN; ++j)
-#pragma unroll
-                    for (int g = 0; g < 16; ++g) sum[i][j][g] = 0.f;
-            }
+        if (__syncthreads_or(out)) {
+            again = gg_needs_fp32<A_KM, B_KM, TILE, WM, WN>(a, m0, M, n0, N, k_begin, k_end, tid, wm, wn,
+                                                            reinterpret_cast<unsigned*>(lds));
+            // one MFMA tile at a time: few registers and enough loads in flight (a rare path, off the other's
+            // registers and instructions)
+            constexpr int U = 16;   // K pairs in flight
             const float* A = static_cast<const float*>(a.A);
             const float* B = static_cast<const float*>(a.B);
-            constexpr int U = TILE == 256 ? 2 : 4;   // K pairs in flight (registers)
-            for (int k0 = k_begin; k0 < k_end; k0 += 2 * U) {
-                float va[U][WM], vb[U][WN];
+#pragma unroll 1
+            for (int ij = 0; ij < WM * WN; ++ij) {
+                if (!(again >> ij & 1)) continue;
+                const int i = ij / WN, j = ij % WN;
+                const int ra = min(m0 + (wm * WM + i) * 32 + frow, M - 1), rb = min(n0 + (wn * WN + j) * 32 + frow, N - 1);
+                f32x16 sum;
 #pragma unroll
-                for (int u = 0; u < U; ++u)
+                for (int g = 0; g < 16; ++g) sum[g] = 0.f;
+#pragma unroll 1
+                for (int k0 = k_begin; k0 < k_end; k0 += 2 * U) {
+                    float va[U], vb[U];
 #pragma unroll
-                    for (int i = 0; i < WM; ++i) va[u][i] = gg_element<A_KM>(A, a.lda, ra[i], k0 + 2 * u + fhalf, k_end);
+                    for (int u = 0; u < U; ++u) va[u] = gg_element<A_KM>(A, a.lda, ra, k0 + 2 * u + fhalf, k_end);
 #pragma unroll
-                for (int u = 0; u < U; ++u)
+                    for (int u = 0; u < U; ++u) vb[u] = gg_element<B_KM>(B, a.ldb, rb, k0 + 2 * u + fhalf, k_end);
 #pragma unroll
-                    for (int j = 0; j < WN; ++j) vb[u][j] = gg_element<B_KM>(B, a.ldb, rb[j], k0 + 2 * u + fhalf, k_end);
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int i = 0; i < WM; ++i)
-#pragma unroll
-                        for (int j = 0; j < WN; ++j)
-                            sum[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[u][j], va[u][i], sum[i][j], 0, 0, 0);
+                    for (int u = 0; u < U; ++u) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[u], va[u], sum, 0, 0, 0);
+                }
+                write(i, j, sum, 1.f);
             }
-            write(sum, 1.f);
-            return;
         }
     }
-    write(acc, PLANES == 3 ? GG_UNSCALE : 1.f);
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+            if (!(again >> (i * WN + j) & 1)) write(i, j, acc[i][j], PLANES == 3 ? GG_UNSCALE : 1.f);
 }
 
 }  // namespace flce

@@ -164,7 +164,9 @@ __device__ __forceinline__ float row_lse(MaxSum a, const T* z, int64_t t, int ro
 // several workgroups fit a CU and overlap one another's memory, reduction and barrier phases;
 // 1024 x 16 (256 KB) beyond, where 16 wavefronts keep the per-thread ALU phases short.  TB/s of
 // algorithmic traffic, kernel alone, 256 x 12 / 512 x 12 / 1024 x 16: 7.1 / 4.5 / 2.2 at 16 KB rows
-// (16384 of them), - / 7.2 / 4.9 at 64 KB (4096), - / 5.3 / 4.8 at 100 KB, - / - / 5.2 at 240 KB.
+// (16384 of them), - / 7.2 / 4.9 at 64 KB (4096), - / 5.3 / 4.8 at 100 KB, - / - / 5.2 at 240 KB.  From 96 to 112 KB
+// (seven row lengths of bf16, four of fp32) whole calls of 512 x 12 against 1024 x 16 take 17.7 / 21.4 us (300
+// rows), 41 / 51 (1024), 150 / 170 (4096) at 97 KB and 20.5 / 23.5, 46 / 56, 161 / 188 at 112 KB; 64 rows 12.8 / 12.5.
 // NL: that many more vectors per thread stay in LDS (9 x 1024: 144 KB; one such workgroup fits a CU by
 // its registers anyway).  Used beyond 400 KB rows, without / with, us: 5734 x 256000 bf16 1164 / 1085, 3328 x
 // 152064 fp32 843 / 775, 2048 x 204807 bf16 (400 KB) 320 / 313; at 297 KB rows 348 / 368, where the little

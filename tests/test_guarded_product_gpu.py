@@ -169,3 +169,21 @@ def test_sums_beyond_the_split_range():
     torch.cuda.synchronize()
     other = torch.arange(130, device="cuda") != 4
     assert torch.isnan(loss) and torch.isnan(dX[4]).all() and (dX[other] == 0).all()
+
+
+@pytest.mark.parametrize("BT,H,V", [(100, 40, 300), (1100, 128, 7000), (4096, 64, 16384)])   # 64, 128 and 256 tiles
+def test_an_infinite_operand_is_computed_again_where_it_matters(BT, H, V):
+    # an infinite activation in an ignored row (no compaction): 0 * inf = NaN in its column of dW, as in
+    # plain products, and the rounding of ordinary sums everywhere else
+    import paper_2410_10989_amd as flce
+    X, W, t = inputs(BT, H, V, 37)
+    t[9], X[9, 2] = -100, float("inf")
+    loss, dX, dW = flce.flce_fwd_bwd_opt(X, W, t, flce.flce_options(row_compaction=False))
+    torch.cuda.synchronize()
+    ok = t != -100
+    rl, rX, rW = reference(X[ok], W, t[ok])
+    assert abs(float(loss) - rl) <= 2e-6 * abs(rl)
+    assert torch.isnan(dW[:, 2]).all() and (dX[~ok] == 0).all()
+    other = torch.arange(H) != 2
+    assert float((dX[ok].double().cpu() - rX).norm() / rX.norm()) <= 2e-6
+    assert float((dW.double().cpu() - rW)[:, other].norm() / rW[:, other].norm()) <= 2e-6
