@@ -663,9 +663,10 @@ int check_launch_limits(const Plan& p, int64_t H, int64_t V) {
     if (p.C > MAX_GRID_X) return FLCE_ERR_SHAPE;
     const bool all_fast = p.fast_logits && p.fast_dx && p.fast_dw_full && p.fast_dw_last;
     if (!all_fast) {
-        const int64_t worst = std::max(std::max(tiles(p.C, V, 128), tiles(V, H, 128)),
-                                       std::max(tiles(V, H, 64), tiles(p.C, V, 64)));
-        if (worst > MAX_GRID_X) return FLCE_ERR_SHAPE;
+        // (64 x 64 tiles are the most; a launch is rounded up to whole rounds over the XCDs)
+        const int64_t worst = std::max(std::max(tiles(V, H, 64), tiles(p.C, V, 64)),
+                                       tiles(p.C, H, p.dx_tile) * p.dx_ranges);
+        if (worst > MAX_GRID_X - FG_XCDS) return FLCE_ERR_SHAPE;
     }
     return FLCE_OK;
 }

@@ -229,3 +229,13 @@ def test_budget_for_a_workspace_of_a_given_size():
     finally:
         flce.flce_set_logits_budget_bytes(old)
     assert flce.flce_logits_budget_for_workspace(0, H, V, code, 1 << 40) == 0
+
+
+def test_launch_limits_are_checked_before_anything_is_launched():
+    # 42966 x 49981 = 2^31 - 2 tiles of 64 x 64 in dW: a launch numbers them rounded up to whole rounds over
+    # 8 XCDs, which does not fit 31 bits.  Refused for the shape, before any memory is touched.
+    L = flce.lib()
+    buf = (ctypes.c_char * 4096)()
+    a = ctypes.addressof(buf)
+    a += (-a) % 256
+    assert L.flce_fwd_bwd(a, a + 256, a + 512, 1, 49981 * 64, 42966 * 64, -100, 0, a + 768, a + 1024, a + 1280, None) == 2
