@@ -951,8 +951,9 @@ int flce_cross_entropy_inplace_noalloc(void* Z, const int64_t* targets, int64_t 
         }
         ptr = static_cast<char*>(g_scratch_ptr[dev]);
     }
-    // The header is reset by the counting kernel and every row's loss slot is written by the
-    // row kernel before it is summed, so nothing of the previous call's contents is read.
+    // The header is reset by the counting kernel or, for small batches, by the row kernel, and every
+    // row's loss slot is written by the row kernel before it is summed, so nothing of the previous
+    // call's contents is read.
     return run_ce_inplace(Z, targets, BT, V, ldz, ignore_index, dtype, loss,
                           reinterpret_cast<DeviceHeader*>(ptr), reinterpret_cast<float*>(ptr + 256), BT,
                           false, static_cast<hipStream_t>(stream));

@@ -9,7 +9,7 @@
 //     dW        += G^T X_c      A = G   column form, B = X_c column form (K = chunk rows)
 //
 // Shape of the kernel (256 x 256 tiles; launches too small to fill the chip with those take
-// 128 x 128 tiles, see gemm_bf16 and tuned_cut)
+// 128 x 128 tiles, see gemm_bf16 and product_ns)
 //  - workgroup = 256 threads = 4 wavefronts (2 x 2); macro tile 256 x 256, K step
 //    64; each wavefront owns 128 x 128 = 4 x 4 MFMA tiles, i.e. 256 fp32
 //    accumulator registers per lane (one wavefront per SIMD, full register file).
@@ -40,9 +40,10 @@
 //    instead of issuing one per MFMA.  The instruction order of the steady state
 //    is pinned with sched_barrier: MFMA, LDS read(s) or one load, MFMA, ...
 //  - workgroup id -> tile: ids are dealt round-robin to the 8 XCDs, so id%8
-//    selects the XCD and each XCD walks its own contiguous span of a grouped
-//    (8 tile rows at a time) tile order; tiles that run together on one XCD
-//    share A and B panels in that XCD's L2.
+//    selects the XCD; rounds of 32 consecutive tiles of a grouped order (4 tile
+//    rows, or for the logits 4 tile columns, at a time) go to the XCDs in turn
+//    (xcd_tile_number), so tiles that run together on one XCD share A and B
+//    panels in that XCD's L2.
 //  - epilogue through LDS: the MFMAs take the B fragment first and the A fragment
 //    second, so a lane's accumulators are four consecutive columns of one row per
 //    register quad; each wavefront stages 32 x 128 values at a time in its own LDS
@@ -556,7 +557,7 @@ __device__ __forceinline__ void fg_tile_origin(int seq, int tiles_m, int tiles_n
 }
 
 // InT: element type of the addend Cin (float or bf16_t), void for no addend.
-// TILE: 256, or 128 for launches whose 256 x 256 tiles would leave CUs idle (see tuned_cut):
+// TILE: 256, or 128 for launches whose 256 x 256 tiles would leave CUs idle (see product_ns):
 // 2 x 2 MFMA tiles per wavefront, half the LDS, two workgroups per CU that fill each other's
 // waits; its LDS reads (as many per K step for a quarter of the arithmetic) are as tight as the
 // matrix pipe.

@@ -80,10 +80,8 @@ struct Plan {
     int64_t C = 0;         // rows per chunk (last chunk may hold fewer)
     int64_t nchunks = 0;
     int64_t ldz = 0;       // row stride of the logits chunk, elements
-    int64_t ldc = 0;       // row stride of the row-transposed scratch, elements
     bool fp32_dw_acc = false;   // dW is accumulated in an fp32 scratch across chunks
-    // which products can run on the tuned bf16 kernel straight from X, W and the
-    // logits chunk; the others need transposed copies and the guarded kernel
+    // which products run on the tuned bf16 kernel; the others run on the guarded one
     bool fast_logits = false, fast_dx = false, fast_dw_full = false, fast_dw_last = false;
     int dx_ranges = 1;     // K ranges of the dX product (K = V), > 1 when C x H has few tiles
     int dx_tile = 256;     // its tile size
@@ -91,8 +89,7 @@ struct Plan {
     // compact.h)
     bool compact = false;
     // byte offsets into the workspace
-    size_t off_hdr = 0, off_row_loss = 0, off_z = 0, off_gt = 0, off_wt = 0, off_xt = 0,
-           off_dwacc = 0, off_dxpart = 0, off_xg = 0, off_dxg = 0, off_idx = 0, off_tv = 0,
+    size_t off_hdr = 0, off_row_loss = 0, off_z = 0, off_dwacc = 0, off_dxpart = 0, off_xg = 0, off_dxg = 0, off_idx = 0, off_tv = 0,
            off_dyn = 0, off_tail = 0, total = 0;
     size_t tail_bytes = 0;   // room at off_tail
 };
@@ -251,7 +248,6 @@ enum class Room { full, bounded, least };
 inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last, size_t budget_bytes,
                     bool allow_compact, size_t dxpart_floor, Room room) {
     const size_t es = elem_size(dtype);
-    p.ldc = round_up(p.C, 64);
     p.fp32_dw_acc = (dtype != 0) && p.nchunks > 1;
     p.fast_logits = p.fast_dx = p.fast_dw_full = p.fast_dw_last = false;
     if (dtype != 0) {
@@ -292,7 +288,6 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     p.off_idx = p.off_tv + maps * sizeof(int64_t);
     p.off_dyn = p.off_idx + maps * sizeof(int32_t);
     p.off_z = take((size_t)p.C * p.ldz * es);
-    p.off_gt = p.off_wt = p.off_xt = off;   // no product needs a transposed copy
     p.off_dwacc = take(p.fp32_dw_acc ? (size_t)V * H * sizeof(float) : 0);
     const size_t dxpart = p.dx_ranges > 1 ? (size_t)p.dx_ranges * p.C * H * sizeof(float) : 0;
     p.off_dxpart = take(std::max(dxpart, dxpart_floor));

@@ -207,7 +207,7 @@ static void scheduler_sweep() {
                             CHECK(p.nchunks >= 1 && p.C >= 1 && p.nchunks * p.C >= BT, "chunks do not cover BT");
                             CHECK((p.nchunks - 1) * p.C < BT, "an empty chunk");
                             CHECK(p.nchunks == 1 || p.C % flce::CHUNK_ALIGN == 0, "unaligned chunk size");
-                            CHECK(p.ldz >= V && p.ldz % 64 == 0 && p.ldc >= p.C, "leading dimensions");
+                            CHECK(p.ldz >= V && p.ldz % 64 == 0, "leading dimension");
                             // the regions in their order: where they start, what they hold, their alignment
                             const size_t es = dtype ? 2 : 4, C = (size_t)p.C, maps = p.compact ? C : 0;
                             const size_t regions[][3] = {

@@ -65,8 +65,7 @@ def test_workspace_is_bounded_independently_of_BT(H, V):
     many = [flce.flce_workspace_bytes(bt, H, V, code) for bt in (single_rows + 1, 4 * C, 8 * C, 64 * C, 4096 * C)
             if bt % C == 0 or bt == single_rows + 1]
     assert len(set(many[1:])) == 1 and all(s <= cap for s in many)
-    # a chunk whose row count is not a multiple of 64 takes the guarded kernels, which
-    # need transposed scratch: larger, but still bounded by the same cap for any BT
+    # batches that do not fill whole chunks: bounded by the same cap for any BT
     ragged = [flce.flce_workspace_bytes(bt, H, V, code) for bt in (C + 1, 9 * C + 3, 10 ** 7 + 1)]
     assert all(0 < s <= cap for s in ragged)
     assert flce.flce_get_logits_budget_bytes() == 0      # automatic: 1 GiB or 4096 rows

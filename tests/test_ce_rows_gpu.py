@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("V,ldz,offset", [
     (1, 1, 0), (5, 5, 1), (7, 9, 3),      # rows shorter than a vector: all head or tail
     (257, 257, 1),                        # 256-thread shape, a different head every row
-    (24571, 24571, 5),                    # up to 48 / 96 KB
+    (24571, 24571, 5),                    # just under 48 KB of bf16, 96 KB of fp32
     (50257, 50257, 0),                    # 512-thread shape (bf16), 1024-thread shape (fp32)
     (57345, 57345, 3),                    # just past 112 KB of bf16
     (131073, 131077, 7),                  # past what the registers hold (fp32: and LDS)
