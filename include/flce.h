@@ -50,7 +50,8 @@
  *    at hand (a smaller buffer, an allocation that fails) the call runs a slower plan
  *    that fits: without the finer cut of a small dX product along K, then also
  *    without row compaction for bf16 with H % 64 != 0 (12 bytes per row of a chunk);
- *    FLCE_ERR_WORKSPACE if even that does not fit.  Calls that overlap in time on the same
+ *    FLCE_ERR_WORKSPACE if even that does not fit.  (An allocation that found too
+ *    little memory is tried again after flce_release_workspace.)  Calls that overlap in time on the same
  *    device share the workspace and therefore race: serialise them on one
  *    stream, or give each call a workspace of its own (flce_options).
  *  - Once the workspace is large enough (after a first call of the same size, or

@@ -43,7 +43,7 @@ struct DeviceWorkspace {
     size_t lent_bytes = 0;
     void* own = nullptr;
     size_t own_bytes = 0;
-    size_t own_failed = 0;   // an allocation of this size failed
+    size_t own_failed = 0;   // an allocation of this size found too little memory, 0 if none did
 };
 
 std::mutex g_mutex;
@@ -138,8 +138,8 @@ struct ScopedKernelTimer {
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 // The device's shared workspace: the lent buffer, or memory of the library's own that grows as needed.
-// last = false: the caller has a plan that needs less, so an allocation that failed once is not tried
-// again (until flce_release_workspace).
+// last = false: the caller has a plan that needs less, so an allocation that found too little memory is
+// not tried again on every call (but after flce_release_workspace, or once one as large succeeds).
 int acquire_workspace(size_t need, char** out, bool last = true) {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
@@ -159,12 +159,14 @@ int acquire_workspace(size_t need, char** out, bool last = true) {
             w.own = nullptr;
             w.own_bytes = 0;
         }
-        if (hipMalloc(&w.own, need) != hipSuccess) {
+        const hipError_t rc = hipMalloc(&w.own, need);
+        if (rc != hipSuccess) {
             (void)hipGetLastError();
             w.own = nullptr;
-            w.own_failed = need;
+            if (rc == hipErrorOutOfMemory) w.own_failed = need;   // (not where a stream is being captured)
             return FLCE_ERR_WORKSPACE;
         }
+        if (need >= w.own_failed) w.own_failed = 0;
         w.own_bytes = need;
     }
     *out = static_cast<char*>(w.own);
