@@ -51,9 +51,10 @@
  *    that fits: without the finer cut of a small dX product along K, then also
  *    without row compaction for bf16 with H % 64 != 0 (12 bytes per row of a chunk);
  *    FLCE_ERR_WORKSPACE if even that does not fit.  (An allocation that found too
- *    little memory is tried again after flce_release_workspace.)  Calls that overlap in time on the same
- *    device share the workspace and therefore race: serialise them on one
- *    stream, or give each call a workspace of its own (flce_options).
+ *    little memory is tried again after flce_release_workspace.)  Calls that
+ *    overlap in time on the same device share the workspace and therefore race:
+ *    serialise them on one stream, or give each call a workspace of its own
+ *    (flce_options).
  *  - Once the workspace is large enough (after a first call of the same size, or
  *    with a lent buffer) a call consists of kernel launches on `stream` only: no
  *    allocation, no memset, no synchronisation.  It can therefore be recorded
