@@ -239,7 +239,7 @@ FLCE_API int flce_cross_entropy_inplace(void* Z, const int64_t* targets, int64_t
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU
  * (different streams, different threads) race; serialise them on one stream.  The
  * array keeps the previous call's contents; the kernels overwrite every slot they
- * read, nothing needs clearing.  The first call on a device looks the array's device
+ * read (a counter of finished workgroups is left at zero), nothing needs clearing.  The first call on a device looks the array's device
  * address up (hipGetSymbolAddress): make one call outside stream capture first.
  */
 #define FLCE_CE_NOALLOC_MAX_ROWS 65536

@@ -25,6 +25,11 @@ using namespace flce;
 // host code this name is only a handle for hipGetSymbolAddress, never an address.
 constexpr size_t CE_NOALLOC_BYTES = 256 + (size_t)FLCE_CE_NOALLOC_MAX_ROWS * sizeof(float);
 static __device__ __align__(256) unsigned char scratch[CE_NOALLOC_BYTES];
+// Counters of ce_rows_kernel (count_done): zero in the image and left at zero by every launch.  The first
+// set is that entry point's; calls of the other one take the rest in turn (theirs cannot be in the
+// workspace, whose contents are anybody's, and calls on different lent buffers may overlap).
+constexpr unsigned CE_DONE_TURNS = 8;
+static __device__ unsigned ce_done[(1 + CE_DONE_TURNS) * DONE_WORDS];
 
 namespace {
 
@@ -48,10 +53,13 @@ struct DeviceWorkspace {
 
 std::mutex g_mutex;
 DeviceWorkspace g_ws[MAX_DEVICES];
-void* g_scratch_ptr[MAX_DEVICES] = {};   // device address of `scratch` on each device, once looked up
+// device addresses of `scratch` and `ce_done` on each device, once looked up
+void* g_scratch_ptr[MAX_DEVICES] = {};
+void* g_done_ptr[MAX_DEVICES] = {};
 // Process-wide settings: read by every call, written by the setters (any thread).
 std::atomic<size_t> g_budget{0};   // 0 = the automatic rule of effective_budget()
 std::atomic<bool> g_compact{true};
+std::atomic<unsigned> g_ce_turn{0};   // which counters the next stand-alone cross entropy takes
 
 // What a call's plan depends on besides the shape: the process-wide settings, or the
 // options a caller passes with the call.
@@ -293,16 +301,21 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
 template <typename T>
 int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int64_t V,
                    int zero_pad, int64_t ignore_index, DeviceHeader* hdr, float* row_loss,
-                   hipStream_t s, const int* n_rows, bool timed, int count_n, float weight, bool fused) {
+                   hipStream_t s, const int* n_rows, bool timed, int count_n, float weight, bool fused,
+                   unsigned* done = nullptr, float* loss = nullptr) {
     ScopedKernelTimer timer(timed ? FLCE_KIND_CE_ROWS : -1, s);
     // shape by row length, nontemporal accesses by size: see ce_rows_kernel
     const int64_t row_bytes = V * (int64_t)sizeof(T);
     const bool nt = !fused && rows * row_bytes > CE_CACHE_BYTES;
-#define CE_LAUNCH(TH, NV, NT, NL)                                                                      \
-    hipLaunchKernelGGL((ce_rows_kernel<T, TH, NV, NT, NL>), dim3((unsigned)rows), dim3(TH), 0, s, Z, ldz,  \
-                       targets, (int)V, zero_pad, ignore_index, hdr, row_loss, n_rows, count_n, weight)
+#define CE_LAUNCH(TH, NV, NT, NL, FOLD)                                                                     \
+    hipLaunchKernelGGL((ce_rows_kernel<T, TH, NV, NT, NL, FOLD>), dim3((unsigned)rows), dim3(TH), 0, s, Z, ldz,  \
+                       targets, (int)V, zero_pad, ignore_index, hdr, row_loss, n_rows, count_n, weight, done, loss)
 #define CE_SHAPE(TH, NV, NL) \
-    do { if (nt) CE_LAUNCH(TH, NV, true, NL); else CE_LAUNCH(TH, NV, false, NL); } while (0)
+    do {                                                                                             \
+        if (done) CE_LAUNCH(TH, NV, false, NL, true);                                                \
+        else if (nt) CE_LAUNCH(TH, NV, true, NL, false);                                             \
+        else CE_LAUNCH(TH, NV, false, NL, false);                                                    \
+    } while (0)
     if (row_bytes > 400 * 1024) CE_SHAPE(RC_THREADS, RC_NV, RC_NL);
     else if (row_bytes > 112 * 1024) CE_SHAPE(RC_THREADS, RC_NV, 0);
     else if (row_bytes > 48 * 1024) CE_SHAPE(RM_THREADS, RM_NV, 0);
@@ -747,11 +760,14 @@ int check_ce_args(const void* Z, const int64_t* targets, int64_t BT, int64_t V, 
 }
 
 // Stand-alone cross entropy on logits Z, `step` rows per launch, with the device header
-// and the per-row losses (`step` floats) in memory the caller of this function provides.
+// and the per-row losses (`step` floats) in memory the caller of this function provides; done:
+// ce_rows_kernel's counters, or null.
 int run_ce_inplace(void* Z, const int64_t* targets, int64_t BT, int64_t V, int64_t ldz,
                    int64_t ignore_index, int dtype, float* loss, DeviceHeader* hdr, float* row_loss,
-                   int64_t step, bool timed, hipStream_t s) {
+                   int64_t step, unsigned* done, bool timed, hipStream_t s) {
     const int count_n = BT <= ce_count_rows(V * (int64_t)elem_size(dtype)) && BT <= step ? (int)BT : 0;
+    // (logits beyond the memory-side cache: milliseconds, and they want the nontemporal variants)
+    if (!count_n || BT > CE_FOLD_ROWS || BT * V * (int64_t)elem_size(dtype) > CE_CACHE_BYTES) done = nullptr;
     if (!count_n) {
         hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
                            1.0f, hdr);
@@ -761,13 +777,34 @@ int run_ce_inplace(void* Z, const int64_t* targets, int64_t BT, int64_t V, int64
         const int64_t rows = (BT - r0 < step) ? BT - r0 : step;
         if (dtype == FLCE_F32)
             FLCE_TRY(launch_ce_rows<float>(static_cast<float*>(Z) + r0 * ldz, ldz, targets + r0,
-                                           rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f, false));
+                                           rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f, false,
+                                           done, loss));
         else
             FLCE_TRY(launch_ce_rows<bf16_t>(static_cast<bf16_t*>(Z) + r0 * ldz, ldz, targets + r0,
-                                            rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f, false));
-        FLCE_TRY(launch_loss(row_loss, rows, hdr,
+                                            rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f, false,
+                                            done, loss));
+        if (!done) FLCE_TRY(launch_loss(row_loss, rows, hdr,
                              r0 + rows == BT ? LossOut{hdr, 1, loss, nullptr, {1.0f}} : LossOut{}, timed, s));
     }
+    return FLCE_OK;
+}
+
+// The current device's copies of `scratch` and `ce_done` (on the first call on a device the runtime is asked).
+int static_addresses(unsigned char** scratch_at, unsigned** done_at) {
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    if (dev < 0 || dev >= MAX_DEVICES) return FLCE_ERR_ARG;
+    std::lock_guard<std::mutex> lock(g_mutex);
+    if (!g_scratch_ptr[dev]) {
+        void *p = nullptr, *q = nullptr;
+        HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
+        HIP_TRY(hipGetSymbolAddress(&q, HIP_SYMBOL(ce_done)));
+        if (!p || !q) return FLCE_ERR_HIP;
+        g_scratch_ptr[dev] = p;
+        g_done_ptr[dev] = q;
+    }
+    *scratch_at = static_cast<unsigned char*>(g_scratch_ptr[dev]);
+    *done_at = static_cast<unsigned*>(g_done_ptr[dev]);
     return FLCE_OK;
 }
 
@@ -928,9 +965,12 @@ int flce_cross_entropy_inplace(void* Z, const int64_t* targets, int64_t BT, int6
     const int64_t step = BT < CE_ROWS_PER_LAUNCH ? BT : CE_ROWS_PER_LAUNCH;
     char* ws = nullptr;
     FLCE_TRY(acquire_workspace(256 + (size_t)step * sizeof(float), &ws));
+    unsigned* done = nullptr;   // (no address: a launch more)
+    unsigned char* unused;
+    if (BT <= CE_FOLD_ROWS && static_addresses(&unused, &done) == FLCE_OK) done += (1 + g_ce_turn.fetch_add(1) % CE_DONE_TURNS) * DONE_WORDS;
     return run_ce_inplace(Z, targets, BT, V, ldz, ignore_index, dtype, loss,
                           reinterpret_cast<DeviceHeader*>(ws), reinterpret_cast<float*>(ws + 256), step,
-                          true, static_cast<hipStream_t>(stream));
+                          done, true, static_cast<hipStream_t>(stream));
 }
 
 int flce_cross_entropy_inplace_noalloc(void* Z, const int64_t* targets, int64_t BT, int64_t V,
@@ -938,27 +978,15 @@ int flce_cross_entropy_inplace_noalloc(void* Z, const int64_t* targets, int64_t 
                                        void* stream) {
     FLCE_TRY(check_ce_args(Z, targets, BT, V, ldz, ignore_index, dtype, loss));
     if (BT > FLCE_CE_NOALLOC_MAX_ROWS) return FLCE_ERR_TOO_LARGE;
-    int dev = 0;
-    HIP_TRY(hipGetDevice(&dev));
-    if (dev < 0 || dev >= MAX_DEVICES) return FLCE_ERR_ARG;
-    char* ptr = nullptr;
-    {
-        // first call on this device: ask the runtime where this device's copy of the array is
-        std::lock_guard<std::mutex> lock(g_mutex);
-        if (!g_scratch_ptr[dev]) {
-            void* p = nullptr;
-            HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-            if (!p) return FLCE_ERR_HIP;
-            g_scratch_ptr[dev] = p;
-        }
-        ptr = static_cast<char*>(g_scratch_ptr[dev]);
-    }
+    unsigned char* ptr = nullptr;
+    unsigned* done = nullptr;
+    FLCE_TRY(static_addresses(&ptr, &done));
     // The header is reset by the counting kernel or, for small batches, by the row kernel, and every
     // row's loss slot is written by the row kernel before it is summed, so nothing of the previous
     // call's contents is read.
     return run_ce_inplace(Z, targets, BT, V, ldz, ignore_index, dtype, loss,
                           reinterpret_cast<DeviceHeader*>(ptr), reinterpret_cast<float*>(ptr + 256), BT,
-                          false, static_cast<hipStream_t>(stream));
+                          done, false, static_cast<hipStream_t>(stream));
 }
 
 size_t flce_workspace_bytes(int64_t BT, int64_t H, int64_t V, int dtype) {

@@ -46,3 +46,23 @@ def test_rows_at_any_address(dtype, tol, V, ldz, offset):
     mask = torch.ones_like(flat, dtype=torch.bool)
     mask[offset:offset + rows * ldz].view(rows, ldz)[:, :V] = False
     assert torch.equal(flat[mask], before[mask])
+
+
+@pytest.mark.parametrize("V", [64, 30000, 100003])   # one row length per shape of the kernel (bf16)
+@pytest.mark.parametrize("rows", [1, 2, 511, 512, 513, 1024, 1025, 1536, 1537])   # both sides of what one launch serves
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_loss_of_small_batches_in_repeated_calls(V, rows, noalloc):
+    """Where the last workgroup of the row kernel sums the loss, its counter has to be zero again for the
+    next call, whichever entry point and however many rows that has."""
+    import paper_2410_10989_amd as flce
+    g = torch.Generator(device="cuda").manual_seed(rows + V)
+    Z0 = (torch.randn(rows, V, device="cuda", generator=g)).to(torch.bfloat16)
+    t = torch.randint(0, V, (rows,), device="cuda", generator=g)
+    t[torch.rand(rows, device="cuda", generator=g) < 0.2] = -100
+    lse = torch.logsumexp(Z0.double(), 1)
+    for n in (rows, max(1, rows // 2), rows, rows):
+        tn, ok = t[:n], t[:n] != -100
+        want = float(((lse[:n] - Z0[:n].double().gather(1, tn.clamp(min=0)[:, None])[:, 0]) * ok).sum() / max(1, int(ok.sum())))
+        loss = flce.flce_cross_entropy_inplace(Z0[:n].clone(), tn, -100, noalloc=noalloc)
+        # a row's loss is a 32-bit number of size log V + |z| <= 20: rounded to 2^-20, some such steps in it
+        assert abs(float(loss) - want) <= 1e-5, n
