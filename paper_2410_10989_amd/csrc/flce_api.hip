@@ -93,10 +93,10 @@ size_t single_chunk_bytes(const Settings& st, int64_t H, int64_t V, int dtype) {
 
 // An explicit budget never takes the full plan: its caller limits memory (see Room).
 Plan plan_for(const Settings& st, int64_t BT, int64_t H, int64_t V, int dtype, Room room = Room::full,
-              bool worst_case_bt = false) {
+              bool worst_case_bt = false, size_t part_bytes = SIZE_MAX) {
     if (st.budget && room == Room::full) room = Room::bounded;
     return make_plan(BT, H, V, dtype, effective_budget(st, V, dtype), worst_case_bt, st.compact,
-                     single_chunk_bytes(st, H, V, dtype), room);
+                     single_chunk_bytes(st, H, V, dtype), room, part_bytes);
 }
 Plan plan_for(int64_t BT, int64_t H, int64_t V, int dtype) { return plan_for(global_settings(), BT, H, V, dtype); }
 
@@ -178,6 +178,16 @@ int acquire_workspace(size_t need, char** out, bool last = true) {
         w.own_bytes = need;
     }
     *out = static_cast<char*>(w.own);
+    return FLCE_OK;
+}
+
+// Bytes of the buffer lent to the current device, 0 if there is none.
+int lent_workspace(size_t* bytes) {
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    if (dev < 0 || dev >= MAX_DEVICES) return FLCE_ERR_ARG;
+    std::lock_guard<std::mutex> lock(g_mutex);
+    *bytes = g_ws[dev].lent ? g_ws[dev].lent_bytes : 0;
     return FLCE_OK;
 }
 
@@ -466,7 +476,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             tc = tv;
             dyn_m.rows = dyn_dx.rows = dyn_dw.rows = n_live;
             dyn_dw.is_k = 1;
-            if (p.fast_dx && p.dx_tile == 256) dyn_dx.ksplit = dyn + DYN_DX_RANGES;
+            if (p.dx_dyn) dyn_dx.ksplit = dyn + DYN_DX_RANGES;
             dyn_dw.first_live = dyn + DYN_FIRST_LIVE;
             dyn_dw.launch = (int)c;
         }
@@ -697,16 +707,24 @@ int plan_and_workspace(const Settings& st, int64_t BT, int64_t H, int64_t V, int
             FLCE_TRY(check_launch_limits(*p, H, V));
             if (st.ws && !aligned(st.ws, 256)) return FLCE_ERR_ALIGN;
         }
+        auto take = [&](size_t need) -> int {
+            if (!st.ws) return acquire_workspace(need, ws, room == Room::least);
+            *ws = static_cast<char*>(st.ws);
+            return st.ws_bytes >= need ? FLCE_OK : FLCE_ERR_WORKSPACE;
+        };
         const size_t need = need_of(*p);
-        if (st.ws) {
-            if (st.ws_bytes >= need) {
-                *ws = static_cast<char*>(st.ws);
-                return FLCE_OK;
+        int rc = take(need);
+        if (rc == FLCE_ERR_WORKSPACE && room == Room::full) {
+            // a buffer between the bounded plan and this one: as many K ranges as there is room for
+            size_t have = st.ws_bytes;
+            if (!st.ws) FLCE_TRY(lent_workspace(&have));
+            if (have < need && need - have < p->dxpart_bytes &&
+                have >= need_of(plan_for(st, BT, H, V, dtype, Room::bounded))) {
+                *p = plan_for(st, BT, H, V, dtype, room, false, p->dxpart_bytes - (need - have));
+                rc = take(need_of(*p));
             }
-        } else {
-            const int rc = acquire_workspace(need, ws, room == Room::least);
-            if (rc != FLCE_ERR_WORKSPACE) return rc;
         }
+        if (rc != FLCE_ERR_WORKSPACE) return rc;
     }
     return FLCE_ERR_WORKSPACE;
 }

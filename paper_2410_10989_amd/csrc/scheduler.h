@@ -85,13 +85,15 @@ struct Plan {
     bool fast_logits = false, fast_dx = false, fast_dw_full = false, fast_dw_last = false;
     int dx_ranges = 1;     // K ranges of the dX product (K = V), > 1 when C x H has few tiles
     int dx_tile = 256;     // its tile size
+    bool dx_dyn = false;   // several rounds of large tiles: fewer live rows may want fewer ranges
     // chunks are compacted, i.e. rows with an ignored target are left out of the products (see
     // compact.h)
     bool compact = false;
     // byte offsets into the workspace
     size_t off_hdr = 0, off_row_loss = 0, off_z = 0, off_dwacc = 0, off_dxpart = 0, off_xg = 0, off_dxg = 0, off_idx = 0, off_tv = 0,
            off_dyn = 0, off_tail = 0, total = 0;
-    size_t tail_bytes = 0;   // room at off_tail
+    size_t tail_bytes = 0;     // room at off_tail
+    size_t dxpart_bytes = 0;   // room at off_dxpart
 };
 
 // How many K ranges to cut a product with `tiles` output tiles and `ksteps` K steps
@@ -161,16 +163,36 @@ inline int64_t cut_ns(int64_t tiles, int64_t tile, int64_t ranges) {
     return ranges > 1 ? 4000 + tiles * tile * tile * ranges / 1000 : 0;
 }
 
+// A dX product whose operands (G and W: (rows + H) V bf16) do not stay in the 256 MB memory-side cache is
+// bound by how many loads the CUs have in flight: a step of a 128-tile takes 0.78 us alone on a CU (0.83
+// at 24 rows, 0.79 at 512, 0.75 at 2048) and 0.62 to 0.75 beside another, of a 256-tile 1.7.  So one round of
+// large tiles in up to 64 ranges, or two small tiles per CU, serve such products.  Measured (M x N x K, 128-tiles
+// alone / two per CU / 256-tiles, ranges in parentheses, us):
+//   24 x 4096 x 128256    208 (8) / 183 (16) / 181 (16)       200 x 832 x 128256    82 (18) / 66 (36) / 64 (64)
+//   512 x 512 x 128256    100 (16) / 87 (32) / 74 (64)        1024 x 512 x 128256  197 (8) / 164 (16) / 117 (32)
+//   2048 x 512 x 128256   377 (4) / 301 (8) / 219 (16)        512 x 2048 x 128256  376 (4) / 315 (8) / 217 (16)
+// and where they do stay: 1024 x 512 x 32000 39.9 (8) / 37.6 (16) / 38.5 (32), 2048 x 2048 x 8192 73.5 (1) / 65 (2) / 61 (4).
+constexpr int64_t DX_STREAM_BYTES = (int64_t)256 << 20;
+inline bool dx_streams(int64_t rows, int64_t H, int64_t V) { return (rows + H) * V * 2 > DX_STREAM_BYTES; }
+inline int64_t dx_streaming_ns(int tile, int64_t tiles, int64_t k) {
+    const int64_t n = rounds_of_256(tiles), steps = (k + 63) / 64;
+    return tile == 256 ? n * (1700 * steps + 4000) : n == 1 ? 780 * steps + 650 : n * (700 * steps + 650);
+}
+
 // The dX product of a chunk (rows x H output, K = V): tile size and K ranges.  The tuned kernel's
-// large tiles keep at least 64 K steps per range (choose_ksplit), the others 512 elements (64-tiles 256).
+// large tiles keep at least 64 K steps per range (choose_ksplit; 16 where a streaming product fills one
+// round), the others 512 elements (64-tiles 256).
 struct ProductCut {
     int tile, ranges;
 };
 //
 // bounded: the partial results may take no more memory than those of the large tiles cut to fill
 // whole rounds (choose_ksplit, at most 16 ranges), which for many small products is none at all.
-inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes, bool bounded) {
+// part_bytes: room for the partial results.
+inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t budget_bytes, bool bounded,
+                         size_t part_bytes = SIZE_MAX) {
     int max_ranges = max_dx_ranges(budget_bytes, round_up(rows, 256), H);
+    max_ranges = (int)std::min<size_t>((size_t)max_ranges, std::max<size_t>(1, part_bytes / ((size_t)rows * H * sizeof(float))));
     if (bounded) {
         const int tile = tuned ? 256 : 128;
         max_ranges = std::min(max_ranges, choose_ksplit(tiles_of(rows, H, tile), tuned ? (V + 63) / 64 : V / 4,
@@ -178,9 +200,11 @@ inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t 
     }
     ProductCut best{0, 1};
     int64_t best_ns = 0;
+    const bool streams = tuned && dx_streams(rows, H, V);
     auto consider = [&](int tile, int ranges) {
-        const int64_t t = tiles_of(rows, H, tile);
-        const int64_t ns = product_ns(tuned, tile, t * ranges, (V + ranges - 1) / ranges) + cut_ns(t, tile, ranges);
+        const int64_t t = tiles_of(rows, H, tile), k = (V + ranges - 1) / ranges;
+        const int64_t ns = (streams ? dx_streaming_ns(tile, t * ranges, k) : product_ns(tuned, tile, t * ranges, k)) +
+                           cut_ns(t, tile, ranges);
         if (!best.tile || ns < best_ns) {
             best = {tile, ranges};
             best_ns = ns;
@@ -193,6 +217,7 @@ inline ProductCut dx_cut(bool tuned, int64_t rows, int64_t H, int64_t V, size_t 
             consider(64, r);
         }
         if (r == 1 || V / r >= 512) consider(128, r);
+        if (streams && V / r >= 1024 && tiles_of(rows, H, 256) * r <= 256) consider(256, r);
     }
     return best;
 }
@@ -246,7 +271,7 @@ enum class Room { full, bounded, least };
 // Byte offsets of the workspace for a plan whose chunking (C, nchunks, rows of the last
 // chunk) is decided; `dxpart_floor` is a lower bound for the K-range partials.
 inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last, size_t budget_bytes,
-                    bool allow_compact, size_t dxpart_floor, Room room) {
+                    bool allow_compact, size_t dxpart_floor, Room room, size_t part_bytes = SIZE_MAX) {
     const size_t es = elem_size(dtype);
     p.fp32_dw_acc = (dtype != 0) && p.nchunks > 1;
     p.fast_logits = p.fast_dx = p.fast_dw_full = p.fast_dw_last = false;
@@ -265,9 +290,10 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     }
     {
         const int64_t rows = p.nchunks > 1 ? p.C : rows_last;
-        const ProductCut cut = dx_cut(p.fast_dx, rows, H, V, budget_bytes, room != Room::full);
+        const ProductCut cut = dx_cut(p.fast_dx, rows, H, V, budget_bytes, room != Room::full, part_bytes / p.C * rows);
         p.dx_tile = cut.tile;
         p.dx_ranges = cut.ranges;
+        p.dx_dyn = p.fast_dx && cut.tile == 256 && tiles_of(rows, H, 256) * cut.ranges > 256;
     }
     // (the copies move 16-byte vectors; bf16 rows of other lengths do not run on the tuned kernel)
     p.compact = allow_compact && !(room == Room::least && dtype != 0 && H % 64 != 0) &&
@@ -290,7 +316,8 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
     p.off_z = take((size_t)p.C * p.ldz * es);
     p.off_dwacc = take(p.fp32_dw_acc ? (size_t)V * H * sizeof(float) : 0);
     const size_t dxpart = p.dx_ranges > 1 ? (size_t)p.dx_ranges * p.C * H * sizeof(float) : 0;
-    p.off_dxpart = take(std::max(dxpart, dxpart_floor));
+    p.dxpart_bytes = std::max(dxpart, dxpart_floor);
+    p.off_dxpart = take(p.dxpart_bytes);
     // a chunk of gathered input rows and of their gradient (also the normalised rows and
     // their gradient when an RMSNorm runs in front)
     p.off_xg = take((size_t)p.C * H * es);
@@ -312,7 +339,7 @@ inline void lay_out(Plan& p, int64_t H, int64_t V, int dtype, int64_t rows_last,
 // can lead to (BT is ignored).
 inline Plan make_plan(int64_t BT, int64_t H, int64_t V, int dtype, size_t budget_bytes,
                       bool worst_case_bt = false, bool allow_compact = true, size_t single_bytes = 0,
-                      Room room = Room::full) {
+                      Room room = Room::full, size_t part_bytes = SIZE_MAX) {
     Plan p;
     const size_t es = elem_size(dtype);
     p.ldz = round_up(V, 64);
@@ -358,7 +385,7 @@ inline Plan make_plan(int64_t BT, int64_t H, int64_t V, int dtype, size_t budget
         p.nchunks = (BT + p.C - 1) / p.C;
         rows_last = BT - (p.nchunks - 1) * p.C;
     }
-    lay_out(p, H, V, dtype, rows_last, budget_bytes, allow_compact, 0, room);
+    lay_out(p, H, V, dtype, rows_last, budget_bytes, allow_compact, 0, room, part_bytes);
     return p;
 }
 

@@ -218,6 +218,21 @@ def test_workspace_without_the_fast_plan(BT, H, V, compacted, how):
         call(need - 256)
 
 
+@pytest.mark.parametrize("share", [0.0, 0.5, 1.0])   # of the room between the bounded plan's and the full one's
+def test_product_that_streams_w_in_any_room(share):
+    # operands beyond the memory-side cache: dX in up to two workgroups per CU, fewer ranges in less room
+    import paper_2410_10989_amd as flce
+    BT, H, V = 24, 3584, 40003
+    X, W, t = make(BT, H, V, torch.bfloat16, "scattered", 7)
+    bounded = flce.flce_workspace_bytes_opt(BT, H, V, flce.FLCE_BF16, flce.flce_options(logits_budget_bytes=1 << 30))
+    full = flce.flce_workspace_bytes(BT, H, V, flce.FLCE_BF16)
+    assert bounded < full
+    buf = torch.full((full + 256,), 255, dtype=torch.uint8, device="cuda")
+    at = -buf.data_ptr() % 256
+    ws = buf[at:at + bounded + int((full - bounded) * share)]
+    check(flce.flce_fwd_bwd_opt(X, W, t, flce.flce_options(workspace=ws)), X, W, t, torch.bfloat16)
+
+
 @pytest.mark.parametrize("BT", [8192, 8193])   # 32 chunks of 256 rows selected by one launch each; 33 found with the cursor
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_selection_changes_over_with_the_chunk_count(BT, dtype):
