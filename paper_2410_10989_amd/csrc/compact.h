@@ -58,7 +58,8 @@ __device__ __forceinline__ int dx_ranges_of(int rows, int dx_tiles_n, int dx_kst
 }
 
 // Launch `c` of `nchunks` for a batch of at most SEL_MAX_ROWS rows: what compact_chunk_kernel,
-// count_valid_kernel, gather_rows_kernel and zero_ignored_rows_kernel do, in one launch.
+// count_valid_kernel, gather_rows_kernel and zero_ignored_rows_kernel do, in one launch, or as the first
+// workgroups of the logits launch (select_in_logits).
 // Workgroup b owns batch rows b R .. b R + R - 1 (R <= 64 rows); it counts the valid rows in front
 // of them and in the whole batch (every workgroup reads all targets), which gives each of its
 // rows its place in the chunk.  One wavefront per row copies it to Xg (X not null; with gamma it
@@ -66,15 +67,38 @@ __device__ __forceinline__ int dx_ranges_of(int rows, int dx_tiles_n, int dx_kst
 // gradient row (zero_out not null, row ignored).  Workgroup 0 writes the header (c = 0) and dyn.
 // Measured, 1024 rows of 512 bf16: 4 launches, 19 us -> one of 5; 4096 x 4096: 32 -> 15 us.
 template <typename T>
-__global__ __launch_bounds__(256) void select_rows_kernel(
-    const int64_t* __restrict__ targets, int BT, int64_t ignore_index, float weight, int C, int c, int nchunks,
-    int dx_tiles_n, int dx_ksteps, int dx_max_ranges, DeviceHeader* __restrict__ hdr, const T* __restrict__ X,
-    int n, T* __restrict__ Xg, T* __restrict__ zero_out, int* __restrict__ idx, int64_t* __restrict__ tv,
-    int* __restrict__ dyn, const T* __restrict__ gamma, float eps, float* __restrict__ rstd) {
-    __shared__ int part[4][2];
+struct SelectArgs {
+    const int64_t* targets;
+    int BT;
+    int64_t ignore_index;
+    float weight;
+    int C, c, nchunks;
+    int dx_tiles_n, dx_ksteps, dx_max_ranges;
+    DeviceHeader* hdr;
+    const T* X;
+    int n;
+    T* Xg;
+    T* zero_out;
+    int* idx;
+    int64_t* tv;
+    int* dyn;
+    const T* gamma;
+    float eps;
+    float* rstd;
+    int blocks;
+};
+template <typename T>
+__device__ __forceinline__ void select_rows(const SelectArgs<T>& s, int block, int (*part)[2]) {   // part: [4][2] in LDS
+    const int64_t* __restrict__ targets = s.targets;
+    const int64_t ignore_index = s.ignore_index;
+    const T* __restrict__ X = s.X;
+    const T* __restrict__ gamma = s.gamma;
+    T* __restrict__ Xg = s.Xg;
+    T* __restrict__ zero_out = s.zero_out;
+    const int BT = s.BT, C = s.C, c = s.c, nchunks = s.nchunks, n = s.n;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
-    const int R = (BT + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int r0 = min(BT, (int)blockIdx.x * R), r1 = min(BT, r0 + R);
+    const int R = (BT + s.blocks - 1) / s.blocks;
+    const int r0 = min(BT, block * R), r1 = min(BT, r0 + R);
     int before = 0, n_valid = 0;
 #pragma unroll 8
     for (int i = tid; i < BT; i += 256) {
@@ -94,11 +118,11 @@ __global__ __launch_bounds__(256) void select_rows_kernel(
     const RowDeal deal = deal_rows(n_valid, C, nchunks);
     const int begin = (c - deal.first_live) * deal.quota;   // of this chunk among the valid rows
     const int count = c < deal.first_live ? 0 : max(0, min(deal.quota, n_valid - begin));
-    if (blockIdx.x == 0 && tid == 0) {
-        if (c == 0) write_header(hdr, n_valid, weight);
-        dyn[DYN_LIVE] = count;
-        dyn[DYN_FIRST_LIVE] = deal.first_live;
-        dyn[DYN_DX_RANGES] = dx_ranges_of(count, dx_tiles_n, dx_ksteps, dx_max_ranges);
+    if (block == 0 && tid == 0) {
+        if (c == 0) write_header(s.hdr, n_valid, s.weight);
+        s.dyn[DYN_LIVE] = count;
+        s.dyn[DYN_FIRST_LIVE] = deal.first_live;
+        s.dyn[DYN_DX_RANGES] = dx_ranges_of(count, s.dx_tiles_n, s.dx_ksteps, s.dx_max_ranges);
     }
     const int64_t t = (r0 + lane < r1) ? targets[r0 + lane] : ignore_index;
     const unsigned long long mask = __ballot(t != ignore_index);
@@ -116,8 +140,8 @@ __global__ __launch_bounds__(256) void select_rows_kernel(
             for (int v = lane; v < nv; v += WAVE) dst[v] = zero;
         } else if (place >= 0 && place < count) {
             if (lane == 0) {
-                idx[place] = r;
-                tv[place] = targets[r];
+                s.idx[place] = r;
+                s.tv[place] = targets[r];
             }
             if (!X) continue;
             const u32x4* src = reinterpret_cast<const u32x4*>(X + (int64_t)r * n);
@@ -137,20 +161,88 @@ __global__ __launch_bounds__(256) void select_rows_kernel(
                 for (int e = 0; e < VEC; ++e) ss += x[e] * x[e];
             }
             ss = wave_sum(ss);
-            const float s = 1.0f / sqrtf(ss / (float)n + eps);
-            if (lane == 0) rstd[place] = s;
+            const float scale = 1.0f / sqrtf(ss / (float)n + s.eps);
+            if (lane == 0) s.rstd[place] = scale;
 #pragma unroll 4
             for (int v = lane; v < nv; v += WAVE) {   // (the row comes from cache this time)
                 float x[VEC], g[VEC];
                 RowVec<T>::unpack(src[v], x);
                 RowVec<T>::unpack(gr[v], g);
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) x[e] = x[e] * s * g[e];
+                for (int e = 0; e < VEC; ++e) x[e] = x[e] * scale * g[e];
                 dst[v] = RowVec<T>::pack(x);
             }
         }
     }
 }
+
+template <typename T>
+__global__ __launch_bounds__(256) void select_rows_kernel(SelectArgs<T> s) {
+    __shared__ int part[4][2];
+    select_rows(s, (int)blockIdx.x, part);
+}
+
+// The selection inside the logits launch of a batch that is one chunk: its workgroups come first and leave
+// what the later launches read; the product's workgroups do not wait for them, each finds the rows of
+// its tile by itself.
+//
+// Valid rows of the batch, and which ones have the places m0 .. m0 + count - 1 among them: begin() by all
+// wavefronts of a workgroup, then place().  Wavefront w looks at its share of the batch, 64 rows at a time, and
+// keeps the first KEEP of these masks (2048 rows and 4 wavefronts: all of them) for place().
+template <int WAVES>
+struct TileRows {
+    static constexpr int KEEP = 8;
+    const int64_t* __restrict__ targets;
+    int64_t ignore_index;
+    int r0, r1, before;   // the wavefront's share, and the valid rows in front of it
+    unsigned long long kept[KEEP];
+
+    __device__ __forceinline__ unsigned long long look(int r) const {   // r: of the first of 64 rows
+        const int mine = r + (int)(threadIdx.x & (WAVE - 1));
+        return __ballot(targets[min(mine, r1 - 1)] != ignore_index && mine < r1);   // (no branch around the load)
+    }
+    __device__ __forceinline__ int begin(const int64_t* t, int BT, int64_t ignore, int* totals) {   // totals: [WAVES] in LDS
+        targets = t;
+        ignore_index = ignore;
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+        const int per = (BT + WAVES * WAVE - 1) / (WAVES * WAVE) * WAVE;
+        r0 = min(BT, wave * per);
+        r1 = min(BT, r0 + per);
+        int n = 0;
+        if (r0 < r1) {
+#pragma unroll
+            for (int g = 0; g < KEEP; ++g) kept[g] = look(r0 + g * WAVE);
+#pragma unroll
+            for (int g = 0; g < KEEP; ++g) n += __popcll(kept[g]);
+            for (int r = r0 + KEEP * WAVE; r < r1; r += WAVE) n += __popcll(look(r));
+        }
+        if ((threadIdx.x & (WAVE - 1)) == 0) totals[wave] = n;
+        __syncthreads();
+        int all = 0;
+        before = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            before += w < wave ? totals[w] : 0;
+            all += totals[w];
+        }
+        return __builtin_amdgcn_readfirstlane(all);
+    }
+    __device__ __forceinline__ void place(int m0, int count, int* rows) const {   // rows: [count] in LDS
+        const int lane = threadIdx.x & (WAVE - 1);
+        int at = before - m0;
+        auto put = [&](int r, unsigned long long mask) {
+            const int mine = at + __popcll(mask & ((1ull << lane) - 1));
+            if (mask >> lane & 1 && mine >= 0 && mine < count) rows[mine] = r + lane;
+            at += __popcll(mask);
+        };
+        if (r0 < r1) {
+#pragma unroll
+            for (int g = 0; g < KEEP; ++g) put(r0 + g * WAVE, kept[g]);
+            for (int r = r0 + KEEP * WAVE; r < r1 && at < count; r += WAVE) put(r, look(r));
+        }
+        __syncthreads();
+    }
+};
 
 // One workgroup; launch `c` of `nchunks`, each sized for `C` rows.  The N valid rows of
 // the batch (N = hdr->n_valid, counted before the loop) are dealt evenly to the LAST

@@ -36,6 +36,7 @@ namespace {
 constexpr int MAX_DEVICES = 64;
 constexpr int64_t MAX_DIM = (int64_t)1 << 30;      // per-dimension limit, keeps int tile math safe
 constexpr int64_t CE_ROWS_PER_LAUNCH = 65536;
+constexpr int64_t SEL_IN_LOGITS_ROWS = 4096, SEL_ROWS_IN_LOGITS = 8;
 constexpr int RIDE_BLOCKS = 1024;   // finish_dx as workgroups of the dW launch: at most this many
 constexpr int64_t ROT_A_BYTES = (int64_t)2 << 20;
 constexpr int64_t CE_CACHE_BYTES = (int64_t)256 << 20;   // memory-side cache
@@ -207,7 +208,8 @@ template <typename T, typename OutT, bool A_KM, bool B_KM>
 int launch_gemm_guarded(int kind, const T* A, int64_t lda, const T* B, int64_t ldb, OutT* C, int64_t ldc,
                         const float* Cin, const OutT* cin_own, int64_t M, int64_t N, int64_t K,
                         hipStream_t s, int tile, int ksplit = 1, int64_t split_stride = 0,
-                        const FastDyn& d = FastDyn{}, const FinishArgs* fin = nullptr) {
+                        const FastDyn& d = FastDyn{}, const FinishArgs* fin = nullptr,
+                        const SelectArgs<T>* sel = nullptr) {
     if (M <= 0 || N <= 0) return FLCE_OK;
     if (ksplit > 1 && (Cin || cin_own)) return FLCE_ERR_SHAPE;
     ScopedKernelTimer timer(kind, s);
@@ -220,14 +222,24 @@ int launch_gemm_guarded(int kind, const T* A, int64_t lda, const T* B, int64_t l
              FG_GROUP_TILES, kind == FLCE_KIND_LOGITS_GEMM ? 1 : 0, 1};
     const int64_t total = ((M + tile - 1) / tile) * ((N + tile - 1) / tile) * ksplit;
     if (total > MAX_GRID_X - FG_XCDS) return FLCE_ERR_SHAPE;   // check_launch_limits refuses such shapes up front
-    const dim3 grid((unsigned)((total + FG_XCDS - 1) / FG_XCDS * FG_XCDS + (fin ? fin->blocks : 0)));
+    const dim3 grid((unsigned)((total + FG_XCDS - 1) / FG_XCDS * FG_XCDS + (fin ? fin->blocks : sel ? sel->blocks : 0)));
     const dim3 block((unsigned)gg_threads(tile));
     // finish_dx rides along with the dW product of fp32 storage
     constexpr bool CAN_FIN = A_KM && B_KM && std::is_same<T, float>::value;
     if (fin && (!CAN_FIN || tile == 256)) return FLCE_ERR_SHAPE;   // (ride_along keeps such calls away)
+    // the selection of the rows with the logits product of fp32 storage
+    constexpr bool CAN_SEL = !A_KM && !B_KM && std::is_same<T, float>::value && std::is_same<OutT, float>::value;
+    if (sel && (!CAN_SEL || tile == 256)) return FLCE_ERR_SHAPE;   // (select_in_logits keeps such calls away)
 #define GG_LAUNCH(TILE) \
     hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, TILE>), grid, block, 0, s, a, NoFinish{})
-    if (fin) {
+    if (sel) {
+        if constexpr (CAN_SEL) {
+            if (tile == 64)
+                hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64, SelectArgs<T>>), grid, block, 0, s, a, *sel);
+            else
+                hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 128, SelectArgs<T>>), grid, block, 0, s, a, *sel);
+        }
+    } else if (fin) {
         if constexpr (CAN_FIN) {
             if (tile == 64)
                 hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64, FinishArgs>), grid, block, 0, s, a, *fin);
@@ -251,7 +263,8 @@ template <typename OutT, typename InT, bool A_KM, bool B_KM>
 int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, OutT* C,
                      int64_t ldc, const InT* Cin, int64_t ldcin, int64_t M, int64_t N, int64_t K,
                      hipStream_t s, int tile, int ksplit = 1, int64_t split_stride = 0, const FastDyn& d = FastDyn{},
-                     float* tail_part = nullptr, size_t tail_bytes = 0, const FinishArgs* fin = nullptr) {
+                     float* tail_part = nullptr, size_t tail_bytes = 0, const FinishArgs* fin = nullptr,
+                     const SelectArgs<bf16_t>* sel = nullptr) {
     if (M <= 0 || N <= 0 || K <= 0) return FLCE_OK;
     if (!aligned(A, 16) || !aligned(B, 16)) return FLCE_ERR_ARG;
     ScopedKernelTimer timer(kind, s);
@@ -272,7 +285,7 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
             wgs_per_xcd = (int64_t)t.begin + (int64_t)t.r * t.s;
         }
     }
-    const dim3 grid((unsigned)(wgs_per_xcd * FG_XCDS + (fin ? fin->blocks : 0)));
+    const dim3 grid((unsigned)(wgs_per_xcd * FG_XCDS + (fin ? fin->blocks : sel ? sel->blocks : 0)));
     constexpr bool CAN_FIN = A_KM && B_KM && std::is_void<InT>::value && std::is_same<OutT, bf16_t>::value;
     if (fin && (!CAN_FIN || tile != 128)) return FLCE_ERR_SHAPE;   // (ride_along keeps such calls away)
     // Row-form operands, one 256-row tile: B is fetched once, and all of A stays in an XCD's L2 (4 MB)
@@ -285,9 +298,18 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
     constexpr int ROT = ROWS ? FG_ROTATED : FG_PLAIN, CUT = ROWS ? FG_K_TAIL : FG_PLAIN;
     const bool tail = ROWS && K % FG_BK != 0;
     const bool rot = ROWS && !tail && M <= FG_BM && M * K * (int64_t)sizeof(bf16_t) <= ROT_A_BYTES;
+    constexpr bool CAN_SEL = ROWS && std::is_void<InT>::value && std::is_same<OutT, bf16_t>::value;
+    if (sel && (!CAN_SEL || tile != 128)) return FLCE_ERR_SHAPE;   // (select_in_logits keeps such calls away)
 #define FG_LAUNCH(TILE, ORDER) \
     hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, TILE, ORDER>), grid, dim3(FG_THREADS), 0, s, a, NoFinish{})
-    if (fin) {
+#define FG_LAUNCH_SEL(ORDER)                                                                                       \
+    hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, 128, ORDER, SelectArgs<bf16_t>>), grid, dim3(FG_THREADS), 0, \
+                       s, a, *sel)
+    if (sel) {
+        if constexpr (CAN_SEL) {
+            if (rot) FG_LAUNCH_SEL(FG_ROTATED); else if (tail) FG_LAUNCH_SEL(FG_K_TAIL); else FG_LAUNCH_SEL(FG_PLAIN);
+        }
+    } else if (fin) {
         if constexpr (CAN_FIN)
             hipLaunchKernelGGL((gemm_bf16<OutT, InT, A_KM, B_KM, 128, FG_PLAIN, FinishArgs>), grid, dim3(FG_THREADS), 0, s,
                                a, *fin);
@@ -297,6 +319,7 @@ int launch_gemm_fast(int kind, const bf16_t* A, int64_t lda, const bf16_t* B, in
         if (rot) FG_LAUNCH(256, ROT); else if (tail) FG_LAUNCH(256, CUT); else FG_LAUNCH(256, FG_PLAIN);
     }
 #undef FG_LAUNCH
+#undef FG_LAUNCH_SEL
     HIP_TRY(hipGetLastError());
     if (a.tail_s > 1) {
         hipLaunchKernelGGL((fg_tail_reduce_kernel<OutT, InT>), dim3((unsigned)(FG_XCDS * a.tail_r * 8)), dim3(256),
@@ -396,6 +419,22 @@ int rmsnorm_vectors_per_thread(int64_t H, const void* x, const void* gamma, cons
 // Partial rows of dgamma that a chunk of C rows can reach.
 inline unsigned rn_slots(int64_t C) { return (unsigned)std::min<int64_t>(C, RN_SLOTS); }
 
+// Whether a batch that is one chunk has its rows selected by workgroups of the logits launch.  That saves a
+// launch (4-5 us, on the host as well) and costs every tile its own look at the targets, 1-2 us per
+// workgroup: for launches that fit the chip, or of one tile row, where the look is short.  Whole calls with the
+// launch of its own / without, us: bf16 24 x 680 x 1026 26.9 / 24.1, 495 x 896 x 3674 36.5 / 33.7, 1572 x 576 x 2176 59.6 /
+// 53.5, 1024 x 512 x 8192 60 / 57, 51 x 3328 x 24297 129 / 119, one tile row in 1136 tiles (31 x 576 x 144923) 100.3 / 96.9;
+// 2664 tiles in three rows (294 x 128 x 113344) 110.5 / 112.9.  A handful of tiles with long K loops waits for its loads
+// alone, and the rows of X are further away than gathered ones: 30 x 2496 x 384 (3 tiles) 34.1 / 35.1,
+// 53 x 2352 x 2560 (20 tiles) 41.8 / 40.1.
+template <typename T>
+bool select_in_logits(const Plan& p, const VocabCut& cut, int64_t BT, int64_t H, int64_t V) {
+    const int64_t tiles = tiles_of(BT, V, cut.tile);
+    return p.nchunks == 1 && cut.main == V && cut.tile < 256 && BT <= SEL_IN_LOGITS_ROWS &&
+           BT * H * (int64_t)sizeof(T) < ((int64_t)1 << 30) && tiles <= (BT <= cut.tile ? 4096 : 512) &&
+           (tiles >= 16 || H <= 1024);
+}
+
 // One head: count its valid rows, then run the chunk loop.  Gradients are scaled by
 // weight / N_valid.  With dx_add the head's dX is added to what dX already holds
 // (rounded to the storage type once per head), otherwise dX is overwritten.  loss_out: where the
@@ -455,18 +494,23 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         const T* Xin = compact ? X : X + r0 * H;   // what the chunk's row indices refer to
         const T* Xc = Xin;
         const int64_t* tc = targets + r0;
+        const VocabCut z_cut = vocab_cut(BF16 && p.fast_logits, V, rows, H, false);
+        const bool in_logits = select && !norm && select_in_logits<T>(p, z_cut, BT, H, V);
+        SelectArgs<T> sel{};
         FastDyn dyn_m, dyn_dx, dyn_dw;   // logits (M = live rows), dX (M and K ranges), dW (K = live rows)
         if (compact) {
             ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
             const int dx_tiles_n = (int)((H + FG_BN - 1) / FG_BN), dx_ksteps = (int)((V + FG_BK - 1) / FG_BK);
             if (select) {
-                const int64_t grid = std::min<int64_t>((BT + 3) / 4, SEL_GRID);
-                hipLaunchKernelGGL((select_rows_kernel<T>), dim3((unsigned)grid), dim3(256), 0, s, targets, (int)BT,
-                                   ignore_index, weight, (int)p.C, (int)c, (int)p.nchunks, dx_tiles_n, dx_ksteps,
-                                   p.dx_ranges, hdr, norm && !norm_in_select ? static_cast<const T*>(nullptr) : X,
-                                   (int)H, Xg, c == 0 ? zero_out : static_cast<T*>(nullptr), idx, tv, dyn,
-                                   norm_in_select ? norm->gamma : static_cast<const T*>(nullptr),
-                                   norm ? norm->eps : 0.f, norm ? norm->rstd : static_cast<float*>(nullptr));
+                sel = {targets, (int)BT, ignore_index, weight, (int)p.C, (int)c, (int)p.nchunks, dx_tiles_n, dx_ksteps,
+                       p.dx_ranges, hdr, norm && !norm_in_select ? static_cast<const T*>(nullptr) : X, (int)H, Xg,
+                       c == 0 ? zero_out : static_cast<T*>(nullptr), idx, tv, dyn,
+                       norm_in_select ? norm->gamma : static_cast<const T*>(nullptr), norm ? norm->eps : 0.f,
+                       norm ? norm->rstd : static_cast<float*>(nullptr), (int)std::min<int64_t>((BT + 3) / 4, SEL_GRID)};
+                if (in_logits)
+                    sel.blocks = (int)((BT + SEL_ROWS_IN_LOGITS - 1) / SEL_ROWS_IN_LOGITS + FG_XCDS - 1) / FG_XCDS * FG_XCDS;
+                else
+                    hipLaunchKernelGGL((select_rows_kernel<T>), dim3((unsigned)sel.blocks), dim3(256), 0, s, sel);
             } else {
                 hipLaunchKernelGGL(compact_chunk_kernel, dim3(1), dim3(CP_THREADS), 0, s, targets, (int)BT,
                                    ignore_index, (int)p.C, (int)c, (int)p.nchunks, hdr, dx_tiles_n, dx_ksteps,
@@ -510,17 +554,20 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         // logits of the chunk: Z = X_c W^T
         {
             const bool fast = BF16 && p.fast_logits;
-            const VocabCut cut = vocab_cut(fast, V, rows, H, false);
+            const VocabCut& cut = z_cut;
+            const SelectArgs<T>* with = in_logits ? &sel : nullptr;   // (the rows are picked from X itself then)
+            const T* Xz = in_logits ? X : Xc;
+            const FastDyn dz = in_logits ? FastDyn{} : dyn_m;
             auto product = [&](int64_t v0, int64_t nv, int tile) -> int {   // columns v0 .. v0 + nv - 1
                 if constexpr (BF16) {
                     if (fast)
-                        return launch_gemm_fast<bf16_t, void, false, false>(FLCE_KIND_LOGITS_GEMM, Xc, H, W + v0 * H, H,
+                        return launch_gemm_fast<bf16_t, void, false, false>(FLCE_KIND_LOGITS_GEMM, Xz, H, W + v0 * H, H,
                                                                             Z + v0, p.ldz, nullptr, 0, rows, nv, H, s,
-                                                                            tile, 1, 0, dyn_m);
+                                                                            tile, 1, 0, dz, nullptr, 0, nullptr, with);
                 }
-                return launch_gemm_guarded<T, T, false, false>(FLCE_KIND_LOGITS_GEMM, Xc, H, W + v0 * H, H, Z + v0,
+                return launch_gemm_guarded<T, T, false, false>(FLCE_KIND_LOGITS_GEMM, Xz, H, W + v0 * H, H, Z + v0,
                                                                p.ldz, nullptr, nullptr, rows, nv, H, s, tile, 1, 0,
-                                                               dyn_m);
+                                                               dz, nullptr, with);
             };
             FLCE_TRY(product(0, cut.main, cut.tile));
             if (cut.main < V) FLCE_TRY(product(cut.main, V - cut.main, cut.rest_tile));

@@ -66,6 +66,7 @@
 #pragma once
 #include <type_traits>
 
+#include "compact.h"
 #include "flce_device.h"
 #include "misc_kernels.h"
 #include "scheduler.h"
@@ -189,8 +190,10 @@ struct FgOperand {
     // base/ld: the matrix; r0: first row (row form) or column (column form) of this
     // tile; extent: number of rows / columns of the matrix; sub: which half of the tile
     // this wavefront multiplies.
+    // rows (row form, not null): LDS, the tile's rows are rows[0], rows[1], ... of the matrix instead, which has
+    // `all` rows (below 2^30 bytes); the caller keeps them there until every thread has returned.
     __device__ __forceinline__ void init(const bf16_t* base, int64_t ld, int r0, int extent, int K,
-                                         int tid, int sub) {
+                                         int tid, int sub, const int* rows_at = nullptr, int all = 0) {
         const int lane = tid & 63, wave = tid >> 6;
         const int ildb = (int)ld * 2;   // leading dimension in bytes
         if constexpr (!KM) {
@@ -204,6 +207,13 @@ struct FgOperand {
             const int piece = (tid & 7) ^ ((ld_row >> 1) & 7);
 #pragma unroll
             for (int r = 0; r < NL; ++r) off[r] = (ld_row + 32 * r) * ildb + piece * 16;
+            if (rows_at) {
+                base0 = reinterpret_cast<const unsigned char*>(base);
+                bytes = (int64_t)all * ildb;
+#pragma unroll
+                for (int r = 0; r < NL; ++r)
+                    off[r] = ld_row + 32 * r < rows ? rows_at[ld_row + 32 * r] * ildb + piece * 16 : 0x7fffffff;
+            }
             kstep = FG_BK * 2;
             const int frow = lane & 31, fhalf = lane >> 5, fsw = (frow >> 1) & 7;
 #pragma unroll
@@ -566,10 +576,15 @@ __device__ __forceinline__ void fg_tile_origin(int seq, int tiles_m, int tiles_n
 // B that is fetched once (few rows in A) from memory whose rows lie a power of two apart (H = 4096:
 // 8 KB), where all tiles at the same K step would ask the same few memory channels at a time.
 // A K % 64 == 0 operand pair without K ranges only.
-// FIN: the first fin.blocks workgroups finish the chunk's dX (see finish_dx_kernel) instead.
+// Fin: the first fin.blocks workgroups finish the chunk's dX (FinishArgs, see finish_dx_kernel) or
+// select its rows (SelectArgs: A's rows are then those of the batch that have a target) instead.
 struct NoFinish {};
+template <typename Fin> struct IsSelect { static constexpr bool value = false; };
+template <typename T> struct IsSelect<SelectArgs<T>> { static constexpr bool value = true; };
 template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE, int ORDER = FG_PLAIN, typename Fin = NoFinish>
 __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGArgs a, Fin fin) {
+    constexpr bool SELECT = IsSelect<Fin>::value;
+    static_assert(!SELECT || !A_KM, "rows are picked from a row-form operand");
     constexpr bool HAS_IN = !std::is_void<InT>::value;
     constexpr int IS = FgInSize<InT>::value;
     constexpr int W = TILE / 64;              // 32 x 32 MFMA tiles per wavefront and direction
@@ -578,7 +593,8 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
     int block = (int)blockIdx.x;
     if constexpr (!std::is_same<Fin, NoFinish>::value) {
         if (block < fin.blocks) {
-            finish_dx<OutT, 4>(fin, block, smem);
+            if constexpr (SELECT) select_rows(fin, block, reinterpret_cast<int (*)[2]>(smem));
+            else finish_dx<OutT, 4>(fin, block, smem);
             return;
         }
         block -= fin.blocks;   // (a multiple of 8: the XCD stays block % 8)
@@ -588,8 +604,10 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
     const int wm = wave >> 1, wn = wave & 1;
 
     // ---- workgroup id -> (K range, tile) (XCD aware, grouped order) ----
-    const FgResolved rs = fg_resolve(a, HAS_IN);
+    FgResolved rs = fg_resolve(a, HAS_IN);
     if (rs.skip) return;
+    TileRows<FG_THREADS / WAVE> picked;
+    if constexpr (SELECT) rs.M = picked.begin(fin.targets, fin.BT, fin.ignore_index, reinterpret_cast<int*>(smem));
     const int M = rs.M, K = rs.K, ksplit = rs.ksplit;
     const bool use_in = rs.use_in;
     // The tile sequence covers the live rows only (a dynamic M can be smaller than the M the
@@ -621,7 +639,14 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
 
     FgOperand<A_KM, TILE, ORDER> opa;
     FgOperand<B_KM, TILE, ORDER> opb;
-    opa.init(a.A, a.lda, m0, M, K, tid, wm);
+    if constexpr (SELECT) {
+        int* rows = reinterpret_cast<int*>(smem) + FG_THREADS / WAVE;
+        picked.place(m0, min(TILE, M - m0), rows);
+        opa.init(a.A, a.lda, m0, M, K, tid, wm, rows, fin.BT);
+        __syncthreads();   // the loads overwrite the list
+    } else {
+        opa.init(a.A, a.lda, m0, M, K, tid, wm);
+    }
     opb.init(a.B, a.ldb, n0, a.N, K, tid, wn);
     const int uwave = __builtin_amdgcn_readfirstlane(wave);
 

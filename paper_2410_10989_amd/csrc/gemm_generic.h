@@ -98,7 +98,9 @@ struct GGStage {
     int lds_at;
     T raw[gg_depth(TILE)][8];
 
-    __device__ __forceinline__ void init(const void* base, int64_t ld_, int r0, int extent, int tid) {
+    // rows_at (row form, not null): LDS, the tile's rows are these of the matrix
+    __device__ __forceinline__ void init(const void* base, int64_t ld_, int r0, int extent, int tid,
+                                         const int* rows_at = nullptr) {
         ld = ld_;
         // column form: a wavefront's lanes are consecutive columns of one piece
         const int row = KM ? tid % TILE : tid / PIECES;
@@ -106,7 +108,7 @@ struct GGStage {
         k8 = piece * 8;
         lds_at = (piece * TILE + (row ^ gg_fold(piece))) * 16;
         // rows past the matrix repeat its last row: they only feed outputs that are not stored
-        const int r = min(r0 + row, extent - 1);
+        const int r = rows_at ? rows_at[min(row, extent - 1 - r0)] : min(r0 + row, extent - 1);
         ptr = static_cast<const T*>(base) + (KM ? (int64_t)r : (int64_t)r * ld);
     }
     // the whole K step starting at k0, into ring position D; V: 16-byte loads (row form)
@@ -179,7 +181,7 @@ __device__ __forceinline__ float gg_element(const float* base, int64_t ld, int r
 // than those of infinity: the row holds a NaN), by all threads of the workgroup; top: LDS, zero before.
 template <bool KM, int TILE>
 __device__ __forceinline__ void gg_row_tops(const float* base, int64_t ld, int r0, int rows, int k0, int k1, int tid,
-                                            unsigned* top) {
+                                            unsigned* top, const int* rows_at = nullptr) {
     constexpr int THREADS = gg_threads(TILE);
     if constexpr (KM) {   // lanes along the rows: contiguous
         const int r = tid % TILE;
@@ -192,7 +194,7 @@ __device__ __forceinline__ void gg_row_tops(const float* base, int64_t ld, int r
         }
     } else {              // lanes along K
         for (int r = tid / WAVE; r < rows; r += THREADS / WAVE) {
-            const float* row = base + (int64_t)(r0 + r) * ld;
+            const float* row = base + (int64_t)(rows_at ? rows_at[r] : r0 + r) * ld;
             unsigned m = 0;
 #pragma unroll 8
             for (int k = k0 + tid % WAVE; k < k1; k += WAVE) m = max(m, __float_as_uint(row[k]) & 0x7fffffffu);
@@ -206,11 +208,12 @@ __device__ __forceinline__ void gg_row_tops(const float* base, int64_t ld, int r
 // among the block's rows without a NaN all |a| and |b| are below 2^103 and K |a| |b| below 2^79.
 template <bool A_KM, bool B_KM, int TILE, int WM, int WN>
 __device__ __forceinline__ unsigned gg_needs_fp32(const GGArgs& a, int m0, int M, int n0, int N, int k0, int k1, int tid,
-                                                  int wm, int wn, unsigned* lds) {   // 2 TILE words
+                                                  int wm, int wn, unsigned* lds,   // 2 TILE words
+                                                  const int* rows_at) {
     for (int i = tid; i < 2 * TILE; i += gg_threads(TILE))   // (rows past the matrix count as NaN)
         lds[i] = (i < TILE ? m0 + i < M : n0 + i - TILE < N) ? 0u : 0xffffffffu;
     __syncthreads();
-    gg_row_tops<A_KM, TILE>(static_cast<const float*>(a.A), a.lda, m0, min(TILE, M - m0), k0, k1, tid, lds);
+    gg_row_tops<A_KM, TILE>(static_cast<const float*>(a.A), a.lda, m0, min(TILE, M - m0), k0, k1, tid, lds, rows_at);
     gg_row_tops<B_KM, TILE>(static_cast<const float*>(a.B), a.ldb, n0, min(TILE, N - n0), k0, k1, tid, lds + TILE);
     __syncthreads();
     auto top_of = [&](const unsigned* row) {   // of 32 rows: 1 + the largest that is no NaN, 0 if there is none
@@ -240,11 +243,15 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
     constexpr int PLANE = TILE * BK * 2;    // bytes of one plane of one operand
     constexpr int SIDE = PLANES * PLANE;
     constexpr int ACCS = TILE == 64 ? 2 : 1;
+    constexpr bool SELECT = IsSelect<Fin>::value;
+    static_assert(!SELECT || !A_KM, "rows are picked from a row-form operand");
     __shared__ __attribute__((aligned(16))) unsigned char lds[2][2 * SIDE];
+    __shared__ int row_list[SELECT ? TILE + gg_threads(TILE) / WAVE : 1];   // SELECT: the tile's rows of A (and the wavefronts' counts)
     int block = (int)blockIdx.x;
     if constexpr (!std::is_same<Fin, NoFinish>::value) {
         if (block < fin.blocks) {
-            finish_dx<OutT, 4>(fin, block, lds);
+            if constexpr (SELECT) select_rows(fin, block, reinterpret_cast<int (*)[2]>(&lds[0][0]));
+            else finish_dx<OutT, 4>(fin, block, lds);
             return;
         }
         block -= fin.blocks;
@@ -254,8 +261,11 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
 
-    const FgResolved rs = fg_resolve(a, a.Cin != nullptr);
+    FgResolved rs = fg_resolve(a, a.Cin != nullptr);
     if (rs.skip) return;
+    TileRows<gg_threads(TILE) / WAVE> picked;
+    if constexpr (SELECT) rs.M = picked.begin(fin.targets, fin.BT, fin.ignore_index, row_list + TILE);
+    const int* rows_at = SELECT ? row_list : nullptr;
     const int M = rs.M, K = rs.K, N = a.N;
     // workgroup id -> (K range, tile): as in gemm_bf16
     const int tiles_m = (M + TILE - 1) / TILE, tiles_n = (N + TILE - 1) / TILE;
@@ -286,7 +296,8 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
 
     GGStage<T, A_KM, TILE> sa;
     GGStage<T, B_KM, TILE> sb;
-    sa.init(a.A, a.lda, m0, M, tid);
+    if constexpr (SELECT) picked.place(m0, min(TILE, M - m0), row_list);
+    sa.init(a.A, a.lda, m0, M, tid, rows_at);
     sb.init(a.B, a.ldb, n0, N, tid);
     const int frow = lane & 31, fhalf = lane >> 5;
 
@@ -461,7 +472,7 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
                 }
         if (__syncthreads_or(out)) {
             again = gg_needs_fp32<A_KM, B_KM, TILE, WM, WN>(a, m0, M, n0, N, k_begin, k_end, tid, wm, wn,
-                                                            reinterpret_cast<unsigned*>(lds));
+                                                            reinterpret_cast<unsigned*>(lds), rows_at);
             // one MFMA tile at a time: few registers and enough loads in flight (a rare path, off the other's
             // registers and instructions)
             constexpr int U = 16;   // K pairs in flight
@@ -471,7 +482,9 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
             for (int ij = 0; ij < WM * WN; ++ij) {
                 if (!(again >> ij & 1)) continue;
                 const int i = ij / WN, j = ij % WN;
-                const int ra = min(m0 + (wm * WM + i) * 32 + frow, M - 1), rb = min(n0 + (wn * WN + j) * 32 + frow, N - 1);
+                int ra = min(m0 + (wm * WM + i) * 32 + frow, M - 1);
+                if constexpr (SELECT) ra = row_list[ra - m0];
+                const int rb = min(n0 + (wn * WN + j) * 32 + frow, N - 1);
                 f32x16 sum;
 #pragma unroll
                 for (int g = 0; g < 16; ++g) sum[g] = 0.f;

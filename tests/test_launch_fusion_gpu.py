@@ -240,3 +240,42 @@ def test_selection_changes_over_with_the_chunk_count(BT, dtype):
     X, W, t = make(BT, 32, 70, dtype, "scattered", BT)
     o = flce.flce_options(logits_budget_bytes=256 * 128 * X.element_size(), row_compaction=True)
     check(flce.flce_fwd_bwd_opt(X, W, t, o), X, W, t, dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("ignore", ["scattered", "front", "all"])
+@pytest.mark.parametrize("BT,H,V", [
+    (3, 8, 300),         # the smallest: one tile row with three rows
+    (130, 72, 1000),     # two tile rows, a K tail (bf16)
+    (256, 128, 2000),    # one chunk of at most 256 rows: rotated K loop (bf16)
+    (257, 1024, 700),    # fewer than 16 tiles, the longest K loop that still has its rows picked; 1032: no longer
+    (257, 1032, 700),
+    (2048, 64, 600),     # the masks of the first look serve the second one; 2049: not all of them
+    (2049, 64, 600),
+    (4096, 64, 1000),    # the longest batch; 4097: a launch of its own
+    (4097, 64, 1000),
+])
+def test_rows_picked_by_the_logits_launch(dtype, ignore, BT, H, V):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, H, V, dtype, ignore, BT + H)
+    X[t == -100] = float("inf")   # rows without a target are never read into a sum
+    got = flce.flce_fwd_bwd(X, W, t)
+    X[t == -100] = 0
+    check(got, X, W, t, dtype)
+
+
+def test_out_of_range_operands_of_picked_rows():
+    # fp32: an infinity in a picked row sends its tile to the fp32 instructions, which look the rows up again
+    import paper_2410_10989_amd as flce
+    X, W, t = make(300, 64, 700, torch.float32, "scattered", 9)
+    row = int((t != -100).nonzero()[100])
+    X[row, 5] = 1e32
+    W[:, 5] = 0
+    loss, dX, dW = flce.flce_fwd_bwd(X, W, t)
+    X2 = X.clone()
+    X2[row, 5] = 0   # times zero weights: the same logits; dW's column 5 apart
+    rl, rX, rW = reference(X2, W, t)
+    assert abs(float(loss) - rl) <= 2e-6 * abs(rl)
+    keep = torch.arange(64) != 5
+    for a, b in ((dX.cpu()[:, keep], rX[:, keep]), (dW.cpu()[:, keep], rW[:, keep])):
+        assert float((a.double() - b).norm() / b.norm()) <= TOL[torch.float32]
