@@ -232,20 +232,29 @@ int launch_gemm_guarded(int kind, const T* A, int64_t lda, const T* B, int64_t l
     if (sel && (!CAN_SEL || tile == 256)) return FLCE_ERR_SHAPE;   // (select_in_logits keeps such calls away)
 #define GG_LAUNCH(TILE) \
     hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, TILE>), grid, block, 0, s, a, NoFinish{})
+    constexpr bool CAN_FEW = std::is_same<T, float>::value && A_KM == B_KM;   // (the dX product comes out the same)
+    const bool few = CAN_FEW && tile == 64 && total <= 256;
     if (sel) {
         if constexpr (CAN_SEL) {
-            if (tile == 64)
+            if (few)
+                hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64, SelectArgs<T>, true>), grid, block, 0, s, a, *sel);
+            else if (tile == 64)
                 hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64, SelectArgs<T>>), grid, block, 0, s, a, *sel);
             else
                 hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 128, SelectArgs<T>>), grid, block, 0, s, a, *sel);
         }
     } else if (fin) {
         if constexpr (CAN_FIN) {
-            if (tile == 64)
+            if (few)
+                hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64, FinishArgs, true>), grid, block, 0, s, a, *fin);
+            else if (tile == 64)
                 hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64, FinishArgs>), grid, block, 0, s, a, *fin);
             else
                 hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 128, FinishArgs>), grid, block, 0, s, a, *fin);
         }
+    } else if (few) {
+        if constexpr (CAN_FEW)
+            hipLaunchKernelGGL((gemm_guarded<T, OutT, A_KM, B_KM, 64, NoFinish, true>), grid, block, 0, s, a, NoFinish{});
     } else if (tile == 64) GG_LAUNCH(64);
     else if (tile == 128) GG_LAUNCH(128);
     else GG_LAUNCH(256);

@@ -234,7 +234,12 @@ __device__ __forceinline__ unsigned gg_needs_fp32(const GGArgs& a, int m0, int M
 }
 
 // Fin: as in gemm_bf16.
-template <typename T, typename OutT, bool A_KM, bool B_KM, int TILE, typename Fin = NoFinish>
+//
+// FEW: for at most one workgroup per CU.  The room in LDS keeps a third workgroup off the CU, so that the
+// compiler spends 250 registers per lane instead of 168 on loads and fragments in flight (no other way was
+// found to make it: waves_per_eu does not).  fp32 64-tiles, whole calls: 29 x 2816 x 1124 74 -> 66 us, 256 x 512 x 4096
+// 52.8 -> 51.0; with two and more workgroups per CU 3 % slower (593 x 256 x 13824 102 -> 107).
+template <typename T, typename OutT, bool A_KM, bool B_KM, int TILE, typename Fin = NoFinish, bool FEW = false>
 __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fin fin) {
     constexpr int PLANES = GGTraits<T>::PLANES;
     constexpr int WAVES_N = TILE == 256 ? 4 : 2;              // wavefronts: 2 x WAVES_N
@@ -245,7 +250,7 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
     constexpr int ACCS = TILE == 64 ? 2 : 1;
     constexpr bool SELECT = IsSelect<Fin>::value;
     static_assert(!SELECT || !A_KM, "rows are picked from a row-form operand");
-    __shared__ __attribute__((aligned(16))) unsigned char lds[2][2 * SIDE];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2][2 * SIDE + (FEW ? 4096 : 0)];
     __shared__ int row_list[SELECT ? TILE + gg_threads(TILE) / WAVE : 1];   // SELECT: the tile's rows of A (and the wavefronts' counts)
     int block = (int)blockIdx.x;
     if constexpr (!std::is_same<Fin, NoFinish>::value) {
