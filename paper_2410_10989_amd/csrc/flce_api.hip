@@ -428,6 +428,58 @@ int rmsnorm_vectors_per_thread(int64_t H, const void* x, const void* gamma, cons
 // Partial rows of dgamma that a chunk of C rows can reach.
 inline unsigned rn_slots(int64_t C) { return (unsigned)std::min<int64_t>(C, RN_SLOTS); }
 
+// Whether the gradients of a batch that is one chunk are one launch (GradArgs).  The two products share the
+// chip and, without K ranges, the launch that puts dX's rows in place goes as well.  Whole calls, us, two
+// launches / one: bf16 18 x 960 x 384 25.8 / 21.5, 1765 x 3584 x 2635 148 / 133, 32 x 1792 x 512 32.9 / 29.3; with K ranges
+// 1024 x 512 x 8192 57.2 / 53.6, 1572 x 576 x 2176 53.9 / 44.7, 124 x 64 x 128256 67.3 / 64.4, 144 x 1472 x 59328 (5060
+// workgroups) 176 / 164; fp32 1871 x 1240 x 2653 277 / 261, 67 x 576 x 1706 36.0 / 33.9.  fp32 with K ranges beyond
+// the 768 workgroups that are on the chip at a time fills two rounds badly (256 x 512 x 4096, 1024 of them: 52.6 / 53.6).
+template <typename T>
+bool grads_in_one(const Plan& p, const VocabCut& dw, bool want_dw, bool dw_fast, int64_t rows, int64_t H, int64_t V) {
+    constexpr bool BF16 = sizeof(T) == 2;
+    if (p.nchunks != 1 || p.dx_tile == 256 || p.fast_dx != BF16 || H % 4 != 0) return false;
+    if (want_dw && (dw_fast != BF16 || dw.main != V || dw.tile != p.dx_tile)) return false;
+    const int64_t blocks = tiles_of(rows, H, p.dx_tile) * p.dx_ranges + (want_dw ? tiles_of(V, H, p.dx_tile) : 0);
+    return p.dx_ranges > 1 ? want_dw && blocks <= (BF16 ? 8192 : 768) : blocks <= 2048;
+}
+
+// dX = G W and dW = G^T X (dW not null) in one launch.
+template <typename T>
+int launch_grad(const T* Z, int64_t ldz, const T* W, const T* Xc, float* part, T* rows_out, T* dW, int64_t rows, int64_t H,
+                int64_t V, const Plan& p, const FastDyn& dm, const FastDyn& dk, GradArgs g, hipStream_t s) {
+    ScopedKernelTimer timer(dW ? FLCE_KIND_DW_GEMM : FLCE_KIND_DX_GEMM, s);
+    const int tile = p.dx_tile, ranges = p.dx_ranges;
+    const bool cut = ranges > 1;
+    auto up = [](int64_t n) { return (n + FG_XCDS - 1) / FG_XCDS * FG_XCDS; };
+    g.dx_blocks = (int)up(tiles_of(rows, H, tile) * ranges);
+    const int64_t dw_blocks = dW ? up(tiles_of(V, H, tile)) : 0;
+    const dim3 grid((unsigned)((cut ? 0 : FG_XCDS) + g.dx_blocks + dw_blocks)), block(256);
+    void* out = cut ? static_cast<void*>(part) : rows_out;
+    if constexpr (sizeof(T) == 2) {
+        auto tiles = [&](int64_t n) { return (int)((n + tile - 1) / tile); };
+        const FGArgs dx{Z, ldz, W, H, out, H, nullptr, 0, (int)rows, (int)H, (int)V, tiles(rows), tiles(H), ranges, p.C * H,
+                        dm.rows, 0, nullptr, nullptr, 0, 0, 0, 1, nullptr, FG_GROUP_TILES, 0, 1};
+        const FGArgs dw{Z, ldz, Xc, H, dW, H, nullptr, 0, (int)V, (int)H, (int)rows, tiles(V), tiles(H), 1, 0,
+                        dk.rows, 1, nullptr, dk.first_live, dk.launch, 0, 0, 1, nullptr, FG_GROUP_TILES, 0, 1};
+        if (cut) hipLaunchKernelGGL((grad_bf16<true>), grid, block, 0, s, dx, dw, g);
+        else hipLaunchKernelGGL((grad_bf16<false>), grid, block, 0, s, dx, dw, g);
+    } else {
+        const GGArgs dx{Z, ldz, W, H, out, H, nullptr, H, 0, (int)rows, (int)H, (int)V, ranges, p.C * H, ldz % 4 == 0, 0, 1,
+                        dm.rows, 0, nullptr, nullptr, 0, FG_GROUP_TILES, 0, 1};
+        const GGArgs dw{Z, ldz, Xc, H, dW, H, nullptr, H, 0, (int)V, (int)H, (int)rows, 1, 0, 0, 0, 1,
+                        dk.rows, 1, nullptr, dk.first_live, dk.launch, FG_GROUP_TILES, 0, 1};
+#define GRAD_LAUNCH(TILE, CUT) hipLaunchKernelGGL((grad_f32<TILE, CUT>), grid, block, 0, s, dx, dw, g)
+        if (tile == 64) {
+            if (cut) GRAD_LAUNCH(64, true); else GRAD_LAUNCH(64, false);
+        } else {
+            if (cut) GRAD_LAUNCH(128, true); else GRAD_LAUNCH(128, false);
+        }
+#undef GRAD_LAUNCH
+    }
+    HIP_TRY(hipGetLastError());
+    return FLCE_OK;
+}
+
 // Whether a batch that is one chunk has its rows selected by workgroups of the logits launch.  That saves a
 // launch (4-5 us, on the host as well) and costs every tile its own look at the targets, 1-2 us per
 // workgroup: for launches that fit the chip, or of one tile row, where the look is short.  Whole calls with the
@@ -503,6 +555,9 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         const T* Xin = compact ? X : X + r0 * H;   // what the chunk's row indices refer to
         const T* Xc = Xin;
         const int64_t* tc = targets + r0;
+        const bool dw_fast = BF16 && (last ? p.fast_dw_last : p.fast_dw_full);
+        const VocabCut dw_cut = vocab_cut(dw_fast, V, H, rows, p.tail_bytes > 0);
+        const bool one_grad = select && want_dx && grads_in_one<T>(p, dw_cut, want_dw, dw_fast, rows, H, V);
         const VocabCut z_cut = vocab_cut(BF16 && p.fast_logits, V, rows, H, false);
         const bool in_logits = select && !norm && select_in_logits<T>(p, z_cut, BT, H, V);
         SelectArgs<T> sel{};
@@ -592,7 +647,17 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         // results when there are few output tiles.  `fin` is what is left to do for dX then.
         FinishArgs fin{};
         bool finish = false;
-        if (want_dx) {
+        const bool loss_in_norm = norm && want_dx;   // (see below)
+        if (one_grad) {
+            float* part = reinterpret_cast<float*>(ws + p.off_dxpart);
+            const bool cut = p.dx_ranges > 1;
+            fin = {cut ? static_cast<const void*>(part) : dXg, cut ? 1 : 0, p.C * H, p.dx_ranges, nullptr,
+                   norm ? nullptr : row_map, n_live, (int)rows, (int)H, norm ? dXg : dX, dx_add,
+                   norm ? nullptr : row_loss, hdr, loss_here, finish_segs(H), (int)finish_blocks(rows, H)};
+            FLCE_TRY(launch_grad<T>(Z, p.ldz, W, Xc, part, dXg, want_dw ? dW : nullptr, rows, H, V, p, dyn_m, dyn_dw,
+                                    GradArgs{fin, 0}, s));
+            if (cut) FLCE_TRY(launch_finish_dx<T>(fin, s));
+        } else if (want_dx) {
             const bool staged = compact || norm;
             const bool scatter = compact && !norm;
             T* dXc = staged ? dXg : dX + r0 * H;
@@ -634,22 +699,19 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         }
         // The chunk's losses are summed by a workgroup of the RMSNorm backward launch, or of the one
         // that finishes dX, or, with neither, by a launch of their own.
-        const bool loss_in_norm = norm && want_dx;
         if (finish && !loss_in_norm) {
             fin.row_loss = row_loss;
             fin.loss = loss_here;
-        } else if (!loss_in_norm) {
+        } else if (!loss_in_norm && !one_grad) {
             FLCE_TRY(launch_loss(row_loss, rows, hdr, loss_here, true, s));
         }
         // dX is finished by workgroups of the dW launch where that is one launch on small tiles
-        const bool dw_fast = BF16 && (last ? p.fast_dw_last : p.fast_dw_full);
-        const VocabCut dw_cut = vocab_cut(dw_fast, V, H, rows, p.tail_bytes > 0);
         const bool ride_along = finish && want_dw && p.nchunks == 1 && dw_cut.main == V && dw_cut.tile < 256 &&
                                 (dw_fast || !BF16) && fin.blocks <= RIDE_BLOCKS && finish_is_vec<T>(fin);
         if (finish && !ride_along) FLCE_TRY(launch_finish_dx<T>(fin, s));
 
         // dW (+)= G^T X_c   (K = the chunk's rows; in a compacted chunk K = *n_live)
-        if (want_dw) {
+        if (want_dw && !one_grad) {
             const bool fast = dw_fast;
             const VocabCut& cut = dw_cut;
             const FinishArgs* with = ride_along ? &fin : nullptr;

@@ -579,33 +579,26 @@ __device__ __forceinline__ void fg_tile_origin(int seq, int tiles_m, int tiles_n
 // Fin: the first fin.blocks workgroups finish the chunk's dX (FinishArgs, see finish_dx_kernel) or
 // select its rows (SelectArgs: A's rows are then those of the batch that have a target) instead.
 struct NoFinish {};
+struct ProductTile {   // the tile a workgroup of a product computed: first row and column, rows (0: none)
+    int m0 = 0, n0 = 0, rows = 0;
+};
 template <typename Fin> struct IsSelect { static constexpr bool value = false; };
 template <typename T> struct IsSelect<SelectArgs<T>> { static constexpr bool value = true; };
-template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE, int ORDER = FG_PLAIN, typename Fin = NoFinish>
-__global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGArgs a, Fin fin) {
+// smem: fg_lds_bytes(TILE) of LDS.
+template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE, int ORDER, typename Fin>
+__device__ __forceinline__ ProductTile fg_product(const FGArgs& a, const Fin& fin, int block, unsigned char* smem) {
     constexpr bool SELECT = IsSelect<Fin>::value;
     static_assert(!SELECT || !A_KM, "rows are picked from a row-form operand");
     constexpr bool HAS_IN = !std::is_void<InT>::value;
     constexpr int IS = FgInSize<InT>::value;
     constexpr int W = TILE / 64;              // 32 x 32 MFMA tiles per wavefront and direction
     constexpr int SLOT = fg_slot_bytes(TILE);
-    __shared__ __attribute__((aligned(16))) unsigned char smem[fg_lds_bytes(TILE)];
-    int block = (int)blockIdx.x;
-    if constexpr (!std::is_same<Fin, NoFinish>::value) {
-        if (block < fin.blocks) {
-            if constexpr (SELECT) select_rows(fin, block, reinterpret_cast<int (*)[2]>(smem));
-            else finish_dx<OutT, 4>(fin, block, smem);
-            return;
-        }
-        block -= fin.blocks;   // (a multiple of 8: the XCD stays block % 8)
-    }
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
 
     // ---- workgroup id -> (K range, tile) (XCD aware, grouped order) ----
     FgResolved rs = fg_resolve(a, HAS_IN);
-    if (rs.skip) return;
+    if (rs.skip) return ProductTile{};
     TileRows<FG_THREADS / WAVE> picked;
     if constexpr (SELECT) rs.M = picked.begin(fin.targets, fin.BT, fin.ignore_index, reinterpret_cast<int*>(smem));
     const int M = rs.M, K = rs.K, ksplit = rs.ksplit;
@@ -623,16 +616,16 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
     int tail_i = 0, tail_n = 1, tail_blk = 0;
     if (TILE == 256 && a.tail_s > 1 && in_xcd >= a.tail_begin) {
         const int u = in_xcd - a.tail_begin;
-        if (u >= a.tail_r * a.tail_s) return;
+        if (u >= a.tail_r * a.tail_s) return ProductTile{};
         const int slot = u % a.tail_r;
         in_xcd = a.tail_begin + slot;
         tail_i = u / a.tail_r;
         tail_n = a.tail_s;
         tail_blk = (xcd * a.tail_r + slot) * a.tail_s + tail_i;
     }
-    if (in_xcd >= per_xcd) return;
+    if (in_xcd >= per_xcd) return ProductTile{};
     const int seq_all = fg_seq(a, xcd, in_xcd, per_xcd);
-    if (seq_all >= total) return;
+    if (seq_all >= total) return ProductTile{};
     const int split = seq_all / tiles;
     int m0, n0;
     fg_tile_origin<TILE>(seq_all - split * tiles, tiles_m, a.tiles_n, a.group_m, a.group_cols, m0, n0);
@@ -817,6 +810,41 @@ __global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGA
 
     // ---- epilogue (see FgOut) ----
     if (TILE == 256 && tail_n > 1) part.write(acc); else out.write(acc);
+    return ProductTile{m0, n0, min(TILE, M - m0)};
+}
+
+template <typename OutT, typename InT, bool A_KM, bool B_KM, int TILE, int ORDER = FG_PLAIN, typename Fin = NoFinish>
+__global__ __launch_bounds__(FG_THREADS, TILE == 256 ? 1 : 2) void gemm_bf16(FGArgs a, Fin fin) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[fg_lds_bytes(TILE)];
+    int block = (int)blockIdx.x;
+    if constexpr (!std::is_same<Fin, NoFinish>::value) {
+        if (block < fin.blocks) {
+            if constexpr (IsSelect<Fin>::value) select_rows(fin, block, reinterpret_cast<int (*)[2]>(smem));
+            else finish_dx<OutT, 4>(fin, block, smem);
+            return;
+        }
+        block -= fin.blocks;   // (a multiple of 8: the XCD stays block % 8)
+    }
+    fg_product<OutT, InT, A_KM, B_KM, TILE, ORDER, Fin>(a, fin, block, smem);
+}
+
+// The dX and the dW product of a small chunk in one launch (see GradArgs), 128-tiles.  CUT: dX in K ranges.
+template <bool CUT>
+__global__ __launch_bounds__(FG_THREADS, 2) void grad_bf16(FGArgs dx, FGArgs dw, GradArgs g) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[fg_lds_bytes(128)];
+    int block = (int)blockIdx.x;
+    if constexpr (!CUT) {
+        if (block == 0 && g.fin.row_loss) loss_accumulate(g.fin.row_loss, g.fin.rows, g.fin.hdr, g.fin.loss, reinterpret_cast<double*>(smem));
+        if (block < FG_XCDS) return;
+        block -= FG_XCDS;
+    }
+    if (block < g.dx_blocks) {
+        using Out = typename std::conditional<CUT, float, bf16_t>::type;
+        const ProductTile t = fg_product<Out, void, false, true, 128, FG_PLAIN>(dx, NoFinish{}, block, smem);
+        if (!CUT && t.rows > 0 && g.fin.idx) place_tile<bf16_t, 128>(g.fin, t.m0, t.n0, t.rows);
+    } else {
+        fg_product<bf16_t, void, true, true, 128, FG_PLAIN>(dw, NoFinish{}, block - g.dx_blocks, smem);
+    }
 }
 
 // Second step of a launch whose last round was cut along K: adds the tail_s fp32 partial

@@ -239,35 +239,31 @@ __device__ __forceinline__ unsigned gg_needs_fp32(const GGArgs& a, int m0, int M
 // compiler spends 250 registers per lane instead of 168 on loads and fragments in flight (no other way was
 // found to make it: waves_per_eu does not).  fp32 64-tiles, whole calls: 29 x 2816 x 1124 74 -> 66 us, 256 x 512 x 4096
 // 52.8 -> 51.0; with two and more workgroups per CU 3 % slower (593 x 256 x 13824 102 -> 107).
-template <typename T, typename OutT, bool A_KM, bool B_KM, int TILE, typename Fin = NoFinish, bool FEW = false>
-__global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fin fin) {
+template <typename T, int TILE, bool FEW = false>
+struct GGLds {
+    static constexpr int PLANE = TILE * gg_bk(TILE) * 2;             // bytes of one plane of one operand
+    static constexpr int SIDE = GGTraits<T>::PLANES * PLANE;
+    unsigned char tiles[2][2 * SIDE + (FEW ? 4096 : 0)];
+};
+template <typename T, typename OutT, bool A_KM, bool B_KM, int TILE, typename Fin, bool FEW>
+__device__ __forceinline__ ProductTile gg_product(const GGArgs& a, const Fin& fin, int block, GGLds<T, TILE, FEW>& smem,
+                                                  int* row_list) {
+    constexpr bool SELECT = IsSelect<Fin>::value;
+    static_assert(!SELECT || !A_KM, "rows are picked from a row-form operand");
     constexpr int PLANES = GGTraits<T>::PLANES;
     constexpr int WAVES_N = TILE == 256 ? 4 : 2;              // wavefronts: 2 x WAVES_N
     constexpr int WM = TILE / 64, WN = TILE / 32 / WAVES_N;   // 32 x 32 MFMA tiles per wavefront
     constexpr int BK = gg_bk(TILE), DEPTH = gg_depth(TILE);
-    constexpr int PLANE = TILE * BK * 2;    // bytes of one plane of one operand
-    constexpr int SIDE = PLANES * PLANE;
+    constexpr int PLANE = GGLds<T, TILE, FEW>::PLANE, SIDE = GGLds<T, TILE, FEW>::SIDE;
     constexpr int ACCS = TILE == 64 ? 2 : 1;
-    constexpr bool SELECT = IsSelect<Fin>::value;
-    static_assert(!SELECT || !A_KM, "rows are picked from a row-form operand");
-    __shared__ __attribute__((aligned(16))) unsigned char lds[2][2 * SIDE + (FEW ? 4096 : 0)];
-    __shared__ int row_list[SELECT ? TILE + gg_threads(TILE) / WAVE : 1];   // SELECT: the tile's rows of A (and the wavefronts' counts)
-    int block = (int)blockIdx.x;
-    if constexpr (!std::is_same<Fin, NoFinish>::value) {
-        if (block < fin.blocks) {
-            if constexpr (SELECT) select_rows(fin, block, reinterpret_cast<int (*)[2]>(&lds[0][0]));
-            else finish_dx<OutT, 4>(fin, block, lds);
-            return;
-        }
-        block -= fin.blocks;
-    }
+    auto& lds = smem.tiles;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
 
     FgResolved rs = fg_resolve(a, a.Cin != nullptr);
-    if (rs.skip) return;
+    if (rs.skip) return ProductTile{};
     TileRows<gg_threads(TILE) / WAVE> picked;
     if constexpr (SELECT) rs.M = picked.begin(fin.targets, fin.BT, fin.ignore_index, row_list + TILE);
     const int* rows_at = SELECT ? row_list : nullptr;
@@ -278,9 +274,9 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
     const int total = tiles * rs.ksplit;
     const int per_xcd = (total + FG_XCDS - 1) / FG_XCDS;
     const int in_xcd = block / FG_XCDS;
-    if (in_xcd >= per_xcd) return;
+    if (in_xcd >= per_xcd) return ProductTile{};
     const int seq = fg_seq(a, block % FG_XCDS, in_xcd, per_xcd);
-    if (seq >= total) return;
+    if (seq >= total) return ProductTile{};
     const int split = seq / tiles;
     int m0, n0;
     fg_tile_origin<TILE>(seq - split * tiles, tiles_m, tiles_n, a.group_m, a.group_cols, m0, n0);
@@ -512,6 +508,41 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fi
 #pragma unroll
         for (int j = 0; j < WN; ++j)
             if (!(again >> (i * WN + j) & 1)) write(i, j, acc[i][j], PLANES == 3 ? GG_UNSCALE : 1.f);
+    return ProductTile{m0, n0, min(TILE, M - m0)};
+}
+
+template <typename T, typename OutT, bool A_KM, bool B_KM, int TILE, typename Fin = NoFinish, bool FEW = false>
+__global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fin fin) {
+    __shared__ __attribute__((aligned(16))) GGLds<T, TILE, FEW> lds;
+    __shared__ int row_list[IsSelect<Fin>::value ? TILE + gg_threads(TILE) / WAVE : 1];   // SELECT: the tile's rows of A (and the wavefronts' counts)
+    int block = (int)blockIdx.x;
+    if constexpr (!std::is_same<Fin, NoFinish>::value) {
+        if (block < fin.blocks) {
+            if constexpr (IsSelect<Fin>::value) select_rows(fin, block, reinterpret_cast<int (*)[2]>(&lds));
+            else finish_dx<OutT, 4>(fin, block, &lds);
+            return;
+        }
+        block -= fin.blocks;
+    }
+    gg_product<T, OutT, A_KM, B_KM, TILE, Fin, FEW>(a, fin, block, lds, row_list);
+}
+
+// As grad_bf16, fp32 storage.
+template <int TILE, bool CUT>
+__global__ __launch_bounds__(gg_threads(TILE), 2) void grad_f32(GGArgs dx, GGArgs dw, GradArgs g) {
+    __shared__ __attribute__((aligned(16))) GGLds<float, TILE> lds;
+    int block = (int)blockIdx.x;
+    if constexpr (!CUT) {
+        if (block == 0 && g.fin.row_loss) loss_accumulate(g.fin.row_loss, g.fin.rows, g.fin.hdr, g.fin.loss, reinterpret_cast<double*>(&lds));
+        if (block < FG_XCDS) return;
+        block -= FG_XCDS;
+    }
+    if (block < g.dx_blocks) {
+        const ProductTile t = gg_product<float, float, false, true, TILE, NoFinish, false>(dx, NoFinish{}, block, lds, nullptr);
+        if (!CUT && t.rows > 0 && g.fin.idx) place_tile<float, TILE>(g.fin, t.m0, t.n0, t.rows);
+    } else {
+        gg_product<float, float, true, true, TILE, NoFinish, false>(dw, NoFinish{}, block - g.dx_blocks, lds, nullptr);
+    }
 }
 
 }  // namespace flce

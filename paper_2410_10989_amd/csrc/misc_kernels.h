@@ -94,4 +94,42 @@ __global__ __launch_bounds__(256) void finish_dx_kernel(FinishArgs f) {
     finish_dx<T, VEC4 ? 4 : 1>(f, (int)blockIdx.x, part);
 }
 
+// One launch for the gradients of a chunk on small tiles: dX's tiles and K ranges (dx_blocks, a multiple of
+// 8) and dW's tiles, which do not depend on one another; without K ranges also a workgroup for the losses
+// (8 ids, in front), and every workgroup puts the rows of its own tile of dX in place, so that no launch follows
+// (fin.idx null: they stay in the chunk's block, for the RMSNorm backward, which also sums the losses).
+// (With K ranges finish_dx_kernel follows.  Having the last workgroup of a tile add its ranges up instead
+// costs 15 us: partial results written through to memory and 64 KB of each read back by one workgroup;
+// 1024 x 512 x 8192 with 8 ranges 58 -> 73 us, 209 x 448 x 2179 with 4 ranges 27 -> 41.)
+struct GradArgs {
+    FinishArgs fin;    // src, idx, n, out, add, and the losses (row_loss null: not here)
+    int dx_blocks;
+};
+
+// Rows of the TILE x TILE tile at (m0, n0) of dX, which this workgroup (256 threads) has just written to
+// f.src, to their places (see finish_dx).
+template <typename T, int TILE>
+__device__ __forceinline__ void place_tile(const FinishArgs& f, int m0, int n0, int rows) {
+    const int tid = threadIdx.x;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the L1 is write-through)
+    __syncthreads();
+    constexpr int LANES = TILE / 4, RPP = 256 / LANES;   // threads per row, rows at a time
+    const int col = n0 + tid % LANES * 4;
+    if (col >= f.n) return;   // (n % 4 == 0)
+    struct alignas(4 * sizeof(T)) Quad { T e[4]; };
+    const T* src = static_cast<const T*>(f.src);
+#pragma unroll 8
+    for (int r = tid / LANES; r < rows; r += RPP) {
+        const int i = m0 + r;
+        Quad q = *reinterpret_cast<const Quad*>(src + (int64_t)i * f.n + col);
+        Quad* to = reinterpret_cast<Quad*>(static_cast<T*>(f.out) + (int64_t)f.idx[i] * f.n + col);
+        if (f.add) {
+            const Quad o = *to;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q.e[e] = from_f32<T>(to_f32(q.e[e]) + to_f32(o.e[e]));
+        }
+        *to = q;
+    }
+}
+
 }  // namespace flce

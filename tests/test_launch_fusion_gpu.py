@@ -279,3 +279,55 @@ def test_out_of_range_operands_of_picked_rows():
     keep = torch.arange(64) != 5
     for a, b in ((dX.cpu()[:, keep], rX[:, keep]), (dW.cpu()[:, keep], rW[:, keep])):
         assert float((a.double() - b).norm() / b.norm()) <= TOL[torch.float32]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("BT,H,V", [
+    (1, 8, 130),        # one row, a tile of 8 columns (fp32: 64-tiles, bf16: 128-tiles)
+    (64, 64, 127),      # whole 64-tiles, ragged vocabulary
+    (129, 136, 300),    # one row and one 8-column strip past a 128-tile
+    (300, 264, 700),    # dX in K ranges (fp32), not (bf16)
+    (200, 72, 3000),    # dX in K ranges
+    (1500, 200, 1100),
+])
+@pytest.mark.parametrize("heads", [1, 2])
+@pytest.mark.parametrize("skip_dw", [False, True])
+def test_both_gradients_in_one_launch(dtype, BT, H, V, heads, skip_dw):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, H, V, dtype, "scattered" if BT > 1 else "none", BT + V)
+    Ws, ts = [W], [t]
+    if heads == 2:
+        Ws.append((W.flip(0) * 0.5).contiguous())
+        ts.append(torch.where(t == -100, t, (t * 7 + 1) % V))
+    weights = [1.0, 0.7][:heads]
+    dX = torch.full_like(X, float("nan"))
+    loss, _, dX, dWs = flce.flce_multihead_fwd_bwd(X, Ws, ts, weights, dX=dX, flags=flce.SKIP_DW if skip_dw else 0)
+    torch.cuda.synchronize()
+    refs = [reference(X.float(), w.float(), u) for w, u in zip(Ws, ts)]
+    tol = TOL[dtype] if dtype == torch.bfloat16 else max(TOL[dtype], 2.0 ** -24 * math.sqrt(6 * max(BT, H, V) / 16))
+    want = sum(c * r[0] for c, r in zip(weights, refs))
+    assert abs(float(loss) - want) <= max(2e-6, tol / 4) * max(abs(want), 1e-30)
+    rX = sum(c * r[1] for c, r in zip(weights, refs))
+    assert float((dX.double().cpu() - rX).norm() / rX.norm()) <= tol
+    assert (dX[t == -100] == 0).all()
+    for c, r, d in zip(weights, refs, dWs or []):
+        assert float((d.double().cpu() - c * r[2]).norm() / (c * r[2]).norm()) <= tol
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("BT,H,V", [(60, 64, 300), (200, 72, 3000)])   # dX uncut, dX in K ranges
+def test_both_gradients_in_one_launch_behind_rmsnorm(dtype, BT, H, V):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, H, V, dtype, "scattered", 5)
+    ones = torch.ones(H, dtype=dtype, device="cuda")
+    loss, dh, dgamma, dW = flce.flce_rmsnorm_fwd_bwd(X, ones, 1e-6, W, t)
+    x = X.double().cpu()
+    rms = torch.sqrt((x * x).mean(1, keepdim=True) + 1e-6)
+    xhat = x / rms
+    rl, rY, rW = reference(xhat, W.float(), t)
+    rh = (rY - (xhat * rY).mean(1, keepdim=True) * xhat) / rms
+    # bf16: the normalised rows are rounded too, one rounding of 2^-9 more than in the plain call
+    tol = 2 * TOL[dtype] if dtype == torch.bfloat16 else max(4e-6, 2.0 ** -23 * math.sqrt(6 * V / 16))
+    assert abs(float(loss) - rl) <= tol * rl
+    for a, b in ((dh, rh), (dgamma, (rY * xhat).sum(0)), (dW, rW)):
+        assert float((a.double().cpu() - b).norm() / b.norm()) <= tol
