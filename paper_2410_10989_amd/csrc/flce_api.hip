@@ -432,15 +432,16 @@ inline unsigned rn_slots(int64_t C) { return (unsigned)std::min<int64_t>(C, RN_S
 // chip and, without K ranges, the launch that puts dX's rows in place goes as well.  Whole calls, us, two
 // launches / one: bf16 18 x 960 x 384 25.8 / 21.5, 1765 x 3584 x 2635 148 / 133, 32 x 1792 x 512 32.9 / 29.3; with K ranges
 // 1024 x 512 x 8192 57.2 / 53.6, 1572 x 576 x 2176 53.9 / 44.7, 124 x 64 x 128256 67.3 / 64.4, 144 x 1472 x 59328 (5060
-// workgroups) 176 / 164; fp32 1871 x 1240 x 2653 277 / 261, 67 x 576 x 1706 36.0 / 33.9.  fp32 with K ranges beyond
-// the 768 workgroups that are on the chip at a time fills two rounds badly (256 x 512 x 4096, 1024 of them: 52.6 / 53.6).
+// workgroups) 176 / 164; fp32 1871 x 1240 x 2653 277 / 261, 67 x 576 x 1706 36.0 / 33.9, 256 x 512 x 4096 (1024 64-tile
+// workgroups) 53.1 / 51.6, 604 x 2112 x 14422 (128-tiles) 721 / 701.  Many 64-tiles keep the two launches, where dX's
+// ranges are added up beside dW's tiles: 54 x 384 x 11328 45.1 / 47.6.
 template <typename T>
 bool grads_in_one(const Plan& p, const VocabCut& dw, bool want_dw, bool dw_fast, int64_t rows, int64_t H, int64_t V) {
     constexpr bool BF16 = sizeof(T) == 2;
     if (p.nchunks != 1 || p.dx_tile == 256 || p.fast_dx != BF16 || H % 4 != 0) return false;
     if (want_dw && (dw_fast != BF16 || dw.main != V || dw.tile != p.dx_tile)) return false;
     const int64_t blocks = tiles_of(rows, H, p.dx_tile) * p.dx_ranges + (want_dw ? tiles_of(V, H, p.dx_tile) : 0);
-    return p.dx_ranges > 1 ? want_dw && blocks <= (BF16 ? 8192 : 768) : blocks <= 2048;
+    return p.dx_ranges > 1 ? want_dw && blocks <= (BF16 ? 8192 : p.dx_tile == 64 ? 1024 : 4096) : blocks <= 2048;
 }
 
 // dX = G W and dW = G^T X (dW not null) in one launch.

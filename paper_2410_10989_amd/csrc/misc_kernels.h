@@ -35,6 +35,10 @@ struct FinishArgs {
 // (Rows are cut into segments so that a few long rows with many partial results fill the chip too:
 // 180 rows of 4096 with 16 ranges took 45 us with a wavefront per row.)
 constexpr int FIN_SEG = 512;
+// K ranges whose loads a wavefront has in flight: with 62 ranges, one wait for memory after the other, this launch
+// was a quarter of the call (whole calls, 4 one by one / 8 together, us: 19 x 448 x 32000 50.9 / 42.6, 58 x 320 x 44288
+// 56.9 / 48.8, 94 x 384 x 23460 43.1 / 38.1, 2 heads of 218 x 312 x 104206 200 / 188).
+constexpr int FIN_AHEAD = 8;
 inline int finish_segs(int64_t n) { return (int)((n + FIN_SEG - 1) / FIN_SEG); }
 inline int64_t finish_blocks(int64_t rows, int64_t n) { return ((rows * finish_segs(n) + 3) / 4 + 1 + 7) / 8 * 8; }
 
@@ -46,7 +50,6 @@ __device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int j0, i
     struct alignas(E * sizeof(SrcT)) In { SrcT e[E]; };
     struct alignas(E * sizeof(T)) Out { T e[E]; };
     const int j1 = min(f.n, j0 + FIN_SEG);
-#pragma unroll 2
     for (int j = j0 + lane * E; j < j1; j += WAVE * E) {
         float v[E];
         const In a = *reinterpret_cast<const In*>(from + j);
@@ -58,11 +61,17 @@ __device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int j0, i
 #pragma unroll
             for (int e = 0; e < E; ++e) v[e] += to_f32(o.e[e]);
         }
-#pragma unroll 4
-        for (int s = 1; s < nsplit; ++s) {
-            const In b = *reinterpret_cast<const In*>(from + (int64_t)s * f.split_stride + j);
+        // all of a group's loads before the first sum: a wavefront waits for memory once per group (past the last
+        // range a group repeats it)
+        for (int s0 = 1; s0 < nsplit; s0 += FIN_AHEAD) {
+            In b[FIN_AHEAD];
 #pragma unroll
-            for (int e = 0; e < E; ++e) v[e] += to_f32(b.e[e]);
+            for (int k = 0; k < FIN_AHEAD; ++k)
+                b[k] = *reinterpret_cast<const In*>(from + (int64_t)min(s0 + k, nsplit - 1) * f.split_stride + j);
+#pragma unroll
+            for (int k = 0; k < FIN_AHEAD; ++k)
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[e] = s0 + k < nsplit ? v[e] + to_f32(b[k].e[e]) : v[e];
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) o.e[e] = from_f32<T>(v[e]);
