@@ -434,14 +434,18 @@ inline unsigned rn_slots(int64_t C) { return (unsigned)std::min<int64_t>(C, RN_S
 // 1024 x 512 x 8192 57.2 / 53.6, 1572 x 576 x 2176 53.9 / 44.7, 124 x 64 x 128256 67.3 / 64.4, 144 x 1472 x 59328 (5060
 // workgroups) 176 / 164; fp32 1871 x 1240 x 2653 277 / 261, 67 x 576 x 1706 36.0 / 33.9, 256 x 512 x 4096 (1024 64-tile
 // workgroups) 53.1 / 51.6, 604 x 2112 x 14422 (128-tiles) 721 / 701.  Many 64-tiles keep the two launches, where dX's
-// ranges are added up beside dW's tiles: 54 x 384 x 11328 45.1 / 47.6.
+// ranges are added up beside dW's tiles: 54 x 384 x 11328 45.1 / 47.6; likewise a dW of one K step, which is bound by
+// its writes: 24 x 1024 x 31078 behind an RMSNorm (2200 workgroups) 64.0 / 66.1, 51 x 3328 x 24297 (5180) 119.5 / 120.7.
+// An uncut dX alone gains the launch that moves its rows, and waits for its own stores: 30 x 2496 x 384 (60 tiles) 34.1 /
+// 33.0, 3195 x 2560 x 829 (360 with a target) 61.3 / 64.2.
 template <typename T>
 bool grads_in_one(const Plan& p, const VocabCut& dw, bool want_dw, bool dw_fast, int64_t rows, int64_t H, int64_t V) {
     constexpr bool BF16 = sizeof(T) == 2;
     if (p.nchunks != 1 || p.dx_tile == 256 || p.fast_dx != BF16 || H % 4 != 0) return false;
     if (want_dw && (dw_fast != BF16 || dw.main != V || dw.tile != p.dx_tile)) return false;
     const int64_t blocks = tiles_of(rows, H, p.dx_tile) * p.dx_ranges + (want_dw ? tiles_of(V, H, p.dx_tile) : 0);
-    return p.dx_ranges > 1 ? want_dw && blocks <= (BF16 ? 8192 : p.dx_tile == 64 ? 1024 : 4096) : blocks <= 2048;
+    if (p.dx_ranges == 1) return blocks <= (want_dw ? 2048 : 256);
+    return want_dw && blocks <= (BF16 ? (rows <= 64 ? 2048 : 8192) : p.dx_tile == 64 ? 1024 : 4096);
 }
 
 // dX = G W and dW = G^T X (dW not null) in one launch.
@@ -454,6 +458,7 @@ int launch_grad(const T* Z, int64_t ldz, const T* W, const T* Xc, float* part, T
     auto up = [](int64_t n) { return (n + FG_XCDS - 1) / FG_XCDS * FG_XCDS; };
     g.dx_blocks = (int)up(tiles_of(rows, H, tile) * ranges);
     const int64_t dw_blocks = dW ? up(tiles_of(V, H, tile)) : 0;
+    g.dw_first = dW && rows > V / ranges ? (int)dw_blocks : 0;
     const dim3 grid((unsigned)((cut ? 0 : FG_XCDS) + g.dx_blocks + dw_blocks)), block(256);
     void* out = cut ? static_cast<void*>(part) : rows_out;
     if constexpr (sizeof(T) == 2) {
@@ -656,7 +661,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                    norm ? nullptr : row_map, n_live, (int)rows, (int)H, norm ? dXg : dX, dx_add,
                    norm ? nullptr : row_loss, hdr, loss_here, finish_segs(H), (int)finish_blocks(rows, H)};
             FLCE_TRY(launch_grad<T>(Z, p.ldz, W, Xc, part, dXg, want_dw ? dW : nullptr, rows, H, V, p, dyn_m, dyn_dw,
-                                    GradArgs{fin, 0}, s));
+                                    GradArgs{fin, 0, 0}, s));
             if (cut) FLCE_TRY(launch_finish_dx<T>(fin, s));
         } else if (want_dx) {
             const bool staged = compact || norm;

@@ -838,6 +838,7 @@ __global__ __launch_bounds__(FG_THREADS, 2) void grad_bf16(FGArgs dx, FGArgs dw,
         if (block < FG_XCDS) return;
         block -= FG_XCDS;
     }
+    block = block < g.dw_first ? block + g.dx_blocks : block - g.dw_first;
     if (block < g.dx_blocks) {
         using Out = typename std::conditional<CUT, float, bf16_t>::type;
         const ProductTile t = fg_product<Out, void, false, true, 128, FG_PLAIN>(dx, NoFinish{}, block, smem);

@@ -537,6 +537,7 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void grad_f32(GGArgs dx, GGArg
         if (block < FG_XCDS) return;
         block -= FG_XCDS;
     }
+    block = block < g.dw_first ? block + g.dx_blocks : block - g.dw_first;
     if (block < g.dx_blocks) {
         const ProductTile t = gg_product<float, float, false, true, TILE, NoFinish, false>(dx, NoFinish{}, block, lds, nullptr);
         if (!CUT && t.rows > 0 && g.fin.idx) place_tile<float, TILE>(g.fin, t.m0, t.n0, t.rows);

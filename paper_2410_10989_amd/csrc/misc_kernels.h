@@ -1,5 +1,7 @@
 // Last step of a dX product: partial results summed, rows put back in place, loss summed.
 #pragma once
+#include <type_traits>
+
 #include "flce_device.h"
 #include "rowreduce.h"
 
@@ -35,7 +37,7 @@ struct FinishArgs {
 // (Rows are cut into segments so that a few long rows with many partial results fill the chip too:
 // 180 rows of 4096 with 16 ranges took 45 us with a wavefront per row.)
 constexpr int FIN_SEG = 512;
-// K ranges whose loads a wavefront has in flight: with 62 ranges, one wait for memory after the other, this launch
+// K ranges whose loads a wavefront has in flight, twice as many where there are more: with 62 ranges, one wait for memory after the other, this launch
 // was a quarter of the call (whole calls, 4 one by one / 8 together, us: 19 x 448 x 32000 50.9 / 42.6, 58 x 320 x 44288
 // 56.9 / 48.8, 94 x 384 x 23460 43.1 / 38.1, 2 heads of 218 x 312 x 104206 200 / 188).
 constexpr int FIN_AHEAD = 8;
@@ -63,16 +65,20 @@ __device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int j0, i
         }
         // all of a group's loads before the first sum: a wavefront waits for memory once per group (past the last
         // range a group repeats it)
-        for (int s0 = 1; s0 < nsplit; s0 += FIN_AHEAD) {
-            In b[FIN_AHEAD];
+        auto add_group = [&](auto ahead_, int s0) {
+            constexpr int AHEAD = decltype(ahead_)::value;
+            In b[AHEAD];
 #pragma unroll
-            for (int k = 0; k < FIN_AHEAD; ++k)
+            for (int k = 0; k < AHEAD; ++k)
                 b[k] = *reinterpret_cast<const In*>(from + (int64_t)min(s0 + k, nsplit - 1) * f.split_stride + j);
 #pragma unroll
-            for (int k = 0; k < FIN_AHEAD; ++k)
+            for (int k = 0; k < AHEAD; ++k)
 #pragma unroll
                 for (int e = 0; e < E; ++e) v[e] = s0 + k < nsplit ? v[e] + to_f32(b[k].e[e]) : v[e];
-        }
+        };
+        int s = 1;
+        for (; nsplit - s > FIN_AHEAD; s += 2 * FIN_AHEAD) add_group(std::integral_constant<int, 2 * FIN_AHEAD>{}, s);
+        if (s < nsplit) add_group(std::integral_constant<int, FIN_AHEAD>{}, s);
 #pragma unroll
         for (int e = 0; e < E; ++e) o.e[e] = from_f32<T>(v[e]);
         *reinterpret_cast<Out*>(to + j) = o;
@@ -113,6 +119,8 @@ __global__ __launch_bounds__(256) void finish_dx_kernel(FinishArgs f) {
 struct GradArgs {
     FinishArgs fin;    // src, idx, n, out, add, and the losses (row_loss null: not here)
     int dx_blocks;
+    int dw_first;      // dW's workgroups where theirs are the longer K loops and they come first, else 0 (a launch that ends
+                       // in its longest workgroups: 7005 x 3392 x 448 200 -> 207 us, 3195 x 2560 x 829 62.5 -> 65.2)
 };
 
 // Rows of the TILE x TILE tile at (m0, n0) of dX, which this workgroup (256 threads) has just written to
