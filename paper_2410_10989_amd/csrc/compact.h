@@ -188,10 +188,10 @@ __global__ __launch_bounds__(256) void select_rows_kernel(SelectArgs<T> s) {
 //
 // Valid rows of the batch, and which ones have the places m0 .. m0 + count - 1 among them: begin() by all
 // wavefronts of a workgroup, then place().  Wavefront w looks at its share of the batch, 64 rows at a time, and
-// keeps the first KEEP of these masks (2048 rows and 4 wavefronts: all of them) for place().
+// keeps these masks for place(): at most MAX_ROWS rows.
 template <int WAVES>
 struct TileRows {
-    static constexpr int KEEP = 8;
+    static constexpr int KEEP = 8, MAX_ROWS = KEEP * WAVE * WAVES;
     const int64_t* __restrict__ targets;
     int64_t ignore_index;
     int r0, r1, before;   // the wavefront's share, and the valid rows in front of it
@@ -214,7 +214,6 @@ struct TileRows {
             for (int g = 0; g < KEEP; ++g) kept[g] = look(r0 + g * WAVE);
 #pragma unroll
             for (int g = 0; g < KEEP; ++g) n += __popcll(kept[g]);
-            for (int r = r0 + KEEP * WAVE; r < r1; r += WAVE) n += __popcll(look(r));
         }
         if ((threadIdx.x & (WAVE - 1)) == 0) totals[wave] = n;
         __syncthreads();
@@ -238,7 +237,6 @@ struct TileRows {
         if (r0 < r1) {
 #pragma unroll
             for (int g = 0; g < KEEP; ++g) put(r0 + g * WAVE, kept[g]);
-            for (int r = r0 + KEEP * WAVE; r < r1 && at < count; r += WAVE) put(r, look(r));
         }
         __syncthreads();
     }

@@ -36,7 +36,7 @@ namespace {
 constexpr int MAX_DEVICES = 64;
 constexpr int64_t MAX_DIM = (int64_t)1 << 30;      // per-dimension limit, keeps int tile math safe
 constexpr int64_t CE_ROWS_PER_LAUNCH = 65536;
-constexpr int64_t SEL_IN_LOGITS_ROWS = 4096, SEL_ROWS_IN_LOGITS = 8;
+constexpr int64_t SEL_IN_LOGITS_ROWS = TileRows<4>::MAX_ROWS, SEL_ROWS_IN_LOGITS = 8;   // 2048
 constexpr int RIDE_BLOCKS = 1024;   // finish_dx as workgroups of the dW launch: at most this many
 constexpr int64_t ROT_A_BYTES = (int64_t)2 << 20;
 constexpr int64_t CE_CACHE_BYTES = (int64_t)256 << 20;   // memory-side cache
@@ -406,10 +406,12 @@ template <typename T>
 int launch_finish_dx(const FinishArgs& f, hipStream_t s) {
     ScopedKernelTimer timer(FLCE_KIND_DX_GEMM, s);
     const dim3 grid((unsigned)f.blocks), block(256);
-    if (finish_is_vec<T>(f))
-        hipLaunchKernelGGL((finish_dx_kernel<T, true>), grid, block, 0, s, f);
+    if (!finish_is_vec<T>(f))
+        hipLaunchKernelGGL((finish_dx_kernel<T, false, false>), grid, block, 0, s, f);
+    else if (f.nsplit > FIN_AHEAD)
+        hipLaunchKernelGGL((finish_dx_kernel<T, true, true>), grid, block, 0, s, f);
     else
-        hipLaunchKernelGGL((finish_dx_kernel<T, false>), grid, block, 0, s, f);
+        hipLaunchKernelGGL((finish_dx_kernel<T, true, false>), grid, block, 0, s, f);
     HIP_TRY(hipGetLastError());
     return FLCE_OK;
 }
@@ -493,7 +495,7 @@ int launch_grad(const T* Z, int64_t ldz, const T* W, const T* Xc, float* part, T
 // 53.5, 1024 x 512 x 8192 60 / 57, 51 x 3328 x 24297 129 / 119, one tile row in 1136 tiles (31 x 576 x 144923) 100.3 / 96.9;
 // 2664 tiles in three rows (294 x 128 x 113344) 110.5 / 112.9.  A handful of tiles with long K loops waits for its loads
 // alone, and the rows of X are further away than gathered ones: 30 x 2496 x 384 (3 tiles) 34.1 / 35.1,
-// 53 x 2352 x 2560 (20 tiles) 41.8 / 40.1.
+// 53 x 2352 x 2560 (20 tiles) 41.8 / 40.1.  Longer batches gain nothing (3195 x 2560 x 829: launches of 10.6 + 25.0 / 36.8).
 template <typename T>
 bool select_in_logits(const Plan& p, const VocabCut& cut, int64_t BT, int64_t H, int64_t V) {
     const int64_t tiles = tiles_of(BT, V, cut.tile);

@@ -37,14 +37,15 @@ struct FinishArgs {
 // (Rows are cut into segments so that a few long rows with many partial results fill the chip too:
 // 180 rows of 4096 with 16 ranges took 45 us with a wavefront per row.)
 constexpr int FIN_SEG = 512;
-// K ranges whose loads a wavefront has in flight, twice as many where there are more: with 62 ranges, one wait for memory after the other, this launch
+// K ranges whose loads a wavefront has in flight, twice as many where there are more (and no more loads than
+// ranges where there are few: 7776 x 2880 with 2 ranges 33 us, 55 with groups of 8): with 62 ranges, one wait for memory after the other, this launch
 // was a quarter of the call (whole calls, 4 one by one / 8 together, us: 19 x 448 x 32000 50.9 / 42.6, 58 x 320 x 44288
 // 56.9 / 48.8, 94 x 384 x 23460 43.1 / 38.1, 2 heads of 218 x 312 x 104206 200 / 188).
 constexpr int FIN_AHEAD = 8;
 inline int finish_segs(int64_t n) { return (int)((n + FIN_SEG - 1) / FIN_SEG); }
 inline int64_t finish_blocks(int64_t rows, int64_t n) { return ((rows * finish_segs(n) + 3) / 4 + 1 + 7) / 8 * 8; }
 
-template <typename T, typename SrcT, bool ADD, int E>
+template <typename T, typename SrcT, bool ADD, int E, bool MANY>
 __device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int j0, int lane) {
     const int nsplit = f.dyn_nsplit ? *f.dyn_nsplit : f.nsplit;
     const SrcT* from = static_cast<const SrcT*>(f.src) + (int64_t)i * f.n;
@@ -52,6 +53,7 @@ __device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int j0, i
     struct alignas(E * sizeof(SrcT)) In { SrcT e[E]; };
     struct alignas(E * sizeof(T)) Out { T e[E]; };
     const int j1 = min(f.n, j0 + FIN_SEG);
+#pragma unroll 2
     for (int j = j0 + lane * E; j < j1; j += WAVE * E) {
         float v[E];
         const In a = *reinterpret_cast<const In*>(from + j);
@@ -63,29 +65,43 @@ __device__ __forceinline__ void finish_row(const FinishArgs& f, int i, int j0, i
 #pragma unroll
             for (int e = 0; e < E; ++e) v[e] += to_f32(o.e[e]);
         }
-        // all of a group's loads before the first sum: a wavefront waits for memory once per group (past the last
-        // range a group repeats it)
-        auto add_group = [&](auto ahead_, int s0) {
-            constexpr int AHEAD = decltype(ahead_)::value;
-            In b[AHEAD];
+        if constexpr (std::is_same<SrcT, float>::value) {   // (rows in the storage type are whole sums)
+            // all of a group's loads before the first sum: a wavefront waits for memory once per group (past the last
+            // range a group repeats it)
+            [[maybe_unused]] auto add_group = [&](auto ahead_, int s0) {
+                constexpr int AHEAD = decltype(ahead_)::value;
+                In b[AHEAD];
 #pragma unroll
-            for (int k = 0; k < AHEAD; ++k)
-                b[k] = *reinterpret_cast<const In*>(from + (int64_t)min(s0 + k, nsplit - 1) * f.split_stride + j);
+                for (int k = 0; k < AHEAD; ++k)
+                    b[k] = *reinterpret_cast<const In*>(from + (int64_t)min(s0 + k, nsplit - 1) * f.split_stride + j);
 #pragma unroll
-            for (int k = 0; k < AHEAD; ++k)
+                for (int k = 0; k < AHEAD; ++k)
 #pragma unroll
-                for (int e = 0; e < E; ++e) v[e] = s0 + k < nsplit ? v[e] + to_f32(b[k].e[e]) : v[e];
-        };
-        int s = 1;
-        for (; nsplit - s > FIN_AHEAD; s += 2 * FIN_AHEAD) add_group(std::integral_constant<int, 2 * FIN_AHEAD>{}, s);
-        if (s < nsplit) add_group(std::integral_constant<int, FIN_AHEAD>{}, s);
+                    for (int e = 0; e < E; ++e) v[e] = s0 + k < nsplit ? v[e] + to_f32(b[k].e[e]) : v[e];
+            };
+            int s = 1;
+            if constexpr (MANY) {
+                for (; nsplit - s > FIN_AHEAD; s += 2 * FIN_AHEAD) add_group(std::integral_constant<int, 2 * FIN_AHEAD>{}, s);
+                if (nsplit - s > FIN_AHEAD / 2) {
+                    add_group(std::integral_constant<int, FIN_AHEAD>{}, s);
+                    s += FIN_AHEAD;
+                }
+            }
+#pragma unroll 4
+            for (; s < nsplit; ++s) {
+                const In b = *reinterpret_cast<const In*>(from + (int64_t)s * f.split_stride + j);
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[e] += to_f32(b.e[e]);
+            }
+        }
 #pragma unroll
         for (int e = 0; e < E; ++e) o.e[e] = from_f32<T>(v[e]);
         *reinterpret_cast<Out*>(to + j) = o;
     }
 }
-// One workgroup of 256 threads; part: 32 bytes of LDS.
-template <typename T, int E>
+// One workgroup of 256 threads; part: 32 bytes of LDS.  MANY: for more than FIN_AHEAD ranges (its registers cost
+// launches that only move rows 10 %).
+template <typename T, int E, bool MANY = true>
 __device__ __forceinline__ void finish_dx(const FinishArgs& f, int block, void* part) {
     if (block == 0) {   // (first: it takes longer than a few rows do)
         if (f.row_loss) loss_accumulate(f.row_loss, f.rows, f.hdr, f.loss, static_cast<double*>(part));
@@ -95,18 +111,18 @@ __device__ __forceinline__ void finish_dx(const FinishArgs& f, int block, void* 
     const int i = u / f.segs, j0 = (u - i * f.segs) * FIN_SEG;
     if (i >= (f.live ? min(f.rows, *f.live) : f.rows)) return;
     if (f.src_f32) {
-        if (f.add) finish_row<T, float, true, E>(f, i, j0, lane); else finish_row<T, float, false, E>(f, i, j0, lane);
+        if (f.add) finish_row<T, float, true, E, MANY>(f, i, j0, lane); else finish_row<T, float, false, E, MANY>(f, i, j0, lane);
     } else if (E == 4 && sizeof(T) == 2 && f.n % 8 == 0) {   // whole rows in the storage type: 16 bytes per lane
         constexpr int E8 = E == 4 ? 8 : E;                   // (dX and the workspace are 16-byte aligned)
-        if (f.add) finish_row<T, T, true, E8>(f, i, j0, lane); else finish_row<T, T, false, E8>(f, i, j0, lane);
+        if (f.add) finish_row<T, T, true, E8, false>(f, i, j0, lane); else finish_row<T, T, false, E8, false>(f, i, j0, lane);
     } else {
-        if (f.add) finish_row<T, T, true, E>(f, i, j0, lane); else finish_row<T, T, false, E>(f, i, j0, lane);
+        if (f.add) finish_row<T, T, true, E, false>(f, i, j0, lane); else finish_row<T, T, false, E, false>(f, i, j0, lane);
     }
 }
-template <typename T, bool VEC4>
+template <typename T, bool VEC4, bool MANY>
 __global__ __launch_bounds__(256) void finish_dx_kernel(FinishArgs f) {
     __shared__ double part[4];
-    finish_dx<T, VEC4 ? 4 : 1>(f, (int)blockIdx.x, part);
+    finish_dx<T, VEC4 ? 4 : 1, MANY>(f, (int)blockIdx.x, part);
 }
 
 // One launch for the gradients of a chunk on small tiles: dX's tiles and K ranges (dx_blocks, a multiple of

@@ -250,10 +250,8 @@ def test_selection_changes_over_with_the_chunk_count(BT, dtype):
     (256, 128, 2000),    # one chunk of at most 256 rows: rotated K loop (bf16)
     (257, 1024, 700),    # fewer than 16 tiles, the longest K loop that still has its rows picked; 1032: no longer
     (257, 1032, 700),
-    (2048, 64, 600),     # the masks of the first look serve the second one; 2049: not all of them
+    (2048, 64, 600),     # the longest batch; 2049: a launch of its own
     (2049, 64, 600),
-    (4096, 64, 1000),    # the longest batch; 4097: a launch of its own
-    (4097, 64, 1000),
 ])
 def test_rows_picked_by_the_logits_launch(dtype, ignore, BT, H, V):
     import paper_2410_10989_amd as flce
