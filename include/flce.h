@@ -232,14 +232,16 @@ FLCE_API int flce_cross_entropy_inplace(void* Z, const int64_t* targets, int64_t
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, same kernels, same results bit for bit, but the device header and
  * the per-row losses live in a fixed array inside the library's device image
- * (256 + 4 * FLCE_CE_NOALLOC_MAX_ROWS bytes = 262 400 bytes on every GPU the library
+ * (256 + 4 * FLCE_CE_NOALLOC_MAX_ROWS bytes = 262 400 bytes, and 8 448 bytes of
+ * counters of this entry point and the one above, on every GPU the library
  * is used on, held until the process ends) instead of the workspace, so the call
  * allocates and frees nothing and ignores flce_set_workspace and flce_timing_enable.
  *   BT > FLCE_CE_NOALLOC_MAX_ROWS returns FLCE_ERR_TOO_LARGE before anything is launched.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU
  * (different streams, different threads) race; serialise them on one stream.  The
  * array keeps the previous call's contents; the kernels overwrite every slot they
- * read (a counter of finished workgroups is left at zero), nothing needs clearing.  The first call on a device looks the array's device
+ * read, nothing needs clearing, and calls that did overlap leave nothing behind that
+ * later ones could trip over.  The first call on a device looks the array's device
  * address up (hipGetSymbolAddress): make one call outside stream capture first.
  */
 #define FLCE_CE_NOALLOC_MAX_ROWS 65536

@@ -25,11 +25,9 @@ using namespace flce;
 // host code this name is only a handle for hipGetSymbolAddress, never an address.
 constexpr size_t CE_NOALLOC_BYTES = 256 + (size_t)FLCE_CE_NOALLOC_MAX_ROWS * sizeof(float);
 static __device__ __align__(256) unsigned char scratch[CE_NOALLOC_BYTES];
-// Counters of ce_rows_kernel (count_done): zero in the image and left at zero by every launch.  The first
-// set is that entry point's; calls of the other one take the rest in turn (theirs cannot be in the
-// workspace, whose contents are anybody's, and calls on different lent buffers may overlap).
-constexpr unsigned CE_DONE_TURNS = 8;
-static __device__ unsigned ce_done[(1 + CE_DONE_TURNS) * DONE_WORDS];
+// Counters of ce_rows_kernel (DoneCount), for calls that must not overlap anyway because they share their
+// scratch memory: one set for that entry point, one for the library's own workspace.
+static __device__ done_t ce_done[2 * DONE_WORDS];
 
 namespace {
 
@@ -60,7 +58,7 @@ void* g_done_ptr[MAX_DEVICES] = {};
 // Process-wide settings: read by every call, written by the setters (any thread).
 std::atomic<size_t> g_budget{0};   // 0 = the automatic rule of effective_budget()
 std::atomic<bool> g_compact{true};
-std::atomic<unsigned> g_ce_turn{0};   // which counters the next stand-alone cross entropy takes
+std::atomic<done_t> g_ce_ticket{0};   // the last one given to a launch that counts its workgroups (DoneCount)
 
 // What a call's plan depends on besides the shape: the process-wide settings, or the
 // options a caller passes with the call.
@@ -149,12 +147,14 @@ inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_
 // The device's shared workspace: the lent buffer, or memory of the library's own that grows as needed.
 // last = false: the caller has a plan that needs less, so an allocation that found too little memory is
 // not tried again on every call (but after flce_release_workspace, or once one as large succeeds).
-int acquire_workspace(size_t need, char** out, bool last = true) {
+// lent: whether it is the lent buffer.
+int acquire_workspace(size_t need, char** out, bool last = true, bool* lent = nullptr) {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= MAX_DEVICES) return FLCE_ERR_ARG;
     std::lock_guard<std::mutex> lock(g_mutex);
     DeviceWorkspace& w = g_ws[dev];
+    if (lent) *lent = w.lent != nullptr;
     if (w.lent) {
         if (w.lent_bytes < need) return FLCE_ERR_WORKSPACE;
         *out = static_cast<char*>(w.lent);
@@ -344,7 +344,7 @@ template <typename T>
 int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int64_t V,
                    int zero_pad, int64_t ignore_index, DeviceHeader* hdr, float* row_loss,
                    hipStream_t s, const int* n_rows, bool timed, int count_n, float weight, bool fused,
-                   unsigned* done = nullptr, float* loss = nullptr) {
+                   const DoneCount& done = DoneCount{}, float* loss = nullptr) {
     ScopedKernelTimer timer(timed ? FLCE_KIND_CE_ROWS : -1, s);
     // shape by row length, nontemporal accesses by size: see ce_rows_kernel
     const int64_t row_bytes = V * (int64_t)sizeof(T);
@@ -354,7 +354,7 @@ int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int6
                        targets, (int)V, zero_pad, ignore_index, hdr, row_loss, n_rows, count_n, weight, done, loss)
 #define CE_SHAPE(TH, NV, NL) \
     do {                                                                                             \
-        if (done) CE_LAUNCH(TH, NV, false, NL, true);                                                \
+        if (done.words) CE_LAUNCH(TH, NV, false, NL, true);                                                \
         else if (nt) CE_LAUNCH(TH, NV, true, NL, false);                                             \
         else CE_LAUNCH(TH, NV, false, NL, false);                                                    \
     } while (0)
@@ -904,14 +904,16 @@ int check_ce_args(const void* Z, const int64_t* targets, int64_t BT, int64_t V, 
 }
 
 // Stand-alone cross entropy on logits Z, `step` rows per launch, with the device header
-// and the per-row losses (`step` floats) in memory the caller of this function provides; done:
-// ce_rows_kernel's counters, or null.
+// and the per-row losses (`step` floats) in memory the caller of this function provides; done_words:
+// the counters that go with that memory, or null.
 int run_ce_inplace(void* Z, const int64_t* targets, int64_t BT, int64_t V, int64_t ldz,
                    int64_t ignore_index, int dtype, float* loss, DeviceHeader* hdr, float* row_loss,
-                   int64_t step, unsigned* done, bool timed, hipStream_t s) {
+                   int64_t step, done_t* done_words, bool timed, hipStream_t s) {
     const int count_n = BT <= ce_count_rows(V * (int64_t)elem_size(dtype)) && BT <= step ? (int)BT : 0;
     // (logits beyond the memory-side cache: milliseconds, and they want the nontemporal variants)
-    if (!count_n || BT > CE_FOLD_ROWS || BT * V * (int64_t)elem_size(dtype) > CE_CACHE_BYTES) done = nullptr;
+    DoneCount done{};
+    if (done_words && count_n && BT * V * (int64_t)elem_size(dtype) <= CE_CACHE_BYTES)
+        done = {done_words, g_ce_ticket.fetch_add(1) + 1};
     if (!count_n) {
         hipLaunchKernelGGL(count_valid_kernel, dim3(1), dim3(1024), 0, s, targets, BT, ignore_index,
                            1.0f, hdr);
@@ -927,14 +929,14 @@ int run_ce_inplace(void* Z, const int64_t* targets, int64_t BT, int64_t V, int64
             FLCE_TRY(launch_ce_rows<bf16_t>(static_cast<bf16_t*>(Z) + r0 * ldz, ldz, targets + r0,
                                             rows, V, 0, ignore_index, hdr, row_loss, s, nullptr, timed, count_n, 1.0f, false,
                                             done, loss));
-        if (!done) FLCE_TRY(launch_loss(row_loss, rows, hdr,
+        if (!done.words) FLCE_TRY(launch_loss(row_loss, rows, hdr,
                              r0 + rows == BT ? LossOut{hdr, 1, loss, nullptr, {1.0f}} : LossOut{}, timed, s));
     }
     return FLCE_OK;
 }
 
 // The current device's copies of `scratch` and `ce_done` (on the first call on a device the runtime is asked).
-int static_addresses(unsigned char** scratch_at, unsigned** done_at) {
+int static_addresses(unsigned char** scratch_at, done_t** done_at) {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= MAX_DEVICES) return FLCE_ERR_ARG;
@@ -948,8 +950,20 @@ int static_addresses(unsigned char** scratch_at, unsigned** done_at) {
         g_done_ptr[dev] = q;
     }
     *scratch_at = static_cast<unsigned char*>(g_scratch_ptr[dev]);
-    *done_at = static_cast<unsigned*>(g_done_ptr[dev]);
+    *done_at = static_cast<done_t*>(g_done_ptr[dev]);
     return FLCE_OK;
+}
+
+// Whether a stand-alone cross entropy may be the one launch that counts its workgroups.  Not while the
+// stream is captured: every replay of the launch would bring the same ticket.
+bool folds_loss(int64_t BT, hipStream_t s) {
+    if (BT > CE_FOLD_ROWS) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusNone;
 }
 
 // flce_multihead_fwd_bwd with the settings given (the process-wide ones, or a call's options)
@@ -1107,14 +1121,17 @@ int flce_cross_entropy_inplace(void* Z, const int64_t* targets, int64_t BT, int6
                                int64_t ignore_index, int dtype, float* loss, void* stream) {
     FLCE_TRY(check_ce_args(Z, targets, BT, V, ldz, ignore_index, dtype, loss));
     const int64_t step = BT < CE_ROWS_PER_LAUNCH ? BT : CE_ROWS_PER_LAUNCH;
+    hipStream_t s = static_cast<hipStream_t>(stream);
     char* ws = nullptr;
-    FLCE_TRY(acquire_workspace(256 + (size_t)step * sizeof(float), &ws));
-    unsigned* done = nullptr;   // (no address: a launch more)
+    bool lent = false;
+    FLCE_TRY(acquire_workspace(256 + (size_t)step * sizeof(float), &ws, true, &lent));
+    // Calls on different lent buffers may overlap, and a buffer's contents are anybody's: no counters for them.
+    done_t* done = nullptr;
     unsigned char* unused;
-    if (BT <= CE_FOLD_ROWS && static_addresses(&unused, &done) == FLCE_OK) done += (1 + g_ce_turn.fetch_add(1) % CE_DONE_TURNS) * DONE_WORDS;
+    if (!lent && folds_loss(BT, s) && static_addresses(&unused, &done) == FLCE_OK) done += DONE_WORDS;
     return run_ce_inplace(Z, targets, BT, V, ldz, ignore_index, dtype, loss,
                           reinterpret_cast<DeviceHeader*>(ws), reinterpret_cast<float*>(ws + 256), step,
-                          done, true, static_cast<hipStream_t>(stream));
+                          done, true, s);
 }
 
 int flce_cross_entropy_inplace_noalloc(void* Z, const int64_t* targets, int64_t BT, int64_t V,
@@ -1122,15 +1139,16 @@ int flce_cross_entropy_inplace_noalloc(void* Z, const int64_t* targets, int64_t 
                                        void* stream) {
     FLCE_TRY(check_ce_args(Z, targets, BT, V, ldz, ignore_index, dtype, loss));
     if (BT > FLCE_CE_NOALLOC_MAX_ROWS) return FLCE_ERR_TOO_LARGE;
+    hipStream_t s = static_cast<hipStream_t>(stream);
     unsigned char* ptr = nullptr;
-    unsigned* done = nullptr;
+    done_t* done = nullptr;
     FLCE_TRY(static_addresses(&ptr, &done));
     // The header is reset by the counting kernel or, for small batches, by the row kernel, and every
     // row's loss slot is written by the row kernel before it is summed, so nothing of the previous
     // call's contents is read.
     return run_ce_inplace(Z, targets, BT, V, ldz, ignore_index, dtype, loss,
                           reinterpret_cast<DeviceHeader*>(ptr), reinterpret_cast<float*>(ptr + 256), BT,
-                          done, false, static_cast<hipStream_t>(stream));
+                          folds_loss(BT, s) ? done : nullptr, false, s);
 }
 
 size_t flce_workspace_bytes(int64_t BT, int64_t H, int64_t V, int dtype) {

@@ -231,21 +231,42 @@ __device__ __forceinline__ void write_header(DeviceHeader* hdr, int n_valid, flo
 inline int64_t ce_count_rows(int64_t row_bytes) {
     return row_bytes > 112 * 1024 ? 512 : row_bytes > 48 * 1024 ? 1024 : 1536;
 }
-// Counters of finished workgroups, zero between launches: workgroup b counts itself in word b % DONE_GROUPS,
-// the last one of a group in the word behind them.  One word takes an arrival every 10-12 ns (1068 rows of
-// one call 14.3 -> 22.5 us with a single word); the words lie in lines of their own.
-constexpr int DONE_GROUPS = 32, DONE_STRIDE = 32;   // words
+// Counters of finished workgroups: workgroup b counts itself in word b % DONE_GROUPS, the last one of a group
+// in the word behind them.  One word takes an arrival every 10-12 ns (1068 rows of one call 14.3 -> 22.5 us
+// with a single word); the words lie in lines of their own.
+//
+// A word holds the launch's ticket and, in its low bits, the count.  It is zero between launches, but launches
+// that overlapped on the same words (which the entry points forbid) may leave anything there.  So no
+// launch trusts what it finds: its workgroups first raise the words they use to its own ticket and count 0,
+// and the count is complete only under that ticket.  Tickets rise from call to call, so the next launch is right again.
+constexpr int DONE_GROUPS = 32, DONE_STRIDE = 16;   // words
 constexpr int DONE_WORDS = (DONE_GROUPS + 1) * DONE_STRIDE;
-// One thread per workgroup; true for the last workgroup of the launch.
-__device__ __forceinline__ bool count_done(unsigned* done) {
+constexpr int DONE_COUNT_BITS = 16;
+using done_t = unsigned long long;
+struct DoneCount {
+    done_t* words;   // null: not counted
+    done_t ticket;   // of this launch alone, above 0
+};
+// One thread per workgroup, early: the update runs beside the row's own work.  The last word is raised by the
+// workgroups whose numbers name the groups: each is in front of its group's last one (count_done).
+__device__ __forceinline__ void open_done(const DoneCount& d) {
+    const done_t none = d.ticket << DONE_COUNT_BITS;
+    __hip_atomic_fetch_max(d.words + blockIdx.x % DONE_GROUPS * DONE_STRIDE, none, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (blockIdx.x < DONE_GROUPS)
+        __hip_atomic_fetch_max(d.words + DONE_GROUPS * DONE_STRIDE, none, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The same thread, once what it has stored before and open_done's updates are in memory; true for the last
+// workgroup of the launch.
+__device__ __forceinline__ bool count_done(const DoneCount& d) {
     const unsigned n = gridDim.x, group = blockIdx.x % DONE_GROUPS;
     const unsigned of_group = (n - group + DONE_GROUPS - 1) / DONE_GROUPS, groups = min(n, (unsigned)DONE_GROUPS);
-    unsigned* word = done + group * DONE_STRIDE;
-    if (__hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != of_group - 1) return false;
-    __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    word = done + DONE_GROUPS * DONE_STRIDE;
-    if (__hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != groups - 1) return false;
-    __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const done_t none = d.ticket << DONE_COUNT_BITS;
+    done_t* word = d.words + group * DONE_STRIDE;
+    if (__hip_atomic_fetch_add(word, (done_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != none + of_group - 1) return false;
+    __hip_atomic_store(word, (done_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    word = d.words + DONE_GROUPS * DONE_STRIDE;
+    if (__hip_atomic_fetch_add(word, (done_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != none + groups - 1) return false;
+    __hip_atomic_store(word, (done_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return true;
 }
 
@@ -253,13 +274,13 @@ __device__ __forceinline__ bool count_done(unsigned* done) {
 // same sum in the same order as loss_accumulate.
 template <int THREADS>
 __device__ __forceinline__ void ce_fold_loss(const int64_t* __restrict__ targets, int64_t ignore_index,
-                                             const float* row_loss, unsigned* done, float* __restrict__ loss,
+                                             const float* row_loss, const DoneCount& done, float* __restrict__ loss,
                                              int* counts) {
     __shared__ int s_last;
     __shared__ double part[4];
     const int tid = threadIdx.x, rows = (int)gridDim.x;
     if (tid == 0) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this row's loss is in memory
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this row's loss and open_done's updates are in memory
         s_last = count_done(done);
     }
     __syncthreads();
@@ -284,9 +305,8 @@ __device__ __forceinline__ void ce_fold_loss(const int64_t* __restrict__ targets
 // launches that follow.  count_n = 0: the header holds the count.
 //
 // FOLD (count_n > 0 only): where the whole batch is one launch and nothing follows it, the loss is summed here as well,
-// by the workgroup that finishes last (no workgroup waits for another): each one counts itself in *done,
-// which is zero before and after a launch, once its row's loss has been written through to memory
-// (the L2s of the XCDs are not coherent).  It saves a launch: whole calls of 19 x 3264 bf16 12.1 -> 9.7 us,
+// by the workgroup that finishes last (no workgroup waits for another): each one counts itself in `done`
+// once its row's loss has been written through to memory (the L2s of the XCDs are not coherent).  It saves a launch: whole calls of 19 x 3264 bf16 12.1 -> 9.7 us,
 // 187 x 8320 bf16 12.3 -> 9.7, 227 x 17107 fp32 12.1 -> 9.9.  Batches beyond CE_FOLD_ROWS have the launch: the count
 // at the end of every workgroup costs them as much (643 x 22336 bf16 14.8 -> 15.5, 800 x 15360 fp32
 // 24.2 -> 25.0, 1068 x 11520 bf16 15.0 -> 14.9, 8174 x 1152 fp32 27.3 -> 30.4).
@@ -295,13 +315,16 @@ template <typename T, int THREADS, int NV, bool NT, int NL = 0, bool FOLD = fals
 __global__ __launch_bounds__(THREADS) void ce_rows_kernel(
     T* __restrict__ Z, int64_t ldz, const int64_t* __restrict__ targets, int V, int zero_pad,
     int64_t ignore_index, DeviceHeader* __restrict__ hdr, float* __restrict__ row_loss,
-    const int* __restrict__ live, int count_n, float weight, unsigned* done, float* __restrict__ loss) {
+    const int* __restrict__ live, int count_n, float weight, DoneCount done, float* __restrict__ loss) {
     constexpr int VEC = RowVec<T>::N;
     const int row = blockIdx.x;
     const int tid = threadIdx.x;
     if (live && row >= *live) {   // past the chunk's live rows (uniform per workgroup)
         if (tid == 0) row_loss[row] = 0.f;
         return;
+    }
+    if constexpr (FOLD) {
+        if (tid == 0) open_done(done);
     }
     T* z = Z + (int64_t)row * ldz;
     const int64_t t = targets[row];

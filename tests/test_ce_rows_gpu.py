@@ -66,3 +66,92 @@ def test_loss_of_small_batches_in_repeated_calls(V, rows, noalloc):
         loss = flce.flce_cross_entropy_inplace(Z0[:n].clone(), tn, -100, noalloc=noalloc)
         # a row's loss is a 32-bit number of size log V + |z| <= 20: rounded to 2^-20, some such steps in it
         assert abs(float(loss) - want) <= 1e-5, n
+
+
+def _small_batch(rows, V, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    Z = torch.randn(rows, V, device="cuda", generator=g).to(torch.bfloat16)
+    t = torch.randint(0, V, (rows,), device="cuda", generator=g)
+    t[torch.rand(rows, device="cuda", generator=g) < 0.2] = -100
+    ok = t != -100
+    lse = torch.logsumexp(Z.double(), 1)
+    return Z, t, float(((lse - Z.double().gather(1, t.clamp(min=0)[:, None])[:, 0]) * ok).sum() / max(1, int(ok.sum())))
+
+
+def _on_two_streams(calls):
+    """calls[j]: what stream j does; both start together, once some milliseconds of other work have ended."""
+    gate, streams = torch.cuda.Stream(), [torch.cuda.Stream() for _ in calls]
+    busy = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(gate):
+        for _ in range(20):
+            busy @ busy
+        opened = gate.record_event()
+    for s, todo in zip(streams, calls):
+        s.wait_event(opened)
+        with torch.cuda.stream(s):
+            for call in todo:
+                call()
+    torch.cuda.synchronize()
+
+
+def test_small_batches_that_overlap_on_lent_buffers():
+    # calls on different lent buffers share nothing: 100 calls on each of two streams at the same time
+    import paper_2410_10989_amd as flce
+    n, sizes = 100, ((300, 30000), (190, 30000))
+    buffers = [torch.empty(1 << 16, dtype=torch.uint8, device="cuda") for _ in sizes]
+    data = [[_small_batch(*size, 31 * j + k) for k in range(3)] for j, size in enumerate(sizes)]
+    Zs = [[data[j][k % 3][0].clone() for k in range(n)] for j in range(2)]
+    losses = [torch.full((n,), float("nan"), device="cuda") for _ in sizes]
+
+    def call(j, k):
+        flce.flce_set_workspace(buffers[j])
+        flce.flce_cross_entropy_inplace(Zs[j][k], data[j][k % 3][1], -100, loss=losses[j][k])
+
+    try:
+        _on_two_streams([[lambda j=j, k=k: call(j, k) for k in range(n)] for j in range(2)])
+    finally:
+        flce.flce_set_workspace(None)
+    for j in range(2):
+        want = torch.tensor([data[j][k % 3][2] for k in range(n)])
+        assert float((losses[j].cpu().double() - want.double()).abs().max()) <= 1e-5, j   # as above
+
+
+def test_small_batches_after_calls_that_overlapped():
+    # overlapping calls of the allocation-free entry point are forbidden and their results open; the calls after
+    # them are right again
+    import paper_2410_10989_amd as flce
+    n = 100
+    data = [_small_batch(rows, 30000, rows) for rows in (300, 190)]
+    Zs = [[d[0].clone() for _ in range(n)] for d in data]
+    out = torch.empty(2 * n, device="cuda")
+    _on_two_streams([[lambda j=j, k=k: flce.flce_cross_entropy_inplace_noalloc(Zs[j][k], data[j][1], -100, loss=out[j * n + k])
+                      for k in range(n)] for j in range(2)])
+    for rows in (300, 17, 512, 33, 1, 300):
+        Z, t, want = _small_batch(rows, 3000, rows)
+        loss = torch.full((), float("nan"), device="cuda")
+        flce.flce_cross_entropy_inplace_noalloc(Z, t, -100, loss=loss)
+        assert abs(float(loss) - want) <= 1e-5, rows
+
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_captured_small_batches_beside_eager_ones(noalloc):
+    # a replay repeats its launches' arguments: captured calls sum the loss in a launch of its own
+    import paper_2410_10989_amd as flce
+    Z0, t, want = _small_batch(100, 3000, 5)
+    Z, loss = Z0.clone(), torch.full((), float("nan"), device="cuda")
+    flce.flce_cross_entropy_inplace(Z0.clone(), t, -100, noalloc=noalloc)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        flce.flce_cross_entropy_inplace(Z, t, -100, loss=loss, noalloc=noalloc)
+    for k in range(4):
+        Z.copy_(Z0)
+        loss.fill_(float("nan"))
+        graph.replay()
+        eager = Z0.clone()
+        loss_eager = flce.flce_cross_entropy_inplace(eager, t, -100, noalloc=noalloc)
+        torch.cuda.synchronize()
+        assert abs(float(loss) - want) <= 1e-5 and float(loss) == float(loss_eager), k
+        assert torch.equal(Z, eager), k
