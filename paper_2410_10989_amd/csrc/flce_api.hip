@@ -430,26 +430,6 @@ int rmsnorm_vectors_per_thread(int64_t H, const void* x, const void* gamma, cons
 // Partial rows of dgamma that a chunk of C rows can reach.
 inline unsigned rn_slots(int64_t C) { return (unsigned)std::min<int64_t>(C, RN_SLOTS); }
 
-// Whether the gradients of a batch that is one chunk are one launch (GradArgs).  The two products share the
-// chip and, without K ranges, the launch that puts dX's rows in place goes as well.  Whole calls, us, two
-// launches / one: bf16 18 x 960 x 384 25.8 / 21.5, 1765 x 3584 x 2635 148 / 133, 32 x 1792 x 512 32.9 / 29.3; with K ranges
-// 1024 x 512 x 8192 57.2 / 53.6, 1572 x 576 x 2176 53.9 / 44.7, 124 x 64 x 128256 67.3 / 64.4, 144 x 1472 x 59328 (5060
-// workgroups) 176 / 164; fp32 1871 x 1240 x 2653 277 / 261, 67 x 576 x 1706 36.0 / 33.9, 256 x 512 x 4096 (1024 64-tile
-// workgroups) 53.1 / 51.6, 604 x 2112 x 14422 (128-tiles) 721 / 701.  Many 64-tiles keep the two launches, where dX's
-// ranges are added up beside dW's tiles: 54 x 384 x 11328 45.1 / 47.6; likewise a dW of one K step, which is bound by
-// its writes: 24 x 1024 x 31078 behind an RMSNorm (2200 workgroups) 64.0 / 66.1, 51 x 3328 x 24297 (5180) 119.5 / 120.7.
-// An uncut dX alone gains the launch that moves its rows, and waits for its own stores: 30 x 2496 x 384 (60 tiles) 34.1 /
-// 33.0, 3195 x 2560 x 829 (360 with a target) 61.3 / 64.2.
-template <typename T>
-bool grads_in_one(const Plan& p, const VocabCut& dw, bool want_dw, bool dw_fast, int64_t rows, int64_t H, int64_t V) {
-    constexpr bool BF16 = sizeof(T) == 2;
-    if (p.nchunks != 1 || p.dx_tile == 256 || p.fast_dx != BF16 || H % 4 != 0) return false;
-    if (want_dw && (dw_fast != BF16 || dw.main != V || dw.tile != p.dx_tile)) return false;
-    const int64_t blocks = tiles_of(rows, H, p.dx_tile) * p.dx_ranges + (want_dw ? tiles_of(V, H, p.dx_tile) : 0);
-    if (p.dx_ranges == 1) return blocks <= (want_dw ? 2048 : 256);
-    return want_dw && blocks <= (BF16 ? (rows <= 64 ? 2048 : 8192) : p.dx_tile == 64 ? 1024 : 4096);
-}
-
 // dX = G W and dW = G^T X (dW not null) in one launch.
 template <typename T>
 int launch_grad(const T* Z, int64_t ldz, const T* W, const T* Xc, float* part, T* rows_out, T* dW, int64_t rows, int64_t H,
@@ -565,7 +545,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         const int64_t* tc = targets + r0;
         const bool dw_fast = BF16 && (last ? p.fast_dw_last : p.fast_dw_full);
         const VocabCut dw_cut = vocab_cut(dw_fast, V, H, rows, p.tail_bytes > 0);
-        const bool one_grad = select && want_dx && grads_in_one<T>(p, dw_cut, want_dw, dw_fast, rows, H, V);
+        const bool one_grad = select && want_dx && grads_in_one(p, dw_cut, BF16, want_dw, dw_fast, !norm, rows, H, V);
         const VocabCut z_cut = vocab_cut(BF16 && p.fast_logits, V, rows, H, false);
         const bool in_logits = select && !norm && select_in_logits<T>(p, z_cut, BT, H, V);
         SelectArgs<T> sel{};

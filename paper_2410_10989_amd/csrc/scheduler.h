@@ -256,6 +256,45 @@ inline VocabCut vocab_cut(bool tuned, int64_t V, int64_t other, int64_t K, bool 
     return best;
 }
 
+// Whether the gradients of a batch that is one chunk are one launch (GradArgs).  The two products share the
+// chip and, without K ranges, the launch that puts dX's rows in place goes as well; with K ranges a launch
+// that adds them up follows, which otherwise runs beside dW's tiles, so that only the better fill is gained.
+// places: the launch puts dX's rows in place (not behind an RMSNorm).
+// Whole calls, us, two launches / one (workgroups of dX + dW), bf16 unless it says fp32:
+// - dX uncut: 18 x 960 x 384 25.8 / 21.5, 1765 x 3584 x 2635 148 / 133, fp32 1871 x 1240 x 2653 277 / 261.
+// - fp32 launches of at most 256 64-tiles have a variant with more loads in flight, which dW's long K loops want:
+//   3639 x 16 x 489 (57 + 8) 114.7 / 110.3, 4474 x 128 x 101 (140 + 4) 125.7 / 128.9, 6723 x 80 x 91 175 / 184.
+// - dX alone waits for its own stores to read them back: 19 x 1408 x 216 27.7 / 26.4, 44 x 368 x 110 19.8 / 19.1,
+//   360 x 16 x 98 19.6 / 18.3, 8010 x 32 x 125 44.6 / 42.3, 77 x 1016 x 161 22.8 / 24.0, 221 x 720 x 101 21.5 / 24.3,
+//   958 x 2600 x 1702 58.4 / 60.3; fp32 5025 x 120 x 284 49.8 / 47.2.
+// - dX in K ranges: 532 x 64 x 2353 (20 + 19) 29.0 / 24.6, 1024 x 512 x 8192 (256 + 256) 57.2 / 53.6, 497 x 2304 x 4240
+//   (216 + 612) 66.3 / 60.4, 3820 x 64 x 39221 (510 + 307) 338 / 316, 377 x 832 x 56112 (252 + 3073) 158 / 152.
+//   A dX of one column of partly filled tiles, one per CU, beside more tiles than fit with it: 459 x 64 x 42658
+//   (244 + 334) 65.8 / 70.6, 835 x 64 x 76419 (252 + 598) 155.5 / 161.4, 2008 x 64 x 37387 (256 + 293) 152 / 156;
+//   just fitting, 1012 x 64 x 34723 (256 + 272) 95.0 / 91.2.
+// - a dW of one or two K steps is bound by its writes, which hold up a dX that covers most CUs: 86 x 824 x 19859
+//   (245 + 1092) 47.2 / 51.6, 16 x 320 x 52308 (189 + 1227) 45.1 / 50.4, 43 x 320 x 31475 (165 + 738) 38.3 / 41.6,
+//   20 x 832 x 23116 behind an RMSNorm (231 + 1267) 54.1 / 56.2; but 2 x 1728 x 5253 (140 + 588) 39.9 / 37.7, 9 x 3264 x 11273
+//   (234 + 2314) 72.1 / 69.7, 102 x 192 x 37246 (118 + 582) 40.3 / 37.2.  In one column of tiles: 16 x 48 x 34492 (60 + 270)
+//   27.5 / 28.4, 21 x 64 x 56186 (63 + 439) 33.8 / 34.8, but 5 x 64 x 15903 (28 + 125) 24.1 / 23.4, 24 x 64 x 154137
+//   (64 + 1205) 70.9 / 64.8.
+// - fp32 with K ranges: 256 x 512 x 4096 (512 + 512 64-tiles) 53.1 / 51.6, 604 x 2112 x 14422 (128-tiles) 721 / 701,
+//   54 x 384 x 11328 (252 + 1062 64-tiles) 45.1 / 47.6.
+inline bool grads_in_one(const Plan& p, const VocabCut& dw, bool bf16, bool want_dw, bool dw_fast, bool places, int64_t rows,
+                         int64_t H, int64_t V) {
+    if (p.nchunks != 1 || p.dx_tile == 256 || p.fast_dx != bf16 || H % 4 != 0) return false;
+    if (want_dw && (dw_fast != bf16 || dw.main != V || dw.tile != p.dx_tile)) return false;
+    const int64_t of_dx = tiles_of(rows, H, p.dx_tile) * p.dx_ranges;
+    const int64_t all = of_dx + (want_dw ? tiles_of(V, H, p.dx_tile) : 0);
+    if (!want_dw) return p.dx_ranges == 1 && all <= 256 && (!bf16 || !places || rows <= 48 || H <= 128);
+    if (p.dx_tile == 64 && all <= 256 && rows > 4096) return false;
+    if (p.dx_ranges == 1) return all <= 2048;
+    if (!bf16) return all <= (p.dx_tile == 64 ? 1024 : 4096);
+    if (rows >= 128) return all <= 8192 && !(H < 128 && of_dx > 200 && of_dx <= 256 && all > 540);
+    return all <= (rows <= 64 ? 2048 : 8192) && !(H <= 1024 && of_dx >= 160 && all > 600) &&
+           !(rows <= 64 && H <= 128 && all > 256 && all < 600);
+}
+
 // Limits of the tuned kernel's 32-bit offsets inside one tile (see gemm_bf16_nt.h).
 inline bool fits_row_form(int64_t ld, int64_t) { return 256 * ld * 2 + 128 < ((int64_t)1 << 30); }
 inline bool fits_col_form(int64_t ld, int64_t) { return 64 * ld * 2 + 512 < ((int64_t)1 << 30); }

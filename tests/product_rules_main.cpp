@@ -111,6 +111,33 @@ int main() {
                         CHECK(least.C == full.C && bounded.C == full.C && least.nchunks == full.nchunks, "the room changes the chunks");
                     }
     CHECK(plans > 0, "no plan");
+    // One launch for both gradients or two: shapes measured on either side of each line of the rule, bf16 unless
+    // it says otherwise (the times stand beside grads_in_one).
+    struct { int dtype; int64_t BT, H, V; bool want_dw, places, one; } const grads[] = {
+        {1, 18, 960, 384, true, true, true}, {0, 3639, 16, 489, true, true, true}, {0, 4474, 128, 101, true, true, false},
+        {0, 6723, 80, 91, true, true, false}, {0, 5018, 64, 622, true, true, false},
+        // dX alone
+        {1, 44, 368, 110, false, true, true}, {1, 77, 1016, 161, false, true, false}, {1, 221, 720, 101, false, true, false},
+        {1, 221, 720, 101, false, false, true}, {1, 8010, 32, 125, false, true, true}, {0, 5025, 120, 284, false, true, true},
+        {1, 1024, 512, 8192, false, true, false},
+        // dX in K ranges
+        {1, 1024, 512, 8192, true, true, true}, {1, 497, 2304, 4240, true, true, true}, {1, 377, 832, 56112, true, true, true},
+        {1, 459, 64, 42658, true, true, false}, {1, 617, 64, 44793, true, true, false}, {1, 2008, 64, 37387, true, true, false},
+        {1, 1012, 64, 34723, true, true, true}, {1, 3820, 64, 39221, true, true, true},
+        {1, 86, 824, 19859, true, true, false}, {1, 102, 192, 37246, true, true, true}, {1, 101, 3328, 9664, true, true, true},
+        {1, 16, 320, 52308, true, true, false}, {1, 20, 832, 23116, true, false, false}, {1, 2, 1728, 5253, true, true, true},
+        {1, 16, 48, 34492, true, true, false}, {1, 5, 64, 15903, true, true, true}, {1, 24, 64, 154137, true, true, true},
+        {1, 24, 1024, 31078, true, false, false}, {0, 256, 512, 4096, true, true, true}, {0, 54, 384, 11328, true, true, false},
+    };
+    for (const auto& g : grads) {
+        const bool bf16 = g.dtype != 0;
+        const size_t budget = std::max<size_t>((size_t)1 << 30, (size_t)4096 * round_up(g.V, 64) * elem_size(g.dtype));
+        const Plan p = make_plan(g.BT, g.H, g.V, g.dtype, budget, false, true, budget);
+        const bool tuned = bf16 && p.fast_dw_last;
+        const VocabCut cut = vocab_cut(tuned, g.V, g.H, g.BT, p.tail_bytes > 0);
+        CHECK(grads_in_one(p, cut, bf16, g.want_dw, tuned, g.places, g.BT, g.H, g.V) == g.one, "%lld x %lld x %lld dtype %d",
+              (long long)g.BT, (long long)g.H, (long long)g.V, g.dtype);
+    }
     // the rotated K loop visits every step once
     for (int nk = 1; nk <= 70; ++nk)
         for (int rot = 0; rot < nk; ++rot) {
