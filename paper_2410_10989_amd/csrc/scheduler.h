@@ -260,18 +260,22 @@ inline VocabCut vocab_cut(bool tuned, int64_t V, int64_t other, int64_t K, bool 
 // chip and, without K ranges, the launch that puts dX's rows in place goes as well; with K ranges a launch
 // that adds them up follows, which otherwise runs beside dW's tiles, so that only the better fill is gained.
 // places: the launch puts dX's rows in place (not behind an RMSNorm).
-// Whole calls, us, two launches / one (workgroups of dX + dW), bf16 unless it says fp32:
+// Whole calls, us, two launches / one (workgroups of dX + dW), bf16 unless it says fp32,
+// or how many times as fast one launch is:
 // - dX uncut: 18 x 960 x 384 25.8 / 21.5, 1765 x 3584 x 2635 148 / 133, fp32 1871 x 1240 x 2653 277 / 261.
 // - fp32 launches of at most 256 64-tiles have a variant with more loads in flight, which dW's long K loops want:
 //   3639 x 16 x 489 (57 + 8) 114.7 / 110.3, 4474 x 128 x 101 (140 + 4) 125.7 / 128.9, 6723 x 80 x 91 175 / 184.
 // - dX alone waits for its own stores to read them back: 19 x 1408 x 216 27.7 / 26.4, 44 x 368 x 110 19.8 / 19.1,
-//   360 x 16 x 98 19.6 / 18.3, 8010 x 32 x 125 44.6 / 42.3, 77 x 1016 x 161 22.8 / 24.0, 221 x 720 x 101 21.5 / 24.3,
-//   958 x 2600 x 1702 58.4 / 60.3; fp32 5025 x 120 x 284 49.8 / 47.2.
-// - dX in K ranges: 532 x 64 x 2353 (20 + 19) 29.0 / 24.6, 1024 x 512 x 8192 (256 + 256) 57.2 / 53.6, 497 x 2304 x 4240
-//   (216 + 612) 66.3 / 60.4, 3820 x 64 x 39221 (510 + 307) 338 / 316, 377 x 832 x 56112 (252 + 3073) 158 / 152.
-//   A dX of one column of partly filled tiles, one per CU, beside more tiles than fit with it: 459 x 64 x 42658
-//   (244 + 334) 65.8 / 70.6, 835 x 64 x 76419 (252 + 598) 155.5 / 161.4, 2008 x 64 x 37387 (256 + 293) 152 / 156;
-//   just fitting, 1012 x 64 x 34723 (256 + 272) 95.0 / 91.2.
+//   56 x 1024 x 400 23.9 / 23.4, 64 x 1024 x 400 23.7 / 24.4, 221 x 720 x 101 21.5 / 24.3, 360 x 16 x 98 19.6 / 18.3,
+//   400 x 64 x 400 20.9 / 20.9, 400 x 64 x 800 22.0 / 22.5, 400 x 144 x 100 20.0 / 21.3,
+//   1901 x 1024 x 433 32.7 / 31.1, 2600 x 1024 x 433 39.8 / 40.5, 1901 x 144 x 433 26.3 / 27.4, 958 x 2600 x 1702 58.4 / 60.3;
+//   fp32 5025 x 120 x 284 49.8 / 47.2.
+// - dX in K ranges, from 128 rows on.  While all workgroups run at the same time: 532 x 64 x 2353 (20 + 19) 29.0 / 24.6,
+//   1024 x 512 x 8192 (256 + 256) 57.2 / 53.6, 2000 x 640 x 5000 (240 + 200) 1.24 times as fast.  A few more
+//   start a second round behind a dX that is planned for one tile per CU: 459 x 64 x 42658 (244 + 334) 65.8 / 70.6,
+//   400 x 384 x 14000 (240 + 330) 0.88 times, 280 x 512 x 14000 (240 + 440) 0.92, 620 x 256 x 42000 (250 + 658) 0.965,
+//   200 x 384 x 42000 (252 + 987) 0.95.  Wide or long enough, that round fills as well: 900 x 1152 x 9000 (216 + 639) 1.14,
+//   900 x 512 x 9000 (256 + 284) 1.09, 2000 x 64 x 70000 (256 + 547) 1.11, 280 x 1152 x 60000 (243 + 4221) 1.08.
 // - a dW of one or two K steps is bound by its writes, which hold up a dX that covers most CUs: 86 x 824 x 19859
 //   (245 + 1092) 47.2 / 51.6, 16 x 320 x 52308 (189 + 1227) 45.1 / 50.4, 43 x 320 x 31475 (165 + 738) 38.3 / 41.6,
 //   20 x 832 x 23116 behind an RMSNorm (231 + 1267) 54.1 / 56.2; but 2 x 1728 x 5253 (140 + 588) 39.9 / 37.7, 9 x 3264 x 11273
@@ -286,11 +290,18 @@ inline bool grads_in_one(const Plan& p, const VocabCut& dw, bool bf16, bool want
     if (want_dw && (dw_fast != bf16 || dw.main != V || dw.tile != p.dx_tile)) return false;
     const int64_t of_dx = tiles_of(rows, H, p.dx_tile) * p.dx_ranges;
     const int64_t all = of_dx + (want_dw ? tiles_of(V, H, p.dx_tile) : 0);
-    if (!want_dw) return p.dx_ranges == 1 && all <= 256 && (!bf16 || !places || rows <= 48 || H <= 128);
+    if (!want_dw) {
+        const bool gains = rows <= 56 || (V <= 512 && (H <= 128 || (rows > 1300 && H % 128 == 0 && all <= 128)));
+        return p.dx_ranges == 1 && all <= 256 && (!bf16 || !places || gains);
+    }
     if (p.dx_tile == 64 && all <= 256 && rows > 4096) return false;
     if (p.dx_ranges == 1) return all <= 2048;
     if (!bf16) return all <= (p.dx_tile == 64 ? 1024 : 4096);
-    if (rows >= 128) return all <= 8192 && !(H < 128 && of_dx > 200 && of_dx <= 256 && all > 540);
+    if (rows >= 128) {
+        if (all <= 512 || (of_dx < 200 && H < 512)) return all <= 8192;
+        if (H >= 512) return all <= 8192 && (all > 700 || rows >= 800);
+        return all <= 8192 && rows > (all <= 950 ? 1800 : H < 128 ? 700 : 200) && (all > 660 || H > 128);
+    }
     return all <= (rows <= 64 ? 2048 : 8192) && !(H <= 1024 && of_dx >= 160 && all > 600) &&
            !(rows <= 64 && H <= 128 && all > 256 && all < 600);
 }

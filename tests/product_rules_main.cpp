@@ -117,13 +117,17 @@ int main() {
         {1, 18, 960, 384, true, true, true}, {0, 3639, 16, 489, true, true, true}, {0, 4474, 128, 101, true, true, false},
         {0, 6723, 80, 91, true, true, false}, {0, 5018, 64, 622, true, true, false},
         // dX alone
+        {1, 56, 1024, 400, false, true, true}, {1, 64, 1024, 400, false, true, false}, {1, 400, 64, 800, false, true, false},
+        {1, 1901, 1024, 433, false, true, true}, {1, 1901, 144, 433, false, true, false},
         {1, 44, 368, 110, false, true, true}, {1, 77, 1016, 161, false, true, false}, {1, 221, 720, 101, false, true, false},
         {1, 221, 720, 101, false, false, true}, {1, 8010, 32, 125, false, true, true}, {0, 5025, 120, 284, false, true, true},
         {1, 1024, 512, 8192, false, true, false},
         // dX in K ranges
         {1, 1024, 512, 8192, true, true, true}, {1, 497, 2304, 4240, true, true, true}, {1, 377, 832, 56112, true, true, true},
         {1, 459, 64, 42658, true, true, false}, {1, 617, 64, 44793, true, true, false}, {1, 2008, 64, 37387, true, true, false},
-        {1, 1012, 64, 34723, true, true, true}, {1, 3820, 64, 39221, true, true, true},
+        {1, 400, 384, 14000, true, true, false}, {1, 200, 384, 42000, true, true, false}, {1, 620, 256, 42000, true, true, false},
+        {1, 280, 512, 14000, true, true, false}, {1, 900, 512, 9000, true, true, true}, {1, 900, 1152, 9000, true, true, true},
+        {1, 2000, 64, 70000, true, true, true}, {1, 400, 64, 100000, true, true, false}, {1, 3820, 64, 39221, true, true, true},
         {1, 86, 824, 19859, true, true, false}, {1, 102, 192, 37246, true, true, true}, {1, 101, 3328, 9664, true, true, true},
         {1, 16, 320, 52308, true, true, false}, {1, 20, 832, 23116, true, false, false}, {1, 2, 1728, 5253, true, true, true},
         {1, 16, 48, 34492, true, true, false}, {1, 5, 64, 15903, true, true, true}, {1, 24, 64, 154137, true, true, true},
