@@ -339,7 +339,8 @@ def main():
     traffic = measured_traffic_bytes() if (args.config == 3 and not variant and not args.budget_mib
                                            and compaction) else {}
     # One product launch per chunk, head and class (the K-range reduction of a cut dX product is
-    # booked with it).  Executed flops of a class per step: 2 * rows projected * H * V.
+    # booked with it; a launch of both gradients is booked half to dX and half to dW, which then
+    # show the rate of that launch).  Executed flops of a class per step: 2 * rows projected * H * V.
     # (with row compaction only the last ceil(N_valid / C) chunk launches of a head do any work)
     chunk_rows = flce.flce_chunk_rows(w.BT, w.H, w.V, code)
     if compaction:

@@ -328,6 +328,11 @@ FLCE_API size_t flce_full_logits_bytes(int64_t BT, int64_t V, int dtype);
  * launch counts per kind into the caller's HOST arrays (FLCE_NUM_KINDS entries
  * each) and clears the records.  At most 8192 launches are kept between two
  * collects; later ones are not recorded.
+ * Launches of small batches do the work of several kinds.  One that computes both
+ * gradients (they take the same number of operations) counts as a launch of either,
+ * with half its time under each.  The selection of the rows is booked with the logits
+ * where it is part of their launch; adding up the K ranges of dX is booked with dX, or
+ * with dW where it runs beside dW's tiles.
  */
 typedef enum {
     FLCE_KIND_LOGITS_GEMM = 0, /* Z_c = X_c W^T                      */

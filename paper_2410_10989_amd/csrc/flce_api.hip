@@ -102,7 +102,7 @@ Plan plan_for(int64_t BT, int64_t H, int64_t V, int dtype) { return plan_for(glo
 // ---- optional per-kernel timing (benchmarks only) ----
 struct TimingRecord {
     hipEvent_t start, stop;
-    int kind;
+    int kind, also;   // also: a second kind of the same launch, which gets half its time, or -1
 };
 constexpr int MAX_TIMING_RECORDS = 8192;
 std::atomic<bool> g_timing_on{false};
@@ -112,7 +112,7 @@ struct ScopedKernelTimer {
     hipStream_t stream;
     bool active = false;
     TimingRecord rec{};
-    ScopedKernelTimer(int kind, hipStream_t s) : stream(s) {   // kind < 0: never timed
+    ScopedKernelTimer(int kind, hipStream_t s, int also = -1) : stream(s) {   // kind < 0: never timed
         if (kind < 0 || !g_timing_on.load()) return;
         {
             std::lock_guard<std::mutex> lock(g_mutex);
@@ -124,6 +124,7 @@ struct ScopedKernelTimer {
             return;
         }
         rec.kind = kind;
+        rec.also = also;
         active = (hipEventRecord(rec.start, stream) == hipSuccess);
     }
     ~ScopedKernelTimer() {
@@ -434,7 +435,7 @@ inline unsigned rn_slots(int64_t C) { return (unsigned)std::min<int64_t>(C, RN_S
 template <typename T>
 int launch_grad(const T* Z, int64_t ldz, const T* W, const T* Xc, float* part, T* rows_out, T* dW, int64_t rows, int64_t H,
                 int64_t V, const Plan& p, const FastDyn& dm, const FastDyn& dk, GradArgs g, hipStream_t s) {
-    ScopedKernelTimer timer(dW ? FLCE_KIND_DW_GEMM : FLCE_KIND_DX_GEMM, s);
+    ScopedKernelTimer timer(FLCE_KIND_DX_GEMM, s, dW ? FLCE_KIND_DW_GEMM : -1);   // (as many operations each)
     const int tile = p.dx_tile, ranges = p.dx_ranges;
     const bool cut = ranges > 1;
     auto up = [](int64_t n) { return (n + FG_XCDS - 1) / FG_XCDS * FG_XCDS; };
@@ -551,7 +552,7 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
         SelectArgs<T> sel{};
         FastDyn dyn_m, dyn_dx, dyn_dw;   // logits (M = live rows), dX (M and K ranges), dW (K = live rows)
         if (compact) {
-            ScopedKernelTimer timer(FLCE_KIND_OTHER, s);
+            ScopedKernelTimer timer(in_logits ? -1 : FLCE_KIND_OTHER, s);   // (else nothing is launched here)
             const int dx_tiles_n = (int)((H + FG_BN - 1) / FG_BN), dx_ksteps = (int)((V + FG_BK - 1) / FG_BK);
             if (select) {
                 sel = {targets, (int)BT, ignore_index, weight, (int)p.C, (int)c, (int)p.nchunks, dx_tiles_n, dx_ksteps,
@@ -1254,8 +1255,11 @@ int flce_timing_collect(double* total_ms, int64_t* launches) {
         float ms = 0.f;
         if (hipEventSynchronize(r.stop) == hipSuccess &&
             hipEventElapsedTime(&ms, r.start, r.stop) == hipSuccess) {
-            total_ms[r.kind] += ms;
-            launches[r.kind] += 1;
+            for (const int kind : {r.kind, r.also}) {
+                if (kind < 0) continue;
+                total_ms[kind] += r.also < 0 ? ms : 0.5 * ms;
+                launches[kind] += 1;
+            }
         } else {
             (void)hipGetLastError();
             rc = FLCE_ERR_HIP;

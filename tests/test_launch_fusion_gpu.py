@@ -329,3 +329,27 @@ def test_both_gradients_in_one_launch_behind_rmsnorm(dtype, BT, H, V):
     assert abs(float(loss) - rl) <= tol * rl
     for a, b in ((dh, rh), (dgamma, (rY * xhat).sum(0)), (dW, rW)):
         assert float((a.double().cpu() - b).norm() / b.norm()) <= tol
+
+
+@pytest.mark.parametrize("dtype,BT,H,V,skip_dw,dx,dw", [
+    (torch.float32, 256, 512, 4096, False, 2, 1),   # both gradients in a launch, one that adds dX's K ranges up
+    (torch.bfloat16, 18, 960, 384, False, 1, 1),    # one launch in all
+    (torch.bfloat16, 44, 368, 110, True, 1, 0),
+])
+def test_timing_of_launches_that_do_several_things(dtype, BT, H, V, skip_dw, dx, dw):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, H, V, dtype, "scattered", 3)
+    call = lambda: flce.flce_fwd_bwd(X, W, t, flags=flce.SKIP_DW if skip_dw else 0)
+    call()
+    flce.flce_timing_collect()
+    flce.flce_timing_enable(True)
+    try:
+        call()
+    finally:
+        flce.flce_timing_enable(False)
+    kinds = flce.flce_timing_collect()
+    # the rows are selected in the logits launch: nothing is left for "other"
+    assert {k: n for k, (_, n) in kinds.items()} == {"logits_gemm": 1, "ce_rows": 1, "dx_gemm": dx, "dw_gemm": dw, "other": 0}
+    assert all((ms > 0) == (n > 0) for ms, n in kinds.values())
+    if dw:   # half of the launch each; dX's share has the rest of its own time on top
+        assert kinds["dx_gemm"][0] == kinds["dw_gemm"][0] if dx == 1 else kinds["dx_gemm"][0] > kinds["dw_gemm"][0]
