@@ -41,7 +41,7 @@ int main() {
                         CHECK(t <= all / 256 * 256 && t > all / 256 * 256 - per, "%lld tiles do not fill the rounds", (long long)t);
                     }
     CHECK(shared > 0 && small > 0, "a branch of the rule is never taken");
-    long cut = 0;
+    long cut = 0, streaming = 0;
     for (int tuned = 0; tuned < 2; ++tuned)
         for (int64_t rows : others)
             for (int64_t H : others)
@@ -56,6 +56,12 @@ int main() {
                               "a bounded cut takes %d ranges", c.ranges);
                         CHECK(c.tile == 256 || c.tile == 128 || (!tuned && c.tile == 64), "dX tile %d", c.tile);
                         CHECK(c.ranges >= 1 && c.ranges <= 64, "dX ranges %d", c.ranges);
+                        // large tiles in more than 16 ranges: operands that stream from HBM, one round of long ranges
+                        if (tuned && c.tile == 256 && c.ranges > 16) {
+                            ++streaming;
+                            CHECK(!bounded && dx_streams(rows, H, V), "streaming cut");
+                            CHECK(V / c.ranges >= 1024 && tiles_of(rows, H, 256) * c.ranges <= 256, "streaming cut into %d", c.ranges);
+                        }
                         if (c.ranges == 1) continue;
                         ++cut;
                         CHECK((size_t)c.ranges * (size_t)rows * (size_t)H * 4 <= budget / 2, "partial results past half the budget");
@@ -70,13 +76,29 @@ int main() {
                         }
                         CHECK(at == steps, "K steps lost");
                     }
-    CHECK(cut > 0, "no dX product is cut");
+    CHECK(cut > 0 && streaming > 0, "no dX product is cut");
     // a few outputs of either size: what the dX tests rely on to reach both tile sizes, and the device's own
     // choice of ranges for fewer live rows (256-tiles only)
     const size_t gib = (size_t)1 << 30;
     CHECK(dx_cut(true, 1024, 512, 8192, gib, false).tile == 128, "small outputs take small tiles");
     CHECK(dx_cut(true, 600, 256, 16384, gib, false).tile == 128, "small outputs take small tiles");
     CHECK(dx_cut(true, 2047, 1000, 50257, gib, false).tile == 256, "long products keep the large tiles");
+    const struct { int64_t rows, H, V; int tile, ranges; } streams[] = {
+        {257, 512, 180001, 256, 64}, {700, 512, 128256, 256, 42}, {1024, 512, 128256, 256, 32}, {2048, 512, 128256, 256, 16},
+        {24, 3584, 40003, 128, 18}, {1024, 512, 8192, 128, 8},   // (the last one's operands stay in the cache)
+    };
+    for (const auto& c : streams) {
+        const ProductCut got = dx_cut(true, c.rows, c.H, c.V, gib, false);
+        CHECK(got.tile == c.tile && got.ranges == c.ranges, "%lld x %lld x %lld: %d ranges of %d-tiles", (long long)c.rows,
+              (long long)c.H, (long long)c.V, got.ranges, got.tile);
+        for (const size_t part : {(size_t)0, (size_t)3 << 20, (size_t)20 << 20}) {   // in less room
+            const ProductCut less = dx_cut(true, c.rows, c.H, c.V, gib, false, part);
+            CHECK(less.ranges == 1 || (size_t)less.ranges * c.rows * c.H * 4 <= part, "%d ranges in %zu bytes", less.ranges, part);
+        }
+        // one round: the live rows do not change the ranges
+        const Plan p = make_plan(c.rows, c.H, c.V, 1, gib, false, true, gib);
+        CHECK(p.dx_dyn == (p.dx_tile == 256 && tiles_of(c.rows, c.H, 256) * p.dx_ranges > 256), "ranges chosen on the device");
+    }
     const ProductCut dyn = dx_cut(true, 4100, 2048, 29596, gib, false);
     auto live = [&](int64_t rows) { return choose_ksplit(tiles_of(rows, 2048, 256), (29596 + 63) / 64, dyn.ranges); };
     CHECK(dyn.tile == 256 && dyn.ranges == 7 && live(2460) == 3 && live(1148) == 6, "tile %d, ranges %d, live %d and %d",

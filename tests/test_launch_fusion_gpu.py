@@ -233,6 +233,34 @@ def test_product_that_streams_w_in_any_room(share):
     check(flce.flce_fwd_bwd_opt(X, W, t, flce.flce_options(workspace=ws)), X, W, t, torch.bfloat16)
 
 
+@pytest.mark.parametrize("BT,H,V,ranges", [
+    (257, 512, 180001, 64),    # 2 x 2 large tiles, as many ranges as there are
+    (700, 512, 128256, 42),    # 3 x 2 tiles: 252 workgroups
+    (1024, 512, 128256, 32),
+])
+@pytest.mark.parametrize("ignored", [0, 0.5])
+def test_streaming_product_in_one_round_of_large_tiles(BT, H, V, ranges, ignored):
+    # with rows ignored the ranges stay (one round holds them all), over fewer tiles.  Against plain torch in 64
+    # bits; bf16 storage of logits, gradients and results: TOL, a lost range would be 1 / 64 of dX's norm or more.
+    import paper_2410_10989_amd as flce
+    assert flce.flce_dx_k_ranges(BT, H, V, flce.FLCE_BF16) == ranges
+    g = torch.Generator(device="cuda").manual_seed(BT)
+    X = torch.randn(BT, H, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(V, H, device="cuda", generator=g) * 0.02).bfloat16()
+    t = torch.randint(0, V, (BT,), device="cuda", generator=g)
+    t[torch.rand(BT, device="cuda", generator=g) < ignored] = -100
+    _, dX, _ = flce.flce_fwd_bwd(X, W, t, flags=flce.SKIP_DW)
+    ok = t != -100
+    x, w = X[ok].double(), W.double()
+    G = torch.softmax(x @ w.T, 1)
+    G[torch.arange(len(x), device="cuda"), t[ok]] -= 1.0
+    want = (G / len(x)) @ w
+    err = float((dX[ok].double() - want).norm() / want.norm())
+    print(f"  {BT} x {H} x {V}, {ignored} ignored: {err:.1e}", flush=True)
+    assert err <= TOL[torch.bfloat16]
+    assert (dX[~ok] == 0).all()
+
+
 @pytest.mark.parametrize("BT", [8192, 8193])   # 32 chunks of 256 rows selected by one launch each; 33 found with the cursor
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_selection_changes_over_with_the_chunk_count(BT, dtype):
@@ -248,8 +276,10 @@ def test_selection_changes_over_with_the_chunk_count(BT, dtype):
     (3, 8, 300),         # the smallest: one tile row with three rows
     (130, 72, 1000),     # two tile rows, a K tail (bf16)
     (256, 128, 2000),    # one chunk of at most 256 rows: rotated K loop (bf16)
-    (257, 1024, 700),    # fewer than 16 tiles, the longest K loop that still has its rows picked; 1032: no longer
+    (257, 1024, 700),    # long K loops in 16 tiles and more
     (257, 1032, 700),
+    (30, 1024, 384),     # fewer than 16 tiles, the longest K loop that still has its rows picked; 1032: no longer
+    (30, 1032, 384),
     (2048, 64, 600),     # the longest batch; 2049: a launch of its own
     (2049, 64, 600),
 ])
@@ -260,6 +290,23 @@ def test_rows_picked_by_the_logits_launch(dtype, ignore, BT, H, V):
     got = flce.flce_fwd_bwd(X, W, t)
     X[t == -100] = 0
     check(got, X, W, t, dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("BT,H,V,picked", [(257, 1032, 700, True), (30, 1024, 384, True), (30, 1032, 384, False),
+                                           (2048, 64, 600, True), (2049, 64, 600, False)])
+def test_which_batches_have_their_rows_picked(dtype, BT, H, V, picked):
+    # the launch of its own is the only one of these calls that is neither a product nor the cross entropy
+    import paper_2410_10989_amd as flce
+    X, W, t = make(BT, H, V, dtype, "scattered", 4)
+    flce.flce_fwd_bwd(X, W, t)
+    flce.flce_timing_collect()
+    flce.flce_timing_enable(True)
+    try:
+        flce.flce_fwd_bwd(X, W, t)
+    finally:
+        flce.flce_timing_enable(False)
+    assert flce.flce_timing_collect()["other"][1] == (0 if picked else 1)
 
 
 def test_out_of_range_operands_of_picked_rows():

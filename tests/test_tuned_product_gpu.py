@@ -39,7 +39,7 @@ def check(BT, H, V, compaction=True):
     (300, 120, 4097),     # H: a K step that lacks its last piece; K ranges of dX with a ragged end
     (1024, 512, 8192),    # 128-tiles in all three products, 8 K ranges
     (2000, 1000, 3001),   # H = 15 whole K steps and 40: tail in the last of many steps
-    (2047, 1000, 50257),  # 256-tiles with a K tail, dX K ranges chosen on the device
+    (2047, 1000, 50257),  # 256-tiles with a K tail, dX in 8 K ranges that fill one round
     (4500, 200, 16384),   # tall: 256-tiles with few K steps
 ])
 @pytest.mark.parametrize("compaction", [True, False])
