@@ -555,8 +555,10 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
             ScopedKernelTimer timer(in_logits ? -1 : FLCE_KIND_OTHER, s);   // (else nothing is launched here)
             const int dx_tiles_n = (int)((H + FG_BN - 1) / FG_BN), dx_ksteps = (int)((V + FG_BK - 1) / FG_BK);
             if (select) {
+                // (logits that pick their rows from X leave the gathered ones to the dW product)
+                const bool gather = norm ? norm_in_select : want_dw || !in_logits;
                 sel = {targets, (int)BT, ignore_index, weight, (int)p.C, (int)c, (int)p.nchunks, dx_tiles_n, dx_ksteps,
-                       p.dx_ranges, hdr, norm && !norm_in_select ? static_cast<const T*>(nullptr) : X, (int)H, Xg,
+                       p.dx_ranges, hdr, gather ? X : static_cast<const T*>(nullptr), (int)H, Xg,
                        c == 0 ? zero_out : static_cast<T*>(nullptr), idx, tv, dyn,
                        norm_in_select ? norm->gamma : static_cast<const T*>(nullptr), norm ? norm->eps : 0.f,
                        norm ? norm->rstd : static_cast<float*>(nullptr), (int)std::min<int64_t>((BT + 3) / 4, SEL_GRID)};

@@ -309,6 +309,23 @@ def test_which_batches_have_their_rows_picked(dtype, BT, H, V, picked):
     assert flce.flce_timing_collect()["other"][1] == (0 if picked else 1)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_picked_rows_are_gathered_for_dw_only(dtype):
+    import paper_2410_10989_amd as flce
+    X, W, t = make(300, 64, 700, dtype, "none", 6)
+    ws = torch.zeros(flce.flce_workspace_bytes(300, 64, 700, flce.FLCE_F32 if dtype == torch.float32 else flce.FLCE_BF16) + 256,
+                     dtype=torch.uint8, device="cuda")
+    row = X[200].cpu().view(torch.uint8).numpy().tobytes()
+    flce.flce_set_workspace(ws[-ws.data_ptr() % 256:])
+    try:
+        for flags in (flce.SKIP_DW, 0):
+            flce.flce_fwd_bwd(X, W, t, flags=flags)
+            torch.cuda.synchronize()
+            assert (row in ws.cpu().numpy().tobytes()) == (flags == 0)
+    finally:
+        flce.flce_set_workspace(None)
+
+
 def test_out_of_range_operands_of_picked_rows():
     # fp32: an infinity in a picked row sends its tile to the fp32 instructions, which look the rows up again
     import paper_2410_10989_amd as flce
