@@ -406,8 +406,9 @@ def flce_mfma_ceiling_launch(pattern: int, workgroups: int, iters: int, std_b: f
     of at least workgroups * 256 elements.  Returns the flops of the launch."""
     if out.dtype != torch.float32 or not out.is_cuda or not out.is_contiguous():
         raise ValueError("out must be a contiguous float32 CUDA tensor")
+    here = torch.device("cuda", torch.cuda.current_device())
     _check(lib().flce_mfma_ceiling_launch(int(pattern), int(workgroups), int(iters), float(std_b),
-                                          out.data_ptr(), out.numel(), _stream_handle(stream, torch.device("cuda", torch.cuda.current_device()))),
+                                          out.data_ptr(), out.numel(), _stream_handle(stream, here)),
            "flce_mfma_ceiling_launch")
     return workgroups * 4 * iters * 16 * 32768.0
 

@@ -355,7 +355,7 @@ int launch_ce_rows(T* Z, int64_t ldz, const int64_t* targets, int64_t rows, int6
                        targets, (int)V, zero_pad, ignore_index, hdr, row_loss, n_rows, count_n, weight, done, loss)
 #define CE_SHAPE(TH, NV, NL) \
     do {                                                                                             \
-        if (done.words) CE_LAUNCH(TH, NV, false, NL, true);                                                \
+        if (done.words) CE_LAUNCH(TH, NV, false, NL, true);                                          \
         else if (nt) CE_LAUNCH(TH, NV, true, NL, false);                                             \
         else CE_LAUNCH(TH, NV, false, NL, false);                                                    \
     } while (0)
@@ -472,11 +472,12 @@ int launch_grad(const T* Z, int64_t ldz, const T* W, const T* Xc, float* part, T
 // Whether a batch that is one chunk has its rows selected by workgroups of the logits launch.  That saves a
 // launch (4-5 us, on the host as well) and costs every tile its own look at the targets, 1-2 us per
 // workgroup: for launches that fit the chip, or of one tile row, where the look is short.  Whole calls with the
-// launch of its own / without, us: bf16 24 x 680 x 1026 26.9 / 24.1, 495 x 896 x 3674 36.5 / 33.7, 1572 x 576 x 2176 59.6 /
-// 53.5, 1024 x 512 x 8192 60 / 57, 51 x 3328 x 24297 129 / 119, one tile row in 1136 tiles (31 x 576 x 144923) 100.3 / 96.9;
-// 2664 tiles in three rows (294 x 128 x 113344) 110.5 / 112.9.  A handful of tiles with long K loops waits for its loads
-// alone, and the rows of X are further away than gathered ones: 30 x 2496 x 384 (3 tiles) 34.1 / 35.1,
-// 53 x 2352 x 2560 (20 tiles) 41.8 / 40.1.  Longer batches gain nothing (3195 x 2560 x 829: launches of 10.6 + 25.0 / 36.8).
+// launch of its own / without, us: bf16 24 x 680 x 1026 26.9 / 24.1, 495 x 896 x 3674 36.5 / 33.7, 1572 x 576 x
+// 2176 59.6 / 53.5, 1024 x 512 x 8192 60 / 57, 51 x 3328 x 24297 129 / 119, one tile row in 1136 tiles (31 x 576 x
+// 144923) 100.3 / 96.9; 2664 tiles in three rows (294 x 128 x 113344) 110.5 / 112.9.  A handful of tiles with long
+// K loops waits for its loads alone, and the rows of X are further away than gathered ones: 30 x 2496 x 384 (3
+// tiles) 34.1 / 35.1, 53 x 2352 x 2560 (20 tiles) 41.8 / 40.1.  Longer batches gain nothing (3195 x 2560 x 829:
+// launches of 10.6 + 25.0 / 36.8).
 template <typename T>
 bool select_in_logits(const Plan& p, const VocabCut& cut, int64_t BT, int64_t H, int64_t V) {
     const int64_t tiles = tiles_of(BT, V, cut.tile);
@@ -666,7 +667,8 @@ int run_head(const T* X, const T* W, const int64_t* targets, int64_t BT, int64_t
                         FLCE_KIND_DX_GEMM, Z, p.ldz, W, H, part, H, nullptr, nullptr, rows, H, V, s, p.dx_tile, p.dx_ranges,
                         p.C * H, dyn_m)));
                 fin = {part, 1, p.C * H, p.dx_ranges, dyn_dx.ksplit, scatter ? row_map : nullptr, n_live, (int)rows, (int)H,
-                       scatter ? dX : dXc, dx_add && (scatter || add_in_gemm), nullptr, hdr, LossOut{}, finish_segs(H), (int)finish_blocks(rows, H)};
+                       scatter ? dX : dXc, dx_add && (scatter || add_in_gemm), nullptr, hdr, LossOut{},
+                       finish_segs(H), (int)finish_blocks(rows, H)};
                 finish = true;
             } else {
                 if constexpr (BF16) {

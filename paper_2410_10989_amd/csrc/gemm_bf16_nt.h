@@ -834,7 +834,8 @@ __global__ __launch_bounds__(FG_THREADS, 2) void grad_bf16(FGArgs dx, FGArgs dw,
     __shared__ __attribute__((aligned(16))) unsigned char smem[fg_lds_bytes(128)];
     int block = (int)blockIdx.x;
     if constexpr (!CUT) {
-        if (block == 0 && g.fin.row_loss) loss_accumulate(g.fin.row_loss, g.fin.rows, g.fin.hdr, g.fin.loss, reinterpret_cast<double*>(smem));
+        if (block == 0 && g.fin.row_loss)
+            loss_accumulate(g.fin.row_loss, g.fin.rows, g.fin.hdr, g.fin.loss, reinterpret_cast<double*>(smem));
         if (block < FG_XCDS) return;
         block -= FG_XCDS;
     }

@@ -514,7 +514,8 @@ __device__ __forceinline__ ProductTile gg_product(const GGArgs& a, const Fin& fi
 template <typename T, typename OutT, bool A_KM, bool B_KM, int TILE, typename Fin = NoFinish, bool FEW = false>
 __global__ __launch_bounds__(gg_threads(TILE), 2) void gemm_guarded(GGArgs a, Fin fin) {
     __shared__ __attribute__((aligned(16))) GGLds<T, TILE, FEW> lds;
-    __shared__ int row_list[IsSelect<Fin>::value ? TILE + gg_threads(TILE) / WAVE : 1];   // SELECT: the tile's rows of A (and the wavefronts' counts)
+    // SELECT: the tile's rows of A, and the wavefronts' counts
+    __shared__ int row_list[IsSelect<Fin>::value ? TILE + gg_threads(TILE) / WAVE : 1];
     int block = (int)blockIdx.x;
     if constexpr (!std::is_same<Fin, NoFinish>::value) {
         if (block < fin.blocks) {
@@ -533,7 +534,8 @@ __global__ __launch_bounds__(gg_threads(TILE), 2) void grad_f32(GGArgs dx, GGArg
     __shared__ __attribute__((aligned(16))) GGLds<float, TILE> lds;
     int block = (int)blockIdx.x;
     if constexpr (!CUT) {
-        if (block == 0 && g.fin.row_loss) loss_accumulate(g.fin.row_loss, g.fin.rows, g.fin.hdr, g.fin.loss, reinterpret_cast<double*>(&lds));
+        if (block == 0 && g.fin.row_loss)
+            loss_accumulate(g.fin.row_loss, g.fin.rows, g.fin.hdr, g.fin.loss, reinterpret_cast<double*>(&lds));
         if (block < FG_XCDS) return;
         block -= FG_XCDS;
     }

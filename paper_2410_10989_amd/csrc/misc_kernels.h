@@ -38,9 +38,10 @@ struct FinishArgs {
 // 180 rows of 4096 with 16 ranges took 45 us with a wavefront per row.)
 constexpr int FIN_SEG = 512;
 // K ranges whose loads a wavefront has in flight, twice as many where there are more (and no more loads than
-// ranges where there are few: 7776 x 2880 with 2 ranges 33 us, 55 with groups of 8): with 62 ranges, one wait for memory after the other, this launch
-// was a quarter of the call (whole calls, 4 one by one / 8 together, us: 19 x 448 x 32000 50.9 / 42.6, 58 x 320 x 44288
-// 56.9 / 48.8, 94 x 384 x 23460 43.1 / 38.1, 2 heads of 218 x 312 x 104206 200 / 188).
+// ranges where there are few: 7776 x 2880 with 2 ranges 33 us, 55 with groups of 8): with 62 ranges, one wait for
+// memory after the other, this launch was a quarter of the call (whole calls, 4 one by one / 8 together, us: 19 x
+// 448 x 32000 50.9 / 42.6, 58 x 320 x 44288 56.9 / 48.8, 94 x 384 x 23460 43.1 / 38.1, 2 heads of 218 x 312 x
+// 104206 200 / 188).
 constexpr int FIN_AHEAD = 8;
 inline int finish_segs(int64_t n) { return (int)((n + FIN_SEG - 1) / FIN_SEG); }
 inline int64_t finish_blocks(int64_t rows, int64_t n) { return ((rows * finish_segs(n) + 3) / 4 + 1 + 7) / 8 * 8; }
@@ -135,8 +136,9 @@ __global__ __launch_bounds__(256) void finish_dx_kernel(FinishArgs f) {
 struct GradArgs {
     FinishArgs fin;    // src, idx, n, out, add, and the losses (row_loss null: not here)
     int dx_blocks;
-    int dw_first;      // dW's workgroups where theirs are the longer K loops and they come first, else 0 (a launch that ends
-                       // in its longest workgroups: 7005 x 3392 x 448 200 -> 207 us, 3195 x 2560 x 829 62.5 -> 65.2)
+    // dW's workgroups where theirs are the longer K loops and they come first, else 0 (a launch that ends in its
+    // longest workgroups: 7005 x 3392 x 448 200 -> 207 us, 3195 x 2560 x 829 62.5 -> 65.2)
+    int dw_first;
 };
 
 // Rows of the TILE x TILE tile at (m0, n0) of dX, which this workgroup (256 threads) has just written to

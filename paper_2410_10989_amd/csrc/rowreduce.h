@@ -251,7 +251,8 @@ struct DoneCount {
 // workgroups whose numbers name the groups: each is in front of its group's last one (count_done).
 __device__ __forceinline__ void open_done(const DoneCount& d) {
     const done_t none = d.ticket << DONE_COUNT_BITS;
-    __hip_atomic_fetch_max(d.words + blockIdx.x % DONE_GROUPS * DONE_STRIDE, none, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_max(d.words + blockIdx.x % DONE_GROUPS * DONE_STRIDE, none, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     if (blockIdx.x < DONE_GROUPS)
         __hip_atomic_fetch_max(d.words + DONE_GROUPS * DONE_STRIDE, none, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -262,10 +263,12 @@ __device__ __forceinline__ bool count_done(const DoneCount& d) {
     const unsigned of_group = (n - group + DONE_GROUPS - 1) / DONE_GROUPS, groups = min(n, (unsigned)DONE_GROUPS);
     const done_t none = d.ticket << DONE_COUNT_BITS;
     done_t* word = d.words + group * DONE_STRIDE;
-    if (__hip_atomic_fetch_add(word, (done_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != none + of_group - 1) return false;
+    if (__hip_atomic_fetch_add(word, (done_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != none + of_group - 1)
+        return false;
     __hip_atomic_store(word, (done_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     word = d.words + DONE_GROUPS * DONE_STRIDE;
-    if (__hip_atomic_fetch_add(word, (done_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != none + groups - 1) return false;
+    if (__hip_atomic_fetch_add(word, (done_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != none + groups - 1)
+        return false;
     __hip_atomic_store(word, (done_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return true;
 }
@@ -306,10 +309,11 @@ __device__ __forceinline__ void ce_fold_loss(const int64_t* __restrict__ targets
 //
 // FOLD (count_n > 0 only): where the whole batch is one launch and nothing follows it, the loss is summed here as well,
 // by the workgroup that finishes last (no workgroup waits for another): each one counts itself in `done`
-// once its row's loss has been written through to memory (the L2s of the XCDs are not coherent).  It saves a launch: whole calls of 19 x 3264 bf16 12.1 -> 9.7 us,
-// 187 x 8320 bf16 12.3 -> 9.7, 227 x 17107 fp32 12.1 -> 9.9.  Batches beyond CE_FOLD_ROWS have the launch: the count
-// at the end of every workgroup costs them as much (643 x 22336 bf16 14.8 -> 15.5, 800 x 15360 fp32
-// 24.2 -> 25.0, 1068 x 11520 bf16 15.0 -> 14.9, 8174 x 1152 fp32 27.3 -> 30.4).
+// once its row's loss has been written through to memory (the L2s of the XCDs are not coherent).  It saves a
+// launch: whole calls of 19 x 3264 bf16 12.1 -> 9.7 us, 187 x 8320 bf16 12.3 -> 9.7, 227 x 17107 fp32 12.1 -> 9.9.
+// Batches beyond CE_FOLD_ROWS have the launch: the count at the end of every workgroup costs them as much (643 x
+// 22336 bf16 14.8 -> 15.5, 800 x 15360 fp32 24.2 -> 25.0, 1068 x 11520 bf16 15.0 -> 14.9, 8174 x 1152 fp32 27.3 ->
+// 30.4).
 constexpr int64_t CE_FOLD_ROWS = 512;
 template <typename T, int THREADS, int NV, bool NT, int NL = 0, bool FOLD = false>
 __global__ __launch_bounds__(THREADS) void ce_rows_kernel(

@@ -90,8 +90,8 @@ struct Plan {
     // compact.h)
     bool compact = false;
     // byte offsets into the workspace
-    size_t off_hdr = 0, off_row_loss = 0, off_z = 0, off_dwacc = 0, off_dxpart = 0, off_xg = 0, off_dxg = 0, off_idx = 0, off_tv = 0,
-           off_dyn = 0, off_tail = 0, total = 0;
+    size_t off_hdr = 0, off_row_loss = 0, off_z = 0, off_dwacc = 0, off_dxpart = 0, off_xg = 0, off_dxg = 0,
+           off_idx = 0, off_tv = 0, off_dyn = 0, off_tail = 0, total = 0;
     size_t tail_bytes = 0;     // room at off_tail
     size_t dxpart_bytes = 0;   // room at off_dxpart
 };
@@ -136,7 +136,8 @@ inline int max_dx_ranges(size_t budget_bytes, int64_t rows, int64_t H) {
 //
 // Tuned bf16 kernel, K steps of 64: a 256 x 256 tile takes 1.55 us per step plus 4 us, a 128 x 128
 // tile 0.53 us per step in long loops (0.39 in short ones; a step's 16 MFMAs per wavefront alone take 0.3 on
-// random data, its loads 0.24, its LDS reads 0.17, and they overlap in part) plus 0.65 us.  Measured (M x N x K, 256-tiles / 128-tiles, us):
+// random data, its loads 0.24, its LDS reads 0.17, and they overlap in part) plus 0.65 us.  Measured (M x N x K,
+// 256-tiles / 128-tiles, us):
 //   1024 x 8192 x 512 (logits)  18.8 / 12.8      4096 x 32000 x 4096 (logits)  809 / 1104
 //   2048 x 4096 x 1024 (logits) 31.9 / 21.6      2048 x 8192 x 1024 (logits)  34.9 / 37.6
 //   8192 x 512 x 1024 (dW)      24.4 / 12.1      50257 x 1000 x 2047 (dW)      202 / 217
@@ -171,7 +172,8 @@ inline int64_t cut_ns(int64_t tiles, int64_t tile, int64_t ranges) {
 //   24 x 4096 x 128256    208 (8) / 183 (16) / 181 (16)       200 x 832 x 128256    82 (18) / 66 (36) / 64 (64)
 //   512 x 512 x 128256    100 (16) / 87 (32) / 74 (64)        1024 x 512 x 128256  197 (8) / 164 (16) / 117 (32)
 //   2048 x 512 x 128256   377 (4) / 301 (8) / 219 (16)        512 x 2048 x 128256  376 (4) / 315 (8) / 217 (16)
-// and where they do stay: 1024 x 512 x 32000 39.9 (8) / 37.6 (16) / 38.5 (32), 2048 x 2048 x 8192 73.5 (1) / 65 (2) / 61 (4).
+// and where they do stay: 1024 x 512 x 32000 39.9 (8) / 37.6 (16) / 38.5 (32), 2048 x 2048 x 8192 73.5 (1) / 65 (2)
+// / 61 (4).
 constexpr int64_t DX_STREAM_BYTES = (int64_t)256 << 20;
 inline bool dx_streams(int64_t rows, int64_t H, int64_t V) { return (rows + H) * V * 2 > DX_STREAM_BYTES; }
 inline int64_t dx_streaming_ns(int tile, int64_t tiles, int64_t k) {
@@ -268,20 +270,21 @@ inline VocabCut vocab_cut(bool tuned, int64_t V, int64_t other, int64_t K, bool 
 // - dX alone waits for its own stores to read them back: 19 x 1408 x 216 27.7 / 26.4, 44 x 368 x 110 19.8 / 19.1,
 //   56 x 1024 x 400 23.9 / 23.4, 64 x 1024 x 400 23.7 / 24.4, 221 x 720 x 101 21.5 / 24.3, 360 x 16 x 98 19.6 / 18.3,
 //   400 x 64 x 400 20.9 / 20.9, 400 x 64 x 800 22.0 / 22.5, 400 x 144 x 100 20.0 / 21.3,
-//   1901 x 1024 x 433 32.7 / 31.1, 2600 x 1024 x 433 39.8 / 40.5, 1901 x 144 x 433 26.3 / 27.4, 958 x 2600 x 1702 58.4 / 60.3;
-//   fp32 5025 x 120 x 284 49.8 / 47.2.
-// - dX in K ranges, from 128 rows on.  While all workgroups run at the same time: 532 x 64 x 2353 (20 + 19) 29.0 / 24.6,
-//   1024 x 512 x 8192 (256 + 256) 57.2 / 53.6, 2000 x 640 x 5000 (240 + 200) 1.24 times as fast.  A few more
+//   1901 x 1024 x 433 32.7 / 31.1, 2600 x 1024 x 433 39.8 / 40.5, 1901 x 144 x 433 26.3 / 27.4, 958 x 2600 x 1702
+//   58.4 / 60.3; fp32 5025 x 120 x 284 49.8 / 47.2.
+// - dX in K ranges, from 128 rows on.  While all workgroups run at the same time: 532 x 64 x 2353 (20 + 19) 29.0 /
+//   24.6, 1024 x 512 x 8192 (256 + 256) 57.2 / 53.6, 2000 x 640 x 5000 (240 + 200) 1.24 times as fast.  A few more
 //   start a second round behind a dX that is planned for one tile per CU: 459 x 64 x 42658 (244 + 334) 65.8 / 70.6,
 //   400 x 384 x 14000 (240 + 330) 0.88 times, 280 x 512 x 14000 (240 + 440) 0.92, 620 x 256 x 42000 (250 + 658) 0.965,
-//   200 x 384 x 42000 (252 + 987) 0.95.  Wide or long enough, that round fills as well: 900 x 1152 x 9000 (216 + 639) 1.14,
-//   900 x 512 x 9000 (256 + 284) 1.09, 2000 x 64 x 70000 (256 + 547) 1.11, 280 x 1152 x 60000 (243 + 4221) 1.08.
+//   200 x 384 x 42000 (252 + 987) 0.95.  Wide or long enough, that round fills as well: 900 x 1152 x 9000 (216 +
+//   639) 1.14, 900 x 512 x 9000 (256 + 284) 1.09, 2000 x 64 x 70000 (256 + 547) 1.11, 280 x 1152 x 60000 (243 +
+//   4221) 1.08.
 // - a dW of one or two K steps is bound by its writes, which hold up a dX that covers most CUs: 86 x 824 x 19859
 //   (245 + 1092) 47.2 / 51.6, 16 x 320 x 52308 (189 + 1227) 45.1 / 50.4, 43 x 320 x 31475 (165 + 738) 38.3 / 41.6,
-//   20 x 832 x 23116 behind an RMSNorm (231 + 1267) 54.1 / 56.2; but 2 x 1728 x 5253 (140 + 588) 39.9 / 37.7, 9 x 3264 x 11273
-//   (234 + 2314) 72.1 / 69.7, 102 x 192 x 37246 (118 + 582) 40.3 / 37.2.  In one column of tiles: 16 x 48 x 34492 (60 + 270)
-//   27.5 / 28.4, 21 x 64 x 56186 (63 + 439) 33.8 / 34.8, but 5 x 64 x 15903 (28 + 125) 24.1 / 23.4, 24 x 64 x 154137
-//   (64 + 1205) 70.9 / 64.8.
+//   20 x 832 x 23116 behind an RMSNorm (231 + 1267) 54.1 / 56.2; but 2 x 1728 x 5253 (140 + 588) 39.9 / 37.7, 9 x
+//   3264 x 11273 (234 + 2314) 72.1 / 69.7, 102 x 192 x 37246 (118 + 582) 40.3 / 37.2.  In one column of tiles: 16 x
+//   48 x 34492 (60 + 270) 27.5 / 28.4, 21 x 64 x 56186 (63 + 439) 33.8 / 34.8, but 5 x 64 x 15903 (28 + 125) 24.1 /
+//   23.4, 24 x 64 x 154137 (64 + 1205) 70.9 / 64.8.
 // - fp32 with K ranges: 256 x 512 x 4096 (512 + 512 64-tiles) 53.1 / 51.6, 604 x 2112 x 14422 (128-tiles) 721 / 701,
 //   54 x 384 x 11328 (252 + 1062 64-tiles) 45.1 / 47.6.
 inline bool grads_in_one(const Plan& p, const VocabCut& dw, bool bf16, bool want_dw, bool dw_fast, bool places, int64_t rows,
