@@ -48,7 +48,8 @@
  *    library allocates one per device on first use and keeps it (growing it if a
  *    later call needs more; growing synchronises the device).  Where less memory is
  *    at hand (a smaller buffer, an allocation that fails) the call runs a slower plan
- *    that fits: without the finer cut of a small dX product along K, then also
+ *    that fits: a lent buffer or a call's own with as many K ranges of a small dX
+ *    product as it has room for, then without their finer cut, then also
  *    without row compaction for bf16 with H % 64 != 0 (12 bytes per row of a chunk);
  *    FLCE_ERR_WORKSPACE if even that does not fit.  (An allocation that found too
  *    little memory is tried again after flce_release_workspace.)  Calls that
@@ -272,8 +273,9 @@ FLCE_API int flce_release_workspace(void);
  * needs is not chunked at all (no more memory than chunking, and faster).  A
  * non-zero value is taken literally: chunks of at most that many bytes, one chunk
  * only when the whole logits fit in it, and no finer cut of a small dX product along
- * K (more workspace for more speed, which only the automatic rule takes).  The getter returns the setting
- * (0 = automatic). */
+ * K (more workspace for more speed, which only the automatic rule takes: up to 64
+ * ranges of chunk rows x H fp32 partial results, at most half the budget; 1024 x 512 x
+ * 128256 bf16: 67 of 332 MB).  The getter returns the setting (0 = automatic). */
 FLCE_API int flce_set_logits_budget_bytes(size_t bytes);
 FLCE_API size_t flce_get_logits_budget_bytes(void);
 
@@ -309,8 +311,9 @@ FLCE_API size_t flce_logits_budget_for_workspace(int64_t BT, int64_t H, int64_t 
 
 /* Number of K ranges (K = V) the launch of one chunk's dX product is sized for, so
  * that few output tiles still fill the chip's CUs; 1 = not cut, at most 64 (host only).
- * In a compacted chunk on 256 x 256 tiles the device takes fewer of them where the
- * chunk's live rows fill whole rounds better with fewer. */
+ * In a compacted chunk on 256 x 256 tiles that run in several rounds of the CUs the
+ * device takes fewer of them where the chunk's live rows fill whole rounds better with
+ * fewer. */
 FLCE_API int flce_dx_k_ranges(int64_t BT, int64_t H, int64_t V, int dtype);
 
 /* The paper's own chunk-size rule, 2^ceil(log2(ceil(BT / ceil(V/H)))), for
